@@ -231,6 +231,7 @@ struct SynthWS {
   float* ld;
   float* lp;                 // [Bk] log2 I_p (passive component)
   float* lmax;               // [3 Q + 1] per material: max log2 k, min lobe coefficient, max log2 I_d; max log2 I_p
+  void* rows;                // row table of the factorised kernels (int2 per row, and the end)
   float* plk;                // [cap][Bk] path-product reading: log2 k over each record's path (or log2 I_d)
   float* plc;                // [cap][Bk] path-product reading: each record's lobe coefficient
 };
@@ -303,7 +304,7 @@ constexpr int32_t TUNE_MAX_TRACE_BLOCKS = 8192;
 struct SynthBatchWS {
   int32_t J;
   int64_t cap;
-  bool mf, mf_bwd;
+  bool mf, mf_bwd;   // forward, adjoint on the matrix cores
   int fold;    // 8 / 4: every band edge on a multiple of 512 / 256 bins, and the bins, in every job; else 0
   int32_t target, target_bwd;   // chunk count the batch aims at
   int32_t chunks, chunks_bwd;   // grid size: target + J bounds the chunk count
@@ -320,6 +321,8 @@ struct SynthBatchWS {
   int64_t* tab;                 // chunk tables (forward, adjoint)
   void* jobs;                   // device job table
   float* tables;                // [J][4 Q Bk + 3 Q + 1] band tables and their per-material bounds
+  int rows;                     // the most rows of a job's spectrum (factorised kernels)
+  void* row_tables;             // [J][rows + 1] row tables
 };
 bool synth_batch_factorised(int32_t J, const et_job* jobs, bool adjoint);
 size_t synth_batch_ws_layout(int32_t J, const et_job* jobs, int64_t cap, const BatchTune& tune, bool adjoint,

@@ -38,6 +38,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <vector>
 
 namespace et {
 
@@ -69,7 +70,51 @@ struct SynthArgs {
   int32_t rec_rows;        // 1 (path-product reading): lk, lc, ld have a row per record and a
                            // record's `mat` in the kernels is its index; 0: a row per material
   const uint64_t* rxv;     // per-receiver line of sight [records] (NULL: the records' visible bit)
+  const int2* rows;        // [nrows + 1] row table (FOLD 0): first bin and bands of each row, then F
+  int32_t nrows;
 };
+
+constexpr int K2 = 64;        // bins per inner run (k = 64 k1 + k2)
+constexpr int KT1 = 64;       // rows per workgroup
+constexpr int SMAX = 16;      // band segments (runs of equal material and directivity band) per tile of rows
+
+// Rows of the factorised kernels: runs of bins within one block of 64 (an outer index) and within
+// one material and one directivity band, so a row starts at every multiple of 64 and at every band
+// edge.  With the band edges on multiples of 64 bins the rows are the outer indices; otherwise an
+// outer index that holds an edge has a row per band, each computing the 64 bins and keeping its own.
+// Returns their number; *max_seg (optional): the most band segments in a tile of KT1 rows.
+int synth_rows(const et_sim_desc* sim, int* max_seg) {
+  const int64_t F = sim->F;
+  std::vector<int64_t> edge;   // first bin of every band but the first
+  for (int pass = 0; pass < 2; ++pass) {
+    const int64_t B = pass == 0 ? sim->Bk : (sim->directivity ? sim->Bd : 0);
+    for (int64_t b = 1; b < B; ++b) {
+      const int64_t k = (b * F + B - 1) / B;
+      if (k > 0 && k < F) edge.push_back(k);
+    }
+  }
+  std::sort(edge.begin(), edge.end());
+  edge.erase(std::unique(edge.begin(), edge.end()), edge.end());
+  int64_t rows = (F + K2 - 1) / K2;
+  for (int64_t e : edge) rows += (e % K2) != 0;
+  if (max_seg) {
+    // segments of the tile that starts at each row: band edges among its rows, and the first one
+    int most = 1, seg = 1;
+    int64_t v = 0, k = 0;
+    size_t ie = 0;
+    while (k < F) {
+      if (v % KT1 == 0) seg = 1;
+      else if (ie > 0 && edge[ie - 1] == k) ++seg;
+      most = std::max(most, seg);
+      int64_t next = (k / K2 + 1) * K2;
+      if (ie < edge.size() && edge[ie] <= next) next = edge[ie++];
+      k = next;
+      ++v;
+    }
+    *max_seg = most;
+  }
+  return (int)std::min<int64_t>(rows, INT32_MAX);
+}
 
 SynthArgs make_args(const et_sim_desc* sim, int32_t P) {
   SynthArgs a;
@@ -92,6 +137,8 @@ SynthArgs make_args(const et_sim_desc* sim, int32_t P) {
   a.lk = a.lc = a.ld = a.lp = a.lmax = nullptr;
   a.rec_rows = 0;
   a.rxv = nullptr;
+  a.rows = nullptr;
+  a.nrows = synth_rows(sim, nullptr);
   return a;
 }
 
@@ -107,26 +154,44 @@ struct Pair {
   int kind;
 };
 
-__device__ inline float dir_gain(const float* tab, int El, int Az, float vx, float vy, float vz) {
+// Cell of the cell-centred directivity grid that a direction of arrival falls into: offsets of its
+// two elevation rows and azimuth columns and the weights of the bilinear interpolation.
+struct DirCell {
+  int r0, r1, i0, i1;   // row offsets (row times Az) and columns
+  float ta, te;
+};
+
+__device__ inline DirCell dir_cell(int El, int Az, float vx, float vy, float vz) {
   const float az = atan2f(vy, vx);
   const float el = atan2f(vz, hypotf(vx, vy));
   float fa = (az + PI_F) / (2.0f * PI_F) * (float)Az - 0.5f;
   float fe = (el + 0.5f * PI_F) / PI_F * (float)El - 0.5f;
   if (!(fa == fa)) fa = 0.f;   // undefined direction (receiver on the point): any cell, indices stay in range
   if (!(fe == fe)) fe = 0.f;
+  DirCell c;
   const float fl = floorf(fa);
-  const float ta = fa - fl;
-  int i0 = (int)fl % Az;
-  if (i0 < 0) i0 += Az;
-  const int i1 = (i0 + 1) % Az;
+  c.ta = fa - fl;
+  c.i0 = (int)fl % Az;
+  if (c.i0 < 0) c.i0 += Az;
+  c.i1 = (c.i0 + 1) % Az;
   int j0, j1;
-  float te;
-  if (fe <= 0.f) { j0 = j1 = 0; te = 0.f; }
-  else if (fe >= (float)(El - 1)) { j0 = j1 = El - 1; te = 0.f; }
-  else { j0 = min((int)floorf(fe), El - 1); j1 = min(j0 + 1, El - 1); te = fe - (float)j0; }
-  const float a0 = (1.f - ta) * tab[j0 * Az + i0] + ta * tab[j0 * Az + i1];
-  const float a1 = (1.f - ta) * tab[j1 * Az + i0] + ta * tab[j1 * Az + i1];
-  return (1.f - te) * a0 + te * a1;
+  if (fe <= 0.f) { j0 = j1 = 0; c.te = 0.f; }
+  else if (fe >= (float)(El - 1)) { j0 = j1 = El - 1; c.te = 0.f; }
+  else { j0 = min((int)floorf(fe), El - 1); j1 = min(j0 + 1, El - 1); c.te = fe - (float)j0; }
+  c.r0 = j0 * Az;
+  c.r1 = j1 * Az;
+  return c;
+}
+
+template <typename T>
+__device__ inline float dir_lerp(const T* tab, const DirCell& c) {
+  const float a0 = (1.f - c.ta) * tab[c.r0 + c.i0] + c.ta * tab[c.r0 + c.i1];
+  const float a1 = (1.f - c.ta) * tab[c.r1 + c.i0] + c.ta * tab[c.r1 + c.i1];
+  return (1.f - c.te) * a0 + c.te * a1;
+}
+
+__device__ inline float dir_gain(const float* tab, int El, int Az, float vx, float vy, float vz) {
+  return dir_lerp(tab, dir_cell(El, Az, vx, vy, vz));
 }
 
 // The gain of dir_gain and its gradient (gx, gy, gz) with respect to the direction v: the
@@ -210,7 +275,7 @@ __device__ inline float band_log2_v(const SynthArgs& a, int kind, int mat, float
 __device__ inline void band_table_entry(const SynthArgs& a, int i, float* lk, float* lc, float* ld, float* lp) {
   const float bt = a.beta[i];
   lk[i] = log2f(a.refl_k[i]);
-  lc[i] = LOG2E_F / (2.0f * bt * bt);
+  lc[i] = fminf(LOG2E_F / (2.0f * bt * bt), 3.0e38f);   // (finite, so that 0 times it is 0)
   ld[i] = log2f(a.dcoef[i]);
   if (i < a.Bk) lp[i] = a.pcoef ? log2f(a.pcoef[i]) : -INFINITY;
 }
@@ -237,7 +302,54 @@ __device__ inline void band_bound_entry(const SynthArgs& a, int q, float* lmax) 
   }
 }
 
-__global__ void k_band_tables(SynthArgs a, float* lk, float* lc, float* ld, float* lp, float* lmax) {
+// Band of bin k of F in B bands (32-bit arithmetic where k B fits).
+__device__ inline int band_of(int k, int B, int F) {
+  return F < (1 << 25) ? (int)(((uint32_t)k * (uint32_t)B) / (uint32_t)F) : (int)(((int64_t)k * B) / F);
+}
+
+// Row table of a pose (see synth_rows): (first bin, material band + directivity band << 16) per row,
+// closed by an entry with first bin F.  One workgroup of 256 threads, each a run of the bins.
+__device__ inline void row_table(const SynthArgs& a, int2* __restrict__ rows) {
+  __shared__ int wsum[4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int per = (int)(((int64_t)a.F + 255) / 256);
+  const int64_t k0 = (int64_t)tid * per, k1 = min(k0 + per, (int64_t)a.F);
+  int at = 0;
+  for (int pass = 0; pass < 2; ++pass) {
+    int n = 0;
+    if (k0 < k1) {
+      int pb = k0 > 0 ? band_of((int)k0 - 1, a.Bk, a.F) : -1, pd = k0 > 0 && a.Bd ? band_of((int)k0 - 1, a.Bd, a.F) : 0;
+      for (int64_t k = k0; k < k1; ++k) {
+        const int b = band_of((int)k, a.Bk, a.F), d = a.Bd ? band_of((int)k, a.Bd, a.F) : 0;
+        if (k % K2 == 0 || b != pb || d != pd) {
+          if (pass == 1) rows[at + n] = make_int2((int)k, b | (d << 16));
+          ++n;
+        }
+        pb = b;
+        pd = d;
+      }
+    }
+    if (pass == 1) break;
+    int inc = n;   // exclusive sum of the counts over the workgroup
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(inc, o);
+      if (lane >= o) inc += v;
+    }
+    if (lane == 63) wsum[wv] = inc;
+    __syncthreads();
+    at = inc - n;
+    for (int w = 0; w < wv; ++w) at += wsum[w];
+  }
+  if (tid == 0) rows[a.nrows] = make_int2(a.F, 0);
+}
+
+// The last workgroup writes the row table (rows not NULL), the others the band tables.
+__global__ __launch_bounds__(256) void k_band_tables(SynthArgs a, float* lk, float* lc, float* ld, float* lp, float* lmax,
+                                                     int2* rows) {
+  if (rows && blockIdx.x + 1 == gridDim.x) {
+    row_table(a, rows);
+    return;
+  }
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < a.Q) band_bound_entry(a, i, lmax);
   if (i >= a.Q * a.Bk) return;
@@ -348,49 +460,126 @@ __global__ void k_vis_all(Ctl* ctl) { ctl->n_vis = ctl->n_rec; }   // no list: t
 
 // ------------------------------------------------------------------ factorised MFMA kernel
 
-constexpr int K2 = 64;        // bins per inner run (k = 64 k1 + k2)
-constexpr int KT1 = 64;       // outer indices per workgroup
 constexpr int RB = 32;        // records per stage (contraction depth per stage)
 constexpr int RPW = RB / 4;   // records per wave and stage
-constexpr int SMAX = 16;      // band segments (runs of equal material and directivity band) per 64-row tile
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ inline uint32_t q32(double cyc) {   // fraction of a cycle in Q0.32 (mod 2^32)
-  return (uint32_t)((cyc - floor(cyc)) * 4294967296.0);   // in [0, 2^32]; the conversion saturates
+  return (uint32_t)(__builtin_amdgcn_fract(cyc) * 4294967296.0);   // in [0, 2^32); the conversion saturates
 }
 
 // Lean per-(record, receiver) setup: FP64 only for the receiver leg, the path and the delay
 // reductions.  Phases of the generated values are integer phase accumulators in Q0.32
 // (a32 + k1 bx32 for X, k2 by32 for Y), exact mod 1 up to the quantisation of the steps
 // (<= 128 * 2^-33 cycles).
+typedef __attribute__((address_space(1))) float GlobalFloat;
+
 struct PairLean {
   uint32_t a32, bx32, by32;
   float base, slope, gamma;
-  float vx, vy, vz;
+  DirCell cell;          // directivity cell of the arrival (forward, with directivity)
   int mat, kind;         // mat: row of the band tables (the material, or the record: rec_rows)
   float lbm;             // bound on the log2 band factor (with directivity) over every band: the
                          // generating factors carry it, so Xa stays below the record's bound and
                          // the per-segment factors below 1
-  // GRAD: receiver-gradient coefficients, d/dx_m of (ln A + j phi) = (c1 + c2 f + j c3 f) u - lobe
+  const GlobalFloat *t1, *t2;   // forward: the record's rows of the band tables, log2 factor = t1[b] - gamma^2 t2[b]
+  // the adjoint's receiver-gradient coefficients, d/dx_m of (ln A + j phi) = (c1 + c2 f + j c3 f) u - lobe
   float gux, guy, guz;   // u = (x_m - p) / l
   float gc1;             // -p / r - ln10 a0 / 20
   float glx, gly, glz;   // 2 (gamma / sin gamma) (d' - cos(gamma) u) / l (specular; 0 otherwise)
 };
 
-// GRAD: the adjoint's set-up (receiver-gradient coefficients; band factors without k).  dmax: the
-// receiver's largest log2 directivity gain (0 without directivity).
-template <bool GRAD = false>
-__device__ inline void pair_lean(const SynthArgs& a, const et_paths& P, const int32_t* __restrict__ idx, int64_t e,
-                                 int64_t hi, int m, PairLean& q, float dmax = 0.f) {
+// Element e of the visible-record list (without a list: every record, hidden ones skipped at set-up).
+__device__ inline int64_t record_at(const int32_t* __restrict__ idx, int64_t e) { return idx ? (int64_t)idx[e] : e; }
+
+// Length l = sqrt(w2) and its reciprocal from the hardware reciprocal square root and two Newton steps in
+// FP64, l then corrected once (within an ulp of the rounded square root; l = 0 for w2 = 0).
+__device__ inline void length_rcp(double w2, double& l, double& il) {
+  double y = __builtin_amdgcn_rsq(w2);
+  const double h = 0.5 * w2;
+  y = fma(y, fma(-h * y, y, 0.5), y);
+  y = fma(y, fma(-h * y, y, 0.5), y);
+  double s = w2 * y;
+  s = fma(0.5 * y, fma(-s, s, w2), s);
+  l = w2 > 0.0 ? s : 0.0;
+  il = y;
+}
+
+// Set-up of record n for receiver m (forward): every field of the record is read at once, whether it counts
+// or not, so that a group waits for memory once and not for the index, the flags and the fields in
+// turn.  valid: the lane has a record of the range.  dmax: the receiver's largest log2 directivity gain (0
+// without directivity).
+template <bool DIR>
+__device__ __forceinline__ void pair_fwd(const SynthArgs& a, const et_paths& P, int64_t n, bool valid, int m, float dmax,
+                                         PairLean& q) {
+  const uint8_t fl = P.flags[n];
+  const int mat = P.mat[n];
+  const double px = P.p[3 * n], py = P.p[3 * n + 1], pz = P.p[3 * n + 2], rtot = P.rtot[n];
+  const float dx = P.dout[3 * n], dy = P.dout[3 * n + 1], dz = P.dout[3 * n + 2];
+  bool ok = valid && (fl & 1);
+  if (a.rxv) ok = ok && ((a.rxv[n] >> m) & 1ull);   // per-receiver line of sight
+  q.kind = (fl >> 1) & 3;
+  ok = ok && !(q.kind == 2 && mat != m);            // a passive record reaches its own receiver only
+  const double wx = a.rx_pos[3 * m] - px, wy = a.rx_pos[3 * m + 1] - py, wz = a.rx_pos[3 * m + 2] - pz;
+  double l, il;
+  length_rcp(wx * wx + wy * wy + wz * wz, l, il);
+  const double r = rtot + l;                        // emitter -> point -> receiver
+  const double cb = r * a.kcb;
+  q.a32 = ok ? q32(r * a.kc0) : 0u;
+  q.bx32 = ok ? q32((double)K2 * cb) : 0u;
+  q.by32 = ok ? q32(cb) : 0u;
+  const float base = -(float)a.ps * __builtin_amdgcn_logf((float)r) + (float)(r * a.kbase);
+  q.slope = ok ? (float)(r * a.kslope) : 0.f;
+  // rows of the band tables: the material's (with per-record tables the record's), one row for passive
+  // records; the lobe's row counts for specular records only (gamma is 0 for the others)
+  const int64_t row = a.rec_rows ? n : (int64_t)mat;
+  const float* t1 = q.kind == 0 ? a.lk : q.kind == 1 ? a.ld : a.lp;
+  q.t1 = (const GlobalFloat*)(t1 + (q.kind == 2 ? 0 : row * a.Bk));
+  q.t2 = (const GlobalFloat*)(a.lc + (q.kind == 0 ? row * a.Bk : 0));
+  const float ux = (float)(wx * il), uy = (float)(wy * il), uz = (float)(wz * il);
+  const float cx = dy * uz - dz * uy, cy = dz * ux - dx * uz, cz = dx * uy - dy * ux;
+  const float gam = atan2f(sqrtf(cx * cx + cy * cy + cz * cz), dx * ux + dy * uy + dz * uz);
+  q.gamma = q.kind == 0 ? gam : 0.f;
+  if (DIR) {   // direction of arrival in the receiver frame: -R_m^T u
+    q.cell = DirCell{0, 0, 0, 0, 0.f, 0.f};
+    if (a.Bd) {
+      float vx = -ux, vy = -uy, vz = -uz;
+      if (a.rx_rot) {
+        const double* R = a.rx_rot + 9 * m;
+        vx = -(float)(R[0] * ux + R[3] * uy + R[6] * uz);
+        vy = -(float)(R[1] * ux + R[4] * uy + R[7] * uz);
+        vz = -(float)(R[2] * ux + R[5] * uy + R[8] * uz);
+      }
+      q.cell = dir_cell(a.El, a.Az, vx, vy, vz);
+    }
+  }
+  // bound on the log2 band factor over every band: from the per-material bounds (at least the largest factor:
+  // k and the lobe's coefficient may peak on different bands), or by taking every band of per-record tables
+  float bm = -INFINITY;
+  if (!a.rec_rows) {
+    const int top = q.kind == 0 ? mat : q.kind == 1 ? 2 * a.Q + mat : 3 * a.Q;
+    bm = a.lmax[top] - q.gamma * q.gamma * a.lmax[a.Q + (q.kind == 0 ? mat : 0)];
+  } else {
+    for (int b = 0; b < a.Bk; ++b) bm = fmaxf(bm, q.t1[b] - q.gamma * q.gamma * q.t2[b]);
+  }
+  q.lbm = bm + dmax;
+  // nothing to add when every band factor is zero (lbm stays finite)
+  q.base = ok && q.lbm != -INFINITY ? base : -INFINITY;
+  if (q.lbm == -INFINITY) q.lbm = 0.f;
+}
+
+// Set-up of the adjoint: receiver-gradient coefficients, band factors without k.
+__device__ inline void pair_adj(const SynthArgs& a, const et_paths& P, const int32_t* __restrict__ idx, int64_t e,
+                                int64_t hi, int m, PairLean& q) {
   q.a32 = q.bx32 = q.by32 = 0;
   q.base = -INFINITY;
   q.lbm = 0.f;
-  q.slope = q.gamma = q.vx = q.vy = q.vz = 0.f;
+  q.slope = q.gamma = 0.f;
   q.mat = q.kind = 0;
-  if (GRAD) q.gux = q.guy = q.guz = q.gc1 = q.glx = q.gly = q.glz = 0.f;
+  q.gux = q.guy = q.guz = q.gc1 = q.glx = q.gly = q.glz = 0.f;
   if (e >= hi) return;
-  const int64_t n = idx ? (int64_t)idx[e] : e;   // no list: every record (hidden ones skipped here)
+  const int64_t n = record_at(idx, e);
   const uint8_t fl = P.flags[n];
   if (!(fl & 1)) return;
   if (a.rxv && !((a.rxv[n] >> m) & 1ull)) return;   // per-receiver line of sight
@@ -399,94 +588,63 @@ __device__ inline void pair_lean(const SynthArgs& a, const et_paths& P, const in
   q.kind = kind;
   const double wx = a.rx_pos[3 * m] - P.p[3 * n], wy = a.rx_pos[3 * m + 1] - P.p[3 * n + 1],
                wz = a.rx_pos[3 * m + 2] - P.p[3 * n + 2];
-  const double l = sqrt(wx * wx + wy * wy + wz * wz);
+  double l, il;
+  length_rcp(wx * wx + wy * wy + wz * wz, l, il);
   const double r = P.rtot[n] + l;                          // emitter -> point -> receiver
   const double cb = r * a.kcb;
   q.a32 = q32(r * a.kc0);
   q.bx32 = q32((double)K2 * cb);
   q.by32 = q32(cb);
-  q.base = -(float)a.ps * log2f((float)r) + (float)(r * a.kbase);
+  q.base = -(float)a.ps * __builtin_amdgcn_logf((float)r) + (float)(r * a.kbase);
   q.slope = (float)(r * a.kslope);
-  q.mat = a.rec_rows ? (int)n : P.mat[n];
-  const double il = 1.0 / l;
+  q.mat = P.mat[n];
   const float ux = (float)(wx * il), uy = (float)(wy * il), uz = (float)(wz * il);
   if (q.kind == 0) {
     const float dx = P.dout[3 * n], dy = P.dout[3 * n + 1], dz = P.dout[3 * n + 2];
     const float cx = dy * uz - dz * uy, cy = dz * ux - dx * uz, cz = dx * uy - dy * ux;
     const float sc = sqrtf(cx * cx + cy * cy + cz * cz), cc = dx * ux + dy * uy + dz * uz;
     q.gamma = atan2f(sc, cc);
-    if (GRAD) {
-      // d(gamma^2)/dx_m = -(2 gamma / sin gamma) (h - cos(gamma) u) / l with h = d' / |d'|
-      const float idn = 1.0f / sqrtf(dx * dx + dy * dy + dz * dz);
-      const float sg = sc * idn, cg = cc * idn;
-      const float ratio = q.gamma < 1e-4f ? 2.0f : 2.0f * q.gamma / sg;
-      const float c = ratio * (float)(2.0 * il);
-      q.glx = c * (dx * idn - cg * ux);
-      q.gly = c * (dy * idn - cg * uy);
-      q.glz = c * (dz * idn - cg * uz);
-    }
+    // d(gamma^2)/dx_m = -(2 gamma / sin gamma) (h - cos(gamma) u) / l with h = d' / |d'|
+    const float idn = 1.0f / sqrtf(dx * dx + dy * dy + dz * dz);
+    const float sg = sc * idn, cg = cc * idn;
+    const float ratio = q.gamma < 1e-4f ? 2.0f : 2.0f * q.gamma / sg;
+    const float c = ratio * (float)(2.0 * il);
+    q.glx = c * (dx * idn - cg * ux);
+    q.gly = c * (dy * idn - cg * uy);
+    q.glz = c * (dz * idn - cg * uz);
   }
-  if (GRAD) {
-    q.gux = ux; q.guy = uy; q.guz = uz;
-    q.gc1 = (float)(-a.ps / r - 2.30258509299404568402 * a.A0 / 20.0);
-  }
-  if (a.Bd) {   // direction of arrival in the receiver frame: -R_m^T u
-    if (a.rx_rot) {
-      const double* R = a.rx_rot + 9 * m;
-      q.vx = -(float)(R[0] * ux + R[3] * uy + R[6] * uz);
-      q.vy = -(float)(R[1] * ux + R[4] * uy + R[7] * uz);
-      q.vz = -(float)(R[2] * ux + R[5] * uy + R[8] * uz);
-    } else {
-      q.vx = -ux; q.vy = -uy; q.vz = -uz;
-    }
-  }
-  // bound on the record's log2 band factor over every band: from the per-material bounds (at
-  // least the largest factor: k and the lobe's coefficient may peak on different bands), or by
-  // taking every band with per-record tables
-  float bm = -INFINITY;
-  if (!a.rec_rows) {
-    bm = q.kind == 0   ? (GRAD ? 0.f : a.lmax[q.mat]) - q.gamma * q.gamma * a.lmax[a.Q + q.mat]
-         : q.kind == 1 ? a.lmax[2 * a.Q + q.mat]
-                       : a.lmax[3 * a.Q];
-  } else {
-    for (int b = 0; b < a.Bk; ++b) bm = fmaxf(bm, band_log2_v<GRAD>(a, q.kind, q.mat, q.gamma, b));
-  }
-  q.lbm = bm + dmax;
+  q.gux = ux; q.guy = uy; q.guz = uz;
+  q.gc1 = (float)(-a.ps / r - 2.30258509299404568402 * a.A0 / 20.0);
+  // bound on the log2 band factor without k, over every band
+  q.lbm = q.kind == 0 ? -q.gamma * q.gamma * a.lmax[a.Q + q.mat] : a.lmax[q.kind == 1 ? 2 * a.Q + q.mat : 3 * a.Q];
   if (q.lbm == -INFINITY) {   // every band factor is zero: nothing to add (lbm stays finite)
     q.base = -INFINITY;
     q.lbm = 0.f;
   }
 }
 
-// The forward contraction runs on the f16 matrix cores (v_mfma_f32_16x16x32_f16: 32 records per
-// instruction, FP32 accumulation).  Each FP32 operand v is split into two halves, hi = f16(v) and
-// lo = f16(v - hi), about 22 significant bits together; a real product takes three half
-// products, hi hi + hi lo + lo hi (lo lo lies below 2^-22 of it), and the complex product the four
-// real ones re re, im im, re im, im re.  The LDS holds the halves k-major: row k (an outer index
-// of X, an inner index of Y) holds the stage's 32 records in 4 chunks of 8, the chunk a lane
-// hands to an instruction (rows 80 bytes apart, so 16 lanes reading 16 bytes land on distinct
-// banks).  f16 has a narrow exponent range: X is scaled by 2^(XTOP - E) with E a workgroup-wide
-// bound on log2 |X| over each group of 256 records, taken before the group is generated; when a
-// group's bound exceeds E the accumulators are rescaled by a power of two (exact).  A record far
-// below the bound loses relative precision in proportion to its negligible share of the sum.
+// The contractions run on the f16 matrix cores with FP32 accumulation.  Each FP32 operand v is split
+// into two halves, hi = f16(v) and lo = f16(v - hi), about 22 significant bits together; a real
+// product takes three half products, hi hi + hi lo + lo hi (lo lo lies below 2^-22 of it), and the
+// complex product the four real ones re re, im im, re im, im re.  f16 has a narrow exponent range: X
+// is scaled by 2^(XTOP - E) with E a wave-wide bound on log2 |X| over each group of 64 records, taken
+// before the group is generated; when a group's bound exceeds E the accumulators are rescaled by a
+// power of two (exact).  A record far below the bound loses relative precision in proportion to its
+// negligible share of the sum.
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-constexpr int HROW = 5;          // halfx8 per LDS row: 4 chunks of 8 records and a pad
 constexpr float XTOP = 12.f;     // log2 of the largest scaled |X| (|Y| <= 1 for non-negative absorption)
-// With SPLIT the Y rows hold no pad: chunk c of row k sits at slot c ^ ((k / 4) % 4), which puts
-// 16 lanes reading or writing one chunk of 16 consecutive rows on distinct banks, and the
-// workgroup's LDS (about 37 KB) lets four workgroups share a CU.
-template <bool SPLIT>
-struct H16Buf {
-  static constexpr int NA = SPLIT ? KT1 / 2 : KT1;   // rows of X (a tile of at most 32 with SPLIT)
-  static constexpr int BROW = SPLIT ? 4 : HROW;
-  halfx8 A[4][NA][HROW];         // X halves: [re hi, re lo, im hi, im lo][k1][record chunk]
-  halfx8 B[4][K2][BROW];         // Y halves: [re hi, re lo, im hi, im lo][k2][record chunk slot]
-  // slot of record chunk c in Y row k
-  static __device__ __forceinline__ int bslot(int k, int c) { return SPLIT ? c ^ ((k >> 2) & 3) : c; }
-};
 
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
+
+// The halves of two values: h = (f16(v0), f16(v1)), l the halves of the differences (see split8).
+__device__ __forceinline__ void split2(float v0, float v1, uint32_t& h, uint32_t& l) {
+  h = __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){v0, v1}, half2v));
+  uint32_t lo;
+  asm("v_fma_mixlo_f16 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(h), "v"(v0));
+  asm("v_fma_mixhi_f16 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(h), "v"(v1));
+  l = lo;
+}
 
 // hi = f16(v) two at a time (round to nearest even); lo = f16(v - hi), the difference taken
 // exactly by a mixed-precision fma from the f16 hi and the f32 v, written into the low, then
@@ -504,24 +662,6 @@ __device__ inline void split8(const float (&v)[8], halfx8& h, halfx8& l) {
   }
   h = H.h8;
   l = L.h8;
-}
-
-typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
-
-// split8 for four values
-__device__ inline void split4(const float (&v)[4], halfx4& h, halfx4& l) {
-  union { halfx4 h4; uint32_t u[2]; } H, L;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const uint32_t xu = __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){v[2 * i], v[2 * i + 1]}, half2v));
-    uint32_t lo;
-    asm("v_fma_mixlo_f16 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(xu), "v"(v[2 * i]));
-    asm("v_fma_mixhi_f16 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(xu), "v"(v[2 * i + 1]));
-    H.u[i] = xu;
-    L.u[i] = lo;
-  }
-  h = H.h4;
-  l = L.h4;
 }
 
 // Two-level generation: X[8a+b] = Xa[a] Xb[b] bf[seg(8a+b)] and Y[8a+b] = Ya[a] Yb[b]:
@@ -607,12 +747,6 @@ __device__ inline void gen_factors(const SynthArgs& a, const PairLean& q, int t,
     const int m_r = __shfl(q.mat, src), k_r = __shfl(q.kind, src);
     float ll = band_log2_v<KFREE>(a, k_r, m_r, g_r, st.sb[segl]);
     float lh = FOLD == 4 ? band_log2_v<KFREE>(a, k_r, m_r, g_r, st.sb[segh]) : 0.f;
-    if (a.Bd) {
-      const float vx = __shfl(q.vx, src), vy = __shfl(q.vy, src), vz = __shfl(q.vz, src);
-      const float* tab = a.dir + (size_t)m * a.Bd * a.El * a.Az;
-      ll += log2f(dir_gain(tab + (size_t)st.sd[segl] * a.El * a.Az, a.El, a.Az, vx, vy, vz));
-      if (FOLD == 4) lh += log2f(dir_gain(tab + (size_t)st.sd[segh] * a.El * a.Az, a.El, a.Az, vx, vy, vz));
-    }
     const float rev = (float)(int32_t)(a_r + k1a * bx_r) * S;
     const float c = __builtin_amdgcn_cosf(rev), sn = __builtin_amdgcn_sinf(rev);
     const float al = ok && 8 * j < nk1 ? __builtin_amdgcn_exp2f(lg0 + ll) : 0.f;
@@ -632,22 +766,6 @@ __device__ inline void gen_factors(const SynthArgs& a, const PairLean& q, int t,
   // band factors of every (record, segment), and zero for the segment past the tile
   if (FOLD) {
     // (folded into Xa and Xh)
-  } else if (!KFREE) {
-    // lane (r, j) takes segments j, j + 8, ... of record r
-    const float g_r = __shfl(q.gamma, src);
-    const int m_r = __shfl(q.mat, src), k_r = __shfl(q.kind, src);
-    float vx = 0.f, vy = 0.f, vz = 0.f;
-    if (a.Bd) {
-      vx = __shfl(q.vx, src);
-      vy = __shfl(q.vy, src);
-      vz = __shfl(q.vz, src);
-    }
-    for (int sg = j; sg < nseg; sg += 8) {
-      // (finite for a skipped record too: its Xa is zero)
-      float lb = band_log2_v(a, k_r, m_r, g_r, st.sb[sg]);
-      if (a.Bd) lb += log2f(dir_gain(a.dir + ((size_t)m * a.Bd + st.sd[sg]) * a.El * a.Az, a.El, a.Az, vx, vy, vz));
-      W.bf[r][sg] = __builtin_amdgcn_exp2f(lb - lbm_r);   // <= 1: the record's bound lbm rides on Xa
-    }
   } else {
     // the adjoint (no directivity): the pairs enumerated over the wave, each lane fetching its
     // record's data (fewer registers live across the loop: measured faster in that kernel)
@@ -666,160 +784,25 @@ __device__ inline void gen_factors(const SynthArgs& a, const PairLean& q, int t,
   __builtin_amdgcn_wave_barrier();
 }
 
-// X and Y values of record rr for this lane's outer and inner index (lane = 8 a + b):
-// X[lane] = Xa[a] Xb[b] bf[segment of the lane's row], Y[lane] = Ya[a] Yb[b].
-// FOLD 4: the band factor is already on Xa (b < 4) or Xh (b >= 4); FOLD 8: on Xa.
-template <int FOLD = 0>
-__device__ inline void xy_value(const WaveScratch& W, int rr, int lane, int myseg, float2& x, float2& y) {
-  const int ka = lane >> 3, kb = lane & 7;
-  y = cmul(W.ya[rr][ka], W.yb[rr][kb]);
-  if (FOLD == 8) {
-    x = cmul(W.xa[rr][ka], W.xb[rr][kb]);
-  } else if (FOLD == 4) {
-    x = cmul(kb < 4 ? W.xa[rr][ka] : W.xh[rr][ka], W.xb[rr][kb]);
-  } else {
-    x = cmul(W.xa[rr][ka], W.xb[rr][kb]);
-    const float f = W.bf[rr][myseg];
-    x.x *= f;
-    x.y *= f;
-  }
-}
-
-// X of record rr at outer index `row` (as in xy_value; seg: the row's band segment)
-template <int FOLD>
-__device__ inline float2 x_value(const WaveScratch& W, int rr, int row, int seg) {
-  const int ka = row >> 3, kb = row & 7;
-  if (FOLD == 8) return cmul(W.xa[rr][ka], W.xb[rr][kb]);
-  if (FOLD == 4) return cmul(kb < 4 ? W.xa[rr][ka] : W.xh[rr][ka], W.xb[rr][kb]);
-  float2 x = cmul(W.xa[rr][ka], W.xb[rr][kb]);
-  const float f = W.bf[rr][seg];
-  x.x *= f;
-  x.y *= f;
-  return x;
-}
-
-// The sub-stage's records as f16 halves: X of this lane's outer index into A, Y of its inner
-// index into B, chunk wv (the wave's 8 records of the stage).  With a tile of at most 32 rows
-// (SPLIT) every lane forms X: lane (row = lane % 32, h = lane / 32) for records 4 h .. 4 h + 3,
-// writing its half of the row's 8-record chunk; segx is the band segment of row lane % 32.
-template <bool SPLIT, int FOLD>
-__device__ inline void write_h16(const WaveScratch& W, int lane, int wv, int myseg, int segx, H16Buf<SPLIT>& buf) {
-  if constexpr (SPLIT) {
-    const int row = lane & 31, hh = lane >> 5;
-    float xr[4], xi[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float2 x = x_value<FOLD>(W, 4 * hh + i, row, segx);
-      xr[i] = x.x;
-      xi[i] = x.y;
-    }
-    halfx4 h4, l4;
-    split4(xr, h4, l4);
-    reinterpret_cast<halfx4*>(&buf.A[0][row][wv])[hh] = h4;
-    reinterpret_cast<halfx4*>(&buf.A[1][row][wv])[hh] = l4;
-    split4(xi, h4, l4);
-    reinterpret_cast<halfx4*>(&buf.A[2][row][wv])[hh] = h4;
-    reinterpret_cast<halfx4*>(&buf.A[3][row][wv])[hh] = l4;
-    const int ka = lane >> 3, kb = lane & 7;
-    float yr[RPW], yi[RPW];
-#pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      const float2 y = cmul(W.ya[rr][ka], W.yb[rr][kb]);
-      yr[rr] = y.x;
-      yi[rr] = y.y;
-    }
-    halfx8 h, l;
-    const int sl = H16Buf<SPLIT>::bslot(lane, wv);
-    split8(yr, h, l);
-    buf.B[0][lane][sl] = h;
-    buf.B[1][lane][sl] = l;
-    split8(yi, h, l);
-    buf.B[2][lane][sl] = h;
-    buf.B[3][lane][sl] = l;
-    return;
-  }
-  float xr[RPW], xi[RPW], yr[RPW], yi[RPW];
-#pragma unroll
-  for (int rr = 0; rr < RPW; ++rr) {
-    float2 x, y;
-    xy_value<FOLD>(W, rr, lane, myseg, x, y);
-    xr[rr] = x.x; xi[rr] = x.y; yr[rr] = y.x; yi[rr] = y.y;
-  }
-  halfx8 h, l;
-  if (lane < H16Buf<SPLIT>::NA) {
-    split8(xr, h, l);
-    buf.A[0][lane][wv] = h;
-    buf.A[1][lane][wv] = l;
-    split8(xi, h, l);
-    buf.A[2][lane][wv] = h;
-    buf.A[3][lane][wv] = l;
-  }
-  split8(yr, h, l);
-  buf.B[0][lane][wv] = h;
-  buf.B[1][lane][wv] = l;
-  split8(yi, h, l);
-  buf.B[2][lane][wv] = h;
-  buf.B[3][lane][wv] = l;
-}
-
 struct BwdBuf;
 __device__ inline void write_bwd(const WaveScratch& W, int lane, int wv, BwdBuf& bb);
 
-// Row and column blocks (16 x 16) of a wave: with 64 rows, the quadrant (wv / 2, wv % 2) as 2 x 2
-// blocks; with at most 32 rows (SPLIT), row block wv % 2 against the column blocks of half wv / 2.
-template <bool SPLIT>
-__device__ inline void wave_blocks(int wv, int& rb0, int& cb0) {
-  rb0 = SPLIT ? (wv & 1) : 2 * (wv >> 1);
-  cb0 = SPLIT ? 2 * (wv >> 1) : 2 * (wv & 1);
+// Maximum over the wave's lanes, the same (scalar) value in every lane: lane moves within rows of 16,
+// then the four rows' values.
+template <int CTRL>
+__device__ inline float dpp_mov(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
 }
-
-// One stage (32 records) into the wave's blocks: acc[0] += Xr Yr, acc[1] += Xi Yi,
-// acc[2] += Xr Yi + Xi Yr, each real product as three half products.
-template <bool SPLIT>
-__device__ inline void contract_h16(const H16Buf<SPLIT>& buf, int wv, int lane, floatx4 (&acc)[3][2][2]) {
-  constexpr int NRB = SPLIT ? 1 : 2;
-  int rb0, cb0;
-  wave_blocks<SPLIT>(wv, rb0, cb0);
-  const int r16 = lane & 15, ch = lane >> 4;
-  halfx8 b[2][4];
-#pragma unroll
-  for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {
-      const int k2 = 16 * (cb0 + jj) + r16;
-      b[jj][f] = buf.B[f][k2][H16Buf<SPLIT>::bslot(k2, ch)];
-    }
-#pragma unroll
-  for (int i = 0; i < NRB; ++i) {
-    halfx8 av[4];
-#pragma unroll
-    for (int f = 0; f < 4; ++f) av[f] = buf.A[f][16 * (rb0 + i) + r16][ch];
-#pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-      floatx4 rr = acc[0][i][jj], ii = acc[1][i][jj], im = acc[2][i][jj];
-      rr = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[0], b[jj][0], rr, 0, 0, 0);
-      rr = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[0], b[jj][1], rr, 0, 0, 0);
-      rr = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[1], b[jj][0], rr, 0, 0, 0);
-      ii = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[2], b[jj][2], ii, 0, 0, 0);
-      ii = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[2], b[jj][3], ii, 0, 0, 0);
-      ii = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[3], b[jj][2], ii, 0, 0, 0);
-      im = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[0], b[jj][2], im, 0, 0, 0);
-      im = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[0], b[jj][3], im, 0, 0, 0);
-      im = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[1], b[jj][2], im, 0, 0, 0);
-      im = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[2], b[jj][0], im, 0, 0, 0);
-      im = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[2], b[jj][1], im, 0, 0, 0);
-      im = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[3], b[jj][0], im, 0, 0, 0);
-      acc[0][i][jj] = rr;
-      acc[1][i][jj] = ii;
-      acc[2][i][jj] = im;
-    }
-  }
-}
-
 __device__ inline float wave_max(float v) {
+  v = fmaxf(v, dpp_mov<0xB1>(v));    // quad_perm [1, 0, 3, 2]
+  v = fmaxf(v, dpp_mov<0x4E>(v));    // quad_perm [2, 3, 0, 1]
+  v = fmaxf(v, dpp_mov<0x141>(v));   // row_half_mirror
+  v = fmaxf(v, dpp_mov<0x140>(v));   // row_mirror
+  const int u = __builtin_bit_cast(int, v);
+  float r[4];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
+  for (int i = 0; i < 4; ++i) r[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(u, 16 * i));
+  return fmaxf(fmaxf(r[0], r[1]), fmaxf(r[2], r[3]));
 }
 
 // Upper bound on log2 |X[k1] Y[k2]| over the tile for the record set up in q (-inf for none):
@@ -849,90 +832,442 @@ __device__ inline float dir_log2_max(const SynthArgs& a, int m, int tid, float* 
   return log2f(v);
 }
 
-// Workgroup = (record chunk p, receiver m, 64 outer indices).  Every 8 stages each wave sets up
-// 64 records (one per lane) and the workgroup bounds their |X|; every stage each wave generates
-// 8 of them as f16 halves into LDS, then each wave contracts all 32 records of the stage into
-// its blocks of (k1, k2) on the matrix cores.
-// FOLD 4 (8): every band edge falls on a multiple of 4 (8) rows and the grid holds whole groups of
-// that many rows (bins a multiple of 256, 512): the band factor rides on Xa.
-template <bool BATCH, bool SPLIT, int FOLD>
-__global__ __launch_bounds__(256, SPLIT ? 4 : 2) void k_synth_mfma(SynthArgs a0, const SynthArgs* __restrict__ jobs,
-                                                                   ChunkTab ct, et_paths P,
-                                                                   const int32_t* __restrict__ idx, const Ctl* ctl,
-                                                                   float* __restrict__ part) {
-  SYNTH_RESOLVE();
-  __shared__ __align__(16) H16Buf<SPLIT> buf;
-  __shared__ WaveScratch wscr[4];
-  __shared__ SegTable st;
-  __shared__ float red[4];
-  const int p = bp, m = bm, k1t = bt;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int K1 = a.F / K2;
-  const int k1_0 = k1t * KT1;
-  const int nk1 = min(KT1, K1 - k1_0);
-  int nseg, myseg;
-  seg_init(a, k1_0, nk1, tid, st, nseg, myseg);
-  // segments of the two half groups of row group lane % 8 (FOLD)
-  const int segl = min(__shfl(myseg, 8 * (lane & 7)), nseg - 1), segh = min(__shfl(myseg, 8 * (lane & 7) + 4), nseg - 1);
-  const int segx = __shfl(myseg, lane & 31);   // (SPLIT: the band segment of row lane % 32)
-  const float dmax = dir_log2_max(a, m, tid, red);
-  const int64_t nst = (hi - lo + 8 * RB - 1) / (8 * RB) * 8;   // whole groups of 8 stages (256 records)
-  floatx4 acc[3][2][2];
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+// The generating factors of a wave's U records (private to it): rows [factor][record] with a pad of 16
+// bytes, so that the lanes that read different factors of the same records land on distinct banks.
+// Factors: Xa of the G = 4 NRB row groups, with FOLD 4 Xa of their upper halves, then Xb, Ya and Yb
+// (8 each); bf: the band factor per (segment, record) with FOLD 0.
+template <int NRB, int FOLD, int U>
+struct Factors {
+  static constexpr int G = 4 * NRB, XH = G, XB = FOLD == 4 ? 2 * G : G, YA = XB + 8, YB = YA + 8;
+  float2 f[YB + 8][U + 2];
+  float bf[FOLD == 0 ? SMAX + 1 : 1][FOLD == 0 ? U + 4 : 4];
+};
+
+__device__ inline const GlobalFloat* shfl_ptr(const GlobalFloat* p, int src) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)v, src), hi = (uint32_t)__shfl((int)(uint32_t)(v >> 32), src);
+  return (const GlobalFloat*)((uint64_t)hi << 32 | lo);
+}
+
+// One wave computes the generating factors of records U s .. U s + U - 1 of the 64 its lanes have set up:
+// with U = 64 every lane those of its own record, with U = 32 lane (r = lane % 32, h = lane / 32) half of
+// record r's.  esh (log2) scales X.  key: with FOLD the bands of the eight row groups, material |
+// directivity << 8 of the first half group, << 16 of the second; with FOLD 0 the bands of the segments.
+template <int NRB, int FOLD, int U, bool DIR>
+__device__ __forceinline__ void gen_factors_u(const SynthArgs& a, const PairLean& q0, int s, int m, int k1_0, int nk1,
+                                              int lane, float esh, int nseg, const int* __restrict__ key,
+                                              Factors<NRB, FOLD, U>& W) {
+  using FT = Factors<NRB, FOLD, U>;
+  constexpr int NH = 64 / U;                     // lanes per record
+  const int r = lane & (U - 1), h = U == 64 ? 0 : lane / U;
+  PairLean q = q0;
+  if (U != 64) {
+    const int src = U * s + r;
+    q.base = __shfl(q0.base, src); q.slope = __shfl(q0.slope, src); q.gamma = __shfl(q0.gamma, src);
+    q.a32 = (uint32_t)__shfl((int)q0.a32, src);
+    q.bx32 = (uint32_t)__shfl((int)q0.bx32, src);
+    q.by32 = (uint32_t)__shfl((int)q0.by32, src);
+    q.t1 = shfl_ptr(q0.t1, src);
+    q.t2 = shfl_ptr(q0.t2, src);
+    if (DIR) {
+      q.cell.r0 = __shfl(q0.cell.r0, src); q.cell.r1 = __shfl(q0.cell.r1, src);
+      q.cell.i0 = __shfl(q0.cell.i0, src); q.cell.i1 = __shfl(q0.cell.i1, src);
+      q.cell.ta = __shfl(q0.cell.ta, src); q.cell.te = __shfl(q0.cell.te, src);
+    }
+    if (FOLD == 0) q.lbm = __shfl(q0.lbm, src);
+  }
+  const GlobalFloat* dtab = (const GlobalFloat*)a.dir + (size_t)m * a.Bd * a.El * a.Az;
+  const size_t dcells = (size_t)a.El * a.Az;
+  const bool dir = DIR && a.Bd != 0;
+  const float g2 = q.gamma * q.gamma;
+  // Xa is zero for a record that adds nothing (and past the tile); then X is zero whatever the
+  // other factors (finite for every record: a skipped record has slope 0 and phase steps 0)
+  const bool ok = q.base != -INFINITY;
+  const float S = 2.3283064365386963e-10f;   // 2^-32: Q0.32 cycles to revolutions
+  // the groups' log2 band factors: all the table reads at once, in flight while Xb, Ya and Yb are formed
+  constexpr int NG = FT::G / NH;
+  const int j0 = NG * h;
+  float ll[NG], lh[FOLD == 4 ? NG : 1];
+  if (FOLD) {
+    uint32_t kb[NG];
 #pragma unroll
-  for (int t = 0; t < 3; ++t)
+    for (int jj = 0; jj < NG; ++jj) {
+      kb[jj] = (uint32_t)key[j0 + jj];
+      if (U == 64) kb[jj] = (uint32_t)__builtin_amdgcn_readfirstlane((int)kb[jj]);
+    }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int jj = 0; jj < NG; ++jj) {
+      ll[jj] = q.t1[kb[jj] & 255] - g2 * q.t2[kb[jj] & 255];
+      if (FOLD == 4) lh[jj] = q.t1[(kb[jj] >> 16) & 255] - g2 * q.t2[(kb[jj] >> 16) & 255];
+    }
+    if (dir) {
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) acc[t][i][jj] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float E = -INFINITY;   // current exponent bound (uniform over the workgroup)
-  PairLean q;
-  for (int64_t s = 0; s < nst; ++s) {
-    const int t = (int)(s & 7);
-    if (t == 0) {
-      // wave w of stage group g owns records [lo + 256 g + 64 w, +64); sub-stage t takes 8 of them
-      pair_lean(a, P, idx, lo + (s >> 3) * (8 * RB) + wv * 64 + lane, hi, m, q, dmax);
-      const float ub = wave_max(record_bound(q, k1_0, nk1));
-      if (lane == 0) red[wv] = ub;
-      __syncthreads();
-      const float Eg = ceilf(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
-      if (Eg > E) {
-        if (E != -INFINITY) {
-          const float r = exp2f(E - Eg);
-#pragma unroll
-          for (int tt = 0; tt < 3; ++tt)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-              for (int jj = 0; jj < 2; ++jj) acc[tt][i][jj] *= r;
-        }
-        E = Eg;
+      for (int jj = 0; jj < NG; ++jj) {
+        ll[jj] += __builtin_amdgcn_logf(dir_lerp(dtab + ((kb[jj] >> 8) & 255) * dcells, q.cell));
+        if (FOLD == 4) lh[jj] += __builtin_amdgcn_logf(dir_lerp(dtab + (kb[jj] >> 24) * dcells, q.cell));
       }
     }
-    gen_factors<false, FOLD>(a, q, t, m, k1_0, nk1, lane, nseg, st, E != -INFINITY ? XTOP - E : 0.f, wscr[wv], segl,
-                             segh);
-    write_h16<SPLIT, FOLD>(wscr[wv], lane, wv, myseg, segx, buf);
-    __syncthreads();
-    contract_h16<SPLIT>(buf, wv, lane, acc);
-    __syncthreads();
   }
-  // accumulator (i, jj, v) of lane l: row k1 = 16 (rb0 + i) + 4 (l / 16) + v, column k2 = 16 (cb0 + jj) + l % 16
-  const float us = E != -INFINITY ? exp2f(E - XTOP) : 0.f;
-  int rb0, cb0;
-  wave_blocks<SPLIT>(wv, rb0, cb0);
-  float* out = part + (((size_t)p * a.M + m) * a.F) * 2;
+  {
+    // (phases by repeated addition: exact modulo a cycle; with U = 64 the factors 0, which are 1, are written
+    // once by the kernel)
+    constexpr int JJ0 = U == 64 ? 1 : 0;
+    const int i0 = 8 / NH * h;
+    uint32_t pb = (uint32_t)(i0 + JJ0) * q.bx32, pyb = (uint32_t)(i0 + JJ0) * q.by32, pya = 8u * pyb;
+    const uint32_t by8 = 8u * q.by32;
+#pragma unroll 4
+    for (int jj = JJ0; jj < 8 / NH; ++jj) {
+      const int j = i0 + jj;
+      const float fj = (float)j;
+      W.f[FT::XB + j][r] = cexp2((fj * K2) * q.slope, (float)(int32_t)pb * S);
+      W.f[FT::YA + j][r] = cexp2((fj * 8.f) * q.slope, (float)(int32_t)pya * S);
+      W.f[FT::YB + j][r] = cexp2(fj * q.slope, (float)(int32_t)pyb * S);
+      pb += q.bx32;
+      pya += by8;
+      pyb += q.by32;
+    }
+  }
+  {
+    uint32_t pa = q.a32 + (uint32_t)(k1_0 + 8 * j0) * q.bx32;
+    const uint32_t bx8 = 8u * q.bx32;
 #pragma unroll
-  for (int i = 0; i < (SPLIT ? 1 : 2); ++i)
+    for (int jj = 0; jj < NG; ++jj) {
+      const int j = j0 + jj;
+      const float lg0 = q.base + (float)((k1_0 + 8 * j) * K2) * q.slope + esh;
+      const float rev = (float)(int32_t)pa * S;
+      pa += bx8;
+      const float c = __builtin_amdgcn_cosf(rev), sn = __builtin_amdgcn_sinf(rev);
+      // with FOLD the group's (FOLD 4: its halves') band factor rides on Xa, else the record's band bound lbm
+      const float al = ok && 8 * j < nk1 ? __builtin_amdgcn_exp2f(lg0 + (FOLD ? ll[jj] : q.lbm)) : 0.f;
+      W.f[j][r] = make_float2(al * c, al * sn);
+      if (FOLD == 4) {
+        const float ah = ok && 8 * j + 4 < nk1 ? __builtin_amdgcn_exp2f(lg0 + lh[jj]) : 0.f;
+        W.f[FT::XH + j][r] = make_float2(ah * c, ah * sn);
+      }
+    }
+  }
+  if (FOLD == 0) {
+    for (int sg = h; sg < nseg; sg += NH) {
+      const int kb = key[sg];
+      float lb = q.t1[kb & 0xffff] - g2 * q.t2[kb & 0xffff];
+      if (dir) lb += __builtin_amdgcn_logf(dir_lerp(dtab + (kb >> 16) * dcells, q.cell));
+      W.bf[sg][r] = __builtin_amdgcn_exp2f(lb - q.lbm);   // <= 1 (finite for a skipped record too: its Xa is zero)
+    }
+  }
+  // the factors are read back by other lanes of this wave only
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Eight records of one row (X) or bin (Y) as a matrix operand: halves of the real and imaginary parts,
+// records 2 e, 2 e + 1 in u[e].
+union Half8 {
+  halfx8 h;
+  uint32_t u[4];
+};
+struct Operand {
+  Half8 rh, rl, ih, il;
+};
+
+// Two records of an operand's two factors (and their band factors f with FOLD 0), in registers.
+struct Pair2 {
+  float4 a, b;
+  __device__ __forceinline__ void load(const char* pa, const char* pb) {
+    a = *reinterpret_cast<const float4*>(pa);
+    b = *reinterpret_cast<const float4*>(pb);
+  }
+  __device__ __forceinline__ void scale(const char* pf) {
+    const float2 f = *reinterpret_cast<const float2*>(pf);
+    a.x *= f.x; a.y *= f.x;
+    a.z *= f.y; a.w *= f.y;
+  }
+  // the products of the factors (into a), then their halves
+  __device__ __forceinline__ void multiply() {
+    const float2 v0 = cmul(make_float2(a.x, a.y), make_float2(b.x, b.y));
+    const float2 v1 = cmul(make_float2(a.z, a.w), make_float2(b.z, b.w));
+    a = make_float4(v0.x, v0.y, v1.x, v1.y);
+  }
+  __device__ __forceinline__ void split(int e, Operand& o) const {
+    split2(a.x, a.z, o.rh.u[e], o.rl.u[e]);
+    split2(a.y, a.w, o.ih.u[e], o.il.u[e]);
+  }
+};
+
+// One 32 x 32 block and 16 records: Re += Xr Yr - Xi Yi, Im += Xr Yi + Xi Yr, three half products per real
+// product, with slice(k) placed after product k (k < 12): the vector work that the matrix pipe covers.
+template <class G>
+__device__ __forceinline__ void contract12(const Operand& x, const Operand& y, floatx16& re, floatx16& im, G&& slice) {
+  Half8 nx;   // -Xi, its high halves, then its low ones
+#define ET_MM(A, B, C, K)                                              \
+  C = __builtin_amdgcn_mfma_f32_32x32x16_f16(A.h, B.h, C, 0, 0, 0);    \
+  slice(K);                                                            \
+  __builtin_amdgcn_sched_barrier(0)
+  ET_MM(x.rh, y.rh, re, 0);
+  ET_MM(x.rh, y.ih, im, 1);
+  ET_MM(x.rh, y.rl, re, 2);
+  ET_MM(x.rh, y.il, im, 3);
+  ET_MM(x.rl, y.rh, re, 4);
+  ET_MM(x.rl, y.ih, im, 5);
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj)
+  for (int e = 0; e < 4; ++e) nx.u[e] = x.ih.u[e] ^ 0x80008000u;
+  ET_MM(nx, y.ih, re, 6);
+  ET_MM(x.ih, y.rh, im, 7);
+  ET_MM(nx, y.il, re, 8);
+  ET_MM(x.ih, y.rl, im, 9);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int k1 = 16 * (rb0 + i) + (lane >> 4) * 4 + v, k2 = 16 * (cb0 + jj) + (lane & 15);
-        if (k1 < nk1) {
-          const size_t o = (size_t)((k1_0 + k1) * K2 + k2) * 2;
-          out[o] = (acc[0][i][jj][v] - acc[1][i][jj][v]) * us;
-          out[o + 1] = acc[2][i][jj][v] * us;
+  for (int e = 0; e < 4; ++e) nx.u[e] = x.il.u[e] ^ 0x80008000u;
+  ET_MM(nx, y.ih, re, 10);
+  ET_MM(x.il, y.rh, im, 11);
+#undef ET_MM
+}
+
+// Workgroup = (record chunk p, receiver m, tile of 64 rows), four waves, each with records of its own: a
+// wave sets up 64 records (one per lane), writes the generating factors of U of them to its own LDS, and per
+// 16 records forms X and Y straight into the registers that the matrix instruction takes
+// (v_mfma_f32_32x32x16_f16: lane l holds records 8 (l / 32) .. + 7 of row, or bin, l % 32) and contracts the
+// whole 64 x 64 tile, accumulating Re and Im.  The blocks go in serpentine order (X0 Ya, X0 Yb, X1 Yb, X1 Ya,
+// then Yb first), so that one operand is free at a time, and the next one is formed between the twelve
+// products of a block: the matrix pipe works through the forming of the operands.  At the end the
+// four waves' sums are added in wave order and written as the chunk's partial spectrum.
+// What bounds it: per 32 records and receiver about 3100 cycles of a SIMD's matrix pipe and 4500 of its vector
+// unit (products and splits of the operands 1900, factors 1500, set-up 900).  The form before this one
+// shared the operands of four waves through LDS (64 KB read and 32 KB written per 32 records besides the
+// factors, LDS busy two thirds of the time, two barriers per stage, matrix and vector work one after the other).
+// NRB: blocks of 32 rows (1: tiles of at most 32 rows).
+// FOLD 4 (8): every band edge falls on a multiple of 4 (8) outer indices and the grid holds whole groups of
+// that many (bins a multiple of 256, 512): the band factor rides on Xa.  FOLD 0: rows from the row table
+// (any bin count and band layout), a band factor per (segment, record).
+// DIR: some pose has a receiver directivity.
+template <bool BATCH, int NRB, int FOLD, bool DIR>
+__global__ __launch_bounds__(256, 2) void k_synth_mfma(SynthArgs a0, const SynthArgs* __restrict__ jobs,
+                                                                      ChunkTab ct, et_paths P,
+                                                                      const int32_t* __restrict__ idx, const Ctl* ctl,
+                                                                      float* __restrict__ part) {
+  SYNTH_RESOLVE();
+  // records per generation: 64 (a lane per record) where the factors of two workgroups fit a CU's 160 KB
+  constexpr int U = FOLD == 8 || (FOLD == 4 && NRB == 1) ? 64 : 32;
+  using FT = Factors<NRB, FOLD, U>;
+  constexpr size_t FAC_BYTES = sizeof(FT) * 4, SUM_BYTES = sizeof(float2) * 4 * 16 * 64;
+  __shared__ __align__(16) char lds[FAC_BYTES > SUM_BYTES ? FAC_BYTES : SUM_BYTES];
+  __shared__ int key[SMAX];
+  __shared__ float red[4];
+  const int p = bp, m = bm;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hf = lane >> 5;
+  const int v0 = bt * KT1;                       // first row of the tile
+  const int nk = min(KT1, (FOLD ? a.F / K2 : a.nrows) - v0);   // its rows
+  if (nk <= 0) return;                           // (a batch's job with fewer rows than others)
+  int k1_0 = v0, nk1 = nk;                       // outer indices [k1_0, k1_0 + nk1) that the rows fall into
+  int nseg = 0;
+  int rinfo[NRB];                                // FOLD 0: of rows l32 + 32 i: outer index - k1_0 | segment << 8
+  FT& W = reinterpret_cast<FT*>(lds)[wv];
+  if (FOLD) {
+    if (tid < 8) {
+      const int r0 = (k1_0 + min(8 * tid, nk - 1)) * K2, r1 = (k1_0 + min(8 * tid + 4, nk - 1)) * K2;
+      uint32_t kb = (uint32_t)band_of(r0, a.Bk, a.F) | (uint32_t)band_of(r1, a.Bk, a.F) << 16;
+      if (a.Bd) kb |= (uint32_t)band_of(r0, a.Bd, a.F) << 8 | (uint32_t)band_of(r1, a.Bd, a.F) << 24;
+      key[tid] = (int)kb;
+    }
+  } else {
+    const int2 row = a.rows[v0 + min(lane, nk - 1)];
+    k1_0 = __shfl(row.x, 0) >> 6;
+    nk1 = (__shfl(row.x, 63) >> 6) - k1_0 + 1;
+    const int prev = __shfl(row.y, (lane + 63) & 63);
+    const uint64_t sm = __ballot(lane == 0 || (lane < nk && row.y != prev));
+    const int seg = __popcll(sm & (~0ull >> (63 - lane))) - 1;
+    nseg = min(__popcll(sm), SMAX);
+    if (wv == 0 && ((sm >> lane) & 1) && seg < SMAX) key[seg] = row.y;
+    const int info = ((row.x >> 6) - k1_0) | (lane < nk ? min(seg, SMAX - 1) : nseg) << 8;
+#pragma unroll
+    for (int i = 0; i < NRB; ++i) rinfo[i] = __shfl(info, l32 + 32 * i);
+    if (hf == 0) W.bf[nseg][l32] = 0.f;   // rows past the tile take the extra segment, whose factor is zero
+  }
+  if (U == 64) W.f[FT::XB][lane] = W.f[FT::YA][lane] = W.f[FT::YB][lane] = make_float2(1.f, 0.f);
+  __syncthreads();
+  const float dmax = DIR ? dir_log2_max(a, m, tid, red) : 0.f;
+  const bool two = NRB == 2 && nk > 32;          // rows in the second block
+  floatx16 acc[2][NRB][2];                       // [re, im][row block][column block]
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int i = 0; i < NRB; ++i)
+#pragma unroll
+      for (int jc = 0; jc < 2; ++jc)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[c][i][jc][v] = 0.f;
+  float E = -INFINITY;   // current exponent bound of the wave
+  // the wave's share of the chunk: whole pairs of steps, 32 records
+  const int64_t pw = ((hi - lo + 3) / 4 + 31) / 32 * 32;
+  const int64_t wlo = lo + wv * pw, whi = min(wlo + pw, hi);
+  int64_t rec = 0;       // this lane's record of the group (the range's last one past its end), read a group ahead
+  if (wlo < whi) rec = record_at(idx, min(wlo + lane, whi - 1));
+  for (int64_t g = wlo; g < whi; g += 64) {
+    PairLean q;
+    pair_fwd<DIR>(a, P, rec, g + lane < whi, m, dmax, q);
+    rec = record_at(idx, min(g + 64 + lane, whi - 1));
+    const float Eg = ceilf(wave_max(record_bound(q, k1_0, nk1)));
+    if (Eg > E) {
+      if (E != -INFINITY) {
+        const float r = exp2f(E - Eg);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int i = 0; i < NRB; ++i)
+#pragma unroll
+            for (int jc = 0; jc < 2; ++jc) acc[c][i][jc] *= r;
+      }
+      E = Eg;
+    }
+    const float esh = E != -INFINITY ? XTOP - E : 0.f;
+    const int nrec = (int)min<int64_t>(64, whi - g);
+    for (int s = 0; U * s < nrec; ++s) {
+      gen_factors_u<NRB, FOLD, U, DIR>(a, q, s, m, k1_0, nk1, lane, esh, nseg, key, W);
+      const int steps = (min(U, nrec - U * s) + 31) / 32 * 2;   // of 16 records, in pairs
+      // Where the factors of this lane's operands lie for its records (8 hf .. + 7) of a step: bin l32 + 32 jc, row
+      // l32 + 32 i; o: the step's and the pair's offset.  (Formed here, from a lane number that the compiler
+      // cannot carry over, so that the addresses hold no registers while the factors are generated.)
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      constexpr int ROW = sizeof(W.f[0]), STEP = 16 * sizeof(float2);
+      const int lb = ln & 31, lh8 = 8 * (ln >> 5);
+      const char* const wb = reinterpret_cast<const char*>(&W) + lh8 * sizeof(float2);
+      const char* const py_a = wb + (FT::YA + (lb >> 3)) * ROW;
+      const char* const py_b = wb + (FT::YB + (lb & 7)) * ROW;
+      const char *px_a[NRB], *px_b[NRB], *px_f[NRB];
+#pragma unroll
+      for (int i = 0; i < NRB; ++i) {
+        const int ri = FOLD ? 0 : rinfo[i];
+        const int ga = FOLD ? (lb >> 3) + 4 * i : (ri & 63) >> 3, gb = FOLD ? lb & 7 : ri & 7;
+        px_a[i] = wb + (FOLD == 4 && (lb & 4) ? FT::XH + ga : ga) * ROW;
+        px_b[i] = wb + (FT::XB + gb) * ROW;
+        px_f[i] = reinterpret_cast<const char*>(&W.bf[FOLD == 0 ? ri >> 8 : 0][0]) + lh8 * sizeof(float);
+      }
+      auto load_y = [&](Pair2& t, int jc, int o, int e) { t.load(py_a + 4 * jc * ROW + o + 16 * e, py_b + o + 16 * e); };
+      auto load_x = [&](Pair2& t, int i, int o, int e) {
+        const int ii = i < NRB ? i : 0;
+        if (FOLD) t.load(px_a[0] + 4 * ii * ROW + o + 16 * e, px_b[0] + o + 16 * e);
+        else t.load(px_a[ii] + o + 16 * e, px_b[ii] + o + 16 * e);
+      };
+      auto scale_x = [&](Pair2& t, int i, int o, int e) { if (FOLD == 0) t.scale(px_f[i < NRB ? i : 0] + o / 2 + 8 * e); };
+      Operand x0, x1, ya, yb;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        Pair2 t, u;
+        load_x(t, 0, 0, e);
+        load_y(u, 0, 0, e);
+        scale_x(t, 0, 0, e);
+        t.multiply();
+        u.multiply();
+        t.split(e, x0);
+        u.split(e, ya);
+      }
+      // The slices of a block that form one operand: two records at a time, loaded three products ahead,
+      // multiplied after one product and split after the next (about seven vector instructions per product,
+      // which take as long as the product does).
+      Pair2 t[2];
+#define ET_SLICE_Y(JC, O, DST)                                                      \
+  [&](int k) {                                                                      \
+    if (k >= 4 && k % 2 == 0 && k <= 10) t[(k - 4) / 2 % 2].split((k - 4) / 2, DST); \
+    if (k % 2 == 0 && k < 8) load_y(t[k / 2 % 2], JC, O, k / 2);                    \
+    if (k >= 3 && k % 2 == 1 && k <= 9) t[(k - 3) / 2 % 2].multiply();              \
+  }
+#define ET_SLICE_X(I, O, DST)                                                       \
+  [&](int k) {                                                                      \
+    if (k >= 4 && k % 2 == 0 && k <= 10) t[(k - 4) / 2 % 2].split((k - 4) / 2, DST); \
+    if (k % 2 == 0 && k < 8) load_x(t[k / 2 % 2], I, O, k / 2);                     \
+    if (k >= 3 && k % 2 == 1 && k <= 9) {                                           \
+      scale_x(t[(k - 3) / 2 % 2], I, O, (k - 3) / 2);                               \
+      t[(k - 3) / 2 % 2].multiply();                                                \
+    }                                                                               \
+  }
+      if constexpr (NRB == 2) {
+        for (int st = 0; st < steps; st += 2) {
+          const int o = st * STEP, on = o + STEP, onn = st + 2 < steps ? o + 2 * STEP : o;
+          contract12(x0, ya, acc[0][0][0], acc[1][0][0], ET_SLICE_Y(1, o, yb));
+          contract12(x0, yb, acc[0][0][1], acc[1][0][1], ET_SLICE_X(1, o, x1));
+          contract12(x1, yb, acc[0][NRB - 1][1], acc[1][NRB - 1][1], ET_SLICE_X(0, on, x0));
+          contract12(x1, ya, acc[0][NRB - 1][0], acc[1][NRB - 1][0], ET_SLICE_Y(1, on, yb));
+          contract12(x0, yb, acc[0][0][1], acc[1][0][1], ET_SLICE_Y(0, on, ya));
+          contract12(x0, ya, acc[0][0][0], acc[1][0][0], ET_SLICE_X(1, on, x1));
+          contract12(x1, ya, acc[0][NRB - 1][0], acc[1][NRB - 1][0], ET_SLICE_X(0, onn, x0));
+          contract12(x1, yb, acc[0][NRB - 1][1], acc[1][NRB - 1][1], ET_SLICE_Y(0, onn, ya));
+        }
+      } else {
+        Pair2 u[2];
+        Operand y1;
+        for (int st = 0; st < steps; ++st) {
+          const int o = st * STEP, on = st + 1 < steps ? o + STEP : o;
+          contract12(x0, ya, acc[0][0][0], acc[1][0][0], ET_SLICE_Y(1, o, yb));
+          contract12(x0, yb, acc[0][0][1], acc[1][0][1], [&](int k) {
+            if (k >= 4 && k % 2 == 0 && k <= 10) {
+              t[(k - 4) / 2 % 2].split((k - 4) / 2, x1);
+              u[(k - 4) / 2 % 2].split((k - 4) / 2, y1);
+            }
+            if (k % 2 == 0 && k < 8) {
+              load_x(t[k / 2 % 2], 0, on, k / 2);
+              load_y(u[k / 2 % 2], 0, on, k / 2);
+            }
+            if (k >= 3 && k % 2 == 1 && k <= 9) {
+              scale_x(t[(k - 3) / 2 % 2], 0, on, (k - 3) / 2);
+              t[(k - 3) / 2 % 2].multiply();
+              u[(k - 3) / 2 % 2].multiply();
+            }
+          });
+          x0 = x1;
+          ya = y1;
         }
       }
+#undef ET_SLICE_X
+#undef ET_SLICE_Y
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // the factors are rewritten next
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  // accumulator v of lane l in block (i, jc): row 32 i + 8 (v / 4) + 4 (l / 32) + v % 4, bin 32 jc + l % 32 of the
+  // row's 64; the four waves' values are added in wave order, a block at a time
+  const float us = E != -INFINITY ? exp2f(E - XTOP) : 0.f;
+  float2* sums = reinterpret_cast<float2*>(lds);   // [wave][v][lane]
+  float2* out = reinterpret_cast<float2*>(part + (((size_t)p * a.M + m) * a.F) * 2);
+#pragma unroll
+  for (int i = 0; i < NRB; ++i) {
+    if (i == 1 && !two) break;
+#pragma unroll
+    for (int jc = 0; jc < 2; ++jc) {
+      __syncthreads();
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        sums[(wv * 16 + v) * 64 + lane] = make_float2(acc[0][i][jc][v] * us, acc[1][i][jc][v] * us);
+      __syncthreads();
+#pragma unroll
+      for (int e0 = 0; e0 < 1024; e0 += 256) {
+        const int e = e0 + tid, v = e >> 6, l = e & 63;
+        const int row = 32 * i + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3), k2 = 32 * jc + (l & 31);
+        if (row < nk) {
+          int k = (k1_0 + row) * K2 + k2;
+          bool in = true;
+          if (FOLD == 0) {
+            const int r0 = a.rows[v0 + row].x, r1 = a.rows[v0 + row + 1].x;
+            k = (r0 & ~(K2 - 1)) + k2;
+            in = k >= r0 && k < r1;
+          }
+          if (in) {
+            float2 t = sums[e];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+              const float2 o = sums[w * 1024 + e];
+              t.x += o.x;
+              t.y += o.y;
+            }
+            out[k] = t;
+          }
+        }
+      }
+    }
+  }
 }
 
 // ------------------------------------------------------------------ direct kernel
@@ -1020,12 +1355,54 @@ __global__ __launch_bounds__(DB) void k_synth_direct(SynthArgs a0, const SynthAr
   }
 }
 
-__global__ void k_reduce_partials(const float* __restrict__ part, int32_t P, int64_t MF2, float* __restrict__ out) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < MF2; i += (int64_t)gridDim.x * blockDim.x) {
-    float s = 0.f;
-    for (int p = 0; p < P; ++p) s += part[(size_t)p * MF2 + i];
+// Sum of the chunks' partial spectra: a workgroup takes 64 complex outputs, its S waves the chunks w,
+// w + S, ... each (eight loads in flight), and the S sums are added in wave order, so the result does not
+// depend on scheduling.  S = 16 while the outputs alone leave the chip idle: one thread per output walked
+// its 256 chunks one load after the other (68 us for 2 x 1024 bins).
+template <int S>
+__global__ __launch_bounds__(64 * S) void k_reduce_partials(const float2* __restrict__ part, int32_t P, int64_t MF,
+                                                            float2* __restrict__ out) {
+  __shared__ float2 red[S][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  float2 s = make_float2(0.f, 0.f);
+  if (i < MF) {
+    int c = w;
+    for (; c + 7 * S < P; c += 8 * S) {
+      float2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(c + u * S) * MF + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        s.x += v[u].x;
+        s.y += v[u].y;
+      }
+    }
+    for (; c < P; c += S) {
+      const float2 v = part[(size_t)c * MF + i];
+      s.x += v.x;
+      s.y += v.y;
+    }
+  }
+  red[w][lane] = s;
+  __syncthreads();
+  if (w == 0 && i < MF) {
+#pragma unroll
+    for (int k = 1; k < S; ++k) {
+      s.x += red[k][lane].x;
+      s.y += red[k][lane].y;
+    }
     out[i] = s;
   }
+}
+
+void reduce_partials(const float* part, int32_t P, int64_t MF, float* out, hipStream_t s) {
+  const unsigned nb = (unsigned)((MF + 63) / 64);
+  // sixteen waves per 64 outputs up to 64 K outputs (1024 workgroups of sixteen waves fill the chip twice)
+  if (MF <= 65536 && P > 8)
+    k_reduce_partials<16><<<nb, 1024, 0, s>>>((const float2*)part, P, MF, (float2*)out);
+  else
+    k_reduce_partials<4><<<nb, 256, 0, s>>>((const float2*)part, P, MF, (float2*)out);
 }
 
 // ------------------------------------------------------------------ adjoint
@@ -1269,10 +1646,6 @@ __device__ inline void write_bwd(const WaveScratch& W, int lane, int wv, BwdBuf&
 
 // Sum of v over each group of 8 consecutive lanes, valid in the group's first lane, added as
 // ((v0 + v1) + (v2 + v3)) + ((v4 + v5) + (v6 + v7)) by lane moves within rows of 16 (no LDS).
-template <int CTRL>
-__device__ inline float dpp_mov(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
-}
 __device__ inline float sum8_first(float v) {
   v += dpp_mov<0xB1>(v);    // quad_perm [1, 0, 3, 2]: lane ^ 1
   v += dpp_mov<0x4E>(v);    // quad_perm [2, 3, 0, 1]: lane ^ 2
@@ -1444,7 +1817,7 @@ __global__ __launch_bounds__(256, 2) void k_synth_bwd_mfma(SynthArgs a0, const S
   PairLean q;
   for (int64_t s = 0; s < nst; ++s) {
     const int t = (int)(s & 7);
-    if (t == 0) pair_lean<true>(a, P, idx, lo + (s >> 3) * (8 * RB) + wv * 64 + lane, hi, m, q);
+    if (t == 0) pair_adj(a, P, idx, lo + (s >> 3) * (8 * RB) + wv * 64 + lane, hi, m, q);
     gen_factors<true, FOLD>(a, q, t, m, k1_0, nk1, lane, nseg, st, 0.f, wscr[wv], segl, segh);
     write_bwd(wscr[wv], lane, wv, bb);
     {
@@ -1674,13 +2047,15 @@ __global__ __launch_bounds__(RED_T) void k_bwd_reduce(const double* __restrict__
 
 inline size_t al(size_t b) { return (b + 255) / 256 * 256; }
 
+// Tiles of at most 64 rows of a pose's spectrum.
+int64_t row_tiles(const et_sim_desc* sim) { return ((int64_t)synth_rows(sim, nullptr) + KT1 - 1) / KT1; }
+
 int choose_P(const et_sim_desc* sim, int64_t cap, bool mfma) {
   // matrix-core kernels: about sixteen workgroups per CU over the launch (measured on the
-  // room's 32 x 4096 forward and adjoint: 2048 workgroups 11.20 / 20.16 ms, 3072 10.90 / 20.05,
-  // 4096 10.76 / 19.87, 6144 10.75 / 19.98, 8192 10.73 / 19.92 ms).  Chunk count a multiple of 8
-  // so that every receiver's workgroups of one chunk share an XCD's L2.
-  const int64_t tiles = mfma ? (int64_t)sim->M * std::max<int64_t>(1, (sim->F / K2 + KT1 - 1) / KT1)
-                             : (int64_t)sim->M * ((sim->F + DTILE - 1) / DTILE);
+  // room's 32 x 4096 adjoint: 2048 workgroups 20.16 ms, 3072 20.05, 4096 19.87, 6144 19.98, 8192
+  // 19.92 ms).  Chunk count a multiple of 8 so that every receiver's workgroups of one chunk share an
+  // XCD's L2.
+  const int64_t tiles = (int64_t)sim->M * (mfma ? row_tiles(sim) : (sim->F + DTILE - 1) / DTILE);
   const int64_t target = mfma ? 4096 : 2048;
   int64_t P = std::max<int64_t>(1, (target + tiles - 1) / tiles);
   if (P >= 8) P = (P + 7) / 8 * 8;
@@ -1697,14 +2072,17 @@ size_t vis_ws(int64_t cap, char* base, size_t off, uint64_t** fl, uint64_t** of,
   return off;
 }
 
-void build_tables(SynthArgs& a, const SynthWS& ws, hipStream_t s) {
+// rows: the row table is needed (the factorised kernels' FOLD 0)
+void build_tables(SynthArgs& a, const SynthWS& ws, bool rows, hipStream_t s) {
   a.lk = ws.lk;
   a.lc = ws.lc;
   a.ld = ws.ld;
   a.lp = ws.lp;
   a.lmax = ws.lmax;
   const int n = a.Q * a.Bk;
-  k_band_tables<<<(n + 255) / 256, 256, 0, s>>>(a, ws.lk, ws.lc, ws.ld, ws.lp, ws.lmax);
+  a.rows = rows ? (const int2*)ws.rows : nullptr;
+  k_band_tables<<<(n + 255) / 256 + (rows ? 1 : 0), 256, 0, s>>>(a, ws.lk, ws.lc, ws.ld, ws.lp, ws.lmax,
+                                                                 rows ? (int2*)ws.rows : nullptr);
 }
 
 // Path-product reading: band tables with a row per record.  Specular record n: the sum of
@@ -1765,6 +2143,8 @@ size_t table_ws(const et_sim_desc* sim, char* base, size_t off, SynthWS& w) {
   off += al(sizeof(float) * sim->Bk);
   w.lmax = (float*)(base ? base + off : nullptr);
   off += al(sizeof(float) * (3 * (size_t)sim->Q + 1));
+  w.rows = base ? base + off : nullptr;
+  off += al(sizeof(int2) * ((size_t)synth_rows(sim, nullptr) + 1));
   return off;
 }
 
@@ -1784,7 +2164,7 @@ struct SynthJobPack {
   SynthArgs j[SJOB_PACK];
   int32_t first, n;
 };
-static_assert(sizeof(SynthJobPack) <= 4000, "job pack must fit the kernel argument space");
+static_assert(sizeof(SynthJobPack) <= 4032, "job pack must fit the kernel argument space");
 
 __global__ void k_put_synth_jobs(SynthJobPack pk, SynthArgs* __restrict__ dst) {
   if ((int)threadIdx.x < pk.n) dst[pk.first + threadIdx.x] = pk.j[threadIdx.x];
@@ -1797,6 +2177,7 @@ __global__ void k_band_tables_batch(const SynthArgs* __restrict__ jobs) {
     band_table_entry(a, i, const_cast<float*>(a.lk), const_cast<float*>(a.lc), const_cast<float*>(a.ld),
                      const_cast<float*>(a.lp));
   for (int q = threadIdx.x; q < a.Q; q += blockDim.x) band_bound_entry(a, q, const_cast<float*>(a.lmax));
+  if (a.rows) row_table(a, const_cast<int2*>(a.rows));
 }
 
 // sort key of each visible record: its job (the ray field of a batch record)
@@ -1880,7 +2261,7 @@ __global__ void k_bwd_reduce_batch(const double* __restrict__ gpx, const double*
 // the bins a multiple of 64 g.
 bool bands_on_groups(const et_sim_desc* sim, int64_t g) {
   const int64_t F = sim->F, Bk = sim->Bk, Bd = sim->directivity ? sim->Bd : 0, K1 = F / K2;
-  if (K1 % g) return false;
+  if (F % (K2 * g)) return false;
   for (int64_t k1 = 1; k1 < K1; ++k1) {
     if (k1 % g == 0) continue;
     const int64_t k = k1 * K2, kp = k - K2;
@@ -1895,21 +2276,40 @@ bool bands_on_groups(const et_sim_desc* sim, int64_t g) {
 // of band factors) otherwise.
 int bands_fold(const et_sim_desc* sim) { return bands_on_groups(sim, 8) ? 8 : bands_on_groups(sim, 4) ? 4 : 0; }
 
-template <bool BATCH, bool SPLIT>
+template <bool BATCH, int NRB, bool DIR>
 void launch_fwd_fold(int fold, dim3 grid, hipStream_t s, const SynthArgs& a, const SynthArgs* jobs, const ChunkTab& ct,
                      const et_paths& P, const int32_t* idx, const Ctl* ctl, float* part) {
-  if (fold == 8) k_synth_mfma<BATCH, SPLIT, 8><<<grid, 256, 0, s>>>(a, jobs, ct, P, idx, ctl, part);
-  else if (fold == 4) k_synth_mfma<BATCH, SPLIT, 4><<<grid, 256, 0, s>>>(a, jobs, ct, P, idx, ctl, part);
-  else k_synth_mfma<BATCH, SPLIT, 0><<<grid, 256, 0, s>>>(a, jobs, ct, P, idx, ctl, part);
+  if (fold == 8) k_synth_mfma<BATCH, NRB, 8, DIR><<<grid, 256, 0, s>>>(a, jobs, ct, P, idx, ctl, part);
+  else if (fold == 4) k_synth_mfma<BATCH, NRB, 4, DIR><<<grid, 256, 0, s>>>(a, jobs, ct, P, idx, ctl, part);
+  else k_synth_mfma<BATCH, NRB, 0, DIR><<<grid, 256, 0, s>>>(a, jobs, ct, P, idx, ctl, part);
 }
 
+// rows: the most rows of a job; tiles of 64 rows, or one block of 32 when that holds them all
 template <bool BATCH>
-void launch_fwd_mfma(bool split, int fold, dim3 grid, hipStream_t s, const SynthArgs& a, const SynthArgs* jobs,
-                     const ChunkTab& ct, const et_paths& P, const int32_t* idx, const Ctl* ctl, float* part) {
-  if (split) launch_fwd_fold<BATCH, true>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
-  else launch_fwd_fold<BATCH, false>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+void launch_fwd_mfma(int rows, int fold, bool dir, int chunks, int M, hipStream_t s, const SynthArgs& a,
+                     const SynthArgs* jobs, const ChunkTab& ct, const et_paths& P, const int32_t* idx, const Ctl* ctl,
+                     float* part) {
+  const dim3 grid(chunks, M, (rows + KT1 - 1) / KT1);
+  if (rows <= 32) {
+    if (dir) launch_fwd_fold<BATCH, 1, true>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+    else launch_fwd_fold<BATCH, 1, false>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+  } else {
+    if (dir) launch_fwd_fold<BATCH, 2, true>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+    else launch_fwd_fold<BATCH, 2, false>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+  }
 }
 
+// The forward synthesis runs on the matrix cores for every band layout whose tiles of 64 rows hold at
+// most SMAX band segments (their factors sit in LDS per segment): per term (k_synth_direct) the 60,000
+// records x 6 receivers x 3000 bins in 7 bands take 540 us, most of it three transcendentals per term.
+bool synth_rows_ok(const et_sim_desc* sim) {
+  if (sim->flags & ET_SYNTH_DIRECT) return false;
+  int seg = 0;
+  synth_rows(sim, &seg);
+  return seg <= SMAX;
+}
+
+// Bands on whole runs of 64 bins: what et_stats reports as kernel 1, and what the factorised adjoint takes.
 bool synth_factorised_ok(const et_sim_desc* sim) {
   // needs k = 64 k1 + k2, material / directivity bands constant over each run of 64 bins
   // (the band factor is per outer index), and at most SMAX band segments per tile of KT1
@@ -1935,8 +2335,7 @@ bool synth_factorised_ok(const et_sim_desc* sim) {
 
 size_t synth_ws_layout(const et_sim_desc* sim, int64_t cap, char* base, SynthWS* ws) {
   cap = std::max<int64_t>(cap, 1);
-  const bool mf = synth_factorised_ok(sim);
-  const int P = choose_P(sim, cap, mf);
+  const int P = choose_P(sim, cap, synth_rows_ok(sim));
   size_t off = 0;
   SynthWS w{};
   w.P = P;
@@ -1957,34 +2356,32 @@ size_t synth_ws_layout(const et_sim_desc* sim, int64_t cap, char* base, SynthWS*
 
 int synth_run(const et_sim_desc* sim, const et_paths* paths, const SynthWS& ws, Ctl* ctl, float* spectra, hipStream_t s,
               hipEvent_t kb, hipEvent_t ke) {
-  const bool mf = synth_factorised_ok(sim);
+  const bool mf = synth_rows_ok(sim);
+  const int fold = mf ? bands_fold(sim) : 0;
   SynthArgs a = make_args(sim, ws.P);
   const et_paths P = *paths;
   build_vis(P, ws, ws.cap, ctl, s);
-  build_tables(a, ws, s);
+  build_tables(a, ws, mf && fold == 0, s);
   set_readings(a, sim, P, ws, ctl, s);
   if (kb) ET_HIP(hipEventRecord(kb, s));
   if (mf) {
-    const int K1 = sim->F / K2;
-    dim3 grid(ws.P, sim->M, (K1 + KT1 - 1) / KT1);
-    launch_fwd_mfma<false>(K1 <= 32, bands_fold(sim), grid, s, a, nullptr, ChunkTab{}, P, ws.vidx, ctl,
-                           ws.partial);
+    launch_fwd_mfma<false>(a.nrows, fold, sim->directivity != nullptr, ws.P, sim->M, s, a, nullptr, ChunkTab{}, P, ws.vidx, ctl, ws.partial);
   } else {
     dim3 grid(ws.P, sim->M, (sim->F + DTILE - 1) / DTILE);
     k_synth_direct<false><<<grid, DB, 0, s>>>(a, nullptr, ChunkTab{}, P, ws.vidx, ctl, ws.partial);
   }
   if (ke) ET_HIP(hipEventRecord(ke, s));
-  const int64_t MF2 = (int64_t)sim->M * sim->F * 2;
-  k_reduce_partials<<<(unsigned)std::min<int64_t>((MF2 + 255) / 256, 4096), 256, 0, s>>>(ws.partial, ws.P, MF2, spectra);
+  reduce_partials(ws.partial, ws.P, (int64_t)sim->M * sim->F, spectra, s);
   ET_HIP(hipGetLastError());
-  return mf ? 1 : 2;
+  return synth_factorised_ok(sim) ? 1 : 2;
 }
 
 int synth_run_noalloc(const et_sim_desc* sim, const et_paths* paths, void* buf, size_t bytes, Ctl* ctl,
                       float* spectra, hipStream_t s, hipEvent_t kb, hipEvent_t ke) {
   ET_CHECK(!(sim->flags & ET_PATH_PRODUCT), ET_E_UNSUPPORTED,
            "ET_PATH_PRODUCT needs per-record tables (a workspace): use et_synthesize");
-  const bool mf = synth_factorised_ok(sim);
+  const bool mf = synth_rows_ok(sim);
+  const int fold = mf ? bands_fold(sim) : 0;
   const int64_t cap = std::max<int64_t>(paths->capacity, 1);
   SynthWS w{};
   const size_t tables = table_ws(sim, nullptr, 0, w);
@@ -2002,23 +2399,19 @@ int synth_run_noalloc(const et_sim_desc* sim, const et_paths* paths, void* buf, 
   SynthArgs a = make_args(sim, w.P);
   const et_paths Pth = *paths;
   k_vis_all<<<1, 1, 0, s>>>(ctl);
-  build_tables(a, w, s);
+  build_tables(a, w, mf && fold == 0, s);
   a.rxv = (sim->flags & ET_PER_RX_VISIBILITY) ? Pth.rx_vis : nullptr;
   if (kb) ET_HIP(hipEventRecord(kb, s));
   if (mf) {
-    const int K1 = sim->F / K2;
-    dim3 grid(w.P, sim->M, (K1 + KT1 - 1) / KT1);
-    launch_fwd_mfma<false>(K1 <= 32, bands_fold(sim), grid, s, a, nullptr, ChunkTab{}, Pth, nullptr, ctl,
-                           w.partial);
+    launch_fwd_mfma<false>(a.nrows, fold, sim->directivity != nullptr, w.P, sim->M, s, a, nullptr, ChunkTab{}, Pth, nullptr, ctl, w.partial);
   } else {
     dim3 grid(w.P, sim->M, (sim->F + DTILE - 1) / DTILE);
     k_synth_direct<false><<<grid, DB, 0, s>>>(a, nullptr, ChunkTab{}, Pth, nullptr, ctl, w.partial);
   }
   if (ke) ET_HIP(hipEventRecord(ke, s));
-  const int64_t MF2 = (int64_t)sim->M * sim->F * 2;
-  k_reduce_partials<<<(unsigned)std::min<int64_t>((MF2 + 255) / 256, 4096), 256, 0, s>>>(w.partial, w.P, MF2, spectra);
+  reduce_partials(w.partial, w.P, (int64_t)sim->M * sim->F, spectra, s);
   ET_HIP(hipGetLastError());
-  return mf ? 1 : 2;
+  return synth_factorised_ok(sim) ? 1 : 2;
 }
 
 bool synth_bwd_factorised_ok(const et_sim_desc* sim) { return !sim->directivity && synth_factorised_ok(sim); }
@@ -2073,7 +2466,7 @@ int synth_bwd_run(const et_sim_desc* sim, const et_paths* paths, const float* gr
   SynthArgs a = make_args(sim, ws.gchunks);
   const et_paths P = *paths;
   build_vis(P, ws, ws.cap, ctl, s);
-  build_tables(a, ws, s);
+  build_tables(a, ws, false, s);
   a.rxv = (sim->flags & ET_PER_RX_VISIBILITY) ? P.rx_vis : nullptr;   // (no path product in the adjoint)
   if (kb) ET_HIP(hipEventRecord(kb, s));
   if (mf) {
@@ -2100,8 +2493,7 @@ int synth_bwd_run(const et_sim_desc* sim, const et_paths* paths, const float* gr
 namespace {
 int chunk_target(const et_sim_desc* s0, bool mf, int32_t wgs) {
   // record chunks over the whole batch for about `wgs` workgroups of the main kernel
-  const int64_t per_chunk = mf ? (int64_t)s0->M * std::max<int64_t>(1, (s0->F / K2 + KT1 - 1) / KT1)
-                               : (int64_t)s0->M * ((s0->F + DTILE - 1) / DTILE);
+  const int64_t per_chunk = (int64_t)s0->M * (mf ? row_tiles(s0) : (s0->F + DTILE - 1) / DTILE);
   return (int)std::max<int64_t>(1, (wgs + per_chunk - 1) / per_chunk);
 }
 }  // namespace
@@ -2119,7 +2511,12 @@ size_t synth_batch_ws_layout(int32_t J, const et_job* jobs, int64_t cap, const B
   SynthBatchWS w{};
   w.J = J;
   w.cap = cap;
-  w.mf = synth_batch_factorised(J, jobs, false);
+  w.mf = true;
+  w.rows = 0;
+  for (int32_t i = 0; i < J; ++i) {
+    w.mf = w.mf && synth_rows_ok(jobs[i].sim);
+    w.rows = std::max(w.rows, synth_rows(jobs[i].sim, nullptr));
+  }
   w.mf_bwd = adjoint && synth_batch_factorised(J, jobs, true);
   w.fold = 8;   // the coarsest folding every job allows
   for (int32_t i = 0; i < J; ++i) w.fold = std::min(w.fold, bands_fold(jobs[i].sim));
@@ -2147,6 +2544,7 @@ size_t synth_batch_ws_layout(int32_t J, const et_job* jobs, int64_t cap, const B
   w.tab = (int64_t*)take(sizeof(int64_t) * (size_t)(3 * J + 2) * 2);
   w.jobs = take(sizeof(SynthArgs) * (size_t)J);
   w.tables = (float*)take(sizeof(float) * (size_t)J * (4 * (size_t)s0->Q * s0->Bk + 3 * s0->Q + 1));
+  w.row_tables = take(sizeof(int2) * (size_t)J * (w.rows + 1));
   if (ws) *ws = w;
   return off;
 }
@@ -2174,6 +2572,7 @@ int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const 
     a.ld = a.lc + QB;
     a.lp = a.ld + QB;
     a.lmax = a.lp + QB;
+    if (w.mf && w.fold == 0) a.rows = (const int2*)w.row_tables + (size_t)i * (w.rows + 1);
     pk.j[pk.n++] = a;
     if (pk.n == SJOB_PACK || i + 1 == J) {
       k_put_synth_jobs<<<1, SJOB_PACK, 0, s>>>(pk, dj);
@@ -2200,8 +2599,9 @@ int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const 
     const SynthArgs a0 = make_args(s0, 0);
     if (ev) ET_HIP(hipEventRecord(ev[0], s));
     if (w.mf) {
-      dim3 grid(w.chunks, s0->M, (s0->F / K2 + KT1 - 1) / KT1);
-      launch_fwd_mfma<true>(s0->F / K2 <= 32, w.fold, grid, s, a0, dj, ct, P, w.vidx, ctl, w.partial);
+      bool dir = false;
+      for (int32_t i = 0; i < J; ++i) dir = dir || jobs[i].sim->directivity != nullptr;
+      launch_fwd_mfma<true>(w.rows, w.fold, dir, w.chunks, s0->M, s, a0, dj, ct, P, w.vidx, ctl, w.partial);
     } else {
       dim3 grid(w.chunks, s0->M, (s0->F + DTILE - 1) / DTILE);
       k_synth_direct<true><<<grid, DB, 0, s>>>(a0, dj, ct, P, w.vidx, ctl, w.partial);
@@ -2231,7 +2631,7 @@ int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const 
     if (adjoint_kernel) *adjoint_kernel = w.mf_bwd ? 1 : 2;
   }
   ET_HIP(hipGetLastError());
-  return w.mf ? 1 : 2;
+  return synth_batch_factorised(J, jobs, false) ? 1 : 2;
 }
 
 __global__ void k_sum_spectra(const float* __restrict__ in, int32_t J, int64_t n, float* __restrict__ out) {

@@ -136,6 +136,9 @@ int64_t diff_draws_max(const et_sim_desc* s) {
   return s->diff_K * ((s->flags & ET_DIFF_PER_MESH) ? s->diff_max_meshes : 1);
 }
 
+// Line-of-sight rays per specular record.
+int32_t los_rays(const et_sim_desc* s) { return (s->flags & ET_PER_RX_VISIBILITY) ? s->M : 1; }
+
 int64_t records_upper_bound(const et_sim_desc* s) {
   int64_t n = 0;
   if (s->flags & ET_SPECULAR) n += s->N * (int64_t)s->max_bounces;
@@ -168,7 +171,7 @@ WsPlan plan(const et_scene* sc, const et_sim_desc* s, int64_t cap) {
   WsPlan w;
   const int64_t N = (s->flags & ET_SPECULAR) ? s->N : 0;
   const int64_t K = diff_draws_max(s);
-  if (sc) w.trace = al(trace_ws_layout(N, sc->d.T, sc->d.n_obj, K, nullptr, nullptr));
+  if (sc) w.trace = al(trace_ws_layout(N, sc->d.T, sc->d.n_obj, K, nullptr, nullptr, 0, los_rays(s)));
   w.synth = al(synth_ws_layout(s, cap, nullptr, nullptr));
   w.bwd = al(synth_bwd_ws_layout(s, cap, nullptr, nullptr));
   return w;
@@ -270,7 +273,7 @@ void trace_impl(et_ctx* ctx, const et_scene* sc, const et_sim_desc* sim, void* w
   ET_CHECK(ws_bytes >= w.trace, ET_E_WORKSPACE, "workspace too small for et_trace");
   TraceWS tw;
   trace_ws_layout((sim->flags & ET_SPECULAR) ? sim->N : 0, sc->d.T, sc->d.n_obj, diff_draws_max(sim), (char*)ws,
-                  &tw);
+                  &tw, 0, los_rays(sim));
   tw.stack_cap = ctx->stack_cap;
   ET_HIP(hipEventRecord(ctx->ev[0], ctx->stream));
   trace_run(sc->d, sim, paths, tw, ctx->ctl, ctx->counting, ctx->stream);
@@ -294,12 +297,6 @@ void synth_impl(et_ctx* ctx, const et_sim_desc* sim, const et_paths* paths, void
   ctx->synth_kernel = synth_run(sim, paths, sw, ctx->ctl, spectra, ctx->stream, ctx->ev[8], ctx->ev[9]);
   ET_HIP(hipEventRecord(ctx->ev[5], ctx->stream));
   ctx->timed |= TM_SYNTH | TM_SYNTH_K;
-}
-
-// number of records to synthesise = min(paths count, capacity); written into the control block
-__global__ void k_set_nrec(Ctl* ctl, const int64_t* count, int64_t cap) {
-  int64_t n = count[0];
-  ctl->n_rec = n < cap ? n : cap;
 }
 
 // A pipelined batch's second control block starts without a deferred error.
@@ -477,8 +474,6 @@ int et_synthesize(et_ctx* ctx, const et_sim_desc* sim, const et_paths* paths, vo
   return guarded(ctx, [&] {
     validate_paths(paths);
     ctx->timed = 0;
-    k_set_nrec<<<1, 1, 0, ctx->stream>>>(ctx->ctl, paths->count, paths->capacity);
-    ET_HIP(hipGetLastError());
     synth_impl(ctx, sim, paths, ws, ws_bytes, spectra, false);
   });
 }
@@ -491,8 +486,6 @@ int et_synthesize_noalloc(et_ctx* ctx, const et_sim_desc* sim, const et_paths* p
     ET_CHECK(spectra, ET_E_INVALID, "spectra is NULL");
     ctx->timed = 0;
     void* buf = noalloc_scratch(ctx->device);
-    k_set_nrec<<<1, 1, 0, ctx->stream>>>(ctx->ctl, paths->count, paths->capacity);
-    ET_HIP(hipGetLastError());
     ET_HIP(hipEventRecord(ctx->ev[4], ctx->stream));
     ctx->synth_kernel = synth_run_noalloc(sim, paths, buf, NOALLOC_SCRATCH_BYTES, ctx->ctl, spectra, ctx->stream,
                                           ctx->ev[8], ctx->ev[9]);
@@ -512,7 +505,6 @@ int et_simulate(et_ctx* ctx, const et_scene* scene, const et_sim_desc* sim, cons
     ET_CHECK(ws, ET_E_INVALID, "workspace is NULL");
     ET_CHECK(ws_bytes >= w.trace + w.synth, ET_E_WORKSPACE, "workspace too small for et_simulate");
     trace_impl(ctx, scene, sim, ws, w.trace, paths);
-    k_set_nrec<<<1, 1, 0, ctx->stream>>>(ctx->ctl, paths->count, paths->capacity);
     synth_impl(ctx, sim, paths, (char*)ws + w.trace, ws_bytes - w.trace, spectra, true);
   });
 }
@@ -531,7 +523,6 @@ int et_synthesize_backward(et_ctx* ctx, const et_sim_desc* sim, const et_paths* 
     const size_t need = synth_bwd_ws_layout(sim, std::max<int64_t>(paths->capacity, 1), nullptr, nullptr);
     ET_CHECK(ws && ws_bytes >= need, ET_E_WORKSPACE, "workspace too small for et_synthesize_backward");
     synth_bwd_ws_layout(sim, std::max<int64_t>(paths->capacity, 1), (char*)ws, &sw);
-    k_set_nrec<<<1, 1, 0, ctx->stream>>>(ctx->ctl, paths->count, paths->capacity);
     ET_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
     ctx->adjoint_kernel = synth_bwd_run(sim, paths, grad_spectra, sw, ctx->ctl, grad_k, grad_rx, ctx->stream,
                                         ctx->ev[10], ctx->ev[11]);
@@ -657,7 +648,6 @@ void batch_impl(et_ctx* ctx, int32_t J, const et_job* jobs, void* ws, size_t ws_
         ET_HIP(hipEventRecord(ctx->pev[1 + k], ts));
         ET_HIP(hipStreamWaitEvent(ctx->stream, ctx->pev[1 + k], 0));
       }
-      k_set_nrec<<<1, 1, 0, ctx->stream>>>(ctl, P.count, P.capacity);
       int ak = 0;
       const hipEvent_t kev[4] = {ev ? ev[2] : nullptr, ev ? ev[3] : nullptr, ev ? ev[4] : nullptr,
                                  ev ? ev[5] : nullptr};
@@ -689,10 +679,9 @@ void batch_impl(et_ctx* ctx, int32_t J, const et_job* jobs, void* ws, size_t ws_
     const WsPlan w = plan(jobs[j].scene, s, cap);
     TraceWS tw;
     trace_ws_layout((s->flags & ET_SPECULAR) ? s->N : 0, jobs[j].scene->d.T, jobs[j].scene->d.n_obj,
-                    diff_draws_max(s), (char*)ws, &tw);
+                    diff_draws_max(s), (char*)ws, &tw, 0, los_rays(s));
     tw.stack_cap = ctx->stack_cap;
     trace_run(jobs[j].scene->d, s, &P, tw, ctx->ctl, false, ctx->stream);
-    k_set_nrec<<<1, 1, 0, ctx->stream>>>(ctx->ctl, P.count, P.capacity);
     SynthWS sw;
     synth_ws_layout(s, cap, (char*)ws + w.trace, &sw);
     ctx->synth_kernel = synth_run(s, &P, sw, ctx->ctl, spectra + (size_t)j * MF2, ctx->stream);

@@ -144,7 +144,8 @@ namespace et {
 struct Ctl {
   uint32_t err;              // DEV_ERR_* bits
   uint32_t pad0;
-  int64_t n_active[2];       // active rays of the current / next bounce
+  int64_t act[257];          // active rays of each bounce
+  int64_t base[257];         // specular records before each bounce (may exceed the capacity)
   int64_t rec_base;          // specular records produced so far (may exceed capacity)
   int64_t rec_prev;          // specular records of the earlier job waves of a batch
   int64_t seg;               // closest-hit segments traced
@@ -162,19 +163,15 @@ struct Ctl {
 };
 
 struct TraceWS {
-  // ray state ping-pong (FP64 origin/direction, path length, previous leaf position, ray id)
-  double* st[2][7];
-  int32_t* prev[2];
-  int32_t* ray[2];
-  int64_t* prec[2];          // record index of the ray's previous reflection (-1 before the first)
-  // per-slot bounce results
-  double* rp[3];
-  double* rd[3];
-  double* rr;
-  int32_t* rpos;
-  uint64_t* rvis;            // line of sight: 0/1, or receiver bits (per-receiver reading)
-  uint64_t* flags;
-  uint64_t* offs;
+  // ray state per slot, updated in place (FP64 origin/direction, path length, previous leaf position, ray id)
+  double* st[7];
+  int32_t* prev;
+  int32_t* ray;
+  int64_t* prec;             // record index of the ray's previous reflection (from the second bounce on)
+  int32_t* list[2];          // slots of the active rays of odd / even bounces (bounce 0: every slot)
+  ulonglong2* masks;         // per 64 active rays: hit and continue masks
+  uint64_t* pre;             // exclusive sums of the masks' counts within blocks, the blocks' sums
+  uint64_t* bsum;
   void* scan_tmp;
   uint32_t* rkeys;           // ray order: direction keys (job in the high bits in a batch)
   int32_t* rperm;            // ray index per slot after sorting by key
@@ -201,8 +198,9 @@ struct TraceWS {
 
 // Workspace layout of et_trace.  base == nullptr: only computes the size.
 // max_blocks: largest bounce-kernel grid the workspace serves (0: the single-pose default)
+// los: line-of-sight rays per record (1, or the receivers in the per-receiver reading)
 size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* base, TraceWS* ws,
-                       int32_t max_blocks = 0);
+                       int32_t max_blocks = 0, int32_t los = 1);
 // Fused batch (specular jobs): all jobs' rays share the bounce kernels; records carry the
 // job index in their ray field.  dev_jobs holds trace_batch_jobs_bytes(J) bytes.
 size_t trace_batch_jobs_bytes(int32_t J);
@@ -222,10 +220,8 @@ struct SynthWS {
   int32_t gchunks;           // adjoint record chunks
   int32_t gtiles;            // adjoint tiles of outer indices (factorised kernel)
   int64_t cap;               // record capacity
-  uint64_t* vflags;          // visible-record compaction: flags, offsets, index list, scan scratch
-  uint64_t* voffs;
+  uint64_t* vsum;            // visible records per tile of the records, and their index list
   int32_t* vidx;
-  void* vscan;
   float* lk;                 // per (material, band): log2 k, log2(e)/(2 beta^2), log2 I_d
   float* lc;
   float* ld;
@@ -312,10 +308,8 @@ struct SynthBatchWS {
   float* partial;               // [chunks][M][F][2]
   double* gpart_x;              // [chunks][T1][M][3]
   double* gpart_k;              // [chunks][T1][M][Q][Bk]
-  uint64_t* vflags;
-  uint64_t* voffs;
+  uint64_t* vsum;
   int32_t* vidx;
-  void* vscan;
   uint64_t* keys;               // job of each visible record (sort keys)
   void* sort_tmp;
   int64_t* tab;                 // chunk tables (forward, adjoint)

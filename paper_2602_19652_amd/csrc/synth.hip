@@ -343,19 +343,6 @@ __device__ inline void row_table(const SynthArgs& a, int2* __restrict__ rows) {
   if (tid == 0) rows[a.nrows] = make_int2(a.F, 0);
 }
 
-// The last workgroup writes the row table (rows not NULL), the others the band tables.
-__global__ __launch_bounds__(256) void k_band_tables(SynthArgs a, float* lk, float* lc, float* ld, float* lp, float* lmax,
-                                                     int2* rows) {
-  if (rows && blockIdx.x + 1 == gridDim.x) {
-    row_table(a, rows);
-    return;
-  }
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < a.Q) band_bound_entry(a, i, lmax);
-  if (i >= a.Q * a.Bk) return;
-  band_table_entry(a, i, lk, lc, ld, lp);
-}
-
 __device__ inline float band_log2(const SynthArgs& a, const Pair& q, int b) {
   return band_log2_v(a, q.kind, q.mat, q.gamma, b);
 }
@@ -442,21 +429,85 @@ __device__ inline void block_coords(int& p, int& m, int& t) {
 
 // ------------------------------------------------------------------ visible-record list
 
-__global__ void k_vis_flags(et_paths P, const Ctl* ctl, uint64_t* __restrict__ flags) {
-  const int64_t n = ctl->n_rec;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    flags[i] = (P.flags[i] & 1) ? 1ull : 0ull;
+// The number of records of a call: what the paths hold, at most their capacity.
+__device__ inline int64_t record_count(const et_paths& P) { return min(P.count[0], P.capacity); }
+
+// Tiles of the records for the visible list: 2048 records, more where that would make over 2048 tiles (every
+// tile sums the counts of those before it).
+constexpr int VIS_TILE = 2048;
+constexpr int64_t VIS_MAX_TILES = 2048;
+__host__ __device__ inline int64_t vis_tile(int64_t cap) {
+  const int64_t t = (cap + VIS_MAX_TILES - 1) / VIS_MAX_TILES;
+  return (t + VIS_TILE - 1) / VIS_TILE * VIS_TILE;
 }
 
-__global__ void k_vis_scatter(const uint64_t* __restrict__ flags, const uint64_t* __restrict__ offs, const Ctl* ctl,
-                              int32_t* __restrict__ idx) {
-  const int64_t n = ctl->n_rec;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    if (flags[i]) idx[offs[i]] = (int32_t)i;
+__device__ inline uint64_t wave_sum_u64(uint64_t v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
 }
 
-__global__ void k_vis_count(Ctl* ctl) { ctl->n_vis = (int64_t)ctl->tot[3]; }
-__global__ void k_vis_all(Ctl* ctl) { ctl->n_vis = ctl->n_rec; }   // no list: the kernels walk every record
+// Visible records of tile t (workgroup of 256 threads).
+__device__ inline void vis_count(const et_paths& P, Ctl* ctl, int64_t t, int64_t tile, uint64_t* __restrict__ vsum) {
+  __shared__ uint64_t red[4];
+  const int64_t n = record_count(P);
+  const int64_t lo = t * tile, hi = min(lo + tile, n);
+  uint64_t c = 0;
+  for (int64_t i = lo + threadIdx.x; i < hi; i += 256) c += P.flags[i] & 1;
+  c = wave_sum_u64(c);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    vsum[t] = red[0] + red[1] + red[2] + red[3];
+    if (t == 0) ctl->n_rec = n;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_vis_count(et_paths P, Ctl* ctl, int64_t tile, uint64_t* __restrict__ vsum) {
+  vis_count(P, ctl, blockIdx.x, tile, vsum);
+}
+
+// The indices of the visible records in order; each wave takes 512 consecutive ones of a tile at a time.
+__global__ __launch_bounds__(256) void k_vis_list(et_paths P, Ctl* ctl, int64_t tile, const uint64_t* __restrict__ vsum,
+                                                  int32_t* __restrict__ idx) {
+  __shared__ uint64_t red[4];
+  __shared__ uint64_t cnt[4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int64_t n = ctl->n_rec;
+  const int64_t lo = blockIdx.x * tile, hi = min(lo + tile, n);
+  if (blockIdx.x > 0 && lo >= n) return;
+  uint64_t s = 0;   // before the tile; the last tile with records also leaves the total
+  for (int64_t k = tid; k < (int64_t)blockIdx.x; k += 256) s += vsum[k];
+  s = wave_sum_u64(s);
+  if (lane == 0) red[wv] = s;
+  __syncthreads();
+  uint64_t at = red[0] + red[1] + red[2] + red[3];
+  if (tid == 0 && hi >= n) ctl->n_vis = (int64_t)(at + vsum[blockIdx.x]);
+  for (int64_t base = lo; base < hi; base += VIS_TILE) {
+    const int64_t w0 = base + wv * (VIS_TILE / 4);
+    uint64_t m[8];
+    uint64_t c = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int64_t i = w0 + 64 * k + lane;
+      m[k] = __ballot(i < hi && (P.flags[i] & 1));
+      c += __popcll(m[k]);
+    }
+    __syncthreads();
+    if (lane == 0) cnt[wv] = c;
+    __syncthreads();
+    uint64_t o = at;
+    for (int k = 0; k < wv; ++k) o += cnt[k];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if ((m[k] >> lane) & 1ull) idx[o + __popcll(m[k] & ((1ull << lane) - 1ull))] = (int32_t)(w0 + 64 * k + lane);
+      o += __popcll(m[k]);
+    }
+    at += cnt[0] + cnt[1] + cnt[2] + cnt[3];
+  }
+}
+
+// no list: the kernels walk every record
+__global__ void k_vis_all(et_paths P, Ctl* ctl) { ctl->n_vis = ctl->n_rec = record_count(P); }
 
 // ------------------------------------------------------------------ factorised MFMA kernel
 
@@ -2063,26 +2114,47 @@ int choose_P(const et_sim_desc* sim, int64_t cap, bool mfma) {
   return (int)std::min<int64_t>(P, 256);
 }
 
-size_t vis_ws(int64_t cap, char* base, size_t off, uint64_t** fl, uint64_t** of, int32_t** idx, void** tmp) {
+size_t vis_ws(int64_t cap, char* base, size_t off, uint64_t** sum, int32_t** idx) {
   auto take = [&](size_t b) -> void* { void* p = base ? (void*)(base + off) : nullptr; off += al(b); return p; };
-  *fl = (uint64_t*)take(sizeof(uint64_t) * (size_t)cap);
-  *of = (uint64_t*)take(sizeof(uint64_t) * (size_t)cap);
+  *sum = (uint64_t*)take(sizeof(uint64_t) * (size_t)((cap + vis_tile(cap) - 1) / vis_tile(cap)));
   *idx = (int32_t*)take(sizeof(int32_t) * (size_t)cap);
-  *tmp = take(scan_temp_bytes(cap));
   return off;
 }
 
-// rows: the row table is needed (the factorised kernels' FOLD 0)
-void build_tables(SynthArgs& a, const SynthWS& ws, bool rows, hipStream_t s) {
+// What a call needs before its kernels, in one launch: the visible records of each tile (vis workgroups), the
+// band tables, and the row table if asked for.
+__global__ __launch_bounds__(256) void k_synth_prep(et_paths P, Ctl* ctl, int64_t tile, unsigned vis,
+                                                    uint64_t* __restrict__ vsum, SynthArgs a, float* lk, float* lc,
+                                                    float* ld, float* lp, float* lmax, int2* rows) {
+  if (blockIdx.x < vis) {
+    vis_count(P, ctl, blockIdx.x, tile, vsum);
+    return;
+  }
+  if (rows && blockIdx.x + 1 == gridDim.x) {
+    row_table(a, rows);
+    return;
+  }
+  const int i = (blockIdx.x - vis) * blockDim.x + threadIdx.x;
+  if (i < a.Q) band_bound_entry(a, i, lmax);
+  if (i < a.Q * a.Bk) band_table_entry(a, i, lk, lc, ld, lp);
+}
+
+// Band tables (and with rows the row table, for the factorised kernels' FOLD 0), and with list the visible-record
+// list of the paths.
+void build_prep(SynthArgs& a, const SynthWS& ws, const et_paths& P, bool list, bool rows, Ctl* ctl, hipStream_t s) {
   a.lk = ws.lk;
   a.lc = ws.lc;
   a.ld = ws.ld;
   a.lp = ws.lp;
   a.lmax = ws.lmax;
-  const int n = a.Q * a.Bk;
   a.rows = rows ? (const int2*)ws.rows : nullptr;
-  k_band_tables<<<(n + 255) / 256 + (rows ? 1 : 0), 256, 0, s>>>(a, ws.lk, ws.lc, ws.ld, ws.lp, ws.lmax,
-                                                                 rows ? (int2*)ws.rows : nullptr);
+  const int n = a.Q * a.Bk;
+  const int64_t tile = vis_tile(ws.cap);
+  const unsigned vis = list ? (unsigned)((ws.cap + tile - 1) / tile) : 0u;
+  k_synth_prep<<<vis + (n + 255) / 256 + (rows ? 1 : 0), 256, 0, s>>>(P, ctl, tile, vis, ws.vsum, a, ws.lk, ws.lc, ws.ld,
+                                                                    ws.lp, ws.lmax, rows ? (int2*)ws.rows : nullptr);
+  if (list) k_vis_list<<<vis, 256, 0, s>>>(P, ctl, tile, ws.vsum, ws.vidx);
+  ET_HIP(hipGetLastError());
 }
 
 // Path-product reading: band tables with a row per record.  Specular record n: the sum of
@@ -2146,15 +2218,6 @@ size_t table_ws(const et_sim_desc* sim, char* base, size_t off, SynthWS& w) {
   w.rows = base ? base + off : nullptr;
   off += al(sizeof(int2) * ((size_t)synth_rows(sim, nullptr) + 1));
   return off;
-}
-
-void build_vis(const et_paths& P, const SynthWS& ws, int64_t cap, Ctl* ctl, hipStream_t s) {
-  const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((cap + 255) / 256, 4096));
-  k_vis_flags<<<nb, 256, 0, s>>>(P, ctl, ws.vflags);
-  scan_exclusive_u64(ws.vflags, ws.voffs, 0, &ctl->n_rec, cap, &ctl->tot[3], ws.vscan, s);
-  k_vis_scatter<<<nb, 256, 0, s>>>(ws.vflags, ws.voffs, ctl, ws.vidx);
-  k_vis_count<<<1, 1, 0, s>>>(ctl);
-  ET_HIP(hipGetLastError());
 }
 
 // ------------------------------------------------------------------ fused batches
@@ -2342,7 +2405,7 @@ size_t synth_ws_layout(const et_sim_desc* sim, int64_t cap, char* base, SynthWS*
   w.cap = cap;
   w.partial = (float*)(base ? base + off : nullptr);
   off += al(sizeof(float) * 2 * (size_t)P * sim->M * sim->F);
-  off = vis_ws(cap, base, off, &w.vflags, &w.voffs, &w.vidx, &w.vscan);
+  off = vis_ws(cap, base, off, &w.vsum, &w.vidx);
   off = table_ws(sim, base, off, w);
   if (sim->flags & ET_PATH_PRODUCT) {
     w.plk = (float*)(base ? base + off : nullptr);
@@ -2360,8 +2423,7 @@ int synth_run(const et_sim_desc* sim, const et_paths* paths, const SynthWS& ws, 
   const int fold = mf ? bands_fold(sim) : 0;
   SynthArgs a = make_args(sim, ws.P);
   const et_paths P = *paths;
-  build_vis(P, ws, ws.cap, ctl, s);
-  build_tables(a, ws, mf && fold == 0, s);
+  build_prep(a, ws, P, true, mf && fold == 0, ctl, s);
   set_readings(a, sim, P, ws, ctl, s);
   if (kb) ET_HIP(hipEventRecord(kb, s));
   if (mf) {
@@ -2398,8 +2460,8 @@ int synth_run_noalloc(const et_sim_desc* sim, const et_paths* paths, void* buf, 
   w.cap = cap;
   SynthArgs a = make_args(sim, w.P);
   const et_paths Pth = *paths;
-  k_vis_all<<<1, 1, 0, s>>>(ctl);
-  build_tables(a, w, mf && fold == 0, s);
+  k_vis_all<<<1, 1, 0, s>>>(Pth, ctl);
+  build_prep(a, w, Pth, false, mf && fold == 0, ctl, s);
   a.rxv = (sim->flags & ET_PER_RX_VISIBILITY) ? Pth.rx_vis : nullptr;
   if (kb) ET_HIP(hipEventRecord(kb, s));
   if (mf) {
@@ -2454,7 +2516,7 @@ size_t synth_bwd_ws_layout(const et_sim_desc* sim, int64_t cap, char* base, Synt
   off += al(sizeof(double) * 3 * (size_t)P * T1 * sim->M);
   w.gpart_k = (double*)(base ? base + off : nullptr);
   off += al(sizeof(double) * (size_t)P * T1 * sim->M * sim->Q * sim->Bk);
-  off = vis_ws(cap, base, off, &w.vflags, &w.voffs, &w.vidx, &w.vscan);
+  off = vis_ws(cap, base, off, &w.vsum, &w.vidx);
   off = table_ws(sim, base, off, w);
   if (ws) *ws = w;
   return off;
@@ -2465,8 +2527,7 @@ int synth_bwd_run(const et_sim_desc* sim, const et_paths* paths, const float* gr
   const bool mf = synth_bwd_factorised_ok(sim);
   SynthArgs a = make_args(sim, ws.gchunks);
   const et_paths P = *paths;
-  build_vis(P, ws, ws.cap, ctl, s);
-  build_tables(a, ws, false, s);
+  build_prep(a, ws, P, true, false, ctl, s);
   a.rxv = (sim->flags & ET_PER_RX_VISIBILITY) ? P.rx_vis : nullptr;   // (no path product in the adjoint)
   if (kb) ET_HIP(hipEventRecord(kb, s));
   if (mf) {
@@ -2538,7 +2599,7 @@ size_t synth_batch_ws_layout(int32_t J, const et_job* jobs, int64_t cap, const B
     w.gpart_x = (double*)take(sizeof(double) * 3 * cb * w.T1 * s0->M);
     w.gpart_k = (double*)take(sizeof(double) * cb * w.T1 * s0->M * s0->Q * s0->Bk);
   }
-  off = vis_ws(cap, base, off, &w.vflags, &w.voffs, &w.vidx, &w.vscan);
+  off = vis_ws(cap, base, off, &w.vsum, &w.vidx);
   w.keys = (uint64_t*)take(sizeof(uint64_t) * (size_t)cap);
   w.sort_tmp = take(sort_temp_bytes(cap, 8));
   w.tab = (int64_t*)take(sizeof(int64_t) * (size_t)(3 * J + 2) * 2);
@@ -2582,9 +2643,10 @@ int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const 
   }
   k_band_tables_batch<<<J, 256, 0, s>>>(dj);
   // visible records, sorted by job (stable: each job keeps its record order)
-  SynthWS vw{};
-  vw.vflags = w.vflags; vw.voffs = w.voffs; vw.vidx = w.vidx; vw.vscan = w.vscan;
-  build_vis(P, vw, w.cap, ctl, s);
+  const int64_t tile = vis_tile(w.cap);
+  const unsigned tiles = (unsigned)((w.cap + tile - 1) / tile);
+  k_vis_count<<<tiles, 256, 0, s>>>(P, ctl, tile, w.vsum);
+  k_vis_list<<<tiles, 256, 0, s>>>(P, ctl, tile, w.vsum, w.vidx);
   const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((w.cap + 255) / 256, 4096));
   k_vis_jobkeys<<<nb, 256, 0, s>>>(P, w.vidx, ctl, w.keys);
   int bits = 0;

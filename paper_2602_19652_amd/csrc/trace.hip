@@ -1,13 +1,13 @@
 // Ray tracing of one pose (Sec. III-C, Algorithm 1) and diffraction sampling (Sec. III-D).
 //
-// Per bounce j, over the compacted list of active rays:
-//   k_bounce   FP32 closest-hit BVH traversal of the FP64 ray rounded to FP32 (which
-//              triangle), FP64 plane intersection, specular reflection about the face
-//              normal and path-length update (where), FP32 any-hit line-of-sight ray from
-//              the hit point toward x_ref
-//   scan       exclusive scan of (hit, continue) flags
-//   k_scatter  stable compaction: records in ray order after the earlier bounces' records,
-//              next-bounce ray state in ray order
+// Per bounce j, over the list of active rays:
+//   k_walk      FP32 closest-hit BVH traversal of the FP64 ray rounded to FP32 (which triangle), FP64 plane
+//               intersection, specular reflection about the face normal and path-length update (where);
+//               in the same launch the FP32 any-hit line-of-sight rays of the previous bounce's records
+//               toward x_ref (or each receiver)
+//   k_mask_sums sums of the waves' hit and continue masks (large ray sets; small ones are summed in place)
+//   k_records   stable compaction: records in ray order after the earlier bounces' records, the list of the
+//               rays that go on in ray order
 // Ray order: a ray set larger than one round of the bounce grid (the threads the chip holds at
 // once) is first sorted (stably) by a 16-bit octahedral Morton key of its world direction, so
 // that a wave's lanes walk nearby parts of the BVH; the stable compaction keeps that order
@@ -35,6 +35,8 @@ constexpr int EMPTY = INT32_MIN;
 // dispatcher balances uneven rays block by block (measured 7% faster than two rays per thread
 // on 2048 blocks, whose second round leaves part of the chip idle).
 constexpr int MAX_BLOCKS = 8192;
+
+constexpr int ROUND_BLOCKS = 256 * TRAV_WAVES_PER_SIMD;   // blocks of 256 threads of a round on 256 compute units
 
 inline unsigned nblk(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + BS - 1) / BS, MAX_BLOCKS)); }
 inline unsigned nblk_full(int64_t n) { return (unsigned)std::max<int64_t>(1, (n + BS - 1) / BS); }
@@ -124,8 +126,9 @@ __device__ inline float tri_test(const float4 a, const float4 b, const float4 c,
   return T / det;
 }
 
+template <int TB>
 struct Stack {
-  int* lds;        // this lane's column: entry i at lds[i * BS]
+  int* lds;        // this lane's column: entry i at lds[i * TB]
   int* glob;       // this lane's global column: entry i at glob[i * gstride]
   int64_t gstride;
   int sp;
@@ -134,7 +137,7 @@ struct Stack {
   // A push beyond the cap drops the subtree (counted; the traversal still ends normally).
   __device__ inline void push(int v) {
     if (sp >= cap) { ++overflow; return; }
-    if (sp < TRAV_LDS_STACK) lds[sp * BS] = v;
+    if (sp < TRAV_LDS_STACK) lds[sp * TB] = v;
     else glob[(int64_t)(sp - TRAV_LDS_STACK) * gstride] = v;
     ++sp;
   }
@@ -144,7 +147,7 @@ struct Stack {
   __device__ inline int pop() {
     if (sp == 0) return EMPTY;
     --sp;
-    if (sp < TRAV_LDS_STACK) return lds[sp * BS];
+    if (sp < TRAV_LDS_STACK) return lds[sp * TB];
     return __builtin_nontemporal_load(glob + (int64_t)(sp - TRAV_LDS_STACK) * gstride);
   }
 };
@@ -157,8 +160,8 @@ struct Stack {
 // whose slab entry equals the hit distance) is always tested, so the hit does not depend on
 // the traversal order, and a refitted tree hits what a rebuilt one hits.
 constexpr float T_WIDEN = 1.0f + 1.9073486328125e-6f;   // 1 + 2^-19
-template <bool ANY, bool COUNT>
-__device__ inline int traverse(const SceneDev& S, const Ray32& r, float tmin, float tmax, int excl, Stack& st,
+template <bool ANY, bool COUNT, int TB>
+__device__ inline int traverse(const SceneDev& S, const Ray32& r, float tmin, float tmax, int excl, Stack<TB>& st,
                                float& t_hit, int64_t& cn, int64_t& ct) {
   int node = S.root;
   st.sp = 0;
@@ -261,10 +264,11 @@ __global__ void k_put_trace_jobs(TraceJobPack pk, TraceJob* __restrict__ dst) {
 
 __device__ inline double dnorm3(double x, double y, double z) { return sqrt(x * x + y * y + z * z); }
 
-// carry: a later job wave of a batch; the totals of the statistics carry over
-__global__ void k_trace_init(Ctl* ctl, int64_t N, int carry) {
-  ctl->n_active[0] = N;
-  ctl->n_active[1] = 0;
+// carry: a later job wave of a batch; the totals of the statistics carry over.  misses: rays of a scene without
+// triangles (every ray misses at its first segment).
+__device__ inline void trace_init(Ctl* ctl, int64_t N, int carry, int64_t misses) {
+  ctl->act[0] = N;
+  ctl->base[0] = 0;
   if (carry) {
     ctl->rec_prev += ctl->rec_base;
   } else {
@@ -274,6 +278,8 @@ __global__ void k_trace_init(Ctl* ctl, int64_t N, int carry) {
     ctl->overflow = 0;
     for (int i = 0; i < 6; ++i) ctl->cnt[i] = 0;
   }
+  ctl->seg += misses;
+  ctl->cnt[4] += misses;
   ctl->rec_base = 0;
   ctl->cmax_bits = 0;
   ctl->n_elig = 0;
@@ -282,6 +288,8 @@ __global__ void k_trace_init(Ctl* ctl, int64_t N, int carry) {
   ctl->n_draw = 0;
   for (int i = 0; i < 4; ++i) ctl->tot[i] = 0;
 }
+
+__global__ void k_trace_init(Ctl* ctl, int64_t N, int carry, int64_t misses) { trace_init(ctl, N, carry, misses); }
 
 // The job of batch ray g (the last job with ray0 <= g; jobs without rays share ray0 with the next).
 __device__ inline int ray_job(const TraceJob* __restrict__ jobs, int32_t J, int64_t g) {
@@ -349,6 +357,7 @@ template <bool BATCH>
 __global__ void k_ray_init(PoseArgs a0, const float* __restrict__ dirs0, const TraceJob* __restrict__ jobs, int32_t J,
                            const int32_t* __restrict__ perm, TraceWS w, Ctl* ctl) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (!BATCH && i == 0) trace_init(ctl, a0.N, 0, 0);
   if (i >= a0.N) return;
   const int64_t g = perm ? perm[i] : i;
   PoseArgs a = a0;
@@ -373,108 +382,135 @@ __global__ void k_ray_init(PoseArgs a0, const float* __restrict__ dirs0, const T
     nrm = 1.0;
     dx = 1.0; dy = 0.0; dz = 0.0;
   }
-  w.st[0][0][i] = a.s[0]; w.st[0][1][i] = a.s[1]; w.st[0][2][i] = a.s[2];
-  w.st[0][3][i] = dx / nrm; w.st[0][4][i] = dy / nrm; w.st[0][5][i] = dz / nrm;
-  w.st[0][6][i] = 0.0;
-  w.prev[0][i] = -1;
-  w.ray[0][i] = tag;
-  w.prec[0][i] = -1;
+  w.st[0][i] = a.s[0]; w.st[1][i] = a.s[1]; w.st[2][i] = a.s[2];
+  w.st[3][i] = dx / nrm; w.st[4][i] = dy / nrm; w.st[5][i] = dz / nrm;
+  w.st[6][i] = 0.0;
+  w.prev[i] = -1;
+  w.ray[i] = tag;
 }
 
+// One launch per bounce (and a last one) walks two kinds of rays, each kind in whole waves: the closest hits of
+// the act[j] active rays, and the line-of-sight rays of the records that bounce j - 1 left, which nothing
+// waits for until the end.  A small pose is bound by the length of one walk after the other (16,384 rays: 48 us
+// a bounce with both walks in one thread, and one line-of-sight ray per receiver made that 720 us for 8
+// receivers); apart, the two walks of a ray run beside each other.
+// The ray state is updated in place: slot s of the state holds the point, reflected direction, path length and
+// leaf of the ray's last hit, which k_records copies into the record; act lists hold the slots that go on.
+// Each wave leaves its 64 rays' hit and continue flags as two masks.
 // BATCH: each ray reads its scene and pose from the job table (the ray field is the job).
-// PERRX: one line-of-sight ray from the hit to each of the M receivers at rxp (bit m of the
-// result) instead of one toward the pose's reference point.
+// PERRX: one line-of-sight ray from the hit to each of the M receivers at rxp (bit m of the result) instead of one
+// toward the pose's reference point.
 // Six waves per SIMD (the register budget that asks for, 80, holds the kernel without spills):
 // measured 7% faster on the room's trace and 15% on foliage's than five.
-template <bool COUNT, bool BATCH, bool PERRX>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_PER_SIMD))) void k_bounce(
-    SceneDev S0, PoseArgs a0, const TraceJob* __restrict__ jobs, TraceWS w, Ctl* ctl, int j,
+// TB: threads per block: 64 while the rays leave compute units without a wave, else 256.
+template <int TB, bool COUNT, bool BATCH, bool PERRX>
+__global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_PER_SIMD))) void k_walk(
+    SceneDev S0, PoseArgs a0, const TraceJob* __restrict__ jobs, TraceWS w, Ctl* ctl, et_paths P, int j, int last,
     const double* __restrict__ rxp, int32_t M) {
-  __shared__ int lds_stack[TRAV_LDS_STACK * BS];
-  const int cur = j & 1;
-  const int64_t n = ctl->n_active[cur];
-  const int64_t gtid = (int64_t)blockIdx.x * BS + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * BS;
-  Stack st;
+  __shared__ int lds_stack[TRAV_LDS_STACK * TB];
+  const int lane = threadIdx.x & 63;
+  const int64_t n = last ? 0 : ctl->act[j];
+  const int64_t r0 = j > 0 ? ctl->base[j - 1] : 0;
+  const int64_t n_los = j > 0 ? (min(ctl->base[j], P.capacity) - r0) * (PERRX ? M : 1) : 0;
+  const int64_t gtid = (int64_t)blockIdx.x * TB + threadIdx.x;
+  const int64_t waves = (int64_t)gridDim.x * (TB / 64);
+  const int64_t nc = (n + 63) / 64, nl = n_los > 0 ? (n_los + 63) / 64 : 0;
+  const int32_t* list = j > 0 ? w.list[j & 1] : nullptr;
+  Stack<TB> st;
   st.lds = lds_stack + threadIdx.x;
   st.glob = w.gstack + gtid;
   st.gstride = w.gstack_threads;
   st.cap = w.stack_cap;
   st.overflow = 0;
   int64_t cn_c = 0, ct_c = 0, cn_a = 0, ct_a = 0, rays_a = 0;
-  for (int64_t i = gtid; i < n; i += stride) {
-    int pos;
-    float th = INFINITY;
-    {
-      SceneDev S = S0;
-      float teps = (float)a0.t_eps;
-      if (BATCH) {
-        const TraceJob* tj = jobs + w.ray[cur][i];
-        S = tj->S;
-        teps = (float)tj->a.t_eps;
+  for (int64_t c = gtid >> 6; c < nc + nl; c += waves) {
+    if (c < nc) {
+      const int64_t i = c * 64 + lane;
+      bool hit = false, cont = false;
+      if (i < n) {
+        const int64_t s = list ? list[i] : i;
+        int pos;
+        float th = INFINITY;
+        {
+          SceneDev S = S0;
+          float teps = (float)a0.t_eps;
+          if (BATCH) {
+            const TraceJob* tj = jobs + w.ray[s];
+            S = tj->S;
+            teps = (float)tj->a.t_eps;
+          }
+          const Ray32 r = make_ray(w.st[0][s], w.st[1][s], w.st[2][s], w.st[3][s], w.st[4][s], w.st[5][s]);
+          pos = (!BATCH || S.T > 0) ? traverse<false, COUNT>(S, r, teps, INFINITY, w.prev[s], st, th, cn_c, ct_c) : -1;
+        }
+        // The FP64 ray state (and a batch ray's job) is read again after the traversal instead of being held in
+        // registers through it; the compiler barrier keeps the two reads apart, so the traversal loop runs
+        // with fewer live registers (more waves per SIMD).
+        __asm__ volatile("" ::: "memory");
+        if (pos >= 0) {
+          SceneDev S = S0;
+          PoseArgs a = a0;
+          if (BATCH) {
+            const TraceJob* tj = jobs + w.ray[s];
+            S = tj->S;
+            a = tj->a;
+          }
+          const double ox = w.st[0][s], oy = w.st[1][s], oz = w.st[2][s];
+          const double dx = w.st[3][s], dy = w.st[4][s], dz = w.st[5][s];
+          const double rtot = w.st[6][s];
+          // FP64 refinement on the chosen triangle: plane intersection, normal, reflection
+          const float4 A = S.tri4[3 * (int64_t)pos], Bv = S.tri4[3 * (int64_t)pos + 1], Cv = S.tri4[3 * (int64_t)pos + 2];
+          const double e1x = (double)Bv.x - A.x, e1y = (double)Bv.y - A.y, e1z = (double)Bv.z - A.z;
+          const double e2x = (double)Cv.x - A.x, e2y = (double)Cv.y - A.y, e2z = (double)Cv.z - A.z;
+          double nx = e1y * e2z - e1z * e2y, ny = e1z * e2x - e1x * e2z, nz = e1x * e2y - e1y * e2x;
+          const double nn = dnorm3(nx, ny, nz);
+          nx /= nn; ny /= nn; nz /= nn;
+          const double dn = dx * nx + dy * ny + dz * nz;
+          const double hp = ((double)A.x - ox) * nx + ((double)A.y - oy) * ny + ((double)A.z - oz) * nz;
+          const double t = dn != 0.0 ? hp / dn : (double)th;
+          const double px = ox + t * dx, py = oy + t * dy, pz = oz + t * dz;
+          const double rnew = (j == 0) ? dnorm3(px - a.s[0], py - a.s[1], pz - a.s[2]) : rtot + t;
+          w.st[0][s] = px; w.st[1][s] = py; w.st[2][s] = pz;
+          w.st[3][s] = dx - 2.0 * dn * nx; w.st[4][s] = dy - 2.0 * dn * ny; w.st[5][s] = dz - 2.0 * dn * nz;
+          w.st[6][s] = rnew;
+          w.prev[s] = pos;
+          hit = true;
+          cont = (j + 1 < a.B) && !(rnew >= a.maxd);
+        }
       }
-      const Ray32 r = make_ray(w.st[cur][0][i], w.st[cur][1][i], w.st[cur][2][i], w.st[cur][3][i], w.st[cur][4][i],
-                               w.st[cur][5][i]);
-      pos = (!BATCH || S.T > 0) ? traverse<false, COUNT>(S, r, teps, INFINITY, w.prev[cur][i], st, th, cn_c, ct_c) : -1;
-    }
-    // The FP64 ray state (and a batch ray's job) is read again after the traversal instead of
-    // being held in registers through it; the compiler barrier keeps the two reads apart, so
-    // the traversal loop runs with fewer live registers (more waves per SIMD).
-    __asm__ volatile("" ::: "memory");
-    SceneDev S = S0;
-    PoseArgs a = a0;
-    if (BATCH) {
-      const TraceJob* tj = jobs + w.ray[cur][i];
-      S = tj->S;
-      a = tj->a;
-    }
-    const float teps = (float)a.t_eps;
-    const double ox = w.st[cur][0][i], oy = w.st[cur][1][i], oz = w.st[cur][2][i];
-    const double dx = w.st[cur][3][i], dy = w.st[cur][4][i], dz = w.st[cur][5][i];
-    const double rtot = w.st[cur][6][i];
-    uint64_t flag = 0;
-    if (pos >= 0) {
-      // FP64 refinement on the chosen triangle: plane intersection, normal, reflection
-      const float4 A = S.tri4[3 * (int64_t)pos], Bv = S.tri4[3 * (int64_t)pos + 1], Cv = S.tri4[3 * (int64_t)pos + 2];
-      const double e1x = (double)Bv.x - A.x, e1y = (double)Bv.y - A.y, e1z = (double)Bv.z - A.z;
-      const double e2x = (double)Cv.x - A.x, e2y = (double)Cv.y - A.y, e2z = (double)Cv.z - A.z;
-      double nx = e1y * e2z - e1z * e2y, ny = e1z * e2x - e1x * e2z, nz = e1x * e2y - e1y * e2x;
-      const double nn = dnorm3(nx, ny, nz);
-      nx /= nn; ny /= nn; nz /= nn;
-      const double dn = dx * nx + dy * ny + dz * nz;
-      const double hp = ((double)A.x - ox) * nx + ((double)A.y - oy) * ny + ((double)A.z - oz) * nz;
-      const double t = dn != 0.0 ? hp / dn : (double)th;
-      const double px = ox + t * dx, py = oy + t * dy, pz = oz + t * dz;
-      const double rnew = (j == 0) ? dnorm3(px - a.s[0], py - a.s[1], pz - a.s[2]) : rtot + t;
-      const double rx = dx - 2.0 * dn * nx, ry = dy - 2.0 * dn * ny, rz = dz - 2.0 * dn * nz;
-      // the bounce's results leave registers before the line-of-sight traversal
-      w.rp[0][i] = px; w.rp[1][i] = py; w.rp[2][i] = pz;
-      w.rd[0][i] = rx; w.rd[1][i] = ry; w.rd[2][i] = rz;
-      w.rr[i] = rnew;
-      w.rpos[i] = pos;
-      const bool cont = (j + 1 < a.B) && !(rnew >= a.maxd);
-      flag = 1ull | ((uint64_t)cont << 32);
-      uint64_t vis = 0;
-      const int n_los = PERRX ? M : 1;
-      for (int m = 0; m < n_los; ++m) {
-        // line of sight from the hit point toward the receiver reference point (or receiver m)
+      const uint64_t hm = __ballot(hit), cm = __ballot(cont);
+      if (lane == 0) w.masks[c] = make_ulonglong2(hm, cm);
+    } else {
+      // line of sight from a record's point toward the receiver reference point (or receiver m)
+      const int64_t e = (c - nc) * 64 + lane;
+      if (e < n_los) {
+        const int64_t r = r0 + (PERRX ? e / M : e);
+        const int m = PERRX ? (int)(e - (r - r0) * M) : 0;
+        SceneDev S = S0;
+        PoseArgs a = a0;
+        if (BATCH) {
+          const TraceJob* tj = jobs + P.ray[r];
+          S = tj->S;
+          a = tj->a;
+        }
+        const double px = P.p[3 * r], py = P.p[3 * r + 1], pz = P.p[3 * r + 2];
         const double tx = PERRX ? rxp[3 * m] : a.xref[0], ty = PERRX ? rxp[3 * m + 1] : a.xref[1],
                      tz = PERRX ? rxp[3 * m + 2] : a.xref[2];
         const double wx = tx - px, wy = ty - py, wz = tz - pz;
         const double L = dnorm3(wx, wy, wz);
         bool v = true;
         if (L > 2.0 * a.t_eps) {
+          const int pos = S.tri_pos[P.tri[r]];
           const Ray32 rv = make_ray(px, py, pz, wx / L, wy / L, wz / L);
           float tv;
-          const int blk = traverse<true, COUNT>(S, rv, teps, (float)(L - a.t_eps), pos, st, tv, cn_a, ct_a);
-          v = blk < 0;
+          v = traverse<true, COUNT>(S, rv, (float)a.t_eps, (float)(L - a.t_eps), pos, st, tv, cn_a, ct_a) < 0;
           ++rays_a;
         }
-        if (v) vis |= 1ull << m;
+        if (v) {
+          P.flags[r] = 1;
+          if (PERRX) atomicOr((unsigned long long*)&P.rx_vis[r], 1ull << m);
+        }
       }
-      w.rvis[i] = vis;
     }
-    w.flags[i] = flag;
   }
   if (st.overflow) atomicAdd((unsigned long long*)&ctl->overflow, (unsigned long long)st.overflow);
   if (st.overflow) atomicOr(&ctl->err, DEV_ERR_STACK);
@@ -487,61 +523,137 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_P
   }
 }
 
-template <bool BATCH>
-__global__ void k_scatter(SceneDev S, const TraceJob* __restrict__ jobs, TraceWS w, Ctl* ctl, et_paths P, int j,
-                          int perrx) {
-  const int cur = j & 1, nxt = cur ^ 1;
-  const int64_t n = ctl->n_active[cur];
-  const int64_t base = ctl->rec_base;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t f = w.flags[i];
-    if (!(f & 1ull)) continue;
-    const uint64_t o = w.offs[i];
-    const int64_t ri = base + (int64_t)(o & 0xffffffffull);
-    const int pos = w.rpos[i];
+// Hits (low half) and continuing rays (high half) of a wave's masks.
+__device__ inline uint64_t mask_counts(ulonglong2 m) {
+  return (uint64_t)__popcll(m.x) | (uint64_t)__popcll(m.y) << 32;
+}
+
+// Exclusive sums of the masks' counts within blocks of 1024, and the blocks' sums (more rays than
+// SCAN_IN_PLACE; fewer are summed by k_records itself).
+constexpr int CHUNKS = 1024;
+constexpr int64_t SCAN_IN_PLACE = 65536;
+__global__ __launch_bounds__(BS) void k_mask_sums(TraceWS w, const Ctl* ctl, int j) {
+  __shared__ uint64_t wsum[BS / 64];
+  const int64_t nc = (ctl->act[j] + 63) / 64;
+  const int64_t c0 = (int64_t)blockIdx.x * CHUNKS + 4 * threadIdx.x;
+  if ((int64_t)blockIdx.x * CHUNKS >= nc) return;
+  uint64_t v[4], s = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    v[k] = c0 + k < nc ? mask_counts(w.masks[c0 + k]) : 0;
+    s += v[k];
+  }
+  uint64_t inc = s;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t t = __shfl_up(inc, o);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) wsum[wv] = inc;
+  __syncthreads();
+  uint64_t ex = inc - s, tot = 0;
+  for (int k = 0; k < BS / 64; ++k) {
+    if (k < wv) ex += wsum[k];
+    tot += wsum[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (c0 + k < nc) w.pre[c0 + k] = ex;
+    ex += v[k];
+  }
+  if (threadIdx.x == 0) w.bsum[blockIdx.x] = tot;
+}
+
+__device__ inline uint64_t block_sum(uint64_t v, uint64_t* red) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = 0;
+  for (int k = 0; k < BS / 64; ++k) v += red[k];
+  __syncthreads();
+  return v;
+}
+
+// The records of bounce j in ray order after the earlier bounces', the list of the slots that go on, and (first
+// workgroup) the counts of the next bounce.  A workgroup takes 256 rays, the masks of four waves; what lies
+// before them comes from k_mask_sums, or (IN_PLACE) from summing the masks before it.
+template <bool BATCH, bool IN_PLACE>
+__global__ __launch_bounds__(BS) void k_records(SceneDev S, const TraceJob* __restrict__ jobs, TraceWS w, Ctl* ctl,
+                                                et_paths P, int j, int perrx) {
+  __shared__ uint64_t red[BS / 64];
+  const int64_t n = ctl->act[j], nc = (n + 63) / 64;
+  const int64_t base = ctl->base[j];
+  const int32_t* list = j > 0 ? w.list[j & 1] : nullptr;
+  int32_t* next = w.list[(j + 1) & 1];
+  if (blockIdx.x == 0) {
+    uint64_t t = 0;
+    if (IN_PLACE) {
+      for (int64_t c = threadIdx.x; c < nc; c += BS) t += mask_counts(w.masks[c]);
+    } else {
+      for (int64_t b = threadIdx.x; b < (nc + CHUNKS - 1) / CHUNKS; b += BS) t += w.bsum[b];
+    }
+    t = block_sum(t, red);
+    if (threadIdx.x == 0) {
+      const int64_t hits = (int64_t)(t & 0xffffffffull);
+      ctl->seg += n;
+      ctl->shadow += hits;
+      ctl->cnt[4] += n;
+      ctl->act[j + 1] = (int64_t)(t >> 32);
+      ctl->base[j + 1] = base + hits;
+      ctl->rec_base = base + hits;
+    }
+  }
+  const int lane = threadIdx.x & 63;
+  for (int64_t i0 = (int64_t)blockIdx.x * BS; i0 < n; i0 += (int64_t)gridDim.x * BS) {
+    const int64_t cb = i0 >> 6, c = cb + (threadIdx.x >> 6);   // the workgroup's first wave of rays, this wave's
+    uint64_t before;
+    if (IN_PLACE) {
+      uint64_t t = 0;
+      for (int64_t k = threadIdx.x; k < cb; k += BS) t += mask_counts(w.masks[k]);
+      before = block_sum(t, red);
+      for (int64_t k = cb; k < c && k < nc; ++k) before += mask_counts(w.masks[k]);
+    } else {
+      uint64_t t = 0;
+      const int64_t b = cb / CHUNKS;   // (four consecutive waves share a block of sums)
+      for (int64_t k = threadIdx.x; k < b; k += BS) t += w.bsum[k];
+      before = block_sum(t, red);
+      if (c < nc) before += w.pre[c];
+    }
+    const int64_t i = i0 + threadIdx.x;
+    if (i >= n) continue;
+    const ulonglong2 m = w.masks[c];
+    const uint64_t below = (1ull << lane) - 1ull;
+    if (!((m.x >> lane) & 1ull)) continue;
+    const int64_t s = list ? list[i] : i;
+    const int64_t ri = base + (int64_t)(before & 0xffffffffull) + __popcll(m.x & below);
     const int32_t* tri_orig = S.tri_orig;
     const int32_t* matp = S.mat;
+    const int32_t tag = w.ray[s];
     if (BATCH) {
-      const TraceJob* tj = jobs + w.ray[cur][i];
+      const TraceJob* tj = jobs + tag;
       tri_orig = tj->S.tri_orig;
       matp = tj->S.mat;
     }
-    const int orig = tri_orig[pos];
+    const int orig = tri_orig[w.prev[s]];
     if (ri < P.capacity) {
-      P.p[3 * ri] = w.rp[0][i]; P.p[3 * ri + 1] = w.rp[1][i]; P.p[3 * ri + 2] = w.rp[2][i];
-      P.dout[3 * ri] = (float)w.rd[0][i]; P.dout[3 * ri + 1] = (float)w.rd[1][i]; P.dout[3 * ri + 2] = (float)w.rd[2][i];
-      P.rtot[ri] = w.rr[i];
+      P.p[3 * ri] = w.st[0][s]; P.p[3 * ri + 1] = w.st[1][s]; P.p[3 * ri + 2] = w.st[2][s];
+      P.dout[3 * ri] = (float)w.st[3][s]; P.dout[3 * ri + 1] = (float)w.st[4][s]; P.dout[3 * ri + 2] = (float)w.st[5][s];
+      P.rtot[ri] = w.st[6][s];
       P.tri[ri] = orig;
       P.mat[ri] = matp[orig];
-      P.ray[ri] = w.ray[cur][i];
+      P.ray[ri] = tag;
       P.bounce[ri] = (uint8_t)j;
-      P.flags[ri] = w.rvis[i] != 0 ? 1 : 0;
-      if (P.prev) P.prev[ri] = w.prec[cur][i];
-      if (perrx) P.rx_vis[ri] = w.rvis[i];
+      P.flags[ri] = 0;   // (set by the line-of-sight ray of the next launch)
+      if (P.prev) P.prev[ri] = j > 0 ? w.prec[s] : -1;
+      if (perrx) P.rx_vis[ri] = 0;
     } else {
       atomicOr(&ctl->err, DEV_ERR_CAPACITY);
     }
-    if (f >> 32) {
-      const int64_t k = (int64_t)(o >> 32);
-      w.st[nxt][0][k] = w.rp[0][i]; w.st[nxt][1][k] = w.rp[1][i]; w.st[nxt][2][k] = w.rp[2][i];
-      w.st[nxt][3][k] = w.rd[0][i]; w.st[nxt][4][k] = w.rd[1][i]; w.st[nxt][5][k] = w.rd[2][i];
-      w.st[nxt][6][k] = w.rr[i];
-      w.prev[nxt][k] = pos;
-      w.ray[nxt][k] = w.ray[cur][i];
-      w.prec[nxt][k] = ri;
+    if ((m.y >> lane) & 1ull) {
+      next[(int64_t)(before >> 32) + __popcll(m.y & below)] = (int32_t)s;
+      w.prec[s] = ri;
     }
   }
-}
-
-__global__ void k_bounce_epi(Ctl* ctl, int j) {
-  const int cur = j & 1;
-  const uint64_t t = ctl->tot[0];
-  const int64_t hits = (int64_t)(t & 0xffffffffull);
-  ctl->seg += ctl->n_active[cur];
-  ctl->shadow += hits;
-  ctl->rec_base += hits;
-  ctl->n_active[cur ^ 1] = (int64_t)(t >> 32);
-  ctl->cnt[4] += ctl->n_active[cur];
 }
 
 // ------------------------------------------------------------------ diffraction (Sec. III-D)
@@ -690,7 +802,7 @@ __global__ __launch_bounds__(BS) void k_diff_sample(SceneDev S, DiffArgs a, cons
   __shared__ int lds_stack[TRAV_LDS_STACK * BS];
   const int64_t gtid = (int64_t)blockIdx.x * BS + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * BS;
-  Stack st;
+  Stack<BS> st;
   st.lds = lds_stack + threadIdx.x;
   st.glob = w.gstack + gtid;
   st.gstride = w.gstack_threads;
@@ -787,7 +899,7 @@ __global__ __launch_bounds__(BS) void k_passive(SceneDev S, PoseArgs a, const do
   __shared__ int lds_stack[TRAV_LDS_STACK * BS];
   const int64_t gtid = (int64_t)blockIdx.x * BS + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * BS;
-  Stack st;
+  Stack<BS> st;
   st.lds = lds_stack + threadIdx.x;
   st.glob = w.gstack + gtid;
   st.gstride = w.gstack_threads;
@@ -833,7 +945,6 @@ __global__ void k_trace_final(Ctl* ctl, et_paths P, int diff, int32_t n_passive)
   const int64_t dk = diff ? (int64_t)ctl->tot[3] : 0;
   ctl->diff_kept = dk;
   const int64_t total = spec + dk + n_passive;
-  ctl->n_rec = total;
   P.count[0] = total;
   P.count[1] = spec;
   P.count[2] = dk;
@@ -844,7 +955,8 @@ inline size_t al(size_t b) { return (b + 255) / 256 * 256; }
 
 }  // namespace
 
-size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* base, TraceWS* w, int32_t max_blocks) {
+size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* base, TraceWS* w, int32_t max_blocks,
+                       int32_t los) {
   const int64_t Nm = std::max<int64_t>(N, 1), Tm = std::max<int64_t>(T, 1), Km = std::max<int64_t>(K, 1);
   size_t off = 0;
   auto take = [&](size_t bytes) -> void* {
@@ -853,27 +965,27 @@ size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* bas
     return p;
   };
   TraceWS x{};
-  for (int b = 0; b < 2; ++b) {
-    for (int k = 0; k < 7; ++k) x.st[b][k] = (double*)take(sizeof(double) * Nm);
-    x.prev[b] = (int32_t*)take(sizeof(int32_t) * Nm);
-    x.ray[b] = (int32_t*)take(sizeof(int32_t) * Nm);
-    x.prec[b] = (int64_t*)take(sizeof(int64_t) * Nm);
-  }
-  for (int k = 0; k < 3; ++k) x.rp[k] = (double*)take(sizeof(double) * Nm);
-  for (int k = 0; k < 3; ++k) x.rd[k] = (double*)take(sizeof(double) * Nm);
-  x.rr = (double*)take(sizeof(double) * Nm);
-  x.rpos = (int32_t*)take(sizeof(int32_t) * Nm);
-  x.rvis = (uint64_t*)take(sizeof(uint64_t) * Nm);
-  x.flags = (uint64_t*)take(sizeof(uint64_t) * Nm);
-  x.offs = (uint64_t*)take(sizeof(uint64_t) * Nm);
+  for (int k = 0; k < 7; ++k) x.st[k] = (double*)take(sizeof(double) * Nm);
+  x.prev = (int32_t*)take(sizeof(int32_t) * Nm);
+  x.ray = (int32_t*)take(sizeof(int32_t) * Nm);
+  x.prec = (int64_t*)take(sizeof(int64_t) * Nm);
+  for (int b = 0; b < 2; ++b) x.list[b] = (int32_t*)take(sizeof(int32_t) * Nm);
+  const int64_t waves = (Nm + 63) / 64;
+  x.masks = (ulonglong2*)take(sizeof(ulonglong2) * waves);
+  x.pre = (uint64_t*)take(sizeof(uint64_t) * waves);
+  x.bsum = (uint64_t*)take(sizeof(uint64_t) * ((waves + CHUNKS - 1) / CHUNKS));
   x.scan_tmp = take(scan_temp_bytes(std::max(std::max(Nm, Tm), Km)));
   x.rkeys = (uint32_t*)take(sizeof(uint32_t) * Nm);
   x.rperm = (int32_t*)take(sizeof(int32_t) * Nm);
   x.rsort_tmp = take(sort_temp_bytes(Nm, 4));
-  // global stack columns: one per thread of the largest traversing grid (bounces over N rays,
-  // diffraction over K draws, the passive rays); a fused batch passes its largest tuned grid
-  const int64_t stack_blocks = max_blocks > 0 ? max_blocks
-                                              : std::max<int64_t>(nblk(std::max<int64_t>(N, 1)), nblk(std::max<int64_t>(K, 1)));
+  // global stack columns: one per thread of the largest traversing grid (bounces over N rays and, up to a
+  // round of the chip, the line-of-sight rays beside them, diffraction over K draws, the passive rays); a
+  // fused batch passes its largest tuned grid
+  const int64_t items = std::max<int64_t>(N, 1) * (1 + (int64_t)std::max<int32_t>(los, 1));
+  const int64_t stack_blocks =
+      max_blocks > 0 ? max_blocks
+                     : std::max<int64_t>(std::max<int64_t>(nblk(std::max<int64_t>(N, 1)), nblk(std::max<int64_t>(K, 1))),
+                                         std::min<int64_t>(nblk(items), ROUND_BLOCKS));
   x.gstack_threads = stack_blocks * BS;
   x.gstack = (int32_t*)take(sizeof(int32_t) * (size_t)(TRAV_STACK - TRAV_LDS_STACK) * (size_t)x.gstack_threads);
   x.stack_cap = TRAV_STACK;
@@ -910,11 +1022,37 @@ int64_t bounce_resident_threads() {
     if (v > 0) return v;
   }
   int per_cu = 0, cus = 0;
-  ET_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_bounce<false, false, false>, BS, 0));
+  ET_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_walk<BS, false, false, false>, BS, 0));
   ET_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   const int64_t v = std::max<int64_t>(1, (int64_t)per_cu * cus) * BS;
   if (slot) slot->store(v, std::memory_order_relaxed);
   return v;
+}
+
+// A bounce's walk: tb threads per block.
+template <bool BATCH, bool PERRX>
+void launch_walk(int tb, bool counting, unsigned blocks, hipStream_t s, const SceneDev& S, const PoseArgs& a,
+                 const TraceJob* jobs, const TraceWS& w, Ctl* ctl, const et_paths& P, int j, int last, const double* rx,
+                 int32_t M) {
+  if (tb == 64) {
+    if (counting) k_walk<64, true, BATCH, PERRX><<<blocks, 64, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rx, M);
+    else k_walk<64, false, BATCH, PERRX><<<blocks, 64, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rx, M);
+  } else {
+    if (counting) k_walk<BS, true, BATCH, PERRX><<<blocks, BS, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rx, M);
+    else k_walk<BS, false, BATCH, PERRX><<<blocks, BS, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rx, M);
+  }
+}
+
+// The records of bounce j and the next bounce's list and counts.
+template <bool BATCH>
+void launch_records(int64_t N, const SceneDev& S, const TraceJob* jobs, const TraceWS& w, Ctl* ctl, const et_paths& P, int j,
+                    int perrx, hipStream_t s) {
+  if (N <= SCAN_IN_PLACE) {
+    k_records<BATCH, true><<<nblk(N), BS, 0, s>>>(S, jobs, w, ctl, P, j, perrx);
+  } else {
+    k_mask_sums<<<(unsigned)(((N + 63) / 64 + CHUNKS - 1) / CHUNKS), BS, 0, s>>>(w, ctl, j);
+    k_records<BATCH, false><<<nblk(N), BS, 0, s>>>(S, jobs, w, ctl, P, j, perrx);
+  }
 }
 
 PoseArgs pose_args(const et_sim_desc* sim) {
@@ -960,7 +1098,7 @@ void trace_batch_run(int32_t J, const et_job* jobs, void* dev_jobs, const et_pat
   PoseArgs all{};
   all.N = N;
   const et_paths P = *paths;
-  k_trace_init<<<1, 1, 0, s>>>(ctl, N, carry ? 1 : 0);
+  k_trace_init<<<1, 1, 0, s>>>(ctl, N, carry ? 1 : 0, 0);
   ET_HIP(hipGetLastError());
   // bounce grid: the tuned block count, within what the workspace's global stacks serve
   const int64_t cap_blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, w.gstack_threads / BS));
@@ -974,14 +1112,11 @@ void trace_batch_run(int32_t J, const et_job* jobs, void* dev_jobs, const et_pat
       radix_sort_u32(w.rkeys, w.rperm, N, RAY_KEY_BITS + jb, w.rsort_tmp, s);
     }
     k_ray_init<true><<<nblk_full(N), BS, 0, s>>>(all, nullptr, dj, J, sorted ? w.rperm : nullptr, w, ctl);
-    for (int j = 0; j < B; ++j) {
-      if (counting) k_bounce<true, true, false><<<gb, BS, 0, s>>>(SceneDev{}, all, dj, w, ctl, j, nullptr, 0);
-      else k_bounce<false, true, false><<<gb, BS, 0, s>>>(SceneDev{}, all, dj, w, ctl, j, nullptr, 0);
-      scan_exclusive_u64(w.flags, w.offs, 0, &ctl->n_active[j & 1], N, &ctl->tot[0], w.scan_tmp, s);
-      k_scatter<true><<<nblk(N), BS, 0, s>>>(SceneDev{}, dj, w, ctl, P, j, 0);
-      k_bounce_epi<<<1, 1, 0, s>>>(ctl, j);
-      ET_HIP(hipGetLastError());
+    for (int j = 0; j <= B; ++j) {
+      launch_walk<true, false>(BS, counting, gb, s, SceneDev{}, all, dj, w, ctl, P, j, j == B, nullptr, 0);
+      if (j < B) launch_records<true>(N, SceneDev{}, dj, w, ctl, P, j, 0, s);
     }
+    ET_HIP(hipGetLastError());
   }
   k_trace_final<<<1, 1, 0, s>>>(ctl, P, 0, 0);
   ET_HIP(hipGetLastError());
@@ -992,8 +1127,6 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
   const PoseArgs a = pose_args(sim);
   const et_paths P = *paths;
   const bool perrx = (sim->flags & ET_PER_RX_VISIBILITY) != 0;
-  k_trace_init<<<1, 1, 0, s>>>(ctl, a.N, 0);
-  ET_HIP(hipGetLastError());
   // every traversing grid below stays within the workspace's global stack columns
   auto stack_fits = [&](int64_t n) {
     ET_CHECK((int64_t)nblk(n) * BS <= w.gstack_threads, ET_E_INTERNAL, "trace grid exceeds the workspace's stacks");
@@ -1006,31 +1139,29 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
       radix_sort_u32(w.rkeys, w.rperm, a.N, RAY_KEY_BITS, w.rsort_tmp, s);
     }
     k_ray_init<false><<<nblk_full(a.N), BS, 0, s>>>(a, sim->ray_dirs, nullptr, 0, sorted ? w.rperm : nullptr, w, ctl);
-    // bounce grid: whole rounds of resident blocks (no partly filled last round), the rays taken
-    // by grid stride (the room's 2^20 rays: 4096 blocks, 2.67 rounds, 2.82 ms per trace; 3072, two
+    // bounce grid: whole rounds of resident blocks (no partly filled last round), the waves taken by grid
+    // stride (the room's 2^20 rays: 4096 blocks, 2.67 rounds, 2.82 ms per trace; 3072, two
     // rounds, 2.73 ms; 2560 2.79, 2048 3.13, 1536 3.06 ms; foliage's 2^22 rays: 8192 blocks 27.7 ms,
-    // 3072 28.7 ms)
+    // 3072 28.7 ms), within the threads that have a global stack column
+    const double* rx = perrx ? sim->rx_pos : nullptr;
+    const int32_t M = perrx ? sim->M : 1;
     const int64_t res_blocks = std::max<int64_t>(1, bounce_resident_threads() / BS);
-    const int64_t nb = nblk(a.N);
-    const unsigned gb = (unsigned)(nb > res_blocks ? nb / res_blocks * res_blocks : nb);
-    for (int j = 0; j < a.B; ++j) {
-      const double* rx = sim->rx_pos;
-      const int32_t M = sim->M;
-      if (perrx) {
-        if (counting) k_bounce<true, false, true><<<gb, BS, 0, s>>>(S, a, nullptr, w, ctl, j, rx, M);
-        else k_bounce<false, false, true><<<gb, BS, 0, s>>>(S, a, nullptr, w, ctl, j, rx, M);
-      } else {
-        if (counting) k_bounce<true, false, false><<<gb, BS, 0, s>>>(S, a, nullptr, w, ctl, j, nullptr, 0);
-        else k_bounce<false, false, false><<<gb, BS, 0, s>>>(S, a, nullptr, w, ctl, j, nullptr, 0);
-      }
-      scan_exclusive_u64(w.flags, w.offs, 0, &ctl->n_active[j & 1], a.N, &ctl->tot[0], w.scan_tmp, s);
-      k_scatter<false><<<nblk(a.N), BS, 0, s>>>(S, nullptr, w, ctl, P, j, perrx ? 1 : 0);
-      k_bounce_epi<<<1, 1, 0, s>>>(ctl, j);
-      ET_HIP(hipGetLastError());
+    for (int j = 0; j <= a.B; ++j) {
+      // closest hits of at most N rays and the line-of-sight rays of as many records
+      const int64_t items = (j < a.B ? a.N : 0) + (j > 0 ? a.N * M : 0);
+      const int64_t nb = std::min<int64_t>(nblk(items), w.gstack_threads / BS);
+      const int tb = nb * (BS / 64) <= 4 * res_blocks / TRAV_WAVES_PER_SIMD ? 64 : BS;
+      const unsigned gb = (unsigned)(tb == 64 ? std::max<int64_t>(1, std::min<int64_t>((items + 63) / 64, w.gstack_threads / 64))
+                                              : nb > res_blocks ? nb / res_blocks * res_blocks : nb);
+      if (perrx) launch_walk<false, true>(tb, counting, gb, s, S, a, nullptr, w, ctl, P, j, j == a.B, rx, M);
+      else launch_walk<false, false>(tb, counting, gb, s, S, a, nullptr, w, ctl, P, j, j == a.B, rx, M);
+      if (j < a.B) launch_records<false>(a.N, S, nullptr, w, ctl, P, j, perrx ? 1 : 0, s);
     }
-  } else if (a.N > 0) {
-    // empty scene: every ray misses at its first segment
-    k_bounce_epi<<<1, 1, 0, s>>>(ctl, 0);
+    ET_HIP(hipGetLastError());
+  } else {
+    // no rays, or an empty scene: every ray misses at its first segment
+    k_trace_init<<<1, 1, 0, s>>>(ctl, a.N, 0, a.N);
+    ET_HIP(hipGetLastError());
   }
   const bool diff = (sim->flags & ET_DIFFRACTION) && sim->diff_K > 0 && S.T > 0;
   if (diff) {

@@ -36,6 +36,7 @@ constexpr int EMPTY = INT32_MIN;
 // on 2048 blocks, whose second round leaves part of the chip idle).
 constexpr int MAX_BLOCKS = 8192;
 
+constexpr int64_t RS_WAVES = 2560;
 constexpr int ROUND_BLOCKS = 256 * TRAV_WAVES_PER_SIMD;   // blocks of 256 threads of a round on 256 compute units
 
 inline unsigned nblk(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + BS - 1) / BS, MAX_BLOCKS)); }
@@ -402,11 +403,13 @@ __global__ void k_ray_init(PoseArgs a0, const float* __restrict__ dirs0, const T
 // toward the pose's reference point.
 // Six waves per SIMD (the register budget that asks for, 80, holds the kernel without spills):
 // measured 7% faster on the room's trace and 15% on foliage's than five.
+// A wave takes 1 << rs rays (its other lanes idle): 64 where there are waves enough to fill the chip; fewer rays of
+// a small pose per wave shorten its walk, which is as long as its longest ray's, and its gathers.
 // TB: threads per block: 64 while the rays leave compute units without a wave, else 256.
 template <int TB, bool COUNT, bool BATCH, bool PERRX>
 __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_PER_SIMD))) void k_walk(
     SceneDev S0, PoseArgs a0, const TraceJob* __restrict__ jobs, TraceWS w, Ctl* ctl, et_paths P, int j, int last,
-    const double* __restrict__ rxp, int32_t M) {
+    int rs, const double* __restrict__ rxp, int32_t M) {
   __shared__ int lds_stack[TRAV_LDS_STACK * TB];
   const int lane = threadIdx.x & 63;
   const int64_t n = last ? 0 : ctl->act[j];
@@ -414,7 +417,8 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_P
   const int64_t n_los = j > 0 ? (min(ctl->base[j], P.capacity) - r0) * (PERRX ? M : 1) : 0;
   const int64_t gtid = (int64_t)blockIdx.x * TB + threadIdx.x;
   const int64_t waves = (int64_t)gridDim.x * (TB / 64);
-  const int64_t nc = (n + 63) / 64, nl = n_los > 0 ? (n_los + 63) / 64 : 0;
+  const int R = 1 << rs;
+  const int64_t nc = (n + R - 1) >> rs, nl = n_los > 0 ? (n_los + R - 1) >> rs : 0;
   const int32_t* list = j > 0 ? w.list[j & 1] : nullptr;
   Stack<TB> st;
   st.lds = lds_stack + threadIdx.x;
@@ -425,9 +429,9 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_P
   int64_t cn_c = 0, ct_c = 0, cn_a = 0, ct_a = 0, rays_a = 0;
   for (int64_t c = gtid >> 6; c < nc + nl; c += waves) {
     if (c < nc) {
-      const int64_t i = c * 64 + lane;
+      const int64_t i = (c << rs) + lane;
       bool hit = false, cont = false;
-      if (i < n) {
+      if (lane < R && i < n) {
         const int64_t s = list ? list[i] : i;
         int pos;
         float th = INFINITY;
@@ -481,8 +485,8 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_P
       if (lane == 0) w.masks[c] = make_ulonglong2(hm, cm);
     } else {
       // line of sight from a record's point toward the receiver reference point (or receiver m)
-      const int64_t e = (c - nc) * 64 + lane;
-      if (e < n_los) {
+      const int64_t e = ((c - nc) << rs) + lane;
+      if (lane < R && e < n_los) {
         const int64_t r = r0 + (PERRX ? e / M : e);
         const int m = PERRX ? (int)(e - (r - r0) * M) : 0;
         SceneDev S = S0;
@@ -523,18 +527,30 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_P
   }
 }
 
+// Record counts of the finished trace.
+__device__ inline void trace_final(Ctl* ctl, const et_paths& P, int diff, int32_t n_passive) {
+  const int64_t spec = ctl->rec_base;
+  const int64_t dk = diff ? (int64_t)ctl->tot[3] : 0;
+  ctl->diff_kept = dk;
+  const int64_t total = spec + dk + n_passive;
+  P.count[0] = total;
+  P.count[1] = spec;
+  P.count[2] = dk;
+  P.count[3] = ctl->seg;
+}
+
 // Hits (low half) and continuing rays (high half) of a wave's masks.
 __device__ inline uint64_t mask_counts(ulonglong2 m) {
   return (uint64_t)__popcll(m.x) | (uint64_t)__popcll(m.y) << 32;
 }
 
-// Exclusive sums of the masks' counts within blocks of 1024, and the blocks' sums (more rays than
-// SCAN_IN_PLACE; fewer are summed by k_records itself).
+// Exclusive sums of the masks' counts within blocks of 1024, and the blocks' sums (more masks than
+// SCAN_IN_PLACE, eight per thread of k_records' workgroups; fewer are summed by k_records itself).
 constexpr int CHUNKS = 1024;
-constexpr int64_t SCAN_IN_PLACE = 65536;
-__global__ __launch_bounds__(BS) void k_mask_sums(TraceWS w, const Ctl* ctl, int j) {
+constexpr int64_t SCAN_IN_PLACE = 2048;
+__global__ __launch_bounds__(BS) void k_mask_sums(TraceWS w, const Ctl* ctl, int j, int rs) {
   __shared__ uint64_t wsum[BS / 64];
-  const int64_t nc = (ctl->act[j] + 63) / 64;
+  const int64_t nc = (ctl->act[j] + (1 << rs) - 1) >> rs;
   const int64_t c0 = (int64_t)blockIdx.x * CHUNKS + 4 * threadIdx.x;
   if ((int64_t)blockIdx.x * CHUNKS >= nc) return;
   uint64_t v[4], s = 0;
@@ -575,13 +591,14 @@ __device__ inline uint64_t block_sum(uint64_t v, uint64_t* red) {
 }
 
 // The records of bounce j in ray order after the earlier bounces', the list of the slots that go on, and (first
-// workgroup) the counts of the next bounce.  A workgroup takes 256 rays, the masks of four waves; what lies
-// before them comes from k_mask_sums, or (IN_PLACE) from summing the masks before it.
+// workgroup) the counts of the next bounce.  A workgroup takes 256 rays, the masks of 256 >> rs waves; what lies
+// before them comes from k_mask_sums, or (IN_PLACE) from summing the masks before it.  fin: this is the last
+// bounce and no other records follow.
 template <bool BATCH, bool IN_PLACE>
 __global__ __launch_bounds__(BS) void k_records(SceneDev S, const TraceJob* __restrict__ jobs, TraceWS w, Ctl* ctl,
-                                                et_paths P, int j, int perrx) {
+                                                et_paths P, int j, int rs, int perrx, int fin) {
   __shared__ uint64_t red[BS / 64];
-  const int64_t n = ctl->act[j], nc = (n + 63) / 64;
+  const int64_t n = ctl->act[j], nc = (n + (1 << rs) - 1) >> rs;
   const int64_t base = ctl->base[j];
   const int32_t* list = j > 0 ? w.list[j & 1] : nullptr;
   int32_t* next = w.list[(j + 1) & 1];
@@ -601,11 +618,12 @@ __global__ __launch_bounds__(BS) void k_records(SceneDev S, const TraceJob* __re
       ctl->act[j + 1] = (int64_t)(t >> 32);
       ctl->base[j + 1] = base + hits;
       ctl->rec_base = base + hits;
+      if (fin) trace_final(ctl, P, 0, 0);
     }
   }
-  const int lane = threadIdx.x & 63;
+  const int bit = threadIdx.x & ((1 << rs) - 1);
   for (int64_t i0 = (int64_t)blockIdx.x * BS; i0 < n; i0 += (int64_t)gridDim.x * BS) {
-    const int64_t cb = i0 >> 6, c = cb + (threadIdx.x >> 6);   // the workgroup's first wave of rays, this wave's
+    const int64_t cb = i0 >> rs, c = cb + (threadIdx.x >> rs);   // the workgroup's first mask, this thread's
     uint64_t before;
     if (IN_PLACE) {
       uint64_t t = 0;
@@ -614,7 +632,7 @@ __global__ __launch_bounds__(BS) void k_records(SceneDev S, const TraceJob* __re
       for (int64_t k = cb; k < c && k < nc; ++k) before += mask_counts(w.masks[k]);
     } else {
       uint64_t t = 0;
-      const int64_t b = cb / CHUNKS;   // (four consecutive waves share a block of sums)
+      const int64_t b = cb / CHUNKS;   // (a workgroup's masks share a block of sums)
       for (int64_t k = threadIdx.x; k < b; k += BS) t += w.bsum[k];
       before = block_sum(t, red);
       if (c < nc) before += w.pre[c];
@@ -622,8 +640,8 @@ __global__ __launch_bounds__(BS) void k_records(SceneDev S, const TraceJob* __re
     const int64_t i = i0 + threadIdx.x;
     if (i >= n) continue;
     const ulonglong2 m = w.masks[c];
-    const uint64_t below = (1ull << lane) - 1ull;
-    if (!((m.x >> lane) & 1ull)) continue;
+    const uint64_t below = (1ull << bit) - 1ull;
+    if (!((m.x >> bit) & 1ull)) continue;
     const int64_t s = list ? list[i] : i;
     const int64_t ri = base + (int64_t)(before & 0xffffffffull) + __popcll(m.x & below);
     const int32_t* tri_orig = S.tri_orig;
@@ -649,7 +667,7 @@ __global__ __launch_bounds__(BS) void k_records(SceneDev S, const TraceJob* __re
     } else {
       atomicOr(&ctl->err, DEV_ERR_CAPACITY);
     }
-    if ((m.y >> lane) & 1ull) {
+    if ((m.y >> bit) & 1ull) {
       next[(int64_t)(before >> 32) + __popcll(m.y & below)] = (int32_t)s;
       w.prec[s] = ri;
     }
@@ -759,20 +777,17 @@ __global__ void k_elig_keys(SceneDev S, int per_mesh, const uint64_t* __restrict
   vals[p] = (int32_t)t;
 }
 
-__global__ void k_elig_count(Ctl* ctl) { ctl->n_elig = (int64_t)ctl->tot[1]; }
-
 __global__ void k_sorted_q(const uint64_t* __restrict__ keys, const Ctl* ctl, uint64_t* __restrict__ qs) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ctl->n_elig) return;
   qs[i] = 4294967296ull - (keys[i] & 0xffffffffull);
 }
 
-// Group starts in the sorted list: a group per mesh (per_mesh), else one group.
-__global__ void k_group_flags(const uint64_t* __restrict__ keys, int per_mesh, const Ctl* ctl,
-                              uint64_t* __restrict__ flag) {
+// Group starts in the sorted list: a group per mesh.
+__global__ void k_group_flags(const uint64_t* __restrict__ keys, const Ctl* ctl, uint64_t* __restrict__ flag) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ctl->n_elig) return;
-  flag[i] = (i == 0 || (per_mesh && (keys[i] >> 32) != (keys[i - 1] >> 32))) ? 1ull : 0ull;
+  flag[i] = (i == 0 || (keys[i] >> 32) != (keys[i - 1] >> 32)) ? 1ull : 0ull;
 }
 
 __global__ void k_group_starts(const uint64_t* __restrict__ flag, const uint64_t* __restrict__ rank, const Ctl* ctl,
@@ -781,11 +796,12 @@ __global__ void k_group_starts(const uint64_t* __restrict__ flag, const uint64_t
   if (i < ctl->n_elig && flag[i]) gstart[rank[i]] = i;
 }
 
-// Group count and draws; more meshes than max_meshes keeps the first ones and reports a
+// Group count and draws (one CDF: one group); more meshes than max_meshes keeps the first ones and reports a
 // capacity error.  The last kept group ends where the first dropped one starts (its entry of
 // gstart is already that start), so only an untruncated list gets the end marker n_elig.
 __global__ void k_group_count(Ctl* ctl, DiffArgs a, int64_t* __restrict__ gstart) {
-  int64_t g = (int64_t)ctl->tot[2];
+  int64_t g = a.per_mesh ? (int64_t)ctl->tot[2] : (ctl->n_elig > 0 ? 1 : 0);
+  if (!a.per_mesh) gstart[0] = 0;
   if (a.per_mesh && g > a.max_meshes) {
     atomicOr(&ctl->err, DEV_ERR_CAPACITY);
     g = a.max_meshes;
@@ -865,7 +881,9 @@ __global__ __launch_bounds__(BS) void k_diff_sample(SceneDev S, DiffArgs a, cons
     atomicAdd((unsigned long long*)&ctl->overflow, (unsigned long long)st.overflow);
     atomicOr(&ctl->err, DEV_ERR_STACK);
   }
-  atomicAdd((unsigned long long*)&ctl->shadow, (unsigned long long)rays);
+  // (one addition per wave: one per thread took most of this kernel's 100 us for 65,536 draws)
+  for (int o = 32; o > 0; o >>= 1) rays += __shfl_xor(rays, o);
+  if ((threadIdx.x & 63) == 0 && rays) atomicAdd((unsigned long long*)&ctl->shadow, (unsigned long long)rays);
 }
 
 __global__ void k_diff_scatter(SceneDev S, DiffArgs a, TraceWS w, Ctl* ctl, et_paths P) {
@@ -940,16 +958,7 @@ __global__ __launch_bounds__(BS) void k_passive(SceneDev S, PoseArgs a, const do
   if (rays) atomicAdd((unsigned long long*)&ctl->shadow, (unsigned long long)rays);
 }
 
-__global__ void k_trace_final(Ctl* ctl, et_paths P, int diff, int32_t n_passive) {
-  const int64_t spec = ctl->rec_base;
-  const int64_t dk = diff ? (int64_t)ctl->tot[3] : 0;
-  ctl->diff_kept = dk;
-  const int64_t total = spec + dk + n_passive;
-  P.count[0] = total;
-  P.count[1] = spec;
-  P.count[2] = dk;
-  P.count[3] = ctl->seg;
-}
+__global__ void k_trace_final(Ctl* ctl, et_paths P, int diff, int32_t n_passive) { trace_final(ctl, P, diff, n_passive); }
 
 inline size_t al(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -970,7 +979,8 @@ size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* bas
   x.ray = (int32_t*)take(sizeof(int32_t) * Nm);
   x.prec = (int64_t*)take(sizeof(int64_t) * Nm);
   for (int b = 0; b < 2; ++b) x.list[b] = (int32_t*)take(sizeof(int32_t) * Nm);
-  const int64_t waves = (Nm + 63) / 64;
+  // (small sets take down to 8 rays per wave: below that many masks of 8)
+  const int64_t waves = std::max<int64_t>((Nm + 63) / 64, std::min<int64_t>((Nm + 7) / 8, 2 * RS_WAVES));
   x.masks = (ulonglong2*)take(sizeof(ulonglong2) * waves);
   x.pre = (uint64_t*)take(sizeof(uint64_t) * waves);
   x.bsum = (uint64_t*)take(sizeof(uint64_t) * ((waves + CHUNKS - 1) / CHUNKS));
@@ -985,7 +995,7 @@ size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* bas
   const int64_t stack_blocks =
       max_blocks > 0 ? max_blocks
                      : std::max<int64_t>(std::max<int64_t>(nblk(std::max<int64_t>(N, 1)), nblk(std::max<int64_t>(K, 1))),
-                                         std::min<int64_t>(nblk(items), ROUND_BLOCKS));
+                                         std::min<int64_t>(nblk(8 * items), ROUND_BLOCKS));
   x.gstack_threads = stack_blocks * BS;
   x.gstack = (int32_t*)take(sizeof(int32_t) * (size_t)(TRAV_STACK - TRAV_LDS_STACK) * (size_t)x.gstack_threads);
   x.stack_cap = TRAV_STACK;
@@ -1032,26 +1042,27 @@ int64_t bounce_resident_threads() {
 // A bounce's walk: tb threads per block.
 template <bool BATCH, bool PERRX>
 void launch_walk(int tb, bool counting, unsigned blocks, hipStream_t s, const SceneDev& S, const PoseArgs& a,
-                 const TraceJob* jobs, const TraceWS& w, Ctl* ctl, const et_paths& P, int j, int last, const double* rx,
-                 int32_t M) {
+                 const TraceJob* jobs, const TraceWS& w, Ctl* ctl, const et_paths& P, int j, int last, int rs,
+                 const double* rx, int32_t M) {
   if (tb == 64) {
-    if (counting) k_walk<64, true, BATCH, PERRX><<<blocks, 64, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rx, M);
-    else k_walk<64, false, BATCH, PERRX><<<blocks, 64, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rx, M);
+    if (counting) k_walk<64, true, BATCH, PERRX><<<blocks, 64, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rs, rx, M);
+    else k_walk<64, false, BATCH, PERRX><<<blocks, 64, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rs, rx, M);
   } else {
-    if (counting) k_walk<BS, true, BATCH, PERRX><<<blocks, BS, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rx, M);
-    else k_walk<BS, false, BATCH, PERRX><<<blocks, BS, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rx, M);
+    if (counting) k_walk<BS, true, BATCH, PERRX><<<blocks, BS, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rs, rx, M);
+    else k_walk<BS, false, BATCH, PERRX><<<blocks, BS, 0, s>>>(S, a, jobs, w, ctl, P, j, last, rs, rx, M);
   }
 }
 
-// The records of bounce j and the next bounce's list and counts.
+// The records of bounce j and the next bounce's list and counts; N: the most rays.
 template <bool BATCH>
 void launch_records(int64_t N, const SceneDev& S, const TraceJob* jobs, const TraceWS& w, Ctl* ctl, const et_paths& P, int j,
-                    int perrx, hipStream_t s) {
-  if (N <= SCAN_IN_PLACE) {
-    k_records<BATCH, true><<<nblk(N), BS, 0, s>>>(S, jobs, w, ctl, P, j, perrx);
+                    int rs, int perrx, int fin, hipStream_t s) {
+  const int64_t masks = (N + (1 << rs) - 1) >> rs;
+  if (masks <= SCAN_IN_PLACE) {
+    k_records<BATCH, true><<<nblk(N), BS, 0, s>>>(S, jobs, w, ctl, P, j, rs, perrx, fin);
   } else {
-    k_mask_sums<<<(unsigned)(((N + 63) / 64 + CHUNKS - 1) / CHUNKS), BS, 0, s>>>(w, ctl, j);
-    k_records<BATCH, false><<<nblk(N), BS, 0, s>>>(S, jobs, w, ctl, P, j, perrx);
+    k_mask_sums<<<(unsigned)((masks + CHUNKS - 1) / CHUNKS), BS, 0, s>>>(w, ctl, j, rs);
+    k_records<BATCH, false><<<nblk(N), BS, 0, s>>>(S, jobs, w, ctl, P, j, rs, perrx, fin);
   }
 }
 
@@ -1113,8 +1124,8 @@ void trace_batch_run(int32_t J, const et_job* jobs, void* dev_jobs, const et_pat
     }
     k_ray_init<true><<<nblk_full(N), BS, 0, s>>>(all, nullptr, dj, J, sorted ? w.rperm : nullptr, w, ctl);
     for (int j = 0; j <= B; ++j) {
-      launch_walk<true, false>(BS, counting, gb, s, SceneDev{}, all, dj, w, ctl, P, j, j == B, nullptr, 0);
-      if (j < B) launch_records<true>(N, SceneDev{}, dj, w, ctl, P, j, 0, s);
+      launch_walk<true, false>(BS, counting, gb, s, SceneDev{}, all, dj, w, ctl, P, j, j == B, 6, nullptr, 0);
+      if (j < B) launch_records<true>(N, SceneDev{}, dj, w, ctl, P, j, 6, 0, 0, s);
     }
     ET_HIP(hipGetLastError());
   }
@@ -1127,6 +1138,9 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
   const PoseArgs a = pose_args(sim);
   const et_paths P = *paths;
   const bool perrx = (sim->flags & ET_PER_RX_VISIBILITY) != 0;
+  const bool diff = (sim->flags & ET_DIFFRACTION) && sim->diff_K > 0 && S.T > 0;
+  const int32_t n_passive = (sim->flags & ET_PASSIVE) ? sim->M : 0;
+  const bool fin = !diff && n_passive == 0 && a.N > 0 && S.T > 0;   // the last bounce's records end the trace
   // every traversing grid below stays within the workspace's global stack columns
   auto stack_fits = [&](int64_t n) {
     ET_CHECK((int64_t)nblk(n) * BS <= w.gstack_threads, ET_E_INTERNAL, "trace grid exceeds the workspace's stacks");
@@ -1146,16 +1160,20 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
     const double* rx = perrx ? sim->rx_pos : nullptr;
     const int32_t M = perrx ? sim->M : 1;
     const int64_t res_blocks = std::max<int64_t>(1, bounce_resident_threads() / BS);
+    // rays per wave: the most that leaves RS_WAVES waves (two and a half per SIMD), from 64 down to 8
+    const int64_t most = a.N * (1 + M);
+    int rs = 6;
+    while (rs > 3 && (most >> rs) < RS_WAVES) --rs;
     for (int j = 0; j <= a.B; ++j) {
       // closest hits of at most N rays and the line-of-sight rays of as many records
-      const int64_t items = (j < a.B ? a.N : 0) + (j > 0 ? a.N * M : 0);
-      const int64_t nb = std::min<int64_t>(nblk(items), w.gstack_threads / BS);
-      const int tb = nb * (BS / 64) <= 4 * res_blocks / TRAV_WAVES_PER_SIMD ? 64 : BS;
-      const unsigned gb = (unsigned)(tb == 64 ? std::max<int64_t>(1, std::min<int64_t>((items + 63) / 64, w.gstack_threads / 64))
+      const int64_t waves = (((j < a.B ? a.N : 0) + (j > 0 ? a.N * M : 0)) >> rs) + 2;
+      const int64_t nb = std::min<int64_t>((waves + BS / 64 - 1) / (BS / 64), w.gstack_threads / BS);
+      const int tb = waves <= 4 * res_blocks / TRAV_WAVES_PER_SIMD ? 64 : BS;
+      const unsigned gb = (unsigned)(tb == 64 ? std::min<int64_t>(waves, w.gstack_threads / 64)
                                               : nb > res_blocks ? nb / res_blocks * res_blocks : nb);
-      if (perrx) launch_walk<false, true>(tb, counting, gb, s, S, a, nullptr, w, ctl, P, j, j == a.B, rx, M);
-      else launch_walk<false, false>(tb, counting, gb, s, S, a, nullptr, w, ctl, P, j, j == a.B, rx, M);
-      if (j < a.B) launch_records<false>(a.N, S, nullptr, w, ctl, P, j, perrx ? 1 : 0, s);
+      if (perrx) launch_walk<false, true>(tb, counting, gb, s, S, a, nullptr, w, ctl, P, j, j == a.B, rs, rx, M);
+      else launch_walk<false, false>(tb, counting, gb, s, S, a, nullptr, w, ctl, P, j, j == a.B, rs, rx, M);
+      if (j < a.B) launch_records<false>(a.N, S, nullptr, w, ctl, P, j, rs, perrx ? 1 : 0, fin && j + 1 == a.B, s);
     }
     ET_HIP(hipGetLastError());
   } else {
@@ -1163,7 +1181,6 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
     k_trace_init<<<1, 1, 0, s>>>(ctl, a.N, 0, a.N);
     ET_HIP(hipGetLastError());
   }
-  const bool diff = (sim->flags & ET_DIFFRACTION) && sim->diff_K > 0 && S.T > 0;
   if (diff) {
     DiffArgs d;
     for (int k = 0; k < 3; ++k) { d.s[k] = sim->emitter_pos[k]; d.axis[k] = sim->emitter_rot[3 * k]; }
@@ -1183,28 +1200,28 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
     k_obj_fov<<<nblk_full(S.n_obj), BS, 0, s>>>(S, d, w.oel);
     k_cmax<<<(unsigned)std::min<int64_t>(nblk_full(S.T), 256), BS, 0, s>>>(S, w.oel, ctl);
     k_qweight<<<nblk_full(S.T), BS, 0, s>>>(S, d, w.oel, ctl, w.dq, w.dflags);
-    scan_exclusive_u64(w.dflags, w.doffs, S.T, nullptr, S.T, &ctl->tot[1], w.scan_tmp, s);
+    scan_exclusive_u64(w.dflags, w.doffs, S.T, nullptr, S.T, (uint64_t*)&ctl->n_elig, w.scan_tmp, s);
     k_elig_keys<<<nblk_full(S.T), BS, 0, s>>>(S, d.per_mesh, w.dq, w.dflags, w.doffs, w.dkeys, w.dvals);
-    k_elig_count<<<1, 1, 0, s>>>(ctl);
     radix_sort_u64(w.dkeys, w.dvals, 0, &ctl->n_elig, S.T, d.per_mesh ? 32 + obj_bits : 32, w.sort_tmp, s);
     // weights in sorted order, then their exclusive prefix sums (the CDF) and total
     k_sorted_q<<<nblk_full(S.T), BS, 0, s>>>(w.dkeys, ctl, w.dq);
     scan_exclusive_u64(w.dq, w.doffs, 0, &ctl->n_elig, S.T, nullptr, w.scan_tmp, s);
     // groups of the sorted list (meshes, or one) and the number of draws
-    k_group_flags<<<nblk_full(S.T), BS, 0, s>>>(w.dkeys, d.per_mesh, ctl, w.dflags);
-    scan_exclusive_u64(w.dflags, w.goffs, 0, &ctl->n_elig, S.T, &ctl->tot[2], w.scan_tmp, s);
-    k_group_starts<<<nblk_full(S.T), BS, 0, s>>>(w.dflags, w.goffs, ctl, w.gstart);
+    if (d.per_mesh) {
+      k_group_flags<<<nblk_full(S.T), BS, 0, s>>>(w.dkeys, ctl, w.dflags);
+      scan_exclusive_u64(w.dflags, w.goffs, 0, &ctl->n_elig, S.T, &ctl->tot[2], w.scan_tmp, s);
+      k_group_starts<<<nblk_full(S.T), BS, 0, s>>>(w.dflags, w.goffs, ctl, w.gstart);
+    }
     k_group_count<<<1, 1, 0, s>>>(ctl, d, w.gstart);
     k_diff_sample<<<nblk(max_draw), BS, 0, s>>>(S, d, w.doffs, w.dq, w.dvals, w, ctl);
     scan_exclusive_u64(w.skeep, w.soffs, 0, &ctl->n_draw, max_draw, &ctl->tot[3], w.scan_tmp, s);
     k_diff_scatter<<<nblk(max_draw), BS, 0, s>>>(S, d, w, ctl, P);
     ET_HIP(hipGetLastError());
   }
-  const int32_t n_passive = (sim->flags & ET_PASSIVE) ? sim->M : 0;
   if (n_passive > 0) stack_fits(n_passive);
   if (n_passive > 0)
     k_passive<<<nblk(n_passive), BS, 0, s>>>(S, a, sim->rx_pos, n_passive, diff ? 1 : 0, w, ctl, P, perrx ? 1 : 0);
-  k_trace_final<<<1, 1, 0, s>>>(ctl, P, diff ? 1 : 0, n_passive);
+  if (!fin) k_trace_final<<<1, 1, 0, s>>>(ctl, P, diff ? 1 : 0, n_passive);
   ET_HIP(hipGetLastError());
 }
 

@@ -42,13 +42,13 @@ ADJ_FLOP_PER_TERM = 16           # two: the band sum conj(g) T and the frequency
 SYNTH_EXEC_FLOP_PER_TERM = 24
 ADJ_EXEC_FLOP_PER_TERM = 48
 FLOP_PER_MFMA_F16 = 2 * 16 * 16 * 32   # v_mfma_f32_16x16x32_f16
-NODE_BYTES, TRI_BYTES, RAY_IO_BYTES = 64, 48, 128
+NODE_BYTES, TRI_BYTES, RAY_IO_BYTES = 128, 48, 128
 # traversal arithmetic per unit, one VALU lane operation each (an FMA counts once): a node visit
-# is the slab test of both child boxes (per box 6 FMA, 6 min/max per axis, 4 for the entry and
+# is the slab test of its four child boxes (per box 6 FMA, 6 min/max per axis, 4 for the entry and
 # exit reductions, the widening multiply, 1 min and 1 compare); a triangle test is the watertight
 # test (9 translations, 6 shears, 6 for the edge functions, 6 sign tests, 2 for the determinant,
 # 3 scalings, 3 for T, 1 division); a ray its set-up (reciprocals, axis choice, shear constants)
-NODE_OPS, TRI_OPS, RAY_OPS = 38, 36, 25
+NODE_OPS, TRI_OPS, RAY_OPS = 76, 36, 25
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # lane operations per second: 256 CUs x 4 SIMDs x 16 lanes
 
 
@@ -417,17 +417,18 @@ def fold_mode(F: int, bands) -> int:
 def fwd_kernel_name(s) -> str:
     """The forward matrix-core kernel's instantiation, as the profiler names it."""
     Bd = s.desc.Bd if s.desc.directivity else 0
-    return f"k_synth_mfma<false, {'true' if s.F // 64 <= 32 else 'false'}, {fold_mode(s.F, [s.desc.Bk, Bd])}>"
+    return (f"k_synth_mfma<false, {1 if s.F // 64 <= 32 else 2}, {fold_mode(s.F, [s.desc.Bk, Bd])}, "
+            f"{'true' if Bd else 'false'}>")
 
 
 def adj_kernel_name(s) -> str:
     return f"k_synth_bwd_mfma<false, {'true' if s.F // 64 <= 32 else 'false'}, {fold_mode(s.F, [s.desc.Bk])}>"
 
 
-def trace_roofline(cnt, ms_trace: float, traffic_key: str = "k_bounce<false, false, false>") -> dict:
+def trace_roofline(cnt, ms_trace: float, traffic_key: str = "k_walk<256, false, false, false>") -> dict:
     """The traversal against HBM bandwidth: the node, triangle and ray bytes its visits touch
     (counting pass) over the trace time of the step.  Caches serve most of them, so they can
-    exceed what HBM delivers; the measured HBM bytes of the bounce kernel are `traffic`.  The
+    exceed what HBM delivers; the measured HBM bytes of the walk kernel are `traffic`.  The
     arithmetic of the same visits against the vector-ALU lane rate is reported beside it."""
     nodes, tris = cnt.nodes_closest + cnt.nodes_any, cnt.tris_closest + cnt.tris_any
     rays = cnt.rays_closest + cnt.rays_any
@@ -435,7 +436,7 @@ def trace_roofline(cnt, ms_trace: float, traffic_key: str = "k_bounce<false, fal
     gbs = trav_bytes / (ms_trace * 1e-3) / 1e9
     ops = nodes * NODE_OPS + tris * TRI_OPS + rays * RAY_OPS
     tops = ops / (ms_trace * 1e-3) / 1e12
-    return {"kernel": "k_bounce<false, false, false>", "bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS,
+    return {"kernel": "k_walk<256, false, false, false>", "bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS,
             "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS, "traffic": counter_for(traffic_key),
             "algorithmic_bytes": trav_bytes,
             "per_unit": f"{NODE_BYTES} B per node visit, {TRI_BYTES} B per triangle test, {RAY_IO_BYTES} B per ray "
@@ -479,7 +480,7 @@ def configs_leg(ctx, et, W, reps):
             roof = mfma_roofline(fwd_kernel_name(s_c), terms_c, st.ms_synth_kernel, SYNTH_FLOP_PER_TERM,
                                  SYNTH_EXEC_FLOP_PER_TERM)
         else:
-            roof = trace_roofline(cnt, st.ms_trace, f"k_bounce<false, false, false> [{name}]")
+            roof = trace_roofline(cnt, st.ms_trace, f"k_walk<256, false, false, false> [{name}]")
         res[name] = {"triangles": len(scene_c["tris"]), "rays": s_c.desc.N, "receivers": s_c.M, "bins": s_c.F,
                      "ms_per_step": ms, "mrays_bounces_per_s": st.segments / (ms * 1e-3) / 1e6,
                      "trace_ms": st.ms_trace, "synth_kernel_ms": st.ms_synth_kernel, "synth_kernel": st.synth_kernel,

@@ -414,15 +414,16 @@ typedef struct {
 } et_stats;
 int et_get_stats(et_ctx* ctx, et_stats* out);   /* synchronises the context stream */
 
-/* Traversal work counters (node and triangle fetches of closest-hit and any-hit queries)
+/* Traversal work counters (four-wide node and triangle fetches of closest-hit and any-hit
+ * queries)
  * for the roofline's algorithmic bytes: enables counting in the next et_trace.  0/1. */
 int et_set_counting(et_ctx* ctx, int enable);
 typedef struct { int64_t nodes_closest, tris_closest, nodes_any, tris_any, rays_closest, rays_any; } et_counters;
 int et_get_counters(et_ctx* ctx, et_counters* out);
 
-/* Test hook for the overflow path of the traversal stack (normally unreachable: 64 entries per
- * lane hold any tree this library builds for up to 2^31 triangles in practice).  Limits the
- * per-lane stack of later traces on this context to `entries` (1 .. 64; 0 restores 64).  A
+/* Test hook for the overflow path of the traversal stack (normally unreachable: it holds any
+ * tree of up to 64 levels, the deepest that a build accepts).  Limits the
+ * stack of later traces on this context to `entries` of those levels (1 .. 64; 0 restores 64).  A
  * traversal that needs more drops the subtrees that do not fit, so those rays may miss their
  * true hits; every kernel still completes, and et_get_stats reports the dropped pushes in
  * stack_overflows with status ET_E_INTERNAL.  ET_E_INVALID outside [0, 64]. */

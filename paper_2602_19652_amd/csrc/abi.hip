@@ -23,7 +23,7 @@ struct et_ctx {
   hipEvent_t pev[5] = {};             // pipelined batch: fork, trace done (2), synthesis done (2)
   bool serial_waves = false;          // the autotuner's runs: job waves in order on one stream
   bool counting = false;
-  int32_t stack_cap = TRAV_STACK;     // per-lane traversal stack entries (et_set_stack_limit)
+  int32_t stack_cap = QUAD_STACK;     // entries of a ray's traversal stack (et_set_stack_limit)
   hipEvent_t ev[12] = {};
   uint32_t timed = 0;   // event pairs holding the last calls' times (TM_* bits)
   std::vector<hipEvent_t> wave_ev;   // fused batches: per job wave, trace / synthesis / adjoint pairs
@@ -137,7 +137,6 @@ int64_t diff_draws_max(const et_sim_desc* s) {
 }
 
 // Line-of-sight rays per specular record.
-int32_t los_rays(const et_sim_desc* s) { return (s->flags & ET_PER_RX_VISIBILITY) ? s->M : 1; }
 
 int64_t records_upper_bound(const et_sim_desc* s) {
   int64_t n = 0;
@@ -171,7 +170,7 @@ WsPlan plan(const et_scene* sc, const et_sim_desc* s, int64_t cap) {
   WsPlan w;
   const int64_t N = (s->flags & ET_SPECULAR) ? s->N : 0;
   const int64_t K = diff_draws_max(s);
-  if (sc) w.trace = al(trace_ws_layout(N, sc->d.T, sc->d.n_obj, K, nullptr, nullptr, 0, los_rays(s)));
+  if (sc) w.trace = al(trace_ws_layout(N, sc->d.T, sc->d.n_obj, K, nullptr, nullptr));
   w.synth = al(synth_ws_layout(s, cap, nullptr, nullptr));
   w.bwd = al(synth_bwd_ws_layout(s, cap, nullptr, nullptr));
   return w;
@@ -221,7 +220,7 @@ FusedPlan fused_plan(et_ctx* ctx, int32_t J, const et_job* jobs) {
     f.tj = std::max(f.tj, al(trace_batch_jobs_bytes(w.n)));
     f.sy = std::max(f.sy, al(synth_batch_ws_layout(w.n, jobs + w.j0, cap, ctx->tune, true, nullptr, nullptr)));
   }
-  f.tw = al(trace_ws_layout(f.N, 0, 0, 0, nullptr, nullptr, TUNE_MAX_TRACE_BLOCKS));
+  f.tw = al(trace_ws_layout(f.N, 0, 0, 0, nullptr, nullptr));
   f.pp = al(paths_bytes(f.cap));
   // with several waves, two record buffers: the next wave's trace fills one while the
   // synthesis reads the other
@@ -273,7 +272,7 @@ void trace_impl(et_ctx* ctx, const et_scene* sc, const et_sim_desc* sim, void* w
   ET_CHECK(ws_bytes >= w.trace, ET_E_WORKSPACE, "workspace too small for et_trace");
   TraceWS tw;
   trace_ws_layout((sim->flags & ET_SPECULAR) ? sim->N : 0, sc->d.T, sc->d.n_obj, diff_draws_max(sim), (char*)ws,
-                  &tw, 0, los_rays(sim));
+                  &tw);
   tw.stack_cap = ctx->stack_cap;
   ET_HIP(hipEventRecord(ctx->ev[0], ctx->stream));
   trace_run(sc->d, sim, paths, tw, ctx->ctl, ctx->counting, ctx->stream);
@@ -631,7 +630,7 @@ void batch_impl(et_ctx* ctx, int32_t J, const et_job* jobs, void* ws, size_t ws_
       const int k = pipe ? (int)(wi & 1) : 0;   // record buffer and control block of this wave
       Ctl* ctl = k ? ctx->ctl2 : ctx->ctl;
       TraceWS tw;
-      trace_ws_layout(wv.N, 0, 0, 0, twb, &tw, TUNE_MAX_TRACE_BLOCKS);
+      trace_ws_layout(wv.N, 0, 0, 0, twb, &tw);
       tw.stack_cap = ctx->stack_cap;
       char* pp = ppb + k * f.pp;
       et_paths P = carve_paths(pp, cap);
@@ -679,7 +678,7 @@ void batch_impl(et_ctx* ctx, int32_t J, const et_job* jobs, void* ws, size_t ws_
     const WsPlan w = plan(jobs[j].scene, s, cap);
     TraceWS tw;
     trace_ws_layout((s->flags & ET_SPECULAR) ? s->N : 0, jobs[j].scene->d.T, jobs[j].scene->d.n_obj,
-                    diff_draws_max(s), (char*)ws, &tw, 0, los_rays(s));
+                    diff_draws_max(s), (char*)ws, &tw);
     tw.stack_cap = ctx->stack_cap;
     trace_run(jobs[j].scene->d, s, &P, tw, ctx->ctl, false, ctx->stream);
     SynthWS sw;
@@ -1032,7 +1031,7 @@ int et_set_counting(et_ctx* ctx, int enable) {
 int et_set_stack_limit(et_ctx* ctx, int32_t entries) {
   return guarded(ctx, [&] {
     ET_CHECK(entries >= 0 && entries <= TRAV_STACK, ET_E_INVALID, "stack limit must be in [0, 64]");
-    ctx->stack_cap = entries == 0 ? TRAV_STACK : entries;
+    ctx->stack_cap = entries == 0 ? QUAD_STACK : entries * QUAD_STACK / TRAV_STACK;
   });
 }
 

@@ -5,7 +5,8 @@
 //     cluster's nearest neighbour within a window is the one whose merged box has the
 //     smallest surface area (the surface-area heuristic's cost driver); mutual nearest
 //     neighbours merge; repeat until one cluster remains
-//  4. packing into 64-byte binary traversal nodes, triangles repacked in leaf order
+//  4. packing into 64-byte binary nodes and the four-wide traversal nodes formed from them, triangles repacked
+//     in leaf order
 //  5. curvature metric C_i of Eq. (1) with the Meyer et al. cotangent operator, FP64
 #include "internal.hpp"
 
@@ -396,7 +397,35 @@ __global__ void k_obj_box(const uint32_t* __restrict__ ob, int32_t n_obj, float*
   if (i < n_obj * 6) out[i] = o2f(ob[i]);
 }
 
-__global__ void k_single_leaf(Node2* nodes) {
+// The four-wide node of binary node n (see internal.hpp); one per binary node, so that a build or a refit forms
+// them in one launch without finding which of them a traversal can reach (190,000 triangles: 8 us).
+__device__ inline void widen(const Node2* nodes, const Node2& n, float4* __restrict__ out) {
+  int slot = 0;
+  auto put = [&](float4 xy, float lz, float hz, int child) {
+    out[2 * slot] = xy;
+    out[2 * slot + 1] = make_float4(lz, hz, __int_as_float(child), 0.f);
+    ++slot;
+  };
+  for (int c = 0; c < 2; ++c) {
+    const int link = c ? n.ch.y : n.ch.x;
+    if (link < 0) {
+      if (c) put(n.xy1, n.zz.z, n.zz.w, link);
+      else put(n.xy0, n.zz.x, n.zz.y, link);
+    } else {
+      const Node2 m = nodes[link];
+      put(m.xy0, m.zz.x, m.zz.y, m.ch.x);
+      put(m.xy1, m.zz.z, m.zz.w, m.ch.y);
+    }
+  }
+  while (slot < 4) put(make_float4(0.f, 0.f, 0.f, 0.f), 0.f, 0.f, INT32_MIN);
+}
+
+__global__ void k_widen(const Node2* __restrict__ nodes, int64_t n_inner, float4* __restrict__ wide) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < n_inner) widen(nodes, nodes[k], wide + 8 * k);
+}
+
+__global__ void k_single_leaf(Node2* nodes, float4* wide) {
   Node2 n;
   // child 0 is leaf 0 with an infinite box; child 1 is an empty box (never hit)
   n.xy0 = make_float4(-INFINITY, INFINITY, -INFINITY, INFINITY);
@@ -404,6 +433,7 @@ __global__ void k_single_leaf(Node2* nodes) {
   n.zz = make_float4(-INFINITY, INFINITY, INFINITY, -INFINITY);
   n.ch = make_int4(~0, ~0, -1, 0);
   nodes[0] = n;
+  widen(nodes, n, wide);
 }
 
 // ------------------------------------------------------------------ refit (dynamic scenes)
@@ -515,6 +545,7 @@ constexpr int MAX_LEVEL = TRAV_STACK + 1;
 size_t scene_blob_bytes(int64_t T, int64_t V, int32_t n_obj) {
   size_t b = 0;
   b += al(sizeof(Node2) * (size_t)std::max<int64_t>(1, T - 1));
+  b += al(sizeof(float4) * 8 * (size_t)std::max<int64_t>(1, T - 1));
   b += al(sizeof(float4) * 3 * (size_t)std::max<int64_t>(1, T));
   b += 2 * al(sizeof(int32_t) * (size_t)std::max<int64_t>(1, T));   // tri_orig, tri_pos
   b += al(sizeof(double) * (size_t)std::max<int64_t>(1, T));
@@ -557,6 +588,7 @@ void scene_build(et_scene* sc, const et_mesh_desc* mesh, void* blob, void* scrat
   char* bp = (char*)blob;
   auto takeb = [&](size_t bytes) { char* p = bp; bp += al(bytes); return (void*)p; };
   d.nodes = (Node2*)takeb(sizeof(Node2) * (size_t)std::max<int64_t>(1, T - 1));
+  d.wide = (float4*)takeb(sizeof(float4) * 8 * (size_t)std::max<int64_t>(1, T - 1));
   d.tri4 = (float4*)takeb(sizeof(float4) * 3 * (size_t)std::max<int64_t>(1, T));
   d.tri_orig = (int32_t*)takeb(sizeof(int32_t) * (size_t)std::max<int64_t>(1, T));
   d.tri_pos = (int32_t*)takeb(sizeof(int32_t) * (size_t)std::max<int64_t>(1, T));
@@ -659,6 +691,7 @@ void scene_build(et_scene* sc, const et_mesh_desc* mesh, void* blob, void* scrat
     root_id = (int)(2 * T - 2);
     k_pack<<<nblk(T - 1), BS, 0, s>>>(nb, T, d.nodes, leaf_parent);
     k_parents<<<nblk(T - 1), BS, 0, s>>>(d.nodes, T - 1);
+    k_widen<<<nblk(T - 1), BS, 0, s>>>(d.nodes, T - 1, d.wide);
     ET_HIP(hipMemsetAsync(depth, 0, sizeof(int32_t), s));
     ET_HIP(hipMemsetAsync(sah, 0, sizeof(double), s));
     k_depth_sah<<<nblk(T), BS, 0, s>>>(d.nodes, leaf_parent, T, nb, root_id, depth, sah);
@@ -670,7 +703,7 @@ void scene_build(et_scene* sc, const et_mesh_desc* mesh, void* blob, void* scrat
     d.root = (int)(T - 2);   // the last node created is the root; packed index = id - T
     sc->n_nodes = T - 1;
   } else {
-    k_single_leaf<<<1, 1, 0, s>>>(d.nodes);
+    k_single_leaf<<<1, 1, 0, s>>>(d.nodes, d.wide);
     d.root = 0;
     sc->n_nodes = 1;
   }
@@ -743,6 +776,7 @@ void scene_refit(et_scene* sc, const float* vertices, double area_ref, uint32_t*
       const int64_t a = sc->lvl_off[l], n = sc->lvl_off[l + 1] - a;
       k_refit_level<<<nblk(n), BS, 0, s>>>(sc->lvl_nodes + a, n, d.tri4, d.nodes);
     }
+    k_widen<<<nblk(T - 1), BS, 0, s>>>(d.nodes, T - 1, d.wide);
     k_fill_u32<<<1, BS, 0, s>>>((uint32_t*)sah, 2, 0u);
     k_refit_sah<<<nblk(T - 1), BS, 0, s>>>(d.nodes, T - 1, d.root, sah);
   }

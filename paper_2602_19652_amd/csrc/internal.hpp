@@ -44,8 +44,7 @@ enum : uint32_t {
 
 // ------------------------------------------------------------------ BVH layout
 
-// Traversal node of the binary BVH (64 bytes, one cache line pair): the two child boxes
-// stored side by side so that one node fetch tests both children.
+// Node of the binary BVH (64 bytes): the two child boxes stored side by side.
 struct __align__(16) Node2 {
   float4 xy0;  // child 0: lo.x hi.x lo.y hi.y
   float4 xy1;  // child 1: lo.x hi.x lo.y hi.y
@@ -62,11 +61,14 @@ struct __align__(16) NodeB {
   int right;
 };
 
-// per-lane stack entries held in LDS: 26 KB per 256-thread block, so six blocks (six waves
-// per SIMD) fit the compute unit's 160 KB
-constexpr int TRAV_LDS_STACK = 26;
+// Four-wide traversal node (128 bytes, a cache line), formed for every binary node: its grandchildren, a child that is
+// a leaf standing for itself.  A slot is two float4s, lo.x hi.x lo.y hi.y and lo.z hi.z child 0, with the child's
+// bits (>= 0 node, < 0 leaf ~position, INT32_MIN none).
 constexpr int TRAV_WAVES_PER_SIMD = 6;
-constexpr int TRAV_STACK = 64;         // total per-lane entries (rest in global memory)
+constexpr int TRAV_STACK = 64;         // deepest binary tree that is traversed
+// entries of a ray's stack: a four-wide step leaves three behind for two binary levels (25 KB of LDS per
+// 256-thread block, so six blocks, six waves per SIMD, fit the compute unit's 160 KB)
+constexpr int QUAD_STACK = TRAV_STACK / 2 * 3;
 constexpr int TRAV_BLOCK = 256;
 constexpr int PLOC_RADIUS = 16;
 
@@ -78,6 +80,7 @@ struct SceneDev {
   const int32_t* mat = nullptr;
   const int32_t* obj = nullptr;
   Node2* nodes = nullptr;       // [max(1, T-1)]
+  float4* wide = nullptr;       // [max(1, T-1)][8]: the four-wide node of each binary node
   float4* tri4 = nullptr;       // [T][3]: v0 (w = original index bits), v1 (w = material bits), v2
   int32_t* tri_orig = nullptr;  // [T] original triangle index per leaf position
   int32_t* tri_pos = nullptr;   // [T] leaf position per original triangle index
@@ -176,9 +179,7 @@ struct TraceWS {
   uint32_t* rkeys;           // ray order: direction keys (job in the high bits in a batch)
   int32_t* rperm;            // ray index per slot after sorting by key
   void* rsort_tmp;
-  int32_t* gstack;           // global part of the traversal stacks
-  int64_t gstack_threads;
-  int32_t stack_cap;         // per-lane stack entries in use (TRAV_STACK; lower only to test overflows)
+  int32_t stack_cap;         // entries of a ray's stack in use (QUAD_STACK; lower only to test overflows)
   // diffraction
   uint8_t* oel;
   uint64_t* dkeys;
@@ -197,10 +198,7 @@ struct TraceWS {
 };
 
 // Workspace layout of et_trace.  base == nullptr: only computes the size.
-// max_blocks: largest bounce-kernel grid the workspace serves (0: the single-pose default)
-// los: line-of-sight rays per record (1, or the receivers in the per-receiver reading)
-size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* base, TraceWS* ws,
-                       int32_t max_blocks = 0, int32_t los = 1);
+size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* base, TraceWS* ws);
 // Fused batch (specular jobs): all jobs' rays share the bounce kernels; records carry the
 // job index in their ray field.  dev_jobs holds trace_batch_jobs_bytes(J) bytes.
 size_t trace_batch_jobs_bytes(int32_t J);

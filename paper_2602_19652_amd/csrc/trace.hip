@@ -10,14 +10,11 @@
 //               rays that go on in ray order
 // Ray order: a ray set larger than one round of the bounce grid (the threads the chip holds at
 // once) is first sorted (stably) by a 16-bit octahedral Morton key of its world direction, so
-// that a wave's lanes walk nearby parts of the BVH; the stable compaction keeps that order
-// through the bounces, and records carry their ray.  Measured in the room: 2^20 rays trace in
-// 3.9 ms sorted against 5.3 ms in seeded order, 2^19 in 2.46 against 2.57 ms; at 2^18 rays,
-// which one round holds, the bounce kernel is slower on sorted rays (0.245 against 0.191 ms per
-// launch), so such sets keep their given order.
-// Traversal: one lane per ray, binary BVH, nearest child first, per-lane stack in LDS
-// (spilling to global memory past TRAV_LDS_STACK entries), leaves postponed until a quarter
-// of the wave's lanes hold one (after Aila & Laine, HPG 2009), watertight ray-triangle test
+// that the rays of a wave walk nearby parts of the BVH; the stable compaction keeps that order
+// through the bounces, and records carry their ray.  Whole pose in the room with 2^20 rays: 11.98 ms
+// sorted, the sort included, against 12.28 ms in seeded order; smaller sets keep their given order.
+// Traversal: four lanes per ray over four-wide nodes (see walk_rays), nearest child first, stacks in LDS, leaves
+// tested together (after Aila & Laine, HPG 2009), watertight ray-triangle test
 // (Woop, Benthin & Wald, JCGT 2013), conservative slab test (Ize 2013).
 #include "internal.hpp"
 
@@ -31,13 +28,12 @@ namespace {
 
 constexpr int BS = TRAV_BLOCK;
 constexpr int EMPTY = INT32_MIN;
-// Bounce grids of up to 8192 blocks: the room's 2^20 rays run one per thread, so the hardware
-// dispatcher balances uneven rays block by block (measured 7% faster than two rays per thread
-// on 2048 blocks, whose second round leaves part of the chip idle).
+// Grids of up to 8192 blocks: the room's 2^20 rays and their line-of-sight rays are a chunk of 64 per wave, so the
+// hardware dispatcher balances uneven chunks (1536 blocks, one round that strides: 3% slower poses, foliage 6%).
 constexpr int MAX_BLOCKS = 8192;
 
+// Waves that a traversal of few rays is spread over, 16 rays to a wave at the least (see k_walk).
 constexpr int64_t RS_WAVES = 2560;
-constexpr int ROUND_BLOCKS = 256 * TRAV_WAVES_PER_SIMD;   // blocks of 256 threads of a round on 256 compute units
 
 inline unsigned nblk(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + BS - 1) / BS, MAX_BLOCKS)); }
 inline unsigned nblk_full(int64_t n) { return (unsigned)std::max<int64_t>(1, (n + BS - 1) / BS); }
@@ -78,27 +74,6 @@ __device__ inline Ray32 make_ray(double ox, double oy, double oz, double dx, dou
   return r;
 }
 
-// Slab test against both child boxes; far distances widened by 1 + 2*gamma(3) (Ize 2013)
-// so that FP32 rounding never rejects a box that the exact ray meets.
-__device__ inline void box2(const Node2& n, const Ray32& r, float tmin, float tmax, bool& h0, bool& h1, float& t0,
-                            float& t1) {
-  const float up = 1.0f + 2.0f * 3.5762786865234375e-7f;   // 1 + 2 * gamma_3, gamma_n = n u / (1 - n u)
-  float lx = (n.xy0.x - r.ox) * r.ix, hx = (n.xy0.y - r.ox) * r.ix;
-  float ly = (n.xy0.z - r.oy) * r.iy, hy = (n.xy0.w - r.oy) * r.iy;
-  float lz = (n.zz.x - r.oz) * r.iz, hz = (n.zz.y - r.oz) * r.iz;
-  float tn = fmaxf(fmaxf(fminf(lx, hx), fminf(ly, hy)), fmaxf(fminf(lz, hz), tmin));
-  float tf = fminf(fminf(fmaxf(lx, hx), fmaxf(ly, hy)), fmaxf(lz, hz)) * up;
-  h0 = tn <= fminf(tf, tmax);
-  t0 = tn;
-  lx = (n.xy1.x - r.ox) * r.ix; hx = (n.xy1.y - r.ox) * r.ix;
-  ly = (n.xy1.z - r.oy) * r.iy; hy = (n.xy1.w - r.oy) * r.iy;
-  lz = (n.zz.z - r.oz) * r.iz; hz = (n.zz.w - r.oz) * r.iz;
-  tn = fmaxf(fmaxf(fminf(lx, hx), fminf(ly, hy)), fmaxf(fminf(lz, hz), tmin));
-  tf = fminf(fminf(fmaxf(lx, hx), fmaxf(ly, hy)), fmaxf(lz, hz)) * up;
-  h1 = tn <= fminf(tf, tmax);
-  t1 = tn;
-}
-
 // Watertight ray-triangle test, two-sided.  Returns t (or a negative value on a miss).
 __device__ inline float tri_test(const float4 a, const float4 b, const float4 c, const Ray32& r) {
 #pragma clang fp contract(off)
@@ -127,110 +102,6 @@ __device__ inline float tri_test(const float4 a, const float4 b, const float4 c,
   return T / det;
 }
 
-template <int TB>
-struct Stack {
-  int* lds;        // this lane's column: entry i at lds[i * TB]
-  int* glob;       // this lane's global column: entry i at glob[i * gstride]
-  int64_t gstride;
-  int sp;
-  int cap;         // entries in use: TRAV_STACK (lower only when a test forces overflows)
-  int overflow;
-  // A push beyond the cap drops the subtree (counted; the traversal still ends normally).
-  __device__ inline void push(int v) {
-    if (sp >= cap) { ++overflow; return; }
-    if (sp < TRAV_LDS_STACK) lds[sp * TB] = v;
-    else glob[(int64_t)(sp - TRAV_LDS_STACK) * gstride] = v;
-    ++sp;
-  }
-  // The global part is read as a non-temporal load, so the compiler keeps the two reads apart
-  // (an LDS read in the common case) rather than merging them into one generic (flat) load
-  // that waits on both memory counters.
-  __device__ inline int pop() {
-    if (sp == 0) return EMPTY;
-    --sp;
-    if (sp < TRAV_LDS_STACK) return lds[sp * TB];
-    return __builtin_nontemporal_load(glob + (int64_t)(sp - TRAV_LDS_STACK) * gstride);
-  }
-};
-
-// Closest hit (ANY = false) or any hit (ANY = true) over t in (tmin, tmax), excluding the
-// leaf position `excl`.  Closest-hit ties in t go to the smaller original triangle index.
-// Boxes are culled against the current best distance widened by 2^-19 relative (about 16
-// ulps, more than the rounding of a box entry plus that of a triangle's t): a triangle whose
-// computed t ties the best (or lies within rounding of it, as on a shared edge or a box face
-// whose slab entry equals the hit distance) is always tested, so the hit does not depend on
-// the traversal order, and a refitted tree hits what a rebuilt one hits.
-constexpr float T_WIDEN = 1.0f + 1.9073486328125e-6f;   // 1 + 2^-19
-template <bool ANY, bool COUNT, int TB>
-__device__ inline int traverse(const SceneDev& S, const Ray32& r, float tmin, float tmax, int excl, Stack<TB>& st,
-                               float& t_hit, int64_t& cn, int64_t& ct) {
-  int node = S.root;
-  st.sp = 0;
-  int best = -1, best_orig = INT32_MAX;
-  float tb = tmax, tbw = tmax * T_WIDEN;
-  while (true) {
-    // inner nodes until this lane has none left or a quarter of the active lanes hold a
-    // postponed leaf: the first leaf met is set aside and the walk goes on, so the wave tests
-    // leaves together (measured against waiting for every lane: room 3.43 -> 3.02 ms, foliage
-    // 38.4 -> 27.7 ms; half 3.21 / 31.2, an eighth 3.01 / 27.5 with slower small sets)
-    int leaf = EMPTY;
-    while (node >= 0) {
-      const Node2 n = S.nodes[node];
-      if (COUNT) ++cn;
-      bool h0, h1;
-      float t0, t1;
-      box2(n, r, tmin, tbw, h0, h1, t0, t1);
-      if (h0 && h1) {
-        const bool first0 = t0 <= t1;
-        st.push(first0 ? n.ch.y : n.ch.x);
-        node = first0 ? n.ch.x : n.ch.y;
-      } else if (h0) {
-        node = n.ch.x;
-      } else if (h1) {
-        node = n.ch.y;
-      } else {
-        node = st.pop();
-      }
-      if (node < 0 && node != EMPTY && leaf == EMPTY) {
-        leaf = node;
-        node = st.pop();
-      }
-      if (__popcll(__ballot(leaf != EMPTY)) * 4 >= __popcll(__ballot(1))) break;
-    }
-    // the postponed leaf, then any leaf the walk stopped on
-    while (leaf != EMPTY) {
-      const int pos = ~leaf;
-      if (COUNT) ++ct;
-      if (pos != excl) {
-        const float4 a = S.tri4[3 * (int64_t)pos], b = S.tri4[3 * (int64_t)pos + 1], c = S.tri4[3 * (int64_t)pos + 2];
-        const float t = tri_test(a, b, c, r);
-        if (t > tmin && t <= tb) {
-          if (ANY) {
-            if (t < tmax) { t_hit = t; return pos; }
-          } else {
-            const int orig = __float_as_int(a.w);
-            if (t < tb || orig < best_orig) {
-              tb = t;
-              tbw = t * T_WIDEN;
-              best = pos;
-              best_orig = orig;
-            }
-          }
-        }
-      }
-      if (node < 0 && node != EMPTY) {
-        leaf = node;
-        node = st.pop();
-      } else {
-        leaf = EMPTY;
-      }
-    }
-    if (node == EMPTY) break;
-  }
-  t_hit = tb;
-  return best;
-}
-
 struct PoseArgs {
   double s[3];
   double R[9];
@@ -249,6 +120,181 @@ struct TraceJob {
   const float* dirs;
   int64_t ray0;
 };
+
+// Four lanes (a quad) walk a ray: each tests one child box of a four-wide node, and up to four leaves at the top of the
+// stack are tested at once, one per lane.  A quad's stack is a column of LDS: entry i (1 .. cap) at col[i * QW], entry 0
+// always EMPTY, so that an empty stack yields EMPTY.
+template <int TB>
+struct QuadLds {
+  static constexpr int QW = TB / 4;             // quads per block
+  int stack[(QUAD_STACK + 1) * QW];
+  int2 res[TB];                                 // hit position and distance bits of each wave's 64 rays
+};
+
+struct QuadStack {
+  int cap;        // entries a quad may hold: QUAD_STACK (lower only when a test forces overflows)
+  int overflow;   // dropped pushes
+};
+
+template <int CTRL>
+__device__ inline int quad_perm(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+constexpr int QP1 = 0xB1, QP2 = 0x4E, QP3 = 0x1B;   // lane q reads lane q ^ 1, q ^ 2, q ^ 3 of its quad
+__device__ inline int quad_or(int v) { v |= quad_perm<QP1>(v); return v | quad_perm<QP2>(v); }
+__device__ inline int quad_sum(int v) { v += quad_perm<QP1>(v); return v + quad_perm<QP2>(v); }
+__device__ inline float quad_min(float v) {
+  v = fminf(v, __int_as_float(quad_perm<QP1>(__float_as_int(v))));
+  return fminf(v, __int_as_float(quad_perm<QP2>(__float_as_int(v))));
+}
+__device__ inline int from_lane(int v, int src4) { return __builtin_amdgcn_ds_bpermute(src4, v); }
+__device__ inline float from_lane(float v, int src4) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(src4, __float_as_int(v)));
+}
+
+// Closest hits (any = false) or any hits (any = true) of the wave's rays: lane l < nr holds ray l; t in (tmin, tmax),
+// excluding the leaf position excl; walked = false: the ray hits nothing.  Called by all 64 lanes; leaves ray
+// l's leaf position (-1: none) and distance in pos, t of lane l.  Closest-hit ties in t go to the smaller original
+// triangle index.
+// Boxes are culled against the current best distance widened by 2^-19 relative (about 16
+// ulps, more than the rounding of a box entry plus that of a triangle's t): a triangle whose
+// computed t ties the best (or lies within rounding of it, as on a shared edge or a box face
+// whose slab entry equals the hit distance) is always tested, so the hit does not depend on
+// the traversal order, and a refitted tree hits what a rebuilt one hits.
+// Bound by the chain of dependent steps where rays are few (a step: node from L2, boxes, stack), by vector
+// instructions and node bytes where they are many.  One lane per ray over binary nodes took twice the steps,
+// ran them with half of the lanes or fewer (32 of 64 in the room, 24 in foliage), and
+// fetched 64 B per ray and step through 64 different lines.  Measured (walks of a pose, before and after): 16,384
+// rays 105 -> 50 us, 50,003 rays in the room 403 -> 204 us, 2^20 there 2.12 -> 1.94 ms, 2^20 in foliage 7.1 -> 6.4 ms.
+// Waiting for half of the quads instead of a quarter at leaves made foliage 2% slower and the room as much faster; for
+// all, foliage 16% slower; handing out rays at 4 or 6 free quads instead of 2 cost 1 to 2%.
+constexpr float T_WIDEN = 1.0f + 1.9073486328125e-6f;   // 1 + 2^-19
+constexpr int REFILL_LANES = 8;   // lanes of quads without a ray that make the wave hand out rays
+template <bool COUNT, int TB>
+__device__ inline void walk_rays(const SceneDev& S, const Ray32& r, bool walked, float tmin, float tmax, int excl, int nr,
+                                 bool any, QuadLds<TB>& L, QuadStack& st, int& pos, float& t, int64_t& cn, int64_t& ct) {
+  constexpr int QW = QuadLds<TB>::QW;
+  const int lane = threadIdx.x & 63, q = lane & 3;
+  int* col = L.stack + (threadIdx.x >> 2);
+  int2* res = L.res + (threadIdx.x & ~63);
+  const int pack = r.kx | r.ky << 2 | r.kz << 4 | (walked ? 64 : 0);
+  const float4* wide = S.wide + 2 * q;
+  const float4* tri4 = S.tri4;
+  Ray32 u;                     // the quad's ray
+  int ex = -1, cur = -1;       // its excluded leaf, its lane
+  int node = EMPTY, sp = 0;    // >= 0 inner node, < 0 leaf ~position, EMPTY: done
+  float bt = 0.f, tb = 0.f, tbw = 0.f;         // this lane's best, the quad's best, widened
+  int best = -1, borig = INT32_MAX;
+  int taken = 0;
+  while (true) {
+    const uint64_t idle = __ballot(node == EMPTY);
+    const int n_idle = __popcll(idle);
+    if (taken < nr ? n_idle >= REFILL_LANES : n_idle == 64) {
+      // finished quads hand in the best of their lanes
+      if (node == EMPTY && cur >= 0) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int tj = m ? quad_perm<QP2>(__float_as_int(bt)) : quad_perm<QP1>(__float_as_int(bt));
+          const int oj = m ? quad_perm<QP2>(borig) : quad_perm<QP1>(borig);
+          const int bj = m ? quad_perm<QP2>(best) : quad_perm<QP1>(best);
+          const float tf = __int_as_float(tj);
+          if (tf < bt || (tf == bt && oj < borig)) { bt = tf; borig = oj; best = bj; }
+        }
+        if (q == 0) res[cur] = make_int2(best, __float_as_int(bt));
+        cur = -1;
+      }
+      if (taken >= nr) break;
+      // and take the next rays
+      const int nx = taken + (int)(__builtin_amdgcn_mbcnt_hi((uint32_t)(idle >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)idle, 0u)) >> 2);
+      const bool get = node == EMPTY && nx < nr;
+      const int src = (get ? nx : lane) * 4;
+      const float ox = from_lane(r.ox, src), oy = from_lane(r.oy, src), oz = from_lane(r.oz, src);
+      const float ix = from_lane(r.ix, src), iy = from_lane(r.iy, src), iz = from_lane(r.iz, src);
+      const float Sx = from_lane(r.Sx, src), Sy = from_lane(r.Sy, src), tx = from_lane(tmax, src);
+      const int pk = from_lane(pack, src), e = from_lane(excl, src);
+      if (get) {
+        u.ox = ox; u.oy = oy; u.oz = oz;
+        u.ix = ix; u.iy = iy; u.iz = iz;
+        u.Sx = Sx; u.Sy = Sy;
+        u.kx = pk & 3; u.ky = pk >> 2 & 3; u.kz = pk >> 4 & 3;
+        u.Sz = sel3(ix, iy, iz, u.kz);     // (the largest component's reciprocal is not clamped)
+        u.okx = sel3(ox, oy, oz, u.kx); u.oky = sel3(ox, oy, oz, u.ky); u.okz = sel3(ox, oy, oz, u.kz);
+        ex = e;
+        cur = nx;
+        node = (pk & 64) ? S.root : EMPTY;
+        sp = 0;
+        bt = tb = tx;
+        tbw = tx * T_WIDEN;
+        best = -1;
+        borig = INT32_MAX;
+      }
+      taken = min(nr, taken + (n_idle >> 2));
+    }
+    // inner nodes, until a quarter of the quads that were at one have left for a leaf or finished
+    int left = __popcll(__ballot(node >= 0));
+    const int enough = left * 3;
+    while (left > 0) {
+      if (node >= 0) {
+        const float4 a = wide[(int64_t)node * 8], b = wide[(int64_t)node * 8 + 1];
+        const int top = col[sp * QW];
+        if (COUNT && q == 0) ++cn;
+        // slab test; far distances widened by 1 + 2*gamma(3) (Ize 2013)
+        // so that FP32 rounding never rejects a box that the exact ray meets
+        const float up = 1.0f + 2.0f * 3.5762786865234375e-7f;   // 1 + 2 * gamma_3, gamma_n = n u / (1 - n u)
+        const float lx = (a.x - u.ox) * u.ix, hx = (a.y - u.ox) * u.ix;
+        const float ly = (a.z - u.oy) * u.iy, hy = (a.w - u.oy) * u.iy;
+        const float lz = (b.x - u.oz) * u.iz, hz = (b.y - u.oz) * u.iz;
+        const float tn = fmaxf(fmaxf(fminf(lx, hx), fminf(ly, hy)), fmaxf(fminf(lz, hz), tmin));
+        const float tf = fminf(fminf(fmaxf(lx, hx), fmaxf(ly, hy)), fmaxf(lz, hz)) * up;
+        const int child = __float_as_int(b.z);
+        const bool h = (tn <= fminf(tf, tbw)) & (child != EMPTY);
+        // rank among the quad's children by entry distance (tn >= 0: its bits are ordered; the low two bits
+        // make the keys distinct); rank 0 comes next, the others go on the stack, the farthest lowest
+        const uint32_t key = h ? (((uint32_t)__float_as_int(tn) & ~3u) | (uint32_t)q) : 0xffffffffu;
+        const int rank = (int)((uint32_t)quad_perm<QP1>((int)key) < key) + (int)((uint32_t)quad_perm<QP2>((int)key) < key) +
+                         (int)((uint32_t)quad_perm<QP3>((int)key) < key);
+        const int c = quad_sum((int)h);
+        if (h & (rank > 0)) {
+          const int i = sp + c - rank;
+          if (i <= st.cap) col[i * QW] = child;
+          else ++st.overflow;
+        }
+        const int first = quad_or((h && rank == 0) ? child : 0);
+        node = c ? first : top;
+        sp = min(sp + c - 1, st.cap);
+      }
+      left = __popcll(__ballot(node >= 0));
+      if (left * 4 <= enough) break;
+    }
+    // leaves: a lane each, of the run of leaves on top of the quad's stack
+    if (node < 0 && node != EMPTY) {
+      const int e = q == 0 ? node : col[max(sp + 1 - q, 0) * QW];
+      const bool lf = (e < 0) & (e != EMPTY);
+      const int n0 = lf ? 0 : 1 << q;                       // bit q: the run ends before lane q
+      const int run = __builtin_ctz(quad_or(n0) | 16);
+      const int nxt = col[(sp + 1 - run) * QW];
+      bool acc = false;
+      if (q < run && ~e != ex) {
+        const int64_t p = ~(int64_t)e;
+        const float4 a = tri4[3 * p], b = tri4[3 * p + 1], c = tri4[3 * p + 2];
+        const float tt = tri_test(a, b, c, u);
+        const int orig = __float_as_int(a.w);
+        acc = (tt > tmin) & (tt <= tb) & ((tt < bt) | (!any & (tt == bt) & (orig < borig)));
+        if (acc) { bt = tt; borig = orig; best = ~e; }
+      }
+      if (COUNT && q < run) ++ct;
+      sp -= run;
+      node = nxt;
+      tb = quad_min(bt);
+      tbw = tb * T_WIDEN;
+      if (any && quad_or((int)acc)) node = EMPTY;
+    }
+  }
+  const int2 v = lane < nr ? res[lane] : make_int2(-1, 0);
+  pos = v.x;
+  t = __int_as_float(v.y);
+}
 
 // Job tables reach the device through kernel arguments, a few jobs per launch, so that no
 // host buffer has to outlive the call (and graph capture records the values).
@@ -401,16 +447,16 @@ __global__ void k_ray_init(PoseArgs a0, const float* __restrict__ dirs0, const T
 // BATCH: each ray reads its scene and pose from the job table (the ray field is the job).
 // PERRX: one line-of-sight ray from the hit to each of the M receivers at rxp (bit m of the result) instead of one
 // toward the pose's reference point.
-// Six waves per SIMD (the register budget that asks for, 80, holds the kernel without spills):
-// measured 7% faster on the room's trace and 15% on foliage's than five.
-// A wave takes 1 << rs rays (its other lanes idle): 64 where there are waves enough to fill the chip; fewer rays of
-// a small pose per wave shorten its walk, which is as long as its longest ray's, and its gathers.
+// Six waves per SIMD (80 registers, 25 KB of stacks per 256 threads; the few spills lie outside the traversal loop):
+// measured 4% faster on the room's pose and 7% on foliage's than five, 6% and 22% than four.
+// A wave takes 1 << rs rays: 64 where there are waves enough to fill the chip, down to the 16 that its quads
+// hold in a small pose.
 // TB: threads per block: 64 while the rays leave compute units without a wave, else 256.
 template <int TB, bool COUNT, bool BATCH, bool PERRX>
 __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_PER_SIMD))) void k_walk(
     SceneDev S0, PoseArgs a0, const TraceJob* __restrict__ jobs, TraceWS w, Ctl* ctl, et_paths P, int j, int last,
     int rs, const double* __restrict__ rxp, int32_t M) {
-  __shared__ int lds_stack[TRAV_LDS_STACK * TB];
+  __shared__ QuadLds<TB> lds;
   const int lane = threadIdx.x & 63;
   const int64_t n = last ? 0 : ctl->act[j];
   const int64_t r0 = j > 0 ? ctl->base[j - 1] : 0;
@@ -420,100 +466,111 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(TRAV_WAVES_P
   const int R = 1 << rs;
   const int64_t nc = (n + R - 1) >> rs, nl = n_los > 0 ? (n_los + R - 1) >> rs : 0;
   const int32_t* list = j > 0 ? w.list[j & 1] : nullptr;
-  Stack<TB> st;
-  st.lds = lds_stack + threadIdx.x;
-  st.glob = w.gstack + gtid;
-  st.gstride = w.gstack_threads;
-  st.cap = w.stack_cap;
-  st.overflow = 0;
+  QuadStack st{w.stack_cap, 0};
+  lds.stack[threadIdx.x >> 2] = EMPTY;
   int64_t cn_c = 0, ct_c = 0, cn_a = 0, ct_a = 0, rays_a = 0;
-  for (int64_t c = gtid >> 6; c < nc + nl; c += waves) {
-    if (c < nc) {
-      const int64_t i = (c << rs) + lane;
-      bool hit = false, cont = false;
-      if (lane < R && i < n) {
-        const int64_t s = list ? list[i] : i;
-        int pos;
-        float th = INFINITY;
-        {
-          SceneDev S = S0;
-          float teps = (float)a0.t_eps;
-          if (BATCH) {
-            const TraceJob* tj = jobs + w.ray[s];
-            S = tj->S;
-            teps = (float)tj->a.t_eps;
-          }
-          const Ray32 r = make_ray(w.st[0][s], w.st[1][s], w.st[2][s], w.st[3][s], w.st[4][s], w.st[5][s]);
-          pos = (!BATCH || S.T > 0) ? traverse<false, COUNT>(S, r, teps, INFINITY, w.prev[s], st, th, cn_c, ct_c) : -1;
-        }
-        // The FP64 ray state (and a batch ray's job) is read again after the traversal instead of being held in
-        // registers through it; the compiler barrier keeps the two reads apart, so the traversal loop runs
-        // with fewer live registers (more waves per SIMD).
-        __asm__ volatile("" ::: "memory");
-        if (pos >= 0) {
-          SceneDev S = S0;
-          PoseArgs a = a0;
-          if (BATCH) {
-            const TraceJob* tj = jobs + w.ray[s];
-            S = tj->S;
-            a = tj->a;
-          }
-          const double ox = w.st[0][s], oy = w.st[1][s], oz = w.st[2][s];
-          const double dx = w.st[3][s], dy = w.st[4][s], dz = w.st[5][s];
-          const double rtot = w.st[6][s];
-          // FP64 refinement on the chosen triangle: plane intersection, normal, reflection
-          const float4 A = S.tri4[3 * (int64_t)pos], Bv = S.tri4[3 * (int64_t)pos + 1], Cv = S.tri4[3 * (int64_t)pos + 2];
-          const double e1x = (double)Bv.x - A.x, e1y = (double)Bv.y - A.y, e1z = (double)Bv.z - A.z;
-          const double e2x = (double)Cv.x - A.x, e2y = (double)Cv.y - A.y, e2z = (double)Cv.z - A.z;
-          double nx = e1y * e2z - e1z * e2y, ny = e1z * e2x - e1x * e2z, nz = e1x * e2y - e1y * e2x;
-          const double nn = dnorm3(nx, ny, nz);
-          nx /= nn; ny /= nn; nz /= nn;
-          const double dn = dx * nx + dy * ny + dz * nz;
-          const double hp = ((double)A.x - ox) * nx + ((double)A.y - oy) * ny + ((double)A.z - oz) * nz;
-          const double t = dn != 0.0 ? hp / dn : (double)th;
-          const double px = ox + t * dx, py = oy + t * dy, pz = oz + t * dz;
-          const double rnew = (j == 0) ? dnorm3(px - a.s[0], py - a.s[1], pz - a.s[2]) : rtot + t;
-          w.st[0][s] = px; w.st[1][s] = py; w.st[2][s] = pz;
-          w.st[3][s] = dx - 2.0 * dn * nx; w.st[4][s] = dy - 2.0 * dn * ny; w.st[5][s] = dz - 2.0 * dn * nz;
-          w.st[6][s] = rnew;
-          w.prev[s] = pos;
-          hit = true;
-          cont = (j + 1 < a.B) && !(rnew >= a.maxd);
-        }
-      }
-      const uint64_t hm = __ballot(hit), cm = __ballot(cont);
-      if (lane == 0) w.masks[c] = make_ulonglong2(hm, cm);
-    } else {
-      // line of sight from a record's point toward the receiver reference point (or receiver m)
-      const int64_t e = ((c - nc) << rs) + lane;
-      if (lane < R && e < n_los) {
-        const int64_t r = r0 + (PERRX ? e / M : e);
-        const int m = PERRX ? (int)(e - (r - r0) * M) : 0;
-        SceneDev S = S0;
-        PoseArgs a = a0;
-        if (BATCH) {
-          const TraceJob* tj = jobs + P.ray[r];
-          S = tj->S;
-          a = tj->a;
-        }
-        const double px = P.p[3 * r], py = P.p[3 * r + 1], pz = P.p[3 * r + 2];
+  for (int64_t c = __builtin_amdgcn_readfirstlane((int)(gtid >> 6)); c < nc + nl; c += waves) {
+    const bool los = c >= nc;
+    const int64_t i0 = (los ? c - nc : c) << rs;
+    const int nr = (int)min((int64_t)R, (los ? n_los : n) - i0);
+    // the wave's rays, one per lane
+    Ray32 ray{};
+    bool walked = false;
+    float tmax = INFINITY;
+    int excl = -1, job = 0;
+    if (lane < nr) {
+      if (!los) {
+        const int64_t s = list ? list[i0 + lane] : i0 + lane;
+        if (BATCH) job = w.ray[s];
+        ray = make_ray(w.st[0][s], w.st[1][s], w.st[2][s], w.st[3][s], w.st[4][s], w.st[5][s]);
+        excl = w.prev[s];
+        walked = !BATCH || jobs[job].S.T > 0;
+      } else {
+        // line of sight from a record's point toward the receiver reference point (or receiver m)
+        const int64_t e = i0 + lane, rec = r0 + (PERRX ? e / M : e);
+        const int m = PERRX ? (int)(e - (rec - r0) * M) : 0;
+        if (BATCH) job = P.ray[rec];
+        const PoseArgs& a = BATCH ? jobs[job].a : a0;
+        const double px = P.p[3 * rec], py = P.p[3 * rec + 1], pz = P.p[3 * rec + 2];
         const double tx = PERRX ? rxp[3 * m] : a.xref[0], ty = PERRX ? rxp[3 * m + 1] : a.xref[1],
                      tz = PERRX ? rxp[3 * m + 2] : a.xref[2];
         const double wx = tx - px, wy = ty - py, wz = tz - pz;
-        const double L = dnorm3(wx, wy, wz);
-        bool v = true;
-        if (L > 2.0 * a.t_eps) {
-          const int pos = S.tri_pos[P.tri[r]];
-          const Ray32 rv = make_ray(px, py, pz, wx / L, wy / L, wz / L);
-          float tv;
-          v = traverse<true, COUNT>(S, rv, (float)a.t_eps, (float)(L - a.t_eps), pos, st, tv, cn_a, ct_a) < 0;
+        const double len = dnorm3(wx, wy, wz);
+        if (len > 2.0 * a.t_eps) {
+          excl = BATCH ? jobs[job].S.tri_pos[P.tri[rec]] : S0.tri_pos[P.tri[rec]];
+          ray = make_ray(px, py, pz, wx / len, wy / len, wz / len);
+          tmax = (float)(len - a.t_eps);
+          walked = true;
           ++rays_a;
         }
-        if (v) {
-          P.flags[r] = 1;
-          if (PERRX) atomicOr((unsigned long long*)&P.rx_vis[r], 1ull << m);
-        }
       }
+    }
+    int pos;
+    float th;
+    int64_t cn = 0, ct = 0;
+    if (!BATCH) {
+      walk_rays<COUNT>(S0, ray, walked, (float)a0.t_eps, tmax, excl, nr, los, lds, st, pos, th, cn, ct);
+    } else {
+      // job after job (rays and records come in job order, so nearly every wave holds one)
+      pos = -1;
+      th = 0.f;
+      for (uint64_t rest = __ballot(walked); rest;) {
+        const int jb = __builtin_amdgcn_readlane(job, (int)__builtin_ctzll(rest));
+        const bool mine = walked && job == jb;
+        int p;
+        float t;
+        walk_rays<COUNT>(jobs[jb].S, ray, mine, (float)jobs[jb].a.t_eps, tmax, excl, nr, los, lds, st, p, t, cn, ct);
+        if (mine) { pos = p; th = t; }
+        rest &= ~__ballot(mine);
+      }
+    }
+    if (COUNT) {
+      cn_c += los ? 0 : cn; ct_c += los ? 0 : ct;
+      cn_a += los ? cn : 0; ct_a += los ? ct : 0;
+    }
+    // The FP64 ray state (and a batch ray's job) is read again after the traversal instead of being held in
+    // registers through it; the compiler barrier keeps the two reads apart, so the traversal loop runs
+    // with fewer live registers (more waves per SIMD).
+    __asm__ volatile("" ::: "memory");
+    if (!los) {
+      bool hit = false, cont = false;
+      if (lane < nr && pos >= 0) {
+        const int64_t s = list ? list[i0 + lane] : i0 + lane;
+        SceneDev S = S0;
+        PoseArgs a = a0;
+        if (BATCH) {
+          const TraceJob* tj = jobs + w.ray[s];
+          S = tj->S;
+          a = tj->a;
+        }
+        const double ox = w.st[0][s], oy = w.st[1][s], oz = w.st[2][s];
+        const double dx = w.st[3][s], dy = w.st[4][s], dz = w.st[5][s];
+        const double rtot = w.st[6][s];
+        // FP64 refinement on the chosen triangle: plane intersection, normal, reflection
+        const float4 A = S.tri4[3 * (int64_t)pos], Bv = S.tri4[3 * (int64_t)pos + 1], Cv = S.tri4[3 * (int64_t)pos + 2];
+        const double e1x = (double)Bv.x - A.x, e1y = (double)Bv.y - A.y, e1z = (double)Bv.z - A.z;
+        const double e2x = (double)Cv.x - A.x, e2y = (double)Cv.y - A.y, e2z = (double)Cv.z - A.z;
+        double nx = e1y * e2z - e1z * e2y, ny = e1z * e2x - e1x * e2z, nz = e1x * e2y - e1y * e2x;
+        const double nn = dnorm3(nx, ny, nz);
+        nx /= nn; ny /= nn; nz /= nn;
+        const double dn = dx * nx + dy * ny + dz * nz;
+        const double hp = ((double)A.x - ox) * nx + ((double)A.y - oy) * ny + ((double)A.z - oz) * nz;
+        const double t = dn != 0.0 ? hp / dn : (double)th;
+        const double px = ox + t * dx, py = oy + t * dy, pz = oz + t * dz;
+        const double rnew = (j == 0) ? dnorm3(px - a.s[0], py - a.s[1], pz - a.s[2]) : rtot + t;
+        w.st[0][s] = px; w.st[1][s] = py; w.st[2][s] = pz;
+        w.st[3][s] = dx - 2.0 * dn * nx; w.st[4][s] = dy - 2.0 * dn * ny; w.st[5][s] = dz - 2.0 * dn * nz;
+        w.st[6][s] = rnew;
+        w.prev[s] = pos;
+        hit = true;
+        cont = (j + 1 < a.B) && !(rnew >= a.maxd);
+      }
+      const uint64_t hm = __ballot(hit), cm = __ballot(cont);
+      if (lane == 0) w.masks[c] = make_ulonglong2(hm, cm);
+    } else if (lane < nr && pos < 0) {
+      const int64_t e = i0 + lane, rec = r0 + (PERRX ? e / M : e);
+      P.flags[rec] = 1;
+      if (PERRX) atomicOr((unsigned long long*)&P.rx_vis[rec], 1ull << (int)(e - (rec - r0) * M));
     }
   }
   if (st.overflow) atomicAdd((unsigned long long*)&ctl->overflow, (unsigned long long)st.overflow);
@@ -814,22 +871,23 @@ __global__ void k_group_count(Ctl* ctl, DiffArgs a, int64_t* __restrict__ gstart
 
 __global__ __launch_bounds__(BS) void k_diff_sample(SceneDev S, DiffArgs a, const uint64_t* __restrict__ W_ex,
                                                     const uint64_t* __restrict__ qs, const int32_t* __restrict__ vals,
-                                                    TraceWS w, Ctl* ctl) {
-  __shared__ int lds_stack[TRAV_LDS_STACK * BS];
-  const int64_t gtid = (int64_t)blockIdx.x * BS + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * BS;
-  Stack<BS> st;
-  st.lds = lds_stack + threadIdx.x;
-  st.glob = w.gstack + gtid;
-  st.gstride = w.gstack_threads;
-  st.cap = w.stack_cap;
-  st.overflow = 0;
+                                                    TraceWS w, Ctl* ctl, int rs) {
+  __shared__ QuadLds<BS> lds;
+  const int lane = threadIdx.x & 63;
+  const int64_t waves = (int64_t)gridDim.x * (BS / 64);
+  QuadStack st{w.stack_cap, 0};
+  lds.stack[threadIdx.x >> 2] = EMPTY;
   const int64_t n_draw = ctl->n_draw;
   int64_t dummy0 = 0, dummy1 = 0, rays = 0;
-  for (int64_t k = gtid; k < n_draw; k += stride) {
-    uint64_t keep = 0;
-    w.stri[k] = -1;
-    {
+  const int first = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (BS / 64) + (threadIdx.x >> 6)));
+  for (int64_t k0 = (int64_t)first << rs; k0 < n_draw; k0 += waves << rs) {
+    const int nr = (int)min((int64_t)1 << rs, n_draw - k0);
+    const int64_t k = k0 + lane;
+    Ray32 ray{};
+    bool ok = false;
+    float tmax = INFINITY;
+    int pos = -1;
+    if (lane < nr) {
       // this draw's group (its mesh, or the one CDF) and the group's running sums
       const int64_t g = a.per_mesh ? k / a.K : 0;
       const int64_t j0 = w.gstart[g], j1 = w.gstart[g + 1];
@@ -847,7 +905,7 @@ __global__ __launch_bounds__(BS) void k_diff_sample(SceneDev S, DiffArgs a, cons
       const double u1 = u01(splitmix(ks, 3ull * (uint64_t)k + 1ull)), u2 = u01(splitmix(ks, 3ull * (uint64_t)k + 2ull));
       const double su = sqrt(u1);
       const double wa = 1.0 - su, wb = su * (1.0 - u2), wc = su * u2;   // uniform point on the triangle
-      const int pos = S.tri_pos[t];
+      pos = S.tri_pos[t];
       const float4 A = S.tri4[3 * (int64_t)pos], B = S.tri4[3 * (int64_t)pos + 1], C = S.tri4[3 * (int64_t)pos + 2];
       const double ax = A.x, ay = A.y, az = A.z, bx = B.x, by = B.y, bz = B.z, cx = C.x, cy = C.y, cz = C.z;
       const double ox = wa * ax + wb * bx + wc * cx, oy = wa * ay + wb * by + wc * cy, oz = wa * az + wb * bz + wc * cz;
@@ -862,20 +920,20 @@ __global__ __launch_bounds__(BS) void k_diff_sample(SceneDev S, DiffArgs a, cons
       const double iL = 1.0 / L;
       const double vx = wx * iL, vy = wy * iL, vz = wz * iL;
       const double ci = fabs(nx * vx + ny * vy + nz * vz);
-      bool ok = ci >= a.cos_max;                                   // incidence-angle constraint
+      ok = ci >= a.cos_max;                                        // incidence-angle constraint
       if (ok) {                                                    // line of sight to the source
-        const Ray32 r = make_ray(ox, oy, oz, vx, vy, vz);
-        float tv;
-        const int blk = traverse<true, false>(S, r, (float)a.t_eps, (float)(L - a.t_eps), pos, st, tv, dummy0, dummy1);
-        ok = blk < 0;
+        ray = make_ray(ox, oy, oz, vx, vy, vz);
+        tmax = (float)(L - a.t_eps);
         ++rays;
       }
       w.stri[k] = t;
       w.so[3 * k] = ox; w.so[3 * k + 1] = oy; w.so[3 * k + 2] = oz;
       w.sr[k] = L;
-      keep = ok ? 1ull : 0ull;
     }
-    w.skeep[k] = keep;
+    int blk;
+    float tv;
+    walk_rays<false>(S, ray, ok, (float)a.t_eps, tmax, pos, nr, true, lds, st, blk, tv, dummy0, dummy1);
+    if (lane < nr) w.skeep[k] = ok && blk < 0 ? 1ull : 0ull;
   }
   if (st.overflow) {
     atomicAdd((unsigned long long*)&ctl->overflow, (unsigned long long)st.overflow);
@@ -914,27 +972,35 @@ __global__ void k_diff_scatter(SceneDev S, DiffArgs a, TraceWS w, Ctl* ctl, et_p
 // emitter as the point, path 0, the receiver in `mat` and `ray`, kind 2 in the flags.
 __global__ __launch_bounds__(BS) void k_passive(SceneDev S, PoseArgs a, const double* __restrict__ rx, int32_t M,
                                                 int diff, TraceWS w, Ctl* ctl, et_paths P, int perrx) {
-  __shared__ int lds_stack[TRAV_LDS_STACK * BS];
-  const int64_t gtid = (int64_t)blockIdx.x * BS + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * BS;
-  Stack<BS> st;
-  st.lds = lds_stack + threadIdx.x;
-  st.glob = w.gstack + gtid;
-  st.gstride = w.gstack_threads;
-  st.cap = w.stack_cap;
-  st.overflow = 0;
+  __shared__ QuadLds<BS> lds;
+  const int lane = threadIdx.x & 63;
+  QuadStack st{w.stack_cap, 0};
+  lds.stack[threadIdx.x >> 2] = EMPTY;
   const int64_t base = ctl->rec_base + (diff ? (int64_t)ctl->tot[3] : 0);
   int64_t dummy0 = 0, dummy1 = 0, rays = 0;
-  for (int64_t m = gtid; m < M; m += stride) {
-    const double wx = rx[3 * m] - a.s[0], wy = rx[3 * m + 1] - a.s[1], wz = rx[3 * m + 2] - a.s[2];
-    const double L = dnorm3(wx, wy, wz);
-    int vis = 1;
-    if (L > 2.0 * a.t_eps && S.T > 0) {
-      const Ray32 r = make_ray(a.s[0], a.s[1], a.s[2], wx / L, wy / L, wz / L);
-      float tv;
-      vis = traverse<true, false>(S, r, (float)a.t_eps, (float)(L - a.t_eps), -1, st, tv, dummy0, dummy1) < 0;
-      ++rays;
+  const int64_t waves = (int64_t)gridDim.x * (BS / 64);
+  const int first = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (BS / 64) + (threadIdx.x >> 6)));
+  for (int64_t m0 = (int64_t)first << 4; m0 < M; m0 += waves << 4) {
+    const int nr = (int)min((int64_t)16, M - m0);
+    const int64_t m = m0 + lane;
+    Ray32 ray{};
+    bool walked = false;
+    float tmax = INFINITY;
+    if (lane < nr) {
+      const double wx = rx[3 * m] - a.s[0], wy = rx[3 * m + 1] - a.s[1], wz = rx[3 * m + 2] - a.s[2];
+      const double L = dnorm3(wx, wy, wz);
+      if (L > 2.0 * a.t_eps && S.T > 0) {
+        ray = make_ray(a.s[0], a.s[1], a.s[2], wx / L, wy / L, wz / L);
+        tmax = (float)(L - a.t_eps);
+        walked = true;
+        ++rays;
+      }
     }
+    int pos;
+    float tv;
+    walk_rays<false>(S, ray, walked, (float)a.t_eps, tmax, -1, nr, true, lds, st, pos, tv, dummy0, dummy1);
+    if (lane >= nr) continue;
+    const int vis = pos < 0;
     const int64_t ri = base + m;
     if (ri < P.capacity) {
       P.p[3 * ri] = a.s[0]; P.p[3 * ri + 1] = a.s[1]; P.p[3 * ri + 2] = a.s[2];
@@ -964,8 +1030,7 @@ inline size_t al(size_t b) { return (b + 255) / 256 * 256; }
 
 }  // namespace
 
-size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* base, TraceWS* w, int32_t max_blocks,
-                       int32_t los) {
+size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* base, TraceWS* w) {
   const int64_t Nm = std::max<int64_t>(N, 1), Tm = std::max<int64_t>(T, 1), Km = std::max<int64_t>(K, 1);
   size_t off = 0;
   auto take = [&](size_t bytes) -> void* {
@@ -979,8 +1044,8 @@ size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* bas
   x.ray = (int32_t*)take(sizeof(int32_t) * Nm);
   x.prec = (int64_t*)take(sizeof(int64_t) * Nm);
   for (int b = 0; b < 2; ++b) x.list[b] = (int32_t*)take(sizeof(int32_t) * Nm);
-  // (small sets take down to 8 rays per wave: below that many masks of 8)
-  const int64_t waves = std::max<int64_t>((Nm + 63) / 64, std::min<int64_t>((Nm + 7) / 8, 2 * RS_WAVES));
+  // (small sets take down to 16 rays per wave)
+  const int64_t waves = std::max<int64_t>((Nm + 63) / 64, std::min<int64_t>((Nm + 15) / 16, 2 * RS_WAVES));
   x.masks = (ulonglong2*)take(sizeof(ulonglong2) * waves);
   x.pre = (uint64_t*)take(sizeof(uint64_t) * waves);
   x.bsum = (uint64_t*)take(sizeof(uint64_t) * ((waves + CHUNKS - 1) / CHUNKS));
@@ -988,17 +1053,7 @@ size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* bas
   x.rkeys = (uint32_t*)take(sizeof(uint32_t) * Nm);
   x.rperm = (int32_t*)take(sizeof(int32_t) * Nm);
   x.rsort_tmp = take(sort_temp_bytes(Nm, 4));
-  // global stack columns: one per thread of the largest traversing grid (bounces over N rays and, up to a
-  // round of the chip, the line-of-sight rays beside them, diffraction over K draws, the passive rays); a
-  // fused batch passes its largest tuned grid
-  const int64_t items = std::max<int64_t>(N, 1) * (1 + (int64_t)std::max<int32_t>(los, 1));
-  const int64_t stack_blocks =
-      max_blocks > 0 ? max_blocks
-                     : std::max<int64_t>(std::max<int64_t>(nblk(std::max<int64_t>(N, 1)), nblk(std::max<int64_t>(K, 1))),
-                                         std::min<int64_t>(nblk(8 * items), ROUND_BLOCKS));
-  x.gstack_threads = stack_blocks * BS;
-  x.gstack = (int32_t*)take(sizeof(int32_t) * (size_t)(TRAV_STACK - TRAV_LDS_STACK) * (size_t)x.gstack_threads);
-  x.stack_cap = TRAV_STACK;
+  x.stack_cap = QUAD_STACK;
   if (K > 0) {
     x.oel = (uint8_t*)take((size_t)std::max<int32_t>(n_obj, 1));
     x.dkeys = (uint64_t*)take(sizeof(uint64_t) * Tm);
@@ -1111,8 +1166,8 @@ void trace_batch_run(int32_t J, const et_job* jobs, void* dev_jobs, const et_pat
   const et_paths P = *paths;
   k_trace_init<<<1, 1, 0, s>>>(ctl, N, carry ? 1 : 0, 0);
   ET_HIP(hipGetLastError());
-  // bounce grid: the tuned block count, within what the workspace's global stacks serve
-  const int64_t cap_blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, w.gstack_threads / BS));
+  // bounce grid: the tuned block count
+  const int64_t cap_blocks = std::max<int64_t>(1, blocks);
   const unsigned gb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((N + BS - 1) / BS, cap_blocks));
   if (N > 0) {
     const bool sorted = N > (int64_t)gb * BS;
@@ -1124,7 +1179,7 @@ void trace_batch_run(int32_t J, const et_job* jobs, void* dev_jobs, const et_pat
     }
     k_ray_init<true><<<nblk_full(N), BS, 0, s>>>(all, nullptr, dj, J, sorted ? w.rperm : nullptr, w, ctl);
     for (int j = 0; j <= B; ++j) {
-      launch_walk<true, false>(BS, counting, gb, s, SceneDev{}, all, dj, w, ctl, P, j, j == B, 6, nullptr, 0);
+      launch_walk<true, false>(64, counting, gb * (BS / 64), s, SceneDev{}, all, dj, w, ctl, P, j, j == B, 6, nullptr, 0);
       if (j < B) launch_records<true>(N, SceneDev{}, dj, w, ctl, P, j, 6, 0, 0, s);
     }
     ET_HIP(hipGetLastError());
@@ -1141,36 +1196,29 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
   const bool diff = (sim->flags & ET_DIFFRACTION) && sim->diff_K > 0 && S.T > 0;
   const int32_t n_passive = (sim->flags & ET_PASSIVE) ? sim->M : 0;
   const bool fin = !diff && n_passive == 0 && a.N > 0 && S.T > 0;   // the last bounce's records end the trace
-  // every traversing grid below stays within the workspace's global stack columns
-  auto stack_fits = [&](int64_t n) {
-    ET_CHECK((int64_t)nblk(n) * BS <= w.gstack_threads, ET_E_INTERNAL, "trace grid exceeds the workspace's stacks");
-  };
   if (a.N > 0 && S.T > 0) {
-    stack_fits(a.N);
     const bool sorted = a.N > bounce_resident_threads() || a.N > (int64_t)nblk(a.N) * BS;
     if (sorted) {
       k_ray_keys<false><<<nblk_full(a.N), BS, 0, s>>>(a, sim->ray_dirs, nullptr, 0, w.rkeys, w.rperm);
       radix_sort_u32(w.rkeys, w.rperm, a.N, RAY_KEY_BITS, w.rsort_tmp, s);
     }
     k_ray_init<false><<<nblk_full(a.N), BS, 0, s>>>(a, sim->ray_dirs, nullptr, 0, sorted ? w.rperm : nullptr, w, ctl);
-    // bounce grid: whole rounds of resident blocks (no partly filled last round), the waves taken by grid
-    // stride (the room's 2^20 rays: 4096 blocks, 2.67 rounds, 2.82 ms per trace; 3072, two
-    // rounds, 2.73 ms; 2560 2.79, 2048 3.13, 1536 3.06 ms; foliage's 2^22 rays: 8192 blocks 27.7 ms,
-    // 3072 28.7 ms), within the threads that have a global stack column
+    // bounce grid: whole rounds of resident blocks (no partly filled last round), the chunks taken by grid
+    // stride (2^20 rays, room and foliage pose: 12.10 and 8.30 ms; a block per four chunks 12.20 and 8.48; one round
+    // 12.48 and 8.81)
     const double* rx = perrx ? sim->rx_pos : nullptr;
     const int32_t M = perrx ? sim->M : 1;
     const int64_t res_blocks = std::max<int64_t>(1, bounce_resident_threads() / BS);
-    // rays per wave: the most that leaves RS_WAVES waves (two and a half per SIMD), from 64 down to 8
+    // rays per wave: the most that leaves RS_WAVES waves (two and a half per SIMD), from 64 down to 16
     const int64_t most = a.N * (1 + M);
     int rs = 6;
-    while (rs > 3 && (most >> rs) < RS_WAVES) --rs;
+    while (rs > 4 && (most >> rs) < RS_WAVES) --rs;
     for (int j = 0; j <= a.B; ++j) {
       // closest hits of at most N rays and the line-of-sight rays of as many records
       const int64_t waves = (((j < a.B ? a.N : 0) + (j > 0 ? a.N * M : 0)) >> rs) + 2;
-      const int64_t nb = std::min<int64_t>((waves + BS / 64 - 1) / (BS / 64), w.gstack_threads / BS);
+      const int64_t nb = std::min<int64_t>((waves + BS / 64 - 1) / (BS / 64), MAX_BLOCKS);
       const int tb = waves <= 4 * res_blocks / TRAV_WAVES_PER_SIMD ? 64 : BS;
-      const unsigned gb = (unsigned)(tb == 64 ? std::min<int64_t>(waves, w.gstack_threads / 64)
-                                              : nb > res_blocks ? nb / res_blocks * res_blocks : nb);
+      const unsigned gb = (unsigned)(tb == 64 ? waves : nb > res_blocks ? nb / res_blocks * res_blocks : nb);
       if (perrx) launch_walk<false, true>(tb, counting, gb, s, S, a, nullptr, w, ctl, P, j, j == a.B, rs, rx, M);
       else launch_walk<false, false>(tb, counting, gb, s, S, a, nullptr, w, ctl, P, j, j == a.B, rs, rx, M);
       if (j < a.B) launch_records<false>(a.N, S, nullptr, w, ctl, P, j, rs, perrx ? 1 : 0, fin && j + 1 == a.B, s);
@@ -1194,7 +1242,6 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
     d.rx_all = perrx ? (sim->M >= 64 ? ~0ull : (1ull << sim->M) - 1ull) : 0ull;
     d.max_meshes = d.per_mesh ? sim->diff_max_meshes : 1;
     const int64_t max_draw = d.K * d.max_meshes;
-    stack_fits(max_draw);
     int obj_bits = 1;
     while (obj_bits < 31 && ((int64_t)1 << obj_bits) < S.n_obj) ++obj_bits;
     k_obj_fov<<<nblk_full(S.n_obj), BS, 0, s>>>(S, d, w.oel);
@@ -1213,14 +1260,15 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
       k_group_starts<<<nblk_full(S.T), BS, 0, s>>>(w.dflags, w.goffs, ctl, w.gstart);
     }
     k_group_count<<<1, 1, 0, s>>>(ctl, d, w.gstart);
-    k_diff_sample<<<nblk(max_draw), BS, 0, s>>>(S, d, w.doffs, w.dq, w.dvals, w, ctl);
+    int rs = 6;
+    while (rs > 4 && (max_draw >> rs) < RS_WAVES) --rs;
+    k_diff_sample<<<nblk(max_draw << (6 - rs)), BS, 0, s>>>(S, d, w.doffs, w.dq, w.dvals, w, ctl, rs);
     scan_exclusive_u64(w.skeep, w.soffs, 0, &ctl->n_draw, max_draw, &ctl->tot[3], w.scan_tmp, s);
     k_diff_scatter<<<nblk(max_draw), BS, 0, s>>>(S, d, w, ctl, P);
     ET_HIP(hipGetLastError());
   }
-  if (n_passive > 0) stack_fits(n_passive);
   if (n_passive > 0)
-    k_passive<<<nblk(n_passive), BS, 0, s>>>(S, a, sim->rx_pos, n_passive, diff ? 1 : 0, w, ctl, P, perrx ? 1 : 0);
+    k_passive<<<nblk(4 * (int64_t)n_passive), BS, 0, s>>>(S, a, sim->rx_pos, n_passive, diff ? 1 : 0, w, ctl, P, perrx ? 1 : 0);
   if (!fin) k_trace_final<<<1, 1, 0, s>>>(ctl, P, diff ? 1 : 0, n_passive);
   ET_HIP(hipGetLastError());
 }

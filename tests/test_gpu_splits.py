@@ -1,0 +1,90 @@
+"""Sizes at the edges of the kernels' splits, against the FP64 oracle: rays per wave and triangles per tree of the
+traversal (partly filled waves, empty node slots, jobs that share a wave), mesh sizes around the
+sort's and the scan's blocks, and band layouts whose rows are cut off 64-bin boundaries."""
+
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+from test_gpu_parity import check_spectra, compare_traces
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx(et):
+    return et.Context(0)
+
+
+def _soup(T, seed):
+    """T random triangles (30-100 cm) in a 4 m box ahead of the emitter."""
+    g = W.rng(seed)
+    c = g.uniform([1.0, -2.0, -2.0], [5.0, 2.0, 2.0], (T, 3))
+    v = (c[:, None, :] + g.normal(0, 0.4, (T, 3, 3))).reshape(-1, 3).astype(np.float32)
+    return {"vertices": v, "tris": np.arange(3 * T, dtype=np.int32).reshape(T, 3), "tri_material": np.zeros(T, np.int32),
+            "tri_object": np.zeros(T, np.int32), "n_objects": 1}
+
+
+@pytest.mark.parametrize("T,N", [(3, 1), (4, 15), (5, 16), (6, 17), (9, 63), (40, 65), (1000, 130), (1000, 20011),
+                                 (2048, 333), (2049, 333), (8193, 333)])
+def test_traces_of_random_triangles(et, ctx, T, N):
+    """Every certified ray's hits, shadow rays included, as the oracle's brute force finds them; per-receiver line of
+    sight too."""
+    scene = _soup(T, 100 + T)
+    _, sim = W.tiny_scene(n_rays=N)
+    sc = et.Scene(ctx, scene)
+    ref = O.trace(scene, sim)
+    gpu = et.trace(ctx, sc, et.Sim(sim)).to_host()
+    assert compare_traces(gpu, ref, ref["certified"]) == 0
+    per = dict(sim, per_rx_visibility=True)
+    ref = O.trace(scene, per)
+    dirs = sim["ray_dirs"][ref["certified"]]
+    if len(dirs):
+        ref = O.trace(scene, per, dirs=dirs)
+        h = et.trace(ctx, sc, et.Sim(per, ray_dirs=dirs)).to_host()
+        key = {(int(r), int(b)): int(x) for r, b, x in zip(ref["ray"], ref["bounce"], ref["rxvis"])}
+        assert {(int(r), int(b)): int(x) for r, b, x in zip(h["ray"], h["bounce"], h["rxvis"])} == key
+
+
+@pytest.mark.parametrize("rays", [(1, 3, 5), (10, 37, 70), (64, 1, 200)])
+def test_batch_jobs_that_share_waves(et, ctx, rays):
+    """Jobs of fewer rays than a wave holds, over scenes of their own (one without triangles): each job's spectra
+    against its own oracle trace.  Spectra within the factorised kernel's 1e-4."""
+    scenes = [_soup(300, 7), _soup(5, 8), {**_soup(1, 9), "tris": np.zeros((0, 3), np.int32),
+                                            "tri_material": np.zeros(0, np.int32), "tri_object": np.zeros(0, np.int32)}]
+    sims, refs = [], []
+    for i, n in enumerate(rays):
+        _, sim = W.tiny_scene(seed=50 + i, n_rays=4 * n + 16, F=256)
+        cert = O.trace(scenes[i], sim)["certified"]
+        # (lobes wide enough that no reflection's factor leaves FP32's range)
+        sim = dict(sim, ray_dirs=sim["ray_dirs"][cert][:n], lobe_beta=np.full_like(sim["lobe_beta"], 1.0))
+        refs.append(O.synth(O.trace(scenes[i], sim), sim))
+        sims.append(et.Sim(sim, flags=et.ET_SPECULAR))
+    H = et.Batch(ctx, [(et.Scene(ctx, sc), s) for sc, s in zip(scenes, sims)]).run().cpu().numpy()
+    for i in range(len(rays)):
+        if np.any(refs[i]):
+            check_spectra(H[i], refs[i], f"job {i} of {rays[i]} rays")
+        else:
+            assert not np.any(H[i])
+
+
+@pytest.mark.parametrize("F,Bk,Q,mics,table", [(31, 1, 1, 1, False), (97, 3, 2, 2, False), (200, 7, 3, 5, True),
+                                               (1000, 16, 16, 3, False), (2049, 5, 2, 33, False), (2080, 13, 4, 2, True),
+                                               (4100, 33, 2, 1, True)])
+def test_rows_off_the_64_bin_blocks(et, ctx, F, Bk, Q, mics, table):
+    """Bands that end inside a 64-bin block (with a directivity's own bands beside the material's), part rows at the
+    end of the grid, receivers that do not fill a group."""
+    scene, sim = W.tiny_scene(n_rays=3000)
+    g = W.rng(F + Bk)
+    scene = dict(scene, tri_material=g.integers(0, Q, len(scene["tris"])).astype(np.int32))
+    sim = dict(sim, F=F, refl_k=g.uniform(0.3, 0.99, (Q, Bk)).astype(np.float32),
+               lobe_beta=g.uniform(0.05, 0.3, (Q, Bk)).astype(np.float32),
+               diff_coef=g.uniform(0.05, 0.3, (Q, Bk)).astype(np.float32),
+               rx_pos=np.asarray(sim["rx_pos"])[:1] + g.normal(0, 0.02, (mics, 3)),
+               rx_rot=np.stack([W.frame_from_forward(v) for v in g.normal(size=(mics, 3))]))
+    if table:
+        sim["directivity"] = W.directivity_table(g, mics, Bd=6, El=8, Az=16)
+    ref = O.trace(scene, sim, certify=False)
+    H = et.synthesize(ctx, et.Sim(sim), et.Paths.from_records(ref)).cpu().numpy()
+    check_spectra(H, O.synth(ref, sim), f"F={F}, {Bk} bands: kernel {ctx.stats().synth_kernel}")

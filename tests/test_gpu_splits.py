@@ -1,6 +1,7 @@
 """Sizes at the edges of the kernels' splits, against the FP64 oracle: rays per wave and triangles per tree of the
 traversal (partly filled waves, empty node slots, jobs that share a wave), mesh sizes around the
-sort's and the scan's blocks, and band layouts whose rows are cut off 64-bin boundaries."""
+sort's and the scan's blocks, band layouts whose rows are cut off 64-bin boundaries, and lengths around the transforms'
+splits."""
 
 import numpy as np
 import pytest
@@ -88,3 +89,46 @@ def test_rows_off_the_64_bin_blocks(et, ctx, F, Bk, Q, mics, table):
     ref = O.trace(scene, sim, certify=False)
     H = et.synthesize(ctx, et.Sim(sim), et.Paths.from_records(ref)).cpu().numpy()
     check_spectra(H, O.synth(ref, sim), f"F={F}, {Bk} bands: kernel {ctx.stats().synth_kernel}")
+
+
+@pytest.mark.parametrize("sigma", [1, -1])
+@pytest.mark.parametrize("F,n_t", [(2, 2), (3, 4), (5, 8), (16, 16), (20, 32), (33, 64), (100, 128), (256, 256),
+                                   (300, 512), (1000, 1024), (700, 2048), (4096, 4096), (5000, 8192), (9000, 16384),
+                                   (4097, 32768), (32768, 32768), (500, 65536)])
+def test_impulse_response_lengths(et, ctx, F, n_t, sigma):
+    """Every transform length, with the bins ending inside and past the first residue's points, against FP64.  Up to 16
+    levels of additions and five products, rounded to 6e-8 of the value each and independently, stay
+    below 1e-6 of the norm."""
+    import torch
+    g = W.rng(F)
+    _, sim = W.tiny_scene(n_rays=16)
+    M = 3
+    sim = dict(sim, F=F, phase_sign=sigma, rx_pos=np.zeros((M, 3)), rx_rot=np.stack([np.eye(3)] * M))
+    H = (g.normal(size=(M, F)) + 1j * g.normal(size=(M, F))).astype(np.complex64)
+    h, dt = et.impulse_response(ctx, et.Sim(sim), torch.as_tensor(H).cuda(), n_t)
+    df = (sim["f_hi"] - sim["f_lo"]) / (F - 1)
+    X = np.zeros((M, n_t), complex)
+    X[:, :F] = H
+    S = np.fft.fft(X, axis=1) if sigma > 0 else np.fft.ifft(X, axis=1) * n_t
+    cyc = sim["f_lo"] * np.arange(n_t) / (n_t * df)
+    ref = 2 * df * np.real(np.exp(-2j * np.pi * sigma * (cyc - np.floor(cyc))) * S)
+    e = np.linalg.norm(h.cpu().numpy() - ref) / np.linalg.norm(ref)
+    print(f"F={F}, {n_t} samples: {e:.2e}")
+    assert e <= 1e-6
+
+
+@pytest.mark.parametrize("n_t,L", [(1, 1), (1, 40), (64, 1), (512, 2), (1024, 512), (1024, 513), (4096, 1024), (4096, 1025),
+                                   (2048, 2049), (16384, 640), (512, 4096), (8192, 4097)])
+def test_convolution_lengths(et, ctx, n_t, L):
+    """Blocks of every length, the last one part filled, responses shorter than the call; against FP64, 1e-6 of the norm
+    (three transforms of up to 14 levels, rounded independently)."""
+    import torch
+    g = W.rng(n_t + L)
+    h = g.normal(size=(3, n_t)).astype(np.float32)
+    call = g.normal(size=L).astype(np.float32)
+    out = et.receiver_signal(ctx, torch.as_tensor(h).cuda(), torch.as_tensor(call).cuda(), 2e-6).cpu().numpy()
+    n = n_t + L - 1
+    ref = 2e-6 * np.fft.ifft(np.fft.fft(h.astype(float), n, axis=1) * np.fft.fft(call.astype(float), n), axis=1).real
+    e = np.linalg.norm(out - ref) / np.linalg.norm(ref)
+    print(f"{n_t} samples, call of {L}: {e:.2e}")
+    assert out.shape == (3, n) and e <= 1e-6

@@ -132,3 +132,37 @@ def test_convolution_lengths(et, ctx, n_t, L):
     e = np.linalg.norm(out - ref) / np.linalg.norm(ref)
     print(f"{n_t} samples, call of {L}: {e:.2e}")
     assert out.shape == (3, n) and e <= 1e-6
+
+
+@pytest.mark.parametrize("rim,extra", [(3, 0), (8, 0), (9, 1), (64, 0), (65, 2), (200, 1)])
+def test_curvature_of_fans(et, ctx, rim, extra):
+    """A vertex of 8, 9, 64, 65 and 200 triangles (eight lanes or a wave per vertex), triangles that repeat a vertex and
+    without area among them: bit for bit the oracle's sums in triangle order."""
+    g = W.rng(rim)
+    ang = np.linspace(0, 2 * np.pi, rim, endpoint=False)
+    v = [[3.0, 0.0, 0.3]] + [[3.0 + g.normal(0, 0.05), np.cos(a), np.sin(a)] for a in ang]
+    t = [[0, 1 + i, 1 + (i + 1) % rim] for i in range(rim)]
+    for k in range(extra):
+        t.insert(2 + 3 * k, [0, 0, 1 + k])
+    n = len(t)
+    scene = {"vertices": np.asarray(v, np.float32), "tris": np.asarray(t, np.int32), "tri_material": np.zeros(n, np.int32),
+             "tri_object": (np.arange(n) * 70 // n).astype(np.int32), "n_objects": 70}
+    C, G = et.Scene(ctx, scene, area_ref=0.01).curvature()
+    G_ref, C_ref = O.curvature(scene, 0.01)
+    assert np.array_equal(C.cpu().numpy(), C_ref) and np.array_equal(G.cpu().numpy(), G_ref)
+
+
+@pytest.mark.parametrize("T", [2, 3, 224, 225, 2047, 2049, 6000])
+def test_refit_equals_build(et, ctx, T):
+    """Mesh sizes around the clustering's workgroups and tail and the refit's narrow levels: a scene refitted to moved
+    vertices hits what a scene built on them hits."""
+    a, b = _soup(T, 300 + T), _soup(T, 300 + T)
+    b["vertices"] = (a["vertices"] + W.rng(T).normal(0, 0.05, a["vertices"].shape)).astype(np.float32)
+    _, sim = W.tiny_scene(n_rays=2000)
+    s = et.Sim(sim)
+    moved, built = et.Scene(ctx, a), et.Scene(ctx, b)
+    assert moved.info().n_nodes == T - 1 and built.info().depth <= 64
+    moved.refit(b["vertices"])
+    x, y = et.trace(ctx, moved, s).to_host(), et.trace(ctx, built, s).to_host()
+    for k in ("ray", "bounce", "tri", "vis"):
+        assert np.array_equal(x[k], y[k]), k

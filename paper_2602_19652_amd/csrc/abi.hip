@@ -18,9 +18,10 @@ struct et_ctx {
   std::string last_error;
   Ctl* ctl = nullptr;                 // device control block (with ctl2, the only library allocations)
   Ctl* ctl2 = nullptr;                // control block of the odd job waves of a pipelined batch
-  hipStream_t aux = nullptr;          // a batch's trace stream (default priority) beside `stream`,
-                                      // created by the first pipelined batch
+  hipStream_t aux = nullptr;          // second stream (default priority) beside `stream`: a batch's traces, a pose's
+                                      // diffraction samples; created by the first call that uses it
   hipEvent_t pev[5] = {};             // pipelined batch: fork, trace done (2), synthesis done (2)
+  hipEvent_t dev_ev[2] = {};          // diffraction beside the walks: fork, join
   bool serial_waves = false;          // the autotuner's runs: job waves in order on one stream
   bool counting = false;
   int32_t stack_cap = QUAD_STACK;     // entries of a ray's traversal stack (et_set_stack_limit)
@@ -261,6 +262,26 @@ void check_materials(const et_scene* sc, const et_sim_desc* sim) {
   ET_CHECK(sc->max_mat < sim->Q, ET_E_INVALID, "a triangle's material is >= Q (the band tables' rows)");
 }
 
+// The trace of one pose on the context's stream, its diffraction samples on the second one (in order where the stream is
+// being captured).
+void trace_pose(et_ctx* ctx, const SceneDev& S, const et_sim_desc* sim, const et_paths* P, const TraceWS& tw, bool counting) {
+  SideStream side{nullptr, ctx->dev_ev[0], ctx->dev_ev[1]};
+  if ((sim->flags & ET_DIFFRACTION) && sim->diff_K > 0) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    ET_HIP(hipStreamIsCapturing(ctx->stream, &status));
+    if (status == hipStreamCaptureStatusNone) {
+      if (!ctx->aux) ET_HIP(hipStreamCreateWithFlags(&ctx->aux, hipStreamNonBlocking));
+      side.stream = ctx->aux;
+    }
+  }
+  try {
+    trace_run(S, sim, P, tw, ctx->ctl, counting, ctx->stream, side.stream ? &side : nullptr);
+  } catch (const Error&) {
+    if (side.stream) (void)hipStreamSynchronize(side.stream);   // nothing of a failed call runs on
+    throw;
+  }
+}
+
 void trace_impl(et_ctx* ctx, const et_scene* sc, const et_sim_desc* sim, void* ws, size_t ws_bytes, const et_paths* paths) {
   check_scene(sc);
   validate_sim(sim, true);
@@ -275,7 +296,7 @@ void trace_impl(et_ctx* ctx, const et_scene* sc, const et_sim_desc* sim, void* w
                   &tw);
   tw.stack_cap = ctx->stack_cap;
   ET_HIP(hipEventRecord(ctx->ev[0], ctx->stream));
-  trace_run(sc->d, sim, paths, tw, ctx->ctl, ctx->counting, ctx->stream);
+  trace_pose(ctx, sc->d, sim, paths, tw, ctx->counting);
   ET_HIP(hipEventRecord(ctx->ev[1], ctx->stream));
   ctx->timed |= TM_TRACE;
   ctx->last_count = paths->count;
@@ -347,6 +368,7 @@ int et_create(int device, void* hip_stream, et_ctx** out) {
     ET_HIP(hipMemset(c->ctl2, 0, sizeof(Ctl)));
     for (auto& e : c->ev) ET_HIP(hipEventCreate(&e));
     for (auto& e : c->pev) ET_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    for (auto& e : c->dev_ev) ET_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     noalloc_init(device);   // this device's address of the allocation-free calls' scratch
   } catch (const Error& e) {
     et_destroy(c);
@@ -365,6 +387,8 @@ int et_destroy(et_ctx* ctx) {
     if (e) (void)hipEventDestroy(e);
   for (auto& e : ctx->wave_ev) (void)hipEventDestroy(e);
   for (auto& e : ctx->pev)
+    if (e) (void)hipEventDestroy(e);
+  for (auto& e : ctx->dev_ev)
     if (e) (void)hipEventDestroy(e);
   if (ctx->aux) (void)hipStreamDestroy(ctx->aux);
   if (ctx->ctl2) (void)hipFree(ctx->ctl2);
@@ -680,7 +704,7 @@ void batch_impl(et_ctx* ctx, int32_t J, const et_job* jobs, void* ws, size_t ws_
     trace_ws_layout((s->flags & ET_SPECULAR) ? s->N : 0, jobs[j].scene->d.T, jobs[j].scene->d.n_obj,
                     diff_draws_max(s), (char*)ws, &tw);
     tw.stack_cap = ctx->stack_cap;
-    trace_run(jobs[j].scene->d, s, &P, tw, ctx->ctl, false, ctx->stream);
+    trace_pose(ctx, jobs[j].scene->d, s, &P, tw, false);
     SynthWS sw;
     synth_ws_layout(s, cap, (char*)ws + w.trace, &sw);
     ctx->synth_kernel = synth_run(s, &P, sw, ctx->ctl, spectra + (size_t)j * MF2, ctx->stream);

@@ -206,8 +206,13 @@ int64_t trace_batch_rays(int32_t J, const et_job* jobs);
 // carry: a later job wave of one batch (segment, line-of-sight and record totals carry over)
 void trace_batch_run(int32_t J, const et_job* jobs, void* dev_jobs, const et_paths* paths, const TraceWS& w,
                      Ctl* ctl, bool counting, int32_t blocks, hipStream_t s, bool carry = false);
+// Second stream (with events for its start and end) for work beside the traversal; NULL: in order on the one stream.
+struct SideStream {
+  hipStream_t stream;
+  hipEvent_t fork, join;
+};
 void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths, const TraceWS& ws, Ctl* ctl,
-               bool counting, hipStream_t s);
+               bool counting, hipStream_t s, const SideStream* side);
 
 // ------------------------------------------------------------------ synthesis (synth.hip)
 struct SynthWS {

@@ -670,7 +670,7 @@ __global__ __launch_bounds__(BS) void k_records(SceneDev S, const TraceJob* __re
     if (threadIdx.x == 0) {
       const int64_t hits = (int64_t)(t & 0xffffffffull);
       ctl->seg += n;
-      ctl->shadow += hits;
+      atomicAdd((unsigned long long*)&ctl->shadow, (unsigned long long)hits);   // (diffraction adds beside)
       ctl->cnt[4] += n;
       ctl->act[j + 1] = (int64_t)(t >> 32);
       ctl->base[j + 1] = base + hits;
@@ -1189,7 +1189,7 @@ void trace_batch_run(int32_t J, const et_job* jobs, void* dev_jobs, const et_pat
 }
 
 void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths, const TraceWS& w, Ctl* ctl,
-               bool counting, hipStream_t s) {
+               bool counting, hipStream_t s, const SideStream* side) {
   const PoseArgs a = pose_args(sim);
   const et_paths P = *paths;
   const bool perrx = (sim->flags & ET_PER_RX_VISIBILITY) != 0;
@@ -1203,6 +1203,10 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
       radix_sort_u32(w.rkeys, w.rperm, a.N, RAY_KEY_BITS, w.rsort_tmp, s);
     }
     k_ray_init<false><<<nblk_full(a.N), BS, 0, s>>>(a, sim->ray_dirs, nullptr, 0, sorted ? w.rperm : nullptr, w, ctl);
+    // The diffraction samples depend on the pose alone, so with a side stream they are drawn beside the walks, which
+    // leave compute units idle in a small pose (some twenty launches of 2 to 10 us: 50,003 rays in the
+    // room with samples on 61 meshes 500 us in order, 382 us beside; an animated frame 980 and 847 us).
+    if (diff && side) ET_HIP(hipEventRecord(side->fork, s));
     // bounce grid: whole rounds of resident blocks (no partly filled last round), the chunks taken by grid
     // stride (2^20 rays, room and foliage pose: 12.10 and 8.30 ms; a block per four chunks 12.20 and 8.48; one round
     // 12.48 and 8.81)
@@ -1230,6 +1234,12 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
     ET_HIP(hipGetLastError());
   }
   if (diff) {
+    if (!(a.N > 0)) side = nullptr;   // (nothing to run beside)
+    const hipStream_t main = s;
+    if (side) {
+      ET_HIP(hipStreamWaitEvent(side->stream, side->fork, 0));
+      s = side->stream;
+    }
     DiffArgs d;
     for (int k = 0; k < 3; ++k) { d.s[k] = sim->emitter_pos[k]; d.axis[k] = sim->emitter_rot[3 * k]; }
     d.cone = sim->diff_cone_half_angle;
@@ -1264,7 +1274,12 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
     while (rs > 4 && (max_draw >> rs) < RS_WAVES) --rs;
     k_diff_sample<<<nblk(max_draw << (6 - rs)), BS, 0, s>>>(S, d, w.doffs, w.dq, w.dvals, w, ctl, rs);
     scan_exclusive_u64(w.skeep, w.soffs, 0, &ctl->n_draw, max_draw, &ctl->tot[3], w.scan_tmp, s);
-    k_diff_scatter<<<nblk(max_draw), BS, 0, s>>>(S, d, w, ctl, P);
+    if (side) {
+      ET_HIP(hipEventRecord(side->join, s));
+      ET_HIP(hipStreamWaitEvent(main, side->join, 0));
+      s = main;
+    }
+    k_diff_scatter<<<nblk(max_draw), BS, 0, s>>>(S, d, w, ctl, P);   // (after the walks' records)
     ET_HIP(hipGetLastError());
   }
   if (n_passive > 0)

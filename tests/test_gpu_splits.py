@@ -166,3 +166,51 @@ def test_refit_equals_build(et, ctx, T):
     x, y = et.trace(ctx, moved, s).to_host(), et.trace(ctx, built, s).to_host()
     for k in ("ray", "bounce", "tri", "vis"):
         assert np.array_equal(x[k], y[k]), k
+
+
+@pytest.mark.parametrize("per_mesh,per_rx", [(False, False), (True, False), (True, True)])
+def test_diffraction_beside_the_walks(et, ctx, per_mesh, per_rx):
+    """Rays and samples in one call (drawn beside the walks) give the rays' records and then the samples' records of the
+    two calls apart (which run in order), call after call, and the same number of shadow rays; also with
+    the call on a stream of its own and captured in a graph (in order there), replayed between eager calls."""
+    import torch
+    scene = W.room_geometry(W.rng(31), n_boxes=8, n_cyl=8)
+    _, base = W.room_scene(n_rays=1 << 14, M=3, F=256, diff_K=64 if per_mesh else 3000)
+    flag = (et.ET_DIFF_PER_MESH if per_mesh else 0) | (et.ET_PER_RX_VISIBILITY if per_rx else 0)
+    sim = dict(base, diff_max_meshes=scene["n_objects"], emitter_pos=[1.0, 4.0, 1.2])
+    sc = et.Scene(ctx, scene, area_ref=W.median_triangle_area(scene))
+    both = et.Sim(sim, flags=et.ET_SPECULAR | et.ET_DIFFRACTION | flag)
+    keys = ("ray", "bounce", "tri", "vis", "rtot", "p", "rxvis")
+    parts, shadow = [], 0
+    for f in (et.ET_SPECULAR, et.ET_DIFFRACTION):
+        parts.append(et.trace(ctx, sc, et.Sim(sim, flags=f | flag)).to_host())
+        shadow += ctx.stats().shadow_rays
+    ref = {k: np.concatenate([x[k] for x in parts]) for k in keys}
+    assert len(parts[0]["ray"]) and len(parts[1]["ray"])
+
+    def check(P):
+        h = P.to_host()
+        for k in keys:
+            assert np.array_equal(h[k], ref[k]), k
+
+    for _ in range(5):
+        check(et.trace(ctx, sc, both))
+        assert ctx.stats().shadow_rays == shadow
+    P, ws = et.Paths(both.capacity()), et.Workspace()
+    out = torch.empty(3, 256, 2, device="cuda")
+    H = et.simulate(ctx, sc, both, paths=P, ws=ws, out=out).clone()
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        et.simulate(ctx, sc, both, paths=P, ws=ws, out=out)
+        check(P)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=side):
+            et.simulate(ctx, sc, both, paths=P, ws=ws, out=out)
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(torch.view_as_complex(out), H)
+        assert torch.equal(et.simulate(ctx, sc, both), H)
+        torch.cuda.synchronize()

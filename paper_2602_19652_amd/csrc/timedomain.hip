@@ -16,9 +16,9 @@
 // Stockham stages over global memory (plus one radix-2 stage for an odd power of two), each a streaming pass, with
 // twiddles from a table, computed in FP64 and rounded to FP32; in a workgroup they stay in FP64, and a product is
 // rounded once.
-// Measured, whole calls: 32 responses of 16,384 samples from 4,096 bins 42 -> 17 us, their convolution with 640 samples
-// 133 -> 16 us (the kernels alone 10 and 15 us, bound by the one chain of passes and barriers of each
-// workgroup); error against FP64 1.26e-7 -> 1.11e-7 and 1.43e-7 -> 1.34e-7.
+// Measured, both calls one after the other: 32 responses of 16,384 samples from 4,096 bins and their convolution with
+// 640 samples 168 -> 20 us (bound by the one chain of passes and barriers of each workgroup; 26 us before the
+// three transforms of a block shared their twiddles' first powers and formed the others by halves); error against FP64 1.26e-7 -> 1.11e-7 and 1.43e-7 -> 1.34e-7.
 #include "internal.hpp"
 
 #include <algorithm>
@@ -236,18 +236,31 @@ struct Row {
 };
 __device__ inline int lds_at(int i) { return i + (i >> 4); }
 
+// The first powers of a thread's twiddles, one per radix-16 pass after the first pass.
+template <int LG>
+struct Twiddles {
+  static constexpr int P = (LG - 1) / 4;
+  double2 w[P > 0 ? P : 1];
+  __device__ inline explicit Twiddles(int t) {
+    int Ns = Row<LG>::R0;
+#pragma unroll
+    for (int p = 0; p < P; ++p, Ns *= 16) w[p] = cis_pi(-2.0 * (double)(t & (Ns - 1)) / (16.0 * Ns));
+  }
+};
+
 // One radix-16 pass, sub-transforms of length Ns growing to 16 Ns, then the following ones.
-template <int LG, int Ns>
-__device__ inline void row_passes(float2 (&v)[Row<LG>::E], float2* lds, int t) {
+template <int LG, int Ns, int PASS = 0>
+__device__ inline void row_passes(float2 (&v)[Row<LG>::E], float2* lds, int t, const Twiddles<LG>& tw) {
   using W = Row<LG>;
   if constexpr (Ns < W::N) {
     const int k = t & (Ns - 1);
-    const double2 w1 = cis_pi(-2.0 * (double)k / (16.0 * Ns));
-    double2 w = w1;
+    // powers by halves: w^r = w^(r / 2) w^(r - r / 2)
+    double2 w[16];
+    w[1] = tw.w[PASS];
 #pragma unroll
     for (int r = 1; r < 16; ++r) {
-      v[r] = twiddle(v[r], w);
-      w = cmuld(w, w1);
+      if (r > 1) w[r] = cmuld(w[r / 2], w[r - r / 2]);
+      v[r] = twiddle(v[r], w[r]);
     }
     dft<16>(v);
     if constexpr (16 * Ns < W::N) {
@@ -257,14 +270,14 @@ __device__ inline void row_passes(float2 (&v)[Row<LG>::E], float2* lds, int t) {
       __syncthreads();
 #pragma unroll
       for (int q = 0; q < 16; ++q) v[q] = lds[lds_at(t + W::T * q)];
-      row_passes<LG, 16 * Ns>(v, lds, t);
+      row_passes<LG, 16 * Ns, PASS + 1>(v, lds, t, tw);
     }
   }
 }
 
 // DFT with e^{-j 2 pi k n / N} of the row in v (Stockham order; the other sign by swapping parts before and after).
 template <int LG>
-__device__ inline void row_fft(float2 (&v)[Row<LG>::E], float2* lds, int t) {
+__device__ inline void row_fft(float2 (&v)[Row<LG>::E], float2* lds, int t, const Twiddles<LG>& tw) {
   using W = Row<LG>;
   constexpr int B = W::E / W::R0;
   float2 u[B][W::R0];
@@ -286,7 +299,7 @@ __device__ inline void row_fft(float2 (&v)[Row<LG>::E], float2* lds, int t) {
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < W::E; ++q) v[q] = lds[lds_at(t + W::T * q)];
-    row_passes<LG, W::R0>(v, lds, t);
+    row_passes<LG, W::R0>(v, lds, t, tw);
   }
 }
 
@@ -333,7 +346,7 @@ __global__ __launch_bounds__(Row<LG>::T) void k_impulse(const float* __restrict_
 #pragma unroll
     for (int q = 0; q < W::E; ++q) v[q] = make_float2(v[q].y, v[q].x);
   }
-  row_fft<LG>(v, lds, t);
+  row_fft<LG>(v, lds, t, Twiddles<LG>(t));
   if (sigma < 0) {
 #pragma unroll
     for (int q = 0; q < W::E; ++q) v[q] = make_float2(v[q].y, v[q].x);
@@ -365,19 +378,20 @@ __global__ __launch_bounds__(Row<LG>::T) void k_convolve(const float* __restrict
     const int k = t + W::T * q;
     e[q] = make_float2(k < L ? se[k] : 0.f, 0.f);
   }
-  row_fft<LG>(e, lds, t);
+  const Twiddles<LG> tw(t);
+  row_fft<LG>(e, lds, t, tw);
 #pragma unroll
   for (int q = 0; q < W::E; ++q) {
     const int64_t i = i0 + t + W::T * q;
     v[q] = make_float2(i >= 0 && i < n_t ? h[m * n_t + i] : 0.f, 0.f);
   }
-  row_fft<LG>(v, lds, t);
+  row_fft<LG>(v, lds, t, tw);
 #pragma unroll
   for (int q = 0; q < W::E; ++q) {
     const float2 p = twiddle(v[q], make_double2(e[q].x, e[q].y));
     v[q] = make_float2(p.y, p.x);   // swapped: the inverse direction
   }
-  row_fft<LG>(v, lds, t);
+  row_fft<LG>(v, lds, t, tw);
 #pragma unroll
   for (int q = 0; q < W::E; ++q) {
     const int n = t + W::T * q;

@@ -647,8 +647,8 @@ __device__ inline uint64_t block_sum(uint64_t v, uint64_t* red) {
   return v;
 }
 
-// The records of bounce j in ray order after the earlier bounces', the list of the slots that go on, and (first
-// workgroup) the counts of the next bounce.  A workgroup takes 256 rays, the masks of 256 >> rs waves; what lies
+// The records of bounce j in ray order after the earlier bounces', the list of the slots that go on, and (last
+// workgroup, which has no rays) the counts of the next bounce.  A workgroup takes 256 rays, the masks of 256 >> rs waves; what lies
 // before them comes from k_mask_sums, or (IN_PLACE) from summing the masks before it.  fin: this is the last
 // bounce and no other records follow.
 template <bool BATCH, bool IN_PLACE>
@@ -659,7 +659,8 @@ __global__ __launch_bounds__(BS) void k_records(SceneDev S, const TraceJob* __re
   const int64_t base = ctl->base[j];
   const int32_t* list = j > 0 ? w.list[j & 1] : nullptr;
   int32_t* next = w.list[(j + 1) & 1];
-  if (blockIdx.x == 0) {
+  const unsigned groups = gridDim.x - 1;
+  if (blockIdx.x == groups) {
     uint64_t t = 0;
     if (IN_PLACE) {
       for (int64_t c = threadIdx.x; c < nc; c += BS) t += mask_counts(w.masks[c]);
@@ -677,9 +678,10 @@ __global__ __launch_bounds__(BS) void k_records(SceneDev S, const TraceJob* __re
       ctl->rec_base = base + hits;
       if (fin) trace_final(ctl, P, 0, 0);
     }
+    return;
   }
   const int bit = threadIdx.x & ((1 << rs) - 1);
-  for (int64_t i0 = (int64_t)blockIdx.x * BS; i0 < n; i0 += (int64_t)gridDim.x * BS) {
+  for (int64_t i0 = (int64_t)blockIdx.x * BS; i0 < n; i0 += (int64_t)groups * BS) {
     const int64_t cb = i0 >> rs, c = cb + (threadIdx.x >> rs);   // the workgroup's first mask, this thread's
     uint64_t before;
     if (IN_PLACE) {
@@ -1114,10 +1116,10 @@ void launch_records(int64_t N, const SceneDev& S, const TraceJob* jobs, const Tr
                     int rs, int perrx, int fin, hipStream_t s) {
   const int64_t masks = (N + (1 << rs) - 1) >> rs;
   if (masks <= SCAN_IN_PLACE) {
-    k_records<BATCH, true><<<nblk(N), BS, 0, s>>>(S, jobs, w, ctl, P, j, rs, perrx, fin);
+    k_records<BATCH, true><<<nblk(N) + 1, BS, 0, s>>>(S, jobs, w, ctl, P, j, rs, perrx, fin);
   } else {
     k_mask_sums<<<(unsigned)((masks + CHUNKS - 1) / CHUNKS), BS, 0, s>>>(w, ctl, j, rs);
-    k_records<BATCH, false><<<nblk(N), BS, 0, s>>>(S, jobs, w, ctl, P, j, rs, perrx, fin);
+    k_records<BATCH, false><<<nblk(N) + 1, BS, 0, s>>>(S, jobs, w, ctl, P, j, rs, perrx, fin);
   }
 }
 

@@ -159,8 +159,18 @@ def _ptr(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
+# the handle of the current device's current stream (torch's own query where it has one: 0.4 us against 5 us for
+# building a Stream object)
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    def _stream() -> int:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+else:
+    def _stream() -> int:
+        return torch.cuda.current_stream().cuda_stream
+
+
 def _dev() -> torch.device:
-    if not torch.cuda.is_available():
+    if not torch.cuda.is_initialized() and not torch.cuda.is_available():
         raise RuntimeError("echotrace needs a HIP GPU (torch.cuda is not available)")
     return torch.device("cuda", torch.cuda.current_device())
 
@@ -190,7 +200,7 @@ class Context:
             raise EchoError(rc, f"{what}: {msg}")
 
     def call(self, name: str, *args):
-        lib().et_set_stream(self.h, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        lib().et_set_stream(self.h, C.c_void_p(_stream()))
         rc = getattr(lib(), name)(self.h, *args)
         self._check(rc, name)
         return rc
@@ -577,7 +587,9 @@ class SpectraFn(torch.autograd.Function):
         sim.refresh()
         fctx.save_for_backward(refl_k, rx_pos)
         fctx.et = (ctx, sim, paths)
-        return synthesize(ctx, sim, paths).clone()
+        H = torch.empty(sim.M, sim.F, dtype=torch.complex64, device=_dev())
+        synthesize(ctx, sim, paths, out=torch.view_as_real(H))
+        return H
 
     @staticmethod
     def backward(fctx, grad_out):

@@ -835,8 +835,6 @@ __device__ inline void gen_factors(const SynthArgs& a, const PairLean& q, int t,
   __builtin_amdgcn_wave_barrier();
 }
 
-struct BwdBuf;
-__device__ inline void write_bwd(const WaveScratch& W, int lane, int wv, BwdBuf& bb);
 
 // Maximum over the wave's lanes, the same (scalar) value in every lane: lane moves within rows of 16,
 // then the four rows' values.
@@ -1662,10 +1660,11 @@ constexpr int BS68 = 68;
 // X carries the band factor without k for specular records: Re(X Z) summed over a band's rows
 // is then dH/dk of that band (also where k = 0), and k enters the other sums per row.
 constexpr int YROW = 9;     // halfx8 per record row of Y halves: 64 inner indices and a pad (144-byte rows)
+template <int FOLD>
 struct __align__(16) BwdBuf {
   halfx8 Y[4][RB][YROW];     // Y halves [re hi, re lo, im hi, im lo][record][chunk of 8 inner indices]
-  float R0[RB][BS68];        // Re(X Z) per (record, row) (band edges off the 4-row groups)
-  float Rg[16][36];          // Re(X Z) summed over a group of 4 rows, per (group, record) (FOLD)
+  float R0[FOLD ? 1 : RB][BS68];   // Re(X Z) per (record, row) (band edges off the 4-row groups)
+  float Rg[FOLD ? 16 : 1][36];     // Re(X Z) summed over a group of 4 rows, per (group, record) (FOLD)
   float2 R1[16][36];         // sum over 4 rows of k X Z' per (row group, record)
   float kv[16][RB];          // 2 S_b of each specular record of the stage (0 for the others), [band][record]
   int32_t kmat[RB];          // the material of each specular record of the stage, -1 for the others
@@ -1678,7 +1677,8 @@ struct __align__(16) BwdBuf {
 // The adjoint's matrix-product operand of the sub-stage's records: Y as f16 halves record-major,
 // lane (r, c) = (lane / 8, lane % 8) forming inner indices 8 c .. 8 c + 7 of record r:
 // Y[8 c + i] = Ya[c] Yb[i].  (X is formed where it is used, from the factors.)
-__device__ inline void write_bwd(const WaveScratch& W, int lane, int wv, BwdBuf& bb) {
+template <int FOLD>
+__device__ inline void write_bwd(const WaveScratch& W, int lane, int wv, BwdBuf<FOLD>& bb) {
   const int row0 = wv * RPW;
   const int r = lane >> 3, c = lane & 7;
   const float2 ya = W.ya[r][c];
@@ -1711,7 +1711,8 @@ __device__ inline float sum8_first(float v) {
 // FP64 totals in LDS (one lane per (material, band)).  With at most 16 materials the sums stay
 // in the FP32 accumulator dkc over a group of 8 stages (64 records) and go to the totals when
 // flush is set.  Every lane of the wave calls it.
-__device__ inline void dk_wave(BwdBuf& bb, int wv, int lane, int Q, int Bk, floatx4& dkc, bool flush) {
+template <int FOLD>
+__device__ inline void dk_wave(BwdBuf<FOLD>& bb, int wv, int lane, int Q, int Bk, floatx4& dkc, bool flush) {
   const int col = lane & 15;   // A: band row; B: material column within the tile
   float av[2];
   int mv[2];
@@ -1756,14 +1757,18 @@ __device__ inline void dk_wave(BwdBuf& bb, int wv, int lane, int Q, int Bk, floa
 // bins) and the grid holds whole groups: each lane's four rows of the matrix-product output belong
 // to one band and are summed in registers, and the band factor rides on Xa as in the forward
 // kernel.
+// Bound by latency between its phases (factors, products, row sums, record sums, with two barriers a stage of 32
+// records): matrix cores 21%, vector units 36% busy with two workgroups per CU.  With folded bands and at most 32 rows
+// the buffers leave room for three (51 KB of LDS, 168 registers, 11 spilled outside the stages): 100,000
+// records x 16 receivers x 2048 bins 443 -> 372 us, a batch's adjoint 8.05 -> 6.8 ms.
 template <bool BATCH, bool SPLIT, int FOLD>
-__global__ __launch_bounds__(256, 2) void k_synth_bwd_mfma(SynthArgs a0, const SynthArgs* __restrict__ jobs,
+__global__ __launch_bounds__(256, SPLIT && FOLD ? 3 : 2) void k_synth_bwd_mfma(SynthArgs a0, const SynthArgs* __restrict__ jobs,
                                                         ChunkTab ct, et_paths P, const int32_t* __restrict__ idx,
                                                         const Ctl* ctl, const float* __restrict__ g,
                                                         double* __restrict__ gpx, double* __restrict__ gpk) {
   SYNTH_RESOLVE();
   if (BATCH) g += (size_t)jb * a.M * a.F * 2;
-  __shared__ __align__(16) BwdBuf bb;
+  __shared__ __align__(16) BwdBuf<FOLD> bb;
   __shared__ WaveScratch wscr[4];
   __shared__ SegTable st;
   __shared__ double red[256];

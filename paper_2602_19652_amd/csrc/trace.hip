@@ -166,8 +166,9 @@ __device__ inline float from_lane(float v, int src4) {
 // ran them with half of the lanes or fewer (32 of 64 in the room, 24 in foliage), and
 // fetched 64 B per ray and step through 64 different lines.  Measured (walks of a pose, before and after): 16,384
 // rays 105 -> 50 us, 50,003 rays in the room 403 -> 204 us, 2^20 there 2.12 -> 1.94 ms, 2^20 in foliage 7.1 -> 6.4 ms.
-// Waiting for half of the quads instead of a quarter at leaves made foliage 2% slower and the room as much faster; for
-// all, foliage 16% slower; handing out rays at 4 or 6 free quads instead of 2 cost 1 to 2%.
+// Leaves wait for three eighths of the quads: for a quarter, poses took 3% longer in the room and 1% in foliage, for
+// an eighth 4 and 9%, for half foliage 2%, for all 16%.  Handing out rays at 4 or 6 free quads instead of 2 cost 1
+// to 2%, at every free one as much.
 constexpr float T_WIDEN = 1.0f + 1.9073486328125e-6f;   // 1 + 2^-19
 constexpr int REFILL_LANES = 8;   // lanes of quads without a ray that make the wave hand out rays
 template <bool COUNT, int TB>
@@ -231,9 +232,9 @@ __device__ inline void walk_rays(const SceneDev& S, const Ray32& r, bool walked,
       }
       taken = min(nr, taken + (n_idle >> 2));
     }
-    // inner nodes, until a quarter of the quads that were at one have left for a leaf or finished
+    // inner nodes, until three eighths of the quads that were at one have left for a leaf or finished
     int left = __popcll(__ballot(node >= 0));
-    const int enough = left * 3;
+    const int enough = left * 5;
     while (left > 0) {
       if (node >= 0) {
         const float4 a = wide[(int64_t)node * 8], b = wide[(int64_t)node * 8 + 1];
@@ -265,7 +266,7 @@ __device__ inline void walk_rays(const SceneDev& S, const Ray32& r, bool walked,
         sp = min(sp + c - 1, st.cap);
       }
       left = __popcll(__ballot(node >= 0));
-      if (left * 4 <= enough) break;
+      if (left * 8 <= enough) break;
     }
     // leaves: a lane each, of the run of leaves on top of the quad's stack
     if (node < 0 && node != EMPTY) {

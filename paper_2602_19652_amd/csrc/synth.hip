@@ -2298,28 +2298,30 @@ __global__ void k_reduce_batch(const float* __restrict__ part, ChunkTab ct, int6
   }
 }
 
-// per job: dL/dk[Q Bk] and dL/dx[M][3] summed over its chunks, tiles and receivers in a fixed order
-__global__ void k_bwd_reduce_batch(const double* __restrict__ gpx, const double* __restrict__ gpk, ChunkTab ct,
-                                   int32_t T1, int32_t M, int32_t QB, double* __restrict__ grad_k,
-                                   double* __restrict__ grad_x) {
-  const int per_job = max(QB, 3 * M);
-  const int64_t total = (int64_t)ct.J * per_job;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t j = e / per_job;
-    const int i = (int)(e - j * per_job);
-    if (i < QB) {
-      double s = 0.0;
-      for (int64_t c = ct.off[j]; c < ct.off[j + 1]; ++c)
-        for (int t = 0; t < T1; ++t)
-          for (int m = 0; m < M; ++m) s += gpk[(((size_t)c * T1 + t) * M + m) * QB + i];
-      grad_k[j * QB + i] = s;
-    }
-    if (i < 3 * M) {
-      double s = 0.0;
-      for (int64_t c = ct.off[j]; c < ct.off[j + 1]; ++c)
-        for (int t = 0; t < T1; ++t) s += gpx[((size_t)c * T1 + t) * M * 3 + i];
-      grad_x[j * 3 * M + i] = s;
-    }
+// Per job dL/dk[Q Bk] and dL/dx[M][3], a workgroup per value as in k_bwd_reduce: its threads sum fixed strided subsets of
+// the job's partials over chunks, tiles (and receivers), and a fixed-shape tree in LDS adds the 256 sums (24
+// jobs of 128 band coefficients and 8 receivers: 83 us with a thread per value, one load after the other).
+__global__ __launch_bounds__(RED_T) void k_bwd_reduce_batch(const double* __restrict__ gpx, const double* __restrict__ gpk,
+                                                            ChunkTab ct, int32_t T1, int32_t M, int32_t QB,
+                                                            double* __restrict__ grad_k, double* __restrict__ grad_x) {
+  __shared__ double red[RED_T];
+  const int o = blockIdx.x, tid = threadIdx.x;
+  const int64_t j = blockIdx.y, c0 = ct.off[j], c1 = ct.off[j + 1];
+  double s = 0.0;
+  if (o < QB) {
+    for (int64_t e = c0 * T1 * M + tid; e < c1 * T1 * M; e += RED_T) s += gpk[e * QB + o];
+  } else {
+    for (int64_t e = c0 * T1 + tid; e < c1 * T1; e += RED_T) s += gpx[e * M * 3 + o - QB];
+  }
+  red[tid] = s;
+  __syncthreads();
+  for (int h = RED_T / 2; h > 0; h >>= 1) {
+    if (tid < h) red[tid] += red[tid + h];
+    __syncthreads();
+  }
+  if (tid == 0) {
+    if (o < QB) grad_k[j * QB + o] = red[0];
+    else grad_x[j * 3 * M + o - QB] = red[0];
   }
 }
 
@@ -2692,9 +2694,12 @@ int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const 
                                                                          w.gpart_k);
     }
     if (ev) ET_HIP(hipEventRecord(ev[3], s));
-    const int64_t n = (int64_t)J * std::max(QB, 3 * s0->M);
-    k_bwd_reduce_batch<<<(unsigned)std::min<int64_t>((n + 255) / 256, 4096), 256, 0, s>>>(
-        w.gpart_x, w.gpart_k, ct, w.T1, s0->M, QB, grad_k, grad_rx);
+    for (int32_t j0 = 0; j0 < J; j0 += 65535) {   // (the grid's second dimension)
+      ChunkTab part = ct;
+      part.off += j0;
+      k_bwd_reduce_batch<<<dim3(QB + 3 * s0->M, std::min(J - j0, 65535)), RED_T, 0, s>>>(
+          w.gpart_x, w.gpart_k, part, w.T1, s0->M, QB, grad_k + (size_t)j0 * QB, grad_rx + (size_t)j0 * 3 * s0->M);
+    }
     if (adjoint_kernel) *adjoint_kernel = w.mf_bwd ? 1 : 2;
   }
   ET_HIP(hipGetLastError());

@@ -41,7 +41,8 @@ ADJ_FLOP_PER_TERM = 16           # two: the band sum conj(g) T and the frequency
 # is four real products, so 12 half products of 2 flop each per term (twice that in the adjoint)
 SYNTH_EXEC_FLOP_PER_TERM = 24
 ADJ_EXEC_FLOP_PER_TERM = 48
-FLOP_PER_MFMA_F16 = 2 * 16 * 16 * 32   # v_mfma_f32_16x16x32_f16
+FLOP_PER_MFMA_F16 = {"k_synth_mfma": 2 * 32 * 32 * 16,       # v_mfma_f32_32x32x16_f16
+                     "k_synth_bwd_mfma": 2 * 16 * 16 * 32}   # v_mfma_f32_16x16x32_f16
 NODE_BYTES, TRI_BYTES, RAY_IO_BYTES = 128, 48, 128
 # traversal arithmetic per unit, one VALU lane operation each (an FMA counts once): a node visit
 # is the slab test of its four child boxes (per box 6 FMA, 6 min/max per axis, 4 for the entry and
@@ -103,14 +104,15 @@ def mfma_roofline(kname: str, terms: int, ms: float, flop_per_term: int, exec_fl
     alg = terms * flop_per_term
     achieved = alg / (ms * 1e-3) / 1e12
     n_mfma = counter_for(kname, "mfma_insts_per_launch")
-    exec_flop = n_mfma * FLOP_PER_MFMA_F16 if n_mfma else terms * exec_flop_per_term
+    per_mfma = FLOP_PER_MFMA_F16[kname.split("<")[0]]
+    exec_flop = n_mfma * per_mfma if n_mfma else terms * exec_flop_per_term
     exec_tf = exec_flop / (ms * 1e-3) / 1e12
     return {"kernel": kname, "bound": "mfma", "achieved": achieved, "peak": PEAK_MFMA_F16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_MFMA_F16_TFLOPS, "traffic": traffic_for(kname), "kernel_ms": ms,
             "algorithmic_flop_per_launch": alg,
             "per_unit": f"{flop_per_term} flop per (visible record, receiver, bin)",
             "executed": {"flop_per_launch": exec_flop, "achieved": exec_tf, "frac": exec_tf / PEAK_MFMA_F16_TFLOPS,
-                         "source": "SQ_INSTS_MFMA x 16384" if n_mfma else
+                         "source": f"SQ_INSTS_MFMA x {per_mfma}" if n_mfma else
                          f"{exec_flop_per_term} flop per term (three f16 half products per real product)"},
             "algorithmic_over_f32_mfma_peak": achieved / PEAK_MFMA_F32_TFLOPS}
 

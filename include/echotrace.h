@@ -402,7 +402,8 @@ typedef struct {
   int64_t diff_eligible;                             /* triangles in the diffraction CDF */
   int64_t stack_overflows;                           /* traversal stack overflows (must be 0) */
   int64_t dropped;                                   /* records beyond capacity */
-  int32_t synth_kernel;                              /* 1 factorised MFMA, 2 direct per-term */
+  int32_t synth_kernel;                              /* 1 bands on whole runs of 64 bins, 2 other layouts (runs cut
+                                                        at band edges, or per term) */
   int32_t status;                                    /* deferred device-side status */
   double ms_trace, ms_diffraction, ms_synth;         /* event-timed phases of the last calls (summed
                                                         over job waves; pipelined waves overlap) */

@@ -2449,12 +2449,17 @@ int synth_run_noalloc(const et_sim_desc* sim, const et_paths* paths, void* buf, 
                       float* spectra, hipStream_t s, hipEvent_t kb, hipEvent_t ke) {
   ET_CHECK(!(sim->flags & ET_PATH_PRODUCT), ET_E_UNSUPPORTED,
            "ET_PATH_PRODUCT needs per-record tables (a workspace): use et_synthesize");
-  const bool mf = synth_rows_ok(sim);
+  bool mf = synth_rows_ok(sim);
   const int fold = mf ? bands_fold(sim) : 0;
   const int64_t cap = std::max<int64_t>(paths->capacity, 1);
   SynthWS w{};
-  const size_t tables = table_ws(sim, nullptr, 0, w);
+  // the row table comes last: left out where the kernel has no use for it, or where only without it one chunk
+  // fits the scratch (then per term)
+  const size_t row_bytes = al(sizeof(int2) * ((size_t)synth_rows(sim, nullptr) + 1));
+  size_t tables = table_ws(sim, nullptr, 0, w);
   const size_t chunk = al(sizeof(float) * 2 * (size_t)sim->M * sim->F);
+  if (mf && fold == 0 && tables + chunk > bytes) mf = false;
+  if (!mf || fold != 0) tables -= row_bytes;
   ET_CHECK(tables + chunk <= bytes, ET_E_UNSUPPORTED,
            "receivers x bins too large for the device scratch of the allocation-free call");
   // record chunks: the usual choice, as many as the scratch holds, a multiple of 8 above 8

@@ -21,8 +21,9 @@
  *    et_destroy) the library allocates no device memory.
  *  - Calls enqueue work on the context's stream and return; outputs are valid once the
  *    stream has completed the work (the Python binding uses torch's current stream).
- *    et_get_stats() synchronises the stream.  A fused batch of several job waves also uses a
- *    second stream of the context's own (default priority, created by the first such call,
+ *    et_get_stats() synchronises the stream.  A fused batch of several job waves, and a pose
+ *    with both rays and diffraction samples (outside stream capture), also use a second
+ *    stream of the context's own (default priority, created by the first such call,
  *    destroyed by et_destroy), forked from and joined back into the context's stream within
  *    the call.
  *  - A context is used by one host thread at a time.  Scenes are immutable after build

@@ -1097,8 +1097,9 @@ __global__ __launch_bounds__(256, 2) void k_synth_mfma(SynthArgs a0, const Synth
                                                                       const int32_t* __restrict__ idx, const Ctl* ctl,
                                                                       float* __restrict__ part) {
   SYNTH_RESOLVE();
-  // records per generation: 64 (a lane per record) where the factors of two workgroups fit a CU's 160 KB
-  constexpr int U = FOLD == 8 || (FOLD == 4 && NRB == 1) ? 64 : 32;
+  // records per generation: 64 (a lane per record) where the factors of two workgroups fit a CU's 160 KB; with a
+  // directivity and two row blocks 64 would spill 50 registers in the loop (foliage pose 8.30 ms, 32 records 7.96 ms)
+  constexpr int U = (FOLD == 8 && !(DIR && NRB == 2)) || (FOLD == 4 && NRB == 1) ? 64 : 32;
   using FT = Factors<NRB, FOLD, U>;
   constexpr size_t FAC_BYTES = sizeof(FT) * 4, SUM_BYTES = sizeof(float2) * 4 * 16 * 64;
   __shared__ __align__(16) char lds[FAC_BYTES > SUM_BYTES ? FAC_BYTES : SUM_BYTES];

@@ -158,7 +158,8 @@ __global__ void k_scan_one(const uint64_t* __restrict__ in, uint64_t* __restrict
 // 8-bit digits, two launches per pass: per-block digit counts, then the scatter, whose workgroups add up the
 // counts before their own block themselves (a row of 256 counts per block, read by one thread per digit).  The
 // passes of 4-bit digits before took three to five launches each, twice as many passes, and ranked the items
-// with 16 counters per thread in LDS (8 us a pass for 45,000 keys).
+// with 16 counters per thread in LDS (8 us a pass for 45,000 keys; a pass of 8 bits takes 4 + 9 us, so half as
+// much a key).  Bound by the scatter's reads of the other blocks' counts and its scattered writes.
 constexpr int RBITS = 8;
 constexpr int RADIX = 1 << RBITS;
 constexpr int RT = 256;   // threads per block: one per digit

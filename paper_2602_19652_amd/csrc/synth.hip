@@ -1086,6 +1086,9 @@ __device__ __forceinline__ void contract12(const Operand& x, const Operand& y, f
 // unit (products and splits of the operands 1900, factors 1500, set-up 900).  The form before this one
 // shared the operands of four waves through LDS (64 KB read and 32 KB written per 32 records besides the
 // factors, LDS busy two thirds of the time, two barriers per stage, matrix and vector work one after the other).
+// Measured: 2.9 million records x 32 receivers x 4096 bins 10.7 -> 9.2 ms (992 TFLOP/s executed, 82% of the 1.2 PFLOP/s
+// that a large fp16 product reaches on the card: under this load the clock falls to 2.05 GHz), 100,000 x 16 x
+// 2048 158 -> 140 us.
 // NRB: blocks of 32 rows (1: tiles of at most 32 rows).
 // FOLD 4 (8): every band edge falls on a multiple of 4 (8) outer indices and the grid holds whole groups of
 // that many (bins a multiple of 256, 512): the band factor rides on Xa.  FOLD 0: rows from the row table

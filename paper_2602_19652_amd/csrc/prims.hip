@@ -303,7 +303,8 @@ void scan_exclusive_u64(const uint64_t* in, uint64_t* out, int64_t n_host, const
 namespace {
 // Items per block of a radix pass: 2048, more where that would make over 512 blocks (every block of the scatter
 // reads the others' counts, 1 KB each).
-int64_t radix_per(int64_t n) { return ceil_div(ceil_div(n, 512), RTILE) * RTILE; }
+constexpr int64_t RADIX_BLOCKS = 512;
+int64_t radix_per(int64_t n) { return ceil_div(ceil_div(n, RADIX_BLOCKS), RTILE) * RTILE; }
 }  // namespace
 
 size_t sort_temp_bytes(int64_t n, int key_bytes) {
@@ -311,7 +312,9 @@ size_t sort_temp_bytes(int64_t n, int key_bytes) {
   size_t b = 0;
   b += (size_t)n * key_bytes + 256;          // key ping-pong
   b += (size_t)n * sizeof(int32_t) + 256;    // value ping-pong
-  b += (size_t)RADIX * ceil_div(n, radix_per(n)) * sizeof(uint32_t) + 256;   // digit counts
+  // digit counts, of as many blocks as any smaller array has (radix_per grows in steps, at which the blocks
+  // become fewer: a scratch sized for an array serves every shorter one)
+  b += (size_t)RADIX * std::min<int64_t>(ceil_div(n, RTILE), RADIX_BLOCKS) * sizeof(uint32_t) + 256;
   return b;
 }
 

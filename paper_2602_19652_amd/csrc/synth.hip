@@ -2125,7 +2125,9 @@ int choose_P(const et_sim_desc* sim, int64_t cap, bool mfma) {
 
 size_t vis_ws(int64_t cap, char* base, size_t off, uint64_t** sum, int32_t** idx) {
   auto take = [&](size_t b) -> void* { void* p = base ? (void*)(base + off) : nullptr; off += al(b); return p; };
-  *sum = (uint64_t*)take(sizeof(uint64_t) * (size_t)((cap + vis_tile(cap) - 1) / vis_tile(cap)));
+  // (as many tiles as any smaller capacity has, so that what is queried for a pose's most records serves paths of
+  // fewer: tiles grow in steps)
+  *sum = (uint64_t*)take(sizeof(uint64_t) * (size_t)std::min<int64_t>((cap + VIS_TILE - 1) / VIS_TILE, VIS_MAX_TILES));
   *idx = (int32_t*)take(sizeof(int32_t) * (size_t)cap);
   return off;
 }

@@ -41,3 +41,15 @@ def test_build_scratch_never_shrinks(built):   # noqa: F811
     n = _around(2, 1 << 20, 2 << 20, 3 << 20)
     b = _sizes(built, "_ZN2et19scene_scratch_bytesEll", n, after=(C.c_int64(1000),))
     assert all(y >= x for x, y in zip(b, b[1:]))
+
+
+@pytest.mark.parametrize("F,Bk", [(256, 8), (1000, 7), (256, 64)])
+@pytest.mark.parametrize("flags", [0, "ET_PATH_PRODUCT", "ET_SYNTH_DIRECT"])
+def test_synthesis_scratch_never_shrinks(built, F, Bk, flags):   # noqa: F811
+    """Records of the paths, up to a pose's most (the workspace query) and fewer (a call on smaller paths)."""
+    import paper_2602_19652_amd as et
+    d = et.SimDesc(M=2, F=F, f_lo=20e3, f_hi=100e3, c=343.0, Q=3, Bk=Bk, flags=getattr(et, flags) if flags else 0)
+    n = _around(64, 256 * 64, 2048, 1 << 20, 4 << 20, 8 << 20, 12 << 20)
+    for name in ("_ZN2et15synth_ws_layoutEPK11et_sim_desclPcPNS_7SynthWSE", "_ZN2et19synth_bwd_ws_layoutEPK11et_sim_desclPcPNS_7SynthWSE"):
+        b = _sizes(built, name, n, before=(C.byref(d),), after=(C.c_void_p(), C.c_void_p()))
+        assert all(y >= x for x, y in zip(b, b[1:]))

@@ -559,8 +559,10 @@ __device__ inline void length_rcp(double w2, double& l, double& il) {
 
 // Set-up of record n for receiver m (forward): every field of the record is read at once, whether it counts
 // or not, so that a group waits for memory once and not for the index, the flags and the fields in
-// turn.  valid: the lane has a record of the range.  dmax: the receiver's largest log2 directivity gain (0
-// without directivity).
+// turn.  What a record that does not count holds is never used: its point and direction may be anything (its
+// gamma and bound are set to 0), and its material, like the receiver that a passive record keeps there, is no
+// index of the tables.  valid: the lane has a record of the range.  dmax: the receiver's largest log2 directivity gain
+// (0 without directivity).
 template <bool DIR>
 __device__ __forceinline__ void pair_fwd(const SynthArgs& a, const et_paths& P, int64_t n, bool valid, int m, float dmax,
                                          PairLean& q) {
@@ -584,14 +586,15 @@ __device__ __forceinline__ void pair_fwd(const SynthArgs& a, const et_paths& P, 
   q.slope = ok ? (float)(r * a.kslope) : 0.f;
   // rows of the band tables: the material's (with per-record tables the record's), one row for passive
   // records; the lobe's row counts for specular records only (gamma is 0 for the others)
-  const int64_t row = a.rec_rows ? n : (int64_t)mat;
+  const int q1 = ok && q.kind != 2 ? mat : 0;
+  const int64_t row = a.rec_rows ? n : (int64_t)q1;
   const float* t1 = q.kind == 0 ? a.lk : q.kind == 1 ? a.ld : a.lp;
   q.t1 = (const GlobalFloat*)(t1 + (q.kind == 2 ? 0 : row * a.Bk));
   q.t2 = (const GlobalFloat*)(a.lc + (q.kind == 0 ? row * a.Bk : 0));
   const float ux = (float)(wx * il), uy = (float)(wy * il), uz = (float)(wz * il);
   const float cx = dy * uz - dz * uy, cy = dz * ux - dx * uz, cz = dx * uy - dy * ux;
   const float gam = atan2f(sqrtf(cx * cx + cy * cy + cz * cz), dx * ux + dy * uy + dz * uz);
-  q.gamma = q.kind == 0 ? gam : 0.f;
+  q.gamma = ok && q.kind == 0 ? gam : 0.f;
   if (DIR) {   // direction of arrival in the receiver frame: -R_m^T u
     q.cell = DirCell{0, 0, 0, 0, 0.f, 0.f};
     if (a.Bd) {
@@ -609,15 +612,15 @@ __device__ __forceinline__ void pair_fwd(const SynthArgs& a, const et_paths& P, 
   // k and the lobe's coefficient may peak on different bands), or by taking every band of per-record tables
   float bm = -INFINITY;
   if (!a.rec_rows) {
-    const int top = q.kind == 0 ? mat : q.kind == 1 ? 2 * a.Q + mat : 3 * a.Q;
-    bm = a.lmax[top] - q.gamma * q.gamma * a.lmax[a.Q + (q.kind == 0 ? mat : 0)];
+    const int top = q.kind == 0 ? q1 : q.kind == 1 ? 2 * a.Q + q1 : 3 * a.Q;
+    bm = a.lmax[top] - q.gamma * q.gamma * a.lmax[a.Q + (q.kind == 0 ? q1 : 0)];
   } else {
     for (int b = 0; b < a.Bk; ++b) bm = fmaxf(bm, q.t1[b] - q.gamma * q.gamma * q.t2[b]);
   }
   q.lbm = bm + dmax;
   // nothing to add when every band factor is zero (lbm stays finite)
   q.base = ok && q.lbm != -INFINITY ? base : -INFINITY;
-  if (q.lbm == -INFINITY) q.lbm = 0.f;
+  if (!ok || q.lbm == -INFINITY) q.lbm = 0.f;
 }
 
 // Set-up of the adjoint: receiver-gradient coefficients, band factors without k.
@@ -1004,7 +1007,7 @@ __device__ __forceinline__ void gen_factors_u(const SynthArgs& a, const PairLean
       const int kb = key[sg];
       float lb = q.t1[kb & 0xffff] - g2 * q.t2[kb & 0xffff];
       if (dir) lb += __builtin_amdgcn_logf(dir_lerp(dtab + (kb >> 16) * dcells, q.cell));
-      W.bf[sg][r] = __builtin_amdgcn_exp2f(lb - q.lbm);   // <= 1 (finite for a skipped record too: its Xa is zero)
+      W.bf[sg][r] = ok ? __builtin_amdgcn_exp2f(lb - q.lbm) : 0.f;   // <= 1
     }
   }
   // the factors are read back by other lanes of this wave only

@@ -586,10 +586,10 @@ __device__ __forceinline__ void pair_fwd(const SynthArgs& a, const et_paths& P, 
   q.slope = ok ? (float)(r * a.kslope) : 0.f;
   // rows of the band tables: the material's (with per-record tables the record's), one row for passive
   // records; the lobe's row counts for specular records only (gamma is 0 for the others)
-  const int q1 = ok && q.kind != 2 ? mat : 0;
+  const int q1 = ok && q.kind < 2 ? mat : 0;
   const int64_t row = a.rec_rows ? n : (int64_t)q1;
   const float* t1 = q.kind == 0 ? a.lk : q.kind == 1 ? a.ld : a.lp;
-  q.t1 = (const GlobalFloat*)(t1 + (q.kind == 2 ? 0 : row * a.Bk));
+  q.t1 = (const GlobalFloat*)(t1 + (q.kind >= 2 ? 0 : row * a.Bk));
   q.t2 = (const GlobalFloat*)(a.lc + (q.kind == 0 ? row * a.Bk : 0));
   const float ux = (float)(wx * il), uy = (float)(wy * il), uz = (float)(wz * il);
   const float cx = dy * uz - dz * uy, cy = dz * ux - dx * uz, cz = dx * uy - dy * ux;

@@ -97,3 +97,17 @@ def test_hidden_from_one_receiver(et, ctx, layout):
     P = et.Paths.from_records(rec)
     for what, H in _forms(et, ctx, sim, et.ET_SPECULAR | et.ET_DIFFRACTION | et.ET_PER_RX_VISIBILITY, P):
         check_spectra(H, ref, f"{layout}, hidden from one receiver, {what}", tol=4e-6)
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_records_of_kind_3_are_passive_at_every_receiver(et, ctx, layout):
+    """(the two bits of the kind hold four values; the per-term kernel reads the fourth so)"""
+    sim, g = _sim(*layout)
+    rec = _records(g, 200, 3, len(sim["rx_pos"]), kinds=(0, 1))
+    rec["kind"][::2] = 3
+    rec["mat"][::2] = g.integers(0, 50, 100)
+    P = et.Paths.from_records(rec)
+    flags = et.ET_SPECULAR | et.ET_PASSIVE
+    D = et.synthesize(ctx, et.Sim(sim, flags=flags | et.ET_SYNTH_DIRECT), P).cpu().numpy()
+    for what, H in _forms(et, ctx, sim, flags, P):
+        check_spectra(H, D, f"{layout}, kind 3, {what}", tol=8e-6)

@@ -275,7 +275,7 @@ __device__ inline float band_log2_v(const SynthArgs& a, int kind, int mat, float
 __device__ inline void band_table_entry(const SynthArgs& a, int i, float* lk, float* lc, float* ld, float* lp) {
   const float bt = a.beta[i];
   lk[i] = log2f(a.refl_k[i]);
-  lc[i] = fminf(LOG2E_F / (2.0f * bt * bt), 3.0e38f);   // (finite, so that 0 times it is 0)
+  lc[i] = LOG2E_F / (2.0f * bt * bt);
   ld[i] = log2f(a.dcoef[i]);
   if (i < a.Bk) lp[i] = a.pcoef ? log2f(a.pcoef[i]) : -INFINITY;
 }
@@ -526,6 +526,10 @@ __device__ inline uint32_t q32(double cyc) {   // fraction of a cycle in Q0.32 (
 // (<= 128 * 2^-33 cycles).
 typedef __attribute__((address_space(1))) float GlobalFloat;
 
+// The lobe coefficients of the records that have no lobe (diffraction and passive ones), for up to 64 bands: a
+// material's own may be infinite (a lobe of width 0), and 0 times that is no factor.
+__device__ const float NO_LOBE[64] = {};
+
 struct PairLean {
   uint32_t a32, bx32, by32;
   float base, slope, gamma;
@@ -585,12 +589,12 @@ __device__ __forceinline__ void pair_fwd(const SynthArgs& a, const et_paths& P, 
   const float base = -(float)a.ps * __builtin_amdgcn_logf((float)r) + (float)(r * a.kbase);
   q.slope = ok ? (float)(r * a.kslope) : 0.f;
   // rows of the band tables: the material's (with per-record tables the record's), one row for passive
-  // records; the lobe's row counts for specular records only (gamma is 0 for the others)
+  // records; the lobe is the specular records' (per-record tables hold 0 for the others)
   const int q1 = ok && q.kind < 2 ? mat : 0;
   const int64_t row = a.rec_rows ? n : (int64_t)q1;
   const float* t1 = q.kind == 0 ? a.lk : q.kind == 1 ? a.ld : a.lp;
   q.t1 = (const GlobalFloat*)(t1 + (q.kind >= 2 ? 0 : row * a.Bk));
-  q.t2 = (const GlobalFloat*)(a.lc + (q.kind == 0 ? row * a.Bk : 0));
+  q.t2 = (const GlobalFloat*)(q.kind == 0 || a.rec_rows ? a.lc + row * a.Bk : NO_LOBE);
   const float ux = (float)(wx * il), uy = (float)(wy * il), uz = (float)(wz * il);
   const float cx = dy * uz - dz * uy, cy = dz * ux - dx * uz, cz = dx * uy - dy * ux;
   const float gam = atan2f(sqrtf(cx * cx + cy * cy + cz * cz), dx * ux + dy * uy + dz * uz);
@@ -613,7 +617,8 @@ __device__ __forceinline__ void pair_fwd(const SynthArgs& a, const et_paths& P, 
   float bm = -INFINITY;
   if (!a.rec_rows) {
     const int top = q.kind == 0 ? q1 : q.kind == 1 ? 2 * a.Q + q1 : 3 * a.Q;
-    bm = a.lmax[top] - q.gamma * q.gamma * a.lmax[a.Q + (q.kind == 0 ? q1 : 0)];
+    const float lobe = q.kind == 0 ? a.lmax[a.Q + q1] : 0.f;
+    bm = a.lmax[top] - q.gamma * q.gamma * lobe;
   } else {
     for (int b = 0; b < a.Bk; ++b) bm = fmaxf(bm, q.t1[b] - q.gamma * q.gamma * q.t2[b]);
   }

@@ -111,3 +111,20 @@ def test_records_of_kind_3_are_passive_at_every_receiver(et, ctx, layout):
     D = et.synthesize(ctx, et.Sim(sim, flags=flags | et.ET_SYNTH_DIRECT), P).cpu().numpy()
     for what, H in _forms(et, ctx, sim, flags, P):
         check_spectra(H, D, f"{layout}, kind 3, {what}", tol=8e-6)
+
+
+@pytest.mark.parametrize("beta", [0.0, 1e-23, np.nan])
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_lobe_widths_are_the_specular_records_own(et, ctx, layout, beta):
+    """Material 0 with lobes of width 0, of a width whose square underflows, and of no width at all: diffraction and passive
+    records of every material, and specular ones of the others, are the oracle's all the same."""
+    sim, g = _sim(*layout)
+    rec = _records(g, 300, 3, len(sim["rx_pos"]), kinds=(0, 1, 1, 2))
+    spec = rec["kind"] == 0
+    rec["mat"][spec] = 1 + rec["mat"][spec] % 2
+    ref_mix, ref_rest = O.synth(rec, sim), O.synth({k: v[~spec] for k, v in rec.items()}, sim)
+    sim["lobe_beta"][0] = beta
+    flags = et.ET_SPECULAR | et.ET_DIFFRACTION | et.ET_PASSIVE
+    for part, ref in ((rec, ref_mix), ({k: v[~spec] for k, v in rec.items()}, ref_rest)):
+        for what, H in _forms(et, ctx, sim, flags, et.Paths.from_records(part)):
+            check_spectra(H, ref, f"{layout}, beta of material 0 {beta}, {what}", tol=4e-6)

@@ -403,15 +403,16 @@ typedef struct {
   int64_t diff_eligible;                             /* triangles in the diffraction CDF */
   int64_t stack_overflows;                           /* traversal stack overflows (must be 0) */
   int64_t dropped;                                   /* records beyond capacity */
-  int32_t synth_kernel;                              /* 1 bands on whole runs of 64 bins, 2 other layouts (runs cut
-                                                        at band edges, or per term) */
+  int32_t synth_kernel;                              /* 1 factorised in f16 halves (bands on whole runs of 64 bins),
+                                                        2 FP32 terms (other layouts; see synth_rows) */
   int32_t status;                                    /* deferred device-side status */
   double ms_trace, ms_diffraction, ms_synth;         /* event-timed phases of the last calls (summed
                                                         over job waves; pipelined waves overlap) */
   double ms_adjoint;                                 /* event-timed et_synthesize_backward */
   double ms_synth_kernel, ms_adjoint_kernel;         /* the main synthesis / adjoint kernel alone */
   int32_t adjoint_kernel;                            /* 1 factorised MFMA, 2 direct per-term */
-  int32_t reserved0;
+  int32_t synth_rows;                                /* with synth_kernel 2: 1 factorised over runs cut at the band
+                                                        edges, 0 direct per-term */
   int64_t passive;                                   /* passive records of the last trace */
 } et_stats;
 int et_get_stats(et_ctx* ctx, et_stats* out);   /* synchronises the context stream */

@@ -72,7 +72,7 @@ class Stats(C.Structure):
                 ("dropped", C.c_int64), ("synth_kernel", C.c_int32), ("status", C.c_int32), ("ms_trace", C.c_double),
                 ("ms_diffraction", C.c_double), ("ms_synth", C.c_double), ("ms_adjoint", C.c_double),
                 ("ms_synth_kernel", C.c_double), ("ms_adjoint_kernel", C.c_double),
-                ("adjoint_kernel", C.c_int32), ("reserved0", C.c_int32), ("passive", C.c_int64)]
+                ("adjoint_kernel", C.c_int32), ("synth_rows", C.c_int32), ("passive", C.c_int64)]
 
 
 class Counters(C.Structure):

@@ -845,7 +845,8 @@ int et_get_stats(et_ctx* ctx, et_stats* out) {
     out->shadow_rays = h.shadow;
     out->diff_eligible = h.n_elig;
     out->stack_overflows = h.overflow;
-    out->synth_kernel = ctx->synth_kernel;
+    out->synth_kernel = ctx->synth_kernel == FWD_ROWS ? FWD_TERM : ctx->synth_kernel;
+    out->synth_rows = ctx->synth_kernel == FWD_ROWS;
     if (ctx->last_count) {
       int64_t cnt[4];
       ET_HIP(hipMemcpy(cnt, ctx->last_count, sizeof(cnt), hipMemcpyDeviceToHost));

@@ -215,6 +215,8 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
                bool counting, hipStream_t s, const SideStream* side);
 
 // ------------------------------------------------------------------ synthesis (synth.hip)
+// Forward kernels: in f16 halves, per term, FP32 over rows.
+enum FwdKernel : int { FWD_HALVES = 1, FWD_TERM = 2, FWD_ROWS = 3 };
 struct SynthWS {
   float* partial;            // [P][M][F][2]
   int32_t P;
@@ -303,7 +305,8 @@ constexpr int32_t TUNE_MAX_TRACE_BLOCKS = 8192;
 struct SynthBatchWS {
   int32_t J;
   int64_t cap;
-  bool mf, mf_bwd;   // forward, adjoint on the matrix cores
+  FwdKernel fwd;
+  bool mf_bwd;   // adjoint on the matrix cores
   int fold;    // 8 / 4: every band edge on a multiple of 512 / 256 bins, and the bins, in every job; else 0
   int32_t target, target_bwd;   // chunk count the batch aims at
   int32_t chunks, chunks_bwd;   // grid size: target + J bounds the chunk count

@@ -147,6 +147,7 @@ struct Pair {
   double c0, cb;     // delay in cycles at f_lo and per bin
   float base;        // log2 amplitude at f_lo without band factors
   float slope;       // log2 amplitude change per bin
+  double base64, slope64;
   double r, l;
   double u[3];
   float gamma;
@@ -250,8 +251,10 @@ __device__ inline bool pair_setup(const SynthArgs& a, const et_paths& P, int64_t
   const double sc = (double)a.sigma * q.r / a.c;
   q.c0 = sc * a.f_lo;
   q.cb = sc * a.df;
-  q.base = (float)(-a.ps * log2(q.r) - (a.A0 + a.A1 * a.f_lo) * q.r / 20.0 * LOG2_10);
-  q.slope = (float)(-a.A1 * a.df * q.r / 20.0 * LOG2_10);
+  q.base64 = -a.ps * log2(q.r) - (a.A0 + a.A1 * a.f_lo) * q.r / 20.0 * LOG2_10;
+  q.slope64 = -a.A1 * a.df * q.r / 20.0 * LOG2_10;
+  q.base = (float)q.base64;
+  q.slope = (float)q.slope64;
   q.mat = a.rec_rows ? (int)n : P.mat[n];
   q.gamma = 0.f;
   if (q.kind == 0) {
@@ -1082,6 +1085,73 @@ __device__ __forceinline__ void contract12(const Operand& x, const Operand& y, f
 #undef ET_MM
 }
 
+// Rows [v0, v0 + nk) of the row table as a tile: its outer indices [k1_0, k1_0 + nk1), its band segments (nseg, their
+// bands in key) and, of this lane's rows l % 32 + 32 i, the outer index - k1_0 | segment << 8 (rows past the tile: the
+// extra segment nseg).
+template <int NRB>
+__device__ __forceinline__ void tile_rows(const SynthArgs& a, int v0, int nk, int lane, int wv, int* __restrict__ key,
+                                          int& k1_0, int& nk1, int& nseg, int (&rinfo)[NRB]) {
+  const int2 row = a.rows[v0 + min(lane, nk - 1)];
+  k1_0 = __shfl(row.x, 0) >> 6;
+  nk1 = (__shfl(row.x, 63) >> 6) - k1_0 + 1;
+  const int prev = __shfl(row.y, (lane + 63) & 63);
+  const uint64_t sm = __ballot(lane == 0 || (lane < nk && row.y != prev));
+  const int seg = __popcll(sm & (~0ull >> (63 - lane))) - 1;
+  nseg = min(__popcll(sm), SMAX);
+  if (wv == 0 && ((sm >> lane) & 1) && seg < SMAX) key[seg] = row.y;
+  const int info = ((row.x >> 6) - k1_0) | (lane < nk ? min(seg, SMAX - 1) : nseg) << 8;
+#pragma unroll
+  for (int i = 0; i < NRB; ++i) rinfo[i] = __shfl(info, (lane & 31) + 32 * i);
+}
+
+// The four waves' sums acc [re, im][row block][column block] of a tile, times us, as the chunk's partial spectrum.
+// Accumulator v of lane l in block (i, jc): row 32 i + 8 (v / 4) + 4 (l / 32) + v % 4, bin 32 jc + l % 32 of the
+// row's 64; the waves' values are added in wave order, a block at a time.  ROWS: rows of the row table, each
+// keeping its own bins of the 64.  sums: LDS [wave][v][lane].
+template <int NRB, bool ROWS>
+__device__ __forceinline__ void write_tile(const SynthArgs& a, const floatx16 (&acc)[2][NRB][2], float us,
+                                           float2* __restrict__ sums, int p, int m, int v0, int nk, int k1_0, bool two,
+                                           int tid, float* __restrict__ part) {
+  const int lane = tid & 63, wv = tid >> 6;
+  float2* out = reinterpret_cast<float2*>(part + (((size_t)p * a.M + m) * a.F) * 2);
+#pragma unroll
+  for (int i = 0; i < NRB; ++i) {
+    if (i == 1 && !two) break;
+#pragma unroll
+    for (int jc = 0; jc < 2; ++jc) {
+      __syncthreads();
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        sums[(wv * 16 + v) * 64 + lane] = make_float2(acc[0][i][jc][v] * us, acc[1][i][jc][v] * us);
+      __syncthreads();
+#pragma unroll
+      for (int e0 = 0; e0 < 1024; e0 += 256) {
+        const int e = e0 + tid, v = e >> 6, l = e & 63;
+        const int row = 32 * i + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3), k2 = 32 * jc + (l & 31);
+        if (row < nk) {
+          int k = (k1_0 + row) * K2 + k2;
+          bool in = true;
+          if (ROWS) {
+            const int r0 = a.rows[v0 + row].x, r1 = a.rows[v0 + row + 1].x;
+            k = (r0 & ~(K2 - 1)) + k2;
+            in = k >= r0 && k < r1;
+          }
+          if (in) {
+            float2 t = sums[e];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+              const float2 o = sums[w * 1024 + e];
+              t.x += o.x;
+              t.y += o.y;
+            }
+            out[k] = t;
+          }
+        }
+      }
+    }
+  }
+}
+
 // Workgroup = (record chunk p, receiver m, tile of 64 rows), four waves, each with records of its own: a
 // wave sets up 64 records (one per lane), writes the generating factors of U of them to its own LDS, and per
 // 16 records forms X and Y straight into the registers that the matrix instruction takes
@@ -1099,8 +1169,8 @@ __device__ __forceinline__ void contract12(const Operand& x, const Operand& y, f
 // 2048 158 -> 140 us.
 // NRB: blocks of 32 rows (1: tiles of at most 32 rows).
 // FOLD 4 (8): every band edge falls on a multiple of 4 (8) outer indices and the grid holds whole groups of
-// that many (bins a multiple of 256, 512): the band factor rides on Xa.  FOLD 0: rows from the row table
-// (any bin count and band layout), a band factor per (segment, record).
+// that many (bins a multiple of 256, 512): the band factor rides on Xa.  FOLD 0: other bands on whole runs of 64 bins,
+// rows from the row table, a band factor per (segment, record).
 // DIR: some pose has a receiver directivity.
 template <bool BATCH, int NRB, int FOLD, bool DIR>
 __global__ __launch_bounds__(256, 2) void k_synth_mfma(SynthArgs a0, const SynthArgs* __restrict__ jobs,
@@ -1134,17 +1204,7 @@ __global__ __launch_bounds__(256, 2) void k_synth_mfma(SynthArgs a0, const Synth
       key[tid] = (int)kb;
     }
   } else {
-    const int2 row = a.rows[v0 + min(lane, nk - 1)];
-    k1_0 = __shfl(row.x, 0) >> 6;
-    nk1 = (__shfl(row.x, 63) >> 6) - k1_0 + 1;
-    const int prev = __shfl(row.y, (lane + 63) & 63);
-    const uint64_t sm = __ballot(lane == 0 || (lane < nk && row.y != prev));
-    const int seg = __popcll(sm & (~0ull >> (63 - lane))) - 1;
-    nseg = min(__popcll(sm), SMAX);
-    if (wv == 0 && ((sm >> lane) & 1) && seg < SMAX) key[seg] = row.y;
-    const int info = ((row.x >> 6) - k1_0) | (lane < nk ? min(seg, SMAX - 1) : nseg) << 8;
-#pragma unroll
-    for (int i = 0; i < NRB; ++i) rinfo[i] = __shfl(info, l32 + 32 * i);
+    tile_rows<NRB>(a, v0, nk, lane, wv, key, k1_0, nk1, nseg, rinfo);
     if (hf == 0) W.bf[nseg][l32] = 0.f;   // rows past the tile take the extra segment, whose factor is zero
   }
   if (U == 64) W.f[FT::XB][lane] = W.f[FT::YA][lane] = W.f[FT::YB][lane] = make_float2(1.f, 0.f);
@@ -1288,47 +1348,222 @@ __global__ __launch_bounds__(256, 2) void k_synth_mfma(SynthArgs a0, const Synth
       __builtin_amdgcn_wave_barrier();
     }
   }
-  // accumulator v of lane l in block (i, jc): row 32 i + 8 (v / 4) + 4 (l / 32) + v % 4, bin 32 jc + l % 32 of the
-  // row's 64; the four waves' values are added in wave order, a block at a time
-  const float us = E != -INFINITY ? exp2f(E - XTOP) : 0.f;
-  float2* sums = reinterpret_cast<float2*>(lds);   // [wave][v][lane]
-  float2* out = reinterpret_cast<float2*>(part + (((size_t)p * a.M + m) * a.F) * 2);
+  write_tile<NRB, FOLD == 0>(a, acc, E != -INFINITY ? exp2f(E - XTOP) : 0.f, reinterpret_cast<float2*>(lds), p, m, v0, nk,
+                             k1_0, two, tid, part);
+}
+
+// ------------------------------------------------------------------ factorised FP32 kernel
+
+// The factorised sum for bands that end inside a block of 64 bins, over the rows of the row table.  What a row does
+// not hold of its 64 bins is computed and dropped.  Everything is FP32 or more: the operands go to the FP32 matrix
+// cores as they are, so that a band or a path far below the tile's largest keeps its own precision, as per term
+// (halves under one exponent per tile lose it: 5e-4 of a band 1e-7 below the others), and the factors' exponents and
+// phases are reduced exactly, so that four factors per term add no more error than the one of a term by itself.
+
+// The generating factors of a wave's 32 records, rows [factor][record] as in Factors: Xa of the 4 NRB groups of outer
+// indices (without the amplitude at f_lo and the band), Xb, Ya and Yb (8 each); bf: amplitude at f_lo times band
+// factor per (segment, record).
+constexpr int RU = 32;
+template <int NRB>
+struct RowFactors {
+  static constexpr int G = 4 * NRB, XB = G, YA = XB + 8, YB = YA + 8;
+  float2 f[YB + 8][RU + 2];
+  float bf[SMAX + 1][RU + 4];
+};
+
+// 2^lg, the whole part of lg exactly (zero, infinite or not a number where lg says so).
+__device__ inline float exp2_64(double lg) {
+  const double x = fmin(fmax(lg, -4096.0), 4096.0), n = rint(x);
+  const float v = __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((float)(x - n)), (int)n);
+  return lg == lg ? v : NAN;
+}
+// e^(2 pi j ph) of a phase in Q0.32 cycles: the nearest quarter turn exactly, the rest (at most an eighth) by the
+// Taylor series of sine and cosine, whose first terms left out are 2e-9.
+__device__ inline float2 cis_q32(uint32_t ph) {
+  const uint32_t q = (ph + 0x20000000u) >> 30;
+  const float t = (float)(int32_t)(ph - (q << 30)) * 1.4629180792671596e-9f;   // 2 pi 2^-32
+  const float u = t * t;
+  const float sn = t * fmaf(u, fmaf(u, fmaf(u, fmaf(u, 1.f / 362880.f, -1.f / 5040.f), 1.f / 120.f), -1.f / 6.f), 1.f);
+  const float cs = fmaf(u, fmaf(u, fmaf(u, fmaf(u, fmaf(u, -1.f / 3628800.f, 1.f / 40320.f), -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
+  const float x = q & 1 ? sn : cs, y = q & 1 ? cs : sn;
+  return make_float2((q ^ (q << 1)) & 2 ? -x : x, q & 2 ? -y : y);
+}
+// 2^(k slope) e^(2 pi j ph), slope = hi + lo with 12 bits in hi: k hi is exact for the multiples k that a factor takes (up
+// to 3 bits and a power of two), and so is its fraction.
+__device__ inline float2 row_factor(float k, float hi, float lo, uint32_t ph) {
+  const float n = rintf(k * hi);
+  const float amp = __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(fmaf(k, lo, fmaf(k, hi, -n))), (int)n);
+  const float2 c = cis_q32(ph);
+  return make_float2(amp * c.x, amp * c.y);
+}
+
+// Workgroup and waves as in k_synth_mfma.  A wave sets up 64 records and, 32 at a time, writes their factors to its own
+// LDS; lane l forms X of row l % 32 (+ 32) and Y of bin l % 32 (+ 32) for records 4 j + 2 (l / 32) and the next, two
+// steps of v_mfma_f32_32x32x2_f32 (a record per half wave).
+// Bound by the FP32 matrix pipe where records are many (250,000 x 32 receivers x 2000 bins: 1.74 ms, 105 TFLOP/s
+// executed, two thirds of the peak; per term 6.7 ms), and by the set-up and the factors of part-filled groups where a wave
+// has few (60,000 x 6 receivers x 3000 bins in 7 bands: 129 us, per term 540).  Error against 64 bits over random grids of
+// 200 to 4160 bins 1.7e-7 to 4.5e-7 of the norm, per term 2.1e-7 to 1.3e-6.
+template <bool BATCH, int NRB, bool DIR>
+__global__ __launch_bounds__(256, 2) void k_synth_rows(SynthArgs a0, const SynthArgs* __restrict__ jobs, ChunkTab ct,
+                                                       et_paths P, const int32_t* __restrict__ idx, const Ctl* ctl,
+                                                       float* __restrict__ part) {
+  SYNTH_RESOLVE();
+  using FT = RowFactors<NRB>;
+  constexpr size_t FAC_BYTES = sizeof(FT) * 4, SUM_BYTES = sizeof(float2) * 4 * 16 * 64;
+  __shared__ __align__(16) char lds[FAC_BYTES > SUM_BYTES ? FAC_BYTES : SUM_BYTES];
+  __shared__ int key[SMAX];
+  const int m = bm;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hf = lane >> 5;
+  const int v0 = bt * KT1;                       // first row of the tile
+  const int nk = min(KT1, a.nrows - v0);         // its rows
+  if (nk <= 0) return;                           // (a batch's job with fewer rows than others)
+  int k1_0, nk1, nseg, rinfo[NRB];
+  tile_rows<NRB>(a, v0, nk, lane, wv, key, k1_0, nk1, nseg, rinfo);
+  FT& W = reinterpret_cast<FT*>(lds)[wv];
+  if (hf == 0) W.bf[nseg][l32] = 0.f;            // rows past the tile
+  __syncthreads();
+  const bool two = NRB == 2 && nk > 32;          // rows in the second block
+  const float* dtab = a.dir + (size_t)m * a.Bd * a.El * a.Az;
+  const size_t dcells = (size_t)a.El * a.Az;
+  const bool dir = DIR && a.Bd != 0;
+  floatx16 acc[2][NRB][2];
 #pragma unroll
-  for (int i = 0; i < NRB; ++i) {
-    if (i == 1 && !two) break;
+  for (int c = 0; c < 2; ++c)
 #pragma unroll
-    for (int jc = 0; jc < 2; ++jc) {
-      __syncthreads();
+    for (int i = 0; i < NRB; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        sums[(wv * 16 + v) * 64 + lane] = make_float2(acc[0][i][jc][v] * us, acc[1][i][jc][v] * us);
-      __syncthreads();
+      for (int jc = 0; jc < 2; ++jc)
 #pragma unroll
-      for (int e0 = 0; e0 < 1024; e0 += 256) {
-        const int e = e0 + tid, v = e >> 6, l = e & 63;
-        const int row = 32 * i + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3), k2 = 32 * jc + (l & 31);
-        if (row < nk) {
-          int k = (k1_0 + row) * K2 + k2;
-          bool in = true;
-          if (FOLD == 0) {
-            const int r0 = a.rows[v0 + row].x, r1 = a.rows[v0 + row + 1].x;
-            k = (r0 & ~(K2 - 1)) + k2;
-            in = k >= r0 && k < r1;
+        for (int v = 0; v < 16; ++v) acc[c][i][jc][v] = 0.f;
+  const int64_t pw = ((hi - lo + 3) / 4 + 3) / 4 * 4;   // the wave's share of the chunk: whole steps of 4 records
+  const int64_t wlo = lo + wv * pw, whi = min(wlo + pw, hi);
+  for (int64_t g = wlo; g < whi; g += 64) {
+    Pair q;
+    DirCell cell{0, 0, 0, 0, 0.f, 0.f};
+    bool ok = false;
+    if (g + lane < whi) ok = pair_setup(a, P, record_at(idx, g + lane), m, q);
+    // phases of the first row's first bin, and steps of 8 rows, a row, 8 bins and a bin
+    uint32_t pa = 0, pa8 = 0, px = 0, py8 = 0, py = 0;
+    float shi = 0.f, slo = 0.f;
+    if (!ok) {
+      q.base64 = q.slope64 = 0.0;
+      q.gamma = 0.f;
+      q.kind = q.mat = 0;
+    } else {
+      pa = q32(q.c0 + (double)(k1_0 * K2) * q.cb);
+      pa8 = q32((double)(8 * K2) * q.cb);
+      px = q32((double)K2 * q.cb);
+      py8 = q32(8.0 * q.cb);
+      py = q32(q.cb);
+      shi = __uint_as_float(__float_as_uint((float)q.slope64) & 0xfffff000u);
+      slo = (float)(q.slope64 - (double)shi);
+    }
+    if (dir && ok) {
+      float vx, vy, vz;
+      arrival(a, q, m, vx, vy, vz);
+      cell = dir_cell(a.El, a.Az, vx, vy, vz);
+    }
+    const int nrec = (int)min<int64_t>(64, whi - g);
+    for (int s = 0; RU * s < nrec; ++s) {
+      const int r = l32, src = RU * s + r;       // lanes r and r + 32: half of record r's factors each
+      {
+        // (the tile's first row may lie at any multiple of the slope)
+        const float amp0 = exp2_64(__shfl((double)(k1_0 * K2) * q.slope64, src));
+        const float hi = __shfl(shi, src), lo = __shfl(slo, src);
+        const uint32_t ba = (uint32_t)__shfl((int)pa, src), b8 = (uint32_t)__shfl((int)pa8, src);
+#pragma unroll
+        for (int jj = 0; jj < FT::G / 2; ++jj) {
+          const int j = FT::G / 2 * hf + jj;
+          const float2 v = row_factor((float)(8 * K2 * j), hi, lo, ba + (uint32_t)j * b8);
+          W.f[j][r] = make_float2(amp0 * v.x, amp0 * v.y);
+        }
+        const uint32_t bx = (uint32_t)__shfl((int)px, src), by8 = (uint32_t)__shfl((int)py8, src), by = (uint32_t)__shfl((int)py, src);
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          const int j = 4 * hf + jj;
+          W.f[FT::XB + j][r] = row_factor((float)(K2 * j), hi, lo, (uint32_t)j * bx);
+          W.f[FT::YA + j][r] = row_factor((float)(8 * j), hi, lo, (uint32_t)j * by8);
+          W.f[FT::YB + j][r] = row_factor((float)j, hi, lo, (uint32_t)j * by);
+        }
+      }
+      {
+        const double base = __shfl(q.base64, src);
+        const float gamma = __shfl(q.gamma, src);
+        const int mat = __shfl(q.mat, src), kind = __shfl(q.kind, src);
+        const bool on = __shfl((int)ok, src) != 0;
+        DirCell c = cell;
+        if (dir) {
+          c.r0 = __shfl(cell.r0, src); c.r1 = __shfl(cell.r1, src);
+          c.i0 = __shfl(cell.i0, src); c.i1 = __shfl(cell.i1, src);
+          c.ta = __shfl(cell.ta, src); c.te = __shfl(cell.te, src);
+        }
+        for (int sg = hf; sg < nseg; sg += 2) {
+          float v = 0.f;
+          if (on) {
+            const int kb = key[sg];
+            const int64_t at = (int64_t)mat * a.Bk + (kb & 0xffff);
+            double lb = kind == 0 ? (double)a.lk[at] - (double)gamma * (double)gamma * (double)a.lc[at]
+                                  : (double)(kind == 1 ? a.ld[at] : a.lp[kb & 0xffff]);
+            if (dir) lb += (double)log2f(dir_lerp(dtab + (kb >> 16) * dcells, c));
+            v = exp2_64(base + lb);
           }
-          if (in) {
-            float2 t = sums[e];
+          W.bf[sg][r] = v;
+        }
+      }
+      // the factors are read back by other lanes of this wave only
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const float2 *px_a[NRB], *px_b[NRB];
+      const float* px_f[NRB];
 #pragma unroll
-            for (int w = 1; w < 4; ++w) {
-              const float2 o = sums[w * 1024 + e];
-              t.x += o.x;
-              t.y += o.y;
+      for (int i = 0; i < NRB; ++i) {
+        px_a[i] = &W.f[(rinfo[i] & 63) >> 3][2 * hf];
+        px_b[i] = &W.f[FT::XB + (rinfo[i] & 7)][2 * hf];
+        px_f[i] = &W.bf[rinfo[i] >> 8][2 * hf];
+      }
+      const float2 *py_a = &W.f[FT::YA + (l32 >> 3)][2 * hf], *py_b = &W.f[FT::YB + (l32 & 7)][2 * hf];
+      constexpr int Y1 = 4 * (RU + 2);           // bins l + 32: four groups of 8 on
+      const int n4 = (min(RU, nrec - RU * s) + 3) / 4;
+      for (int j = 0; j < n4; ++j) {
+        float2 y[2][2], x[NRB][2];               // [block][step]
+#pragma unroll
+        for (int jc = 0; jc < 2; ++jc) {
+          const float4 u = *reinterpret_cast<const float4*>(py_a + jc * Y1 + 4 * j), v = *reinterpret_cast<const float4*>(py_b + 4 * j);
+          y[jc][0] = cmul(make_float2(u.x, u.y), make_float2(v.x, v.y));
+          y[jc][1] = cmul(make_float2(u.z, u.w), make_float2(v.z, v.w));
+        }
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) {
+          const float4 u = *reinterpret_cast<const float4*>(px_a[i] + 4 * j), v = *reinterpret_cast<const float4*>(px_b[i] + 4 * j);
+          const float2 f = *reinterpret_cast<const float2*>(px_f[i] + 4 * j);
+          x[i][0] = cmul(make_float2(u.x * f.x, u.y * f.x), make_float2(v.x, v.y));
+          x[i][1] = cmul(make_float2(u.z * f.y, u.w * f.y), make_float2(v.z, v.w));
+        }
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) {
+          if (i == 1 && !two) break;
+#pragma unroll
+          for (int st = 0; st < 2; ++st) {
+#pragma unroll
+            for (int jc = 0; jc < 2; ++jc) {
+              acc[0][i][jc] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i][st].x, y[jc][st].x, acc[0][i][jc], 0, 0, 0);
+              acc[1][i][jc] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i][st].x, y[jc][st].y, acc[1][i][jc], 0, 0, 0);
             }
-            out[k] = t;
+#pragma unroll
+            for (int jc = 0; jc < 2; ++jc) {
+              acc[0][i][jc] = __builtin_amdgcn_mfma_f32_32x32x2f32(-x[i][st].y, y[jc][st].y, acc[0][i][jc], 0, 0, 0);
+              acc[1][i][jc] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i][st].y, y[jc][st].x, acc[1][i][jc], 0, 0, 0);
+            }
           }
         }
       }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // the factors are rewritten next
+      __builtin_amdgcn_wave_barrier();
     }
   }
+  write_tile<NRB, true>(a, acc, 1.f, reinterpret_cast<float2*>(lds), bp, m, v0, nk, k1_0, two, tid, part);
 }
 
 // ------------------------------------------------------------------ direct kernel
@@ -2368,32 +2603,33 @@ void launch_fwd_fold(int fold, dim3 grid, hipStream_t s, const SynthArgs& a, con
   else k_synth_mfma<BATCH, NRB, 0, DIR><<<grid, 256, 0, s>>>(a, jobs, ct, P, idx, ctl, part);
 }
 
+template <bool BATCH, int NRB, bool DIR>
+void launch_fwd_tiles(FwdKernel fk, int fold, dim3 grid, hipStream_t s, const SynthArgs& a, const SynthArgs* jobs,
+                      const ChunkTab& ct, const et_paths& P, const int32_t* idx, const Ctl* ctl, float* part) {
+  if (fk == FWD_ROWS) k_synth_rows<BATCH, NRB, DIR><<<grid, 256, 0, s>>>(a, jobs, ct, P, idx, ctl, part);
+  else launch_fwd_fold<BATCH, NRB, DIR>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+}
+
 // rows: the most rows of a job; tiles of 64 rows, or one block of 32 when that holds them all
 template <bool BATCH>
-void launch_fwd_mfma(int rows, int fold, bool dir, int chunks, int M, hipStream_t s, const SynthArgs& a,
-                     const SynthArgs* jobs, const ChunkTab& ct, const et_paths& P, const int32_t* idx, const Ctl* ctl,
-                     float* part) {
+void launch_fwd(FwdKernel fk, int rows, int fold, bool dir, int chunks, int M, hipStream_t s, const SynthArgs& a,
+                const SynthArgs* jobs, const ChunkTab& ct, const et_paths& P, const int32_t* idx, const Ctl* ctl,
+                float* part) {
+  if (fk == FWD_TERM) {
+    k_synth_direct<BATCH><<<dim3(chunks, M, (a.F + DTILE - 1) / DTILE), DB, 0, s>>>(a, jobs, ct, P, idx, ctl, part);
+    return;
+  }
   const dim3 grid(chunks, M, (rows + KT1 - 1) / KT1);
   if (rows <= 32) {
-    if (dir) launch_fwd_fold<BATCH, 1, true>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
-    else launch_fwd_fold<BATCH, 1, false>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+    if (dir) launch_fwd_tiles<BATCH, 1, true>(fk, fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+    else launch_fwd_tiles<BATCH, 1, false>(fk, fold, grid, s, a, jobs, ct, P, idx, ctl, part);
   } else {
-    if (dir) launch_fwd_fold<BATCH, 2, true>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
-    else launch_fwd_fold<BATCH, 2, false>(fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+    if (dir) launch_fwd_tiles<BATCH, 2, true>(fk, fold, grid, s, a, jobs, ct, P, idx, ctl, part);
+    else launch_fwd_tiles<BATCH, 2, false>(fk, fold, grid, s, a, jobs, ct, P, idx, ctl, part);
   }
 }
 
-// The forward synthesis runs on the matrix cores for every band layout whose tiles of 64 rows hold at
-// most SMAX band segments (their factors sit in LDS per segment): per term (k_synth_direct) the 60,000
-// records x 6 receivers x 3000 bins in 7 bands take 540 us, most of it three transcendentals per term.
-bool synth_rows_ok(const et_sim_desc* sim) {
-  if (sim->flags & ET_SYNTH_DIRECT) return false;
-  int seg = 0;
-  synth_rows(sim, &seg);
-  return seg <= SMAX;
-}
-
-// Bands on whole runs of 64 bins: what et_stats reports as kernel 1, and what the factorised adjoint takes.
+// Bands on whole runs of 64 bins: what k_synth_mfma and the factorised adjoint take.
 bool synth_factorised_ok(const et_sim_desc* sim) {
   // needs k = 64 k1 + k2, material / directivity bands constant over each run of 64 bins
   // (the band factor is per outer index), and at most SMAX band segments per tile of KT1
@@ -2417,9 +2653,21 @@ bool synth_factorised_ok(const et_sim_desc* sim) {
   return true;
 }
 
+// The forward kernel of a pose: in halves where the bands lie on whole runs of 64 bins, in FP32 over rows for any other
+// layout whose tiles of 64 rows hold at most SMAX band segments (their factors sit in LDS per segment), else per
+// term.  Per term the 60,000 records x 6 receivers x 3000 bins in 7 bands take 540 us, most of it three
+// transcendentals per term.
+FwdKernel fwd_kernel(const et_sim_desc* sim) {
+  if (sim->flags & ET_SYNTH_DIRECT) return FWD_TERM;
+  if (synth_factorised_ok(sim)) return FWD_HALVES;
+  int seg = 0;
+  synth_rows(sim, &seg);
+  return seg <= SMAX ? FWD_ROWS : FWD_TERM;
+}
+
 size_t synth_ws_layout(const et_sim_desc* sim, int64_t cap, char* base, SynthWS* ws) {
   cap = std::max<int64_t>(cap, 1);
-  const int P = choose_P(sim, cap, synth_rows_ok(sim));
+  const int P = choose_P(sim, cap, fwd_kernel(sim) != FWD_TERM);
   size_t off = 0;
   SynthWS w{};
   w.P = P;
@@ -2440,31 +2688,27 @@ size_t synth_ws_layout(const et_sim_desc* sim, int64_t cap, char* base, SynthWS*
 
 int synth_run(const et_sim_desc* sim, const et_paths* paths, const SynthWS& ws, Ctl* ctl, float* spectra, hipStream_t s,
               hipEvent_t kb, hipEvent_t ke) {
-  const bool mf = synth_rows_ok(sim);
-  const int fold = mf ? bands_fold(sim) : 0;
+  const FwdKernel fk = fwd_kernel(sim);
+  const int fold = fk == FWD_HALVES ? bands_fold(sim) : 0;
   SynthArgs a = make_args(sim, ws.P);
   const et_paths P = *paths;
-  build_prep(a, ws, P, true, mf && fold == 0, ctl, s);
+  build_prep(a, ws, P, true, fk != FWD_TERM && fold == 0, ctl, s);
   set_readings(a, sim, P, ws, ctl, s);
   if (kb) ET_HIP(hipEventRecord(kb, s));
-  if (mf) {
-    launch_fwd_mfma<false>(a.nrows, fold, sim->directivity != nullptr, ws.P, sim->M, s, a, nullptr, ChunkTab{}, P, ws.vidx, ctl, ws.partial);
-  } else {
-    dim3 grid(ws.P, sim->M, (sim->F + DTILE - 1) / DTILE);
-    k_synth_direct<false><<<grid, DB, 0, s>>>(a, nullptr, ChunkTab{}, P, ws.vidx, ctl, ws.partial);
-  }
+  launch_fwd<false>(fk, a.nrows, fold, sim->directivity != nullptr, ws.P, sim->M, s, a, nullptr, ChunkTab{}, P, ws.vidx, ctl,
+                    ws.partial);
   if (ke) ET_HIP(hipEventRecord(ke, s));
   reduce_partials(ws.partial, ws.P, (int64_t)sim->M * sim->F, spectra, s);
   ET_HIP(hipGetLastError());
-  return synth_factorised_ok(sim) ? 1 : 2;
+  return fk;
 }
 
 int synth_run_noalloc(const et_sim_desc* sim, const et_paths* paths, void* buf, size_t bytes, Ctl* ctl,
                       float* spectra, hipStream_t s, hipEvent_t kb, hipEvent_t ke) {
   ET_CHECK(!(sim->flags & ET_PATH_PRODUCT), ET_E_UNSUPPORTED,
            "ET_PATH_PRODUCT needs per-record tables (a workspace): use et_synthesize");
-  bool mf = synth_rows_ok(sim);
-  const int fold = mf ? bands_fold(sim) : 0;
+  FwdKernel fk = fwd_kernel(sim);
+  const int fold = fk == FWD_HALVES ? bands_fold(sim) : 0;
   const int64_t cap = std::max<int64_t>(paths->capacity, 1);
   SynthWS w{};
   // the row table comes last: left out where the kernel has no use for it, or where only without it one chunk
@@ -2472,12 +2716,12 @@ int synth_run_noalloc(const et_sim_desc* sim, const et_paths* paths, void* buf, 
   const size_t row_bytes = al(sizeof(int2) * ((size_t)synth_rows(sim, nullptr) + 1));
   size_t tables = table_ws(sim, nullptr, 0, w);
   const size_t chunk = al(sizeof(float) * 2 * (size_t)sim->M * sim->F);
-  if (mf && fold == 0 && tables + chunk > bytes) mf = false;
-  if (!mf || fold != 0) tables -= row_bytes;
+  if (fk != FWD_TERM && fold == 0 && tables + chunk > bytes) fk = FWD_TERM;
+  if (fk == FWD_TERM || fold != 0) tables -= row_bytes;
   ET_CHECK(tables + chunk <= bytes, ET_E_UNSUPPORTED,
            "receivers x bins too large for the device scratch of the allocation-free call");
   // record chunks: the usual choice, as many as the scratch holds, a multiple of 8 above 8
-  int64_t P = std::min<int64_t>(choose_P(sim, cap, mf), (int64_t)((bytes - tables) / chunk));
+  int64_t P = std::min<int64_t>(choose_P(sim, cap, fk != FWD_TERM), (int64_t)((bytes - tables) / chunk));
   if (P > 8) P = P / 8 * 8;
   char* base = (char*)buf;
   table_ws(sim, base, 0, w);
@@ -2487,19 +2731,15 @@ int synth_run_noalloc(const et_sim_desc* sim, const et_paths* paths, void* buf, 
   SynthArgs a = make_args(sim, w.P);
   const et_paths Pth = *paths;
   k_vis_all<<<1, 1, 0, s>>>(Pth, ctl);
-  build_prep(a, w, Pth, false, mf && fold == 0, ctl, s);
+  build_prep(a, w, Pth, false, fk != FWD_TERM && fold == 0, ctl, s);
   a.rxv = (sim->flags & ET_PER_RX_VISIBILITY) ? Pth.rx_vis : nullptr;
   if (kb) ET_HIP(hipEventRecord(kb, s));
-  if (mf) {
-    launch_fwd_mfma<false>(a.nrows, fold, sim->directivity != nullptr, w.P, sim->M, s, a, nullptr, ChunkTab{}, Pth, nullptr, ctl, w.partial);
-  } else {
-    dim3 grid(w.P, sim->M, (sim->F + DTILE - 1) / DTILE);
-    k_synth_direct<false><<<grid, DB, 0, s>>>(a, nullptr, ChunkTab{}, Pth, nullptr, ctl, w.partial);
-  }
+  launch_fwd<false>(fk, a.nrows, fold, sim->directivity != nullptr, w.P, sim->M, s, a, nullptr, ChunkTab{}, Pth, nullptr, ctl,
+                    w.partial);
   if (ke) ET_HIP(hipEventRecord(ke, s));
   reduce_partials(w.partial, w.P, (int64_t)sim->M * sim->F, spectra, s);
   ET_HIP(hipGetLastError());
-  return synth_factorised_ok(sim) ? 1 : 2;
+  return fk;
 }
 
 bool synth_bwd_factorised_ok(const et_sim_desc* sim) { return !sim->directivity && synth_factorised_ok(sim); }
@@ -2598,22 +2838,27 @@ size_t synth_batch_ws_layout(int32_t J, const et_job* jobs, int64_t cap, const B
   SynthBatchWS w{};
   w.J = J;
   w.cap = cap;
-  w.mf = true;
+  // one kernel for every job: in halves if each allows it, else FP32 over rows if each allows that (a job with its
+  // bands on whole runs too), else per term
+  w.fwd = FWD_HALVES;
   w.rows = 0;
   for (int32_t i = 0; i < J; ++i) {
-    w.mf = w.mf && synth_rows_ok(jobs[i].sim);
-    w.rows = std::max(w.rows, synth_rows(jobs[i].sim, nullptr));
+    const FwdKernel k = fwd_kernel(jobs[i].sim);
+    if (k == FWD_TERM || (k == FWD_ROWS && w.fwd == FWD_HALVES)) w.fwd = k;
+    if (w.fwd == FWD_TERM) break;
   }
+  for (int32_t i = 0; i < J; ++i) w.rows = std::max(w.rows, synth_rows(jobs[i].sim, nullptr));
   w.mf_bwd = adjoint && synth_batch_factorised(J, jobs, true);
   w.fold = 8;   // the coarsest folding every job allows
   for (int32_t i = 0; i < J; ++i) w.fold = std::min(w.fold, bands_fold(jobs[i].sim));
-  w.target = chunk_target(s0, w.mf, tune.synth_wgs);
+  const bool mf = w.fwd != FWD_TERM;
+  w.target = chunk_target(s0, mf, tune.synth_wgs);
   w.target_bwd = chunk_target(s0, w.mf_bwd, tune.adjoint_wgs);
   // grid size: the chunk count is at most target + J (sum_j ceil(n_j / per)); buffers are
   // sized for the largest target the tuner tries, so that tuning keeps the workspace valid
   w.chunks = w.target + J;
   w.chunks_bwd = w.target_bwd + J;
-  const int64_t cmax = chunk_target(s0, w.mf, TUNE_MAX_WGS) + J;
+  const int64_t cmax = chunk_target(s0, mf, TUNE_MAX_WGS) + J;
   const int64_t cmax_bwd = chunk_target(s0, w.mf_bwd, TUNE_MAX_WGS) + J;
   w.T1 = w.mf_bwd ? (int)((s0->F / K2 + KT1 - 1) / KT1) : 1;
   size_t off = 0;
@@ -2651,6 +2896,7 @@ int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const 
   const int QB = s0->Q * s0->Bk;
   // job table with per-job band tables
   SynthArgs* dj = (SynthArgs*)w.jobs;
+  const bool row_tables = w.fwd == FWD_ROWS || (w.fwd == FWD_HALVES && w.fold == 0);
   SynthJobPack pk{};
   for (int32_t i = 0; i < J; ++i) {
     SynthArgs a = make_args(jobs[i].sim, 0);
@@ -2659,7 +2905,7 @@ int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const 
     a.ld = a.lc + QB;
     a.lp = a.ld + QB;
     a.lmax = a.lp + QB;
-    if (w.mf && w.fold == 0) a.rows = (const int2*)w.row_tables + (size_t)i * (w.rows + 1);
+    if (row_tables) a.rows = (const int2*)w.row_tables + (size_t)i * (w.rows + 1);
     pk.j[pk.n++] = a;
     if (pk.n == SJOB_PACK || i + 1 == J) {
       k_put_synth_jobs<<<1, SJOB_PACK, 0, s>>>(pk, dj);
@@ -2686,14 +2932,9 @@ int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const 
                                    const_cast<int64_t*>(ct.hi), const_cast<int64_t*>(ct.per));
     const SynthArgs a0 = make_args(s0, 0);
     if (ev) ET_HIP(hipEventRecord(ev[0], s));
-    if (w.mf) {
-      bool dir = false;
-      for (int32_t i = 0; i < J; ++i) dir = dir || jobs[i].sim->directivity != nullptr;
-      launch_fwd_mfma<true>(w.rows, w.fold, dir, w.chunks, s0->M, s, a0, dj, ct, P, w.vidx, ctl, w.partial);
-    } else {
-      dim3 grid(w.chunks, s0->M, (s0->F + DTILE - 1) / DTILE);
-      k_synth_direct<true><<<grid, DB, 0, s>>>(a0, dj, ct, P, w.vidx, ctl, w.partial);
-    }
+    bool dir = false;
+    for (int32_t i = 0; i < J; ++i) dir = dir || jobs[i].sim->directivity != nullptr;
+    launch_fwd<true>(w.fwd, w.rows, w.fold, dir, w.chunks, s0->M, s, a0, dj, ct, P, w.vidx, ctl, w.partial);
     if (ev) ET_HIP(hipEventRecord(ev[1], s));
     k_reduce_batch<<<(unsigned)std::min<int64_t>((J * MF2 + 255) / 256, 8192), 256, 0, s>>>(w.partial, ct, MF2, spectra);
   }
@@ -2722,7 +2963,7 @@ int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const 
     if (adjoint_kernel) *adjoint_kernel = w.mf_bwd ? 1 : 2;
   }
   ET_HIP(hipGetLastError());
-  return synth_batch_factorised(J, jobs, false) ? 1 : 2;
+  return w.fwd;
 }
 
 __global__ void k_sum_spectra(const float* __restrict__ in, int32_t J, int64_t n, float* __restrict__ out) {

@@ -128,3 +128,32 @@ def test_lobe_widths_are_the_specular_records_own(et, ctx, layout, beta):
     for part, ref in ((rec, ref_mix), ({k: v[~spec] for k, v in rec.items()}, ref_rest)):
         for what, H in _forms(et, ctx, sim, flags, et.Paths.from_records(part)):
             check_spectra(H, ref, f"{layout}, beta of material 0 {beta}, {what}", tol=4e-6)
+
+
+@pytest.mark.parametrize("weak", [1e-4, 1e-6, 1e-8, 1e-12])
+@pytest.mark.parametrize("F,Bk,Bd,direct", [(3000, 7, 0, False), (3000, 7, 3, False), (500, 4, 0, False), (130, 3, 0, False),
+                                            (3000, 7, 0, True)])
+def test_weak_bands_keep_their_precision(et, ctx, F, Bk, Bd, direct, weak):
+    """Bands off the 64-bin blocks with coefficients from 1 down to `weak`, on paths of 1 to 65 m with the default absorption
+    (up to 190 dB more in the last band than in the first): every band's own relative error, not the whole spectrum's.
+    An FP32 term's exponent (below 64 with the weakest band) is rounded to 2^-19, 1.3e-6 of the term; with the
+    lobe's angle and the sums 5e-6."""
+    sim, g = _sim(F, Bk, Bd, seed=17)
+    k = np.geomspace(1.0, weak, Bk).astype(np.float32)
+    sim.update(refl_k=np.stack([np.roll(k, i) for i in range(3)]), diff_coef=np.stack([np.roll(k, -i) for i in range(3)]),
+               passive_coef=k[::-1].copy(), lobe_beta=np.full((3, Bk), 1.5, np.float32), atm_a0=0.0, atm_a1=3.5e-5)
+    far = g.random(500) < 0.5
+    flags = et.ET_SPECULAR | et.ET_DIFFRACTION | et.ET_PASSIVE | (et.ET_SYNTH_DIRECT if direct else 0)
+    for pick in (far, ~far, np.ones(500, bool)):
+        rec = _records(g, 500, 3, len(sim["rx_pos"]))
+        rec["rtot"] = np.where(far, g.uniform(55, 60, 500), g.uniform(0.5, 4, 500))
+        # (one material: every record weak in the same band)
+        rec["mat"] = np.where(rec["kind"] == 2, rec["mat"], 0)
+        rec = {a: v[pick] for a, v in rec.items()}
+        ref = O.synth(rec, sim)
+        band = np.arange(F) * Bk // F
+        for what, H in _forms(et, ctx, sim, flags, et.Paths.from_records(rec)):
+            assert ctx.stats().synth_kernel == 2 and ctx.stats().synth_rows == (0 if direct else 1)
+            for b in range(Bk):
+                e = np.linalg.norm(H[:, band == b] - ref[:, band == b]) / np.linalg.norm(ref[:, band == b])
+                assert e <= 5e-6, f"band {b} of {Bk}, {what}: {e:.2e}"

@@ -41,3 +41,30 @@ def test_noalloc_synthesis_matches_workspace_call(et):
     # the scratch keeps the last call's contents: a repeated call still starts from zero
     H = et.synthesize_noalloc(ctx, s1, P1, outs[0]).cpu().numpy()
     check_spectra(H, et.synthesize(ctx, s1, P1).cpu().numpy(), "room again after smaller calls")
+
+
+def test_noalloc_per_term_where_the_rows_do_not_fit(et):
+    """Receivers and bins whose partial spectra fill the scratch but for 8 KB, bands off the 64-bin blocks: the row table does
+    not fit beside them, so the call runs per term; the workspace call, over rows.  Sampled bins against the
+    oracle: 4e-6 over rows; per term the phase's step per bin is rounded to 2^-33 cycles, 1e-4 of a turn's radius at
+    the last of 131,056 bins."""
+    import torch
+
+    import oracle as O
+    M, F, Bk = 64, 131056, 7
+    g = W.rng(3)
+    scene, sim = W.tiny_scene(n_rays=256)
+    sim = dict(sim, F=F, rx_pos=g.normal(0, 0.05, (M, 3)), rx_rot=np.repeat(np.eye(3)[None], M, 0),
+               refl_k=g.uniform(0.3, 0.99, (1, Bk)).astype(np.float32), lobe_beta=np.full((1, Bk), 1.0, np.float32),
+               diff_coef=np.full((1, Bk), 0.1, np.float32))
+    ref = O.trace(scene, sim, certify=False)
+    ref = {k: (v[:40] if isinstance(v, np.ndarray) and len(v) == len(ref["rtot"]) else v) for k, v in ref.items()}
+    ctx, s, P = et.Context(0), et.Sim(sim, flags=et.ET_SPECULAR), et.Paths.from_records(ref)
+    H = et.synthesize(ctx, s, P)
+    assert ctx.stats().synth_kernel == 2 and ctx.stats().synth_rows == 1
+    N = et.synthesize_noalloc(ctx, s, P, torch.empty(M, F, 2, device="cuda"))
+    assert ctx.stats().synth_kernel == 2 and ctx.stats().synth_rows == 0
+    bins = np.sort(g.choice(F, 300, replace=False))
+    want = O.synth(ref, sim, bins=bins)
+    check_spectra(H.cpu().numpy()[:, bins], want, "over rows, sampled bins", tol=4e-6)
+    check_spectra(N.cpu().numpy()[:, bins], want, "per term, sampled bins", tol=1e-4)

@@ -551,19 +551,6 @@ struct PairLean {
 // Element e of the visible-record list (without a list: every record, hidden ones skipped at set-up).
 __device__ inline int64_t record_at(const int32_t* __restrict__ idx, int64_t e) { return idx ? (int64_t)idx[e] : e; }
 
-// Length l = sqrt(w2) and its reciprocal from the hardware reciprocal square root and two Newton steps in
-// FP64, l then corrected once (within an ulp of the rounded square root; l = 0 for w2 = 0).
-__device__ inline void length_rcp(double w2, double& l, double& il) {
-  double y = __builtin_amdgcn_rsq(w2);
-  const double h = 0.5 * w2;
-  y = fma(y, fma(-h * y, y, 0.5), y);
-  y = fma(y, fma(-h * y, y, 0.5), y);
-  double s = w2 * y;
-  s = fma(0.5 * y, fma(-s, s, w2), s);
-  l = w2 > 0.0 ? s : 0.0;
-  il = y;
-}
-
 // Set-up of record n for receiver m (forward): every field of the record is read at once, whether it counts
 // or not, so that a group waits for memory once and not for the index, the flags and the fields in
 // turn.  What a record that does not count holds is never used: its point and direction may be anything (its
@@ -582,14 +569,13 @@ __device__ __forceinline__ void pair_fwd(const SynthArgs& a, const et_paths& P, 
   q.kind = (fl >> 1) & 3;
   ok = ok && !(q.kind == 2 && mat != m);            // a passive record reaches its own receiver only
   const double wx = a.rx_pos[3 * m] - px, wy = a.rx_pos[3 * m + 1] - py, wz = a.rx_pos[3 * m + 2] - pz;
-  double l, il;
-  length_rcp(wx * wx + wy * wy + wz * wz, l, il);
+  const double l = sqrt(wx * wx + wy * wy + wz * wz), il = 1.0 / l;
   const double r = rtot + l;                        // emitter -> point -> receiver
   const double cb = r * a.kcb;
   q.a32 = ok ? q32(r * a.kc0) : 0u;
   q.bx32 = ok ? q32((double)K2 * cb) : 0u;
   q.by32 = ok ? q32(cb) : 0u;
-  const float base = -(float)a.ps * __builtin_amdgcn_logf((float)r) + (float)(r * a.kbase);
+  const float base = -(float)a.ps * log2f((float)r) + (float)(r * a.kbase);
   q.slope = ok ? (float)(r * a.kslope) : 0.f;
   // rows of the band tables: the material's (with per-record tables the record's), one row for passive
   // records; the lobe is the specular records' (per-record tables hold 0 for the others)
@@ -650,14 +636,13 @@ __device__ inline void pair_adj(const SynthArgs& a, const et_paths& P, const int
   q.kind = kind;
   const double wx = a.rx_pos[3 * m] - P.p[3 * n], wy = a.rx_pos[3 * m + 1] - P.p[3 * n + 1],
                wz = a.rx_pos[3 * m + 2] - P.p[3 * n + 2];
-  double l, il;
-  length_rcp(wx * wx + wy * wy + wz * wz, l, il);
+  const double l = sqrt(wx * wx + wy * wy + wz * wz), il = 1.0 / l;
   const double r = P.rtot[n] + l;                          // emitter -> point -> receiver
   const double cb = r * a.kcb;
   q.a32 = q32(r * a.kc0);
   q.bx32 = q32((double)K2 * cb);
   q.by32 = q32(cb);
-  q.base = -(float)a.ps * __builtin_amdgcn_logf((float)r) + (float)(r * a.kbase);
+  q.base = -(float)a.ps * log2f((float)r) + (float)(r * a.kbase);
   q.slope = (float)(r * a.kslope);
   q.mat = P.mat[n];
   const float ux = (float)(wx * il), uy = (float)(wy * il), uz = (float)(wz * il);
@@ -967,8 +952,8 @@ __device__ __forceinline__ void gen_factors_u(const SynthArgs& a, const PairLean
     if (dir) {
 #pragma unroll
       for (int jj = 0; jj < NG; ++jj) {
-        ll[jj] += __builtin_amdgcn_logf(dir_lerp(dtab + ((kb[jj] >> 8) & 255) * dcells, q.cell));
-        if (FOLD == 4) lh[jj] += __builtin_amdgcn_logf(dir_lerp(dtab + (kb[jj] >> 24) * dcells, q.cell));
+        ll[jj] += log2f(dir_lerp(dtab + ((kb[jj] >> 8) & 255) * dcells, q.cell));
+        if (FOLD == 4) lh[jj] += log2f(dir_lerp(dtab + (kb[jj] >> 24) * dcells, q.cell));
       }
     }
   }
@@ -1014,7 +999,7 @@ __device__ __forceinline__ void gen_factors_u(const SynthArgs& a, const PairLean
     for (int sg = h; sg < nseg; sg += NH) {
       const int kb = key[sg];
       float lb = q.t1[kb & 0xffff] - g2 * q.t2[kb & 0xffff];
-      if (dir) lb += __builtin_amdgcn_logf(dir_lerp(dtab + (kb >> 16) * dcells, q.cell));
+      if (dir) lb += log2f(dir_lerp(dtab + (kb >> 16) * dcells, q.cell));
       W.bf[sg][r] = ok ? __builtin_amdgcn_exp2f(lb - q.lbm) : 0.f;   // <= 1
     }
   }

@@ -157,3 +157,16 @@ def test_weak_bands_keep_their_precision(et, ctx, F, Bk, Bd, direct, weak):
             for b in range(Bk):
                 e = np.linalg.norm(H[:, band == b] - ref[:, band == b]) / np.linalg.norm(ref[:, band == b])
                 assert e <= 5e-6, f"band {b} of {Bk}, {what}: {e:.2e}"
+
+
+@pytest.mark.parametrize("layout", [l for l in LAYOUTS if l[2]] + [(4096, 64, 3)])
+def test_gains_below_the_normal_range(et, ctx, layout):
+    """Directivity gains around 1e-40 (FP32 keeps 16 bits of them, 2e-5) beside coefficients of 1e30 are gains, not nothing."""
+    sim, g = _sim(*layout)
+    sim["directivity"] = (sim["directivity"] * np.float32(1e-20) * np.float32(1e-20)).astype(np.float32)
+    assert np.all(sim["directivity"] < 1.2e-38) and np.any(sim["directivity"] > 1e-41)
+    sim.update(refl_k=sim["refl_k"] * np.float32(1e30), diff_coef=sim["diff_coef"] * np.float32(1e30))
+    rec = _records(g, 300, 3, len(sim["rx_pos"]), kinds=(0, 1))
+    ref = O.synth(rec, sim)
+    for what, H in _forms(et, ctx, sim, et.ET_SPECULAR | et.ET_DIFFRACTION, et.Paths.from_records(rec)):
+        check_spectra(H, ref, f"{layout}, gains of 1e-40, {what}", tol=1e-4)

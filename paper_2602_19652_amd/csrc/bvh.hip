@@ -634,8 +634,10 @@ __global__ __launch_bounds__(BS) void k_vertex_curv(const float* __restrict__ V,
           term[wv][3][first + k] = c.m[k];
         }
       const int count = __popcll(n1) + __popcll(n2) + __popcll(n3);
+      wave_order();
 #pragma unroll 8
       for (int i = 0; i < count; ++i) sum += term[wv][lane & 3][i];
+      wave_order();
     }
     const double sx = __shfl(sum, 0), sy = __shfl(sum, 1), sz = __shfl(sum, 2), sm = __shfl(sum, 3);
     if (lane >> 3 == src >> 3) { Kx = sx; Ky = sy; Kz = sz; Am = sm; }

@@ -42,6 +42,13 @@ enum : uint32_t {
   DEV_ERR_VERTEX = 1u << 5,     // non-finite coordinate of a vertex that a triangle uses
 };
 
+// Between one lane's write to LDS and another lane's use of it (or a rewrite of what another lane read) within a wave: the
+// hardware keeps a wave's LDS operations in order, and this keeps the compiler from moving them across.
+__device__ inline void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ------------------------------------------------------------------ BVH layout
 
 // Node of the binary BVH (64 bytes): the two child boxes stored side by side.

@@ -204,6 +204,7 @@ __device__ inline void walk_rays(const SceneDev& S, const Ray32& r, bool walked,
         if (q == 0) res[cur] = make_int2(best, __float_as_int(bt));
         cur = -1;
       }
+      wave_order();   // (lane `cur` reads the result)
       if (taken >= nr) break;
       // and take the next rays
       const int nx = taken + (int)(__builtin_amdgcn_mbcnt_hi((uint32_t)(idle >> 32),
@@ -261,6 +262,7 @@ __device__ inline void walk_rays(const SceneDev& S, const Ray32& r, bool walked,
           if (i <= st.cap) col[i * QW] = child;
           else ++st.overflow;
         }
+        wave_order();   // (the quad's other lanes read the entry)
         const int first = quad_or((h && rank == 0) ? child : 0);
         node = c ? first : top;
         sp = min(sp + c - 1, st.cap);
@@ -293,6 +295,7 @@ __device__ inline void walk_rays(const SceneDev& S, const Ray32& r, bool walked,
     }
   }
   const int2 v = lane < nr ? res[lane] : make_int2(-1, 0);
+  wave_order();   // (the next call's rays leave theirs there)
   pos = v.x;
   t = __int_as_float(v.y);
 }

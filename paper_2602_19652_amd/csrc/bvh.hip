@@ -595,8 +595,8 @@ __device__ inline Corners corners(const float* __restrict__ V, const int32_t* __
 // centres with 120: 102 us with a lane per vertex, 52 us with eight for all, 26 us so).
 __global__ __launch_bounds__(BS) void k_vertex_curv(const float* __restrict__ V, const int32_t* __restrict__ tris,
                               const uint64_t* __restrict__ offs, const uint64_t* __restrict__ cnt,
-                              const int32_t* __restrict__ adj, int64_t nV, double* __restrict__ G) {
-  const int64_t v = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3;
+                              const int32_t* __restrict__ adj, int64_t v0, int64_t nV, double* __restrict__ G) {
+  const int64_t v = v0 + (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3);
   __shared__ double term[BS / 64][4][3 * 64];
   const int lane = threadIdx.x & 63, sub = threadIdx.x & 7, wv = threadIdx.x >> 6;
   double Kx = 0.0, Ky = 0.0, Kz = 0.0, Am = 0.0;
@@ -645,6 +645,14 @@ __global__ __launch_bounds__(BS) void k_vertex_curv(const float* __restrict__ V,
   if (v >= nV || sub != 0) return;
   double kn = sqrt(Kx * Kx + Ky * Ky + Kz * Kz);
   G[v] = Am > 0.0 ? kn / (4.0 * Am) : 0.0;   // G = |K| / 2 with K = sum / (2 A_mixed)
+}
+
+// In launches of 2^28 vertices (a launch holds fewer than 2^32 threads).
+void vertex_curv(const float* V, const int32_t* tris, const uint64_t* offs, const uint64_t* cnt, const int32_t* adj,
+                 int64_t nV, double* G, hipStream_t s) {
+  constexpr int64_t PER = (int64_t)1 << 28;
+  for (int64_t v0 = 0; v0 < nV; v0 += PER)
+    k_vertex_curv<<<(unsigned)((8 * std::min(nV - v0, PER) + BS - 1) / BS), BS, 0, s>>>(V, tris, offs, cnt, adj, v0, nV, G);
 }
 
 __global__ void k_tri_curv(const float* __restrict__ V, const int32_t* __restrict__ tris, int64_t T,
@@ -1025,14 +1033,14 @@ void scene_build(et_scene* sc, const et_mesh_desc* mesh, void* blob, void* scrat
   k_fill_u32<<<1, BS, 0, s>>>((uint32_t*)sc->rscratch, REFIT_SCRATCH / 4, 0u);
   // curvature (Eq. 1)
   if (T > 0 && V > 0) {
-    k_fill_u32<<<nblk(2 * V), BS, 0, s>>>((uint32_t*)vcnt, 2 * V, 0u);
+    k_fill_u32<<<std::min(nblk(2 * V), 1u << 20), BS, 0, s>>>((uint32_t*)vcnt, 2 * V, 0u);
     k_vcount<<<nblk(T), BS, 0, s>>>(d.tris, T, vcnt);
     scan_exclusive_u64(vcnt, voff, V, nullptr, V, nullptr, scan_tmp, s);
     k_vkeys<<<nblk(3 * T), BS, 0, s>>>(d.tris, 3 * T, vkey, adj);
     int vbits = 1;
     while (vbits < 32 && ((int64_t)1 << vbits) < V) ++vbits;
     radix_sort_u32(vkey, adj, 3 * T, vbits, vsort_tmp, s);
-    k_vertex_curv<<<nblk(8 * V), BS, 0, s>>>(d.verts, d.tris, voff, vcnt, adj, V, d.G);
+    vertex_curv(d.verts, d.tris, voff, vcnt, adj, V, d.G, s);
     k_tri_curv<<<nblk(T), BS, 0, s>>>(d.verts, d.tris, T, d.G, mesh->area_ref, d.C);
     ET_HIP(hipGetLastError());
   }
@@ -1102,7 +1110,7 @@ void scene_refit(et_scene* sc, const float* vertices, double area_ref, uint32_t*
     k_refit_sah<<<std::min(nblk(4 * (T - 1)), (unsigned)SUM_BLOCKS * 2), BS, 0, s>>>(d.nodes, T - 1, d.root, d.wide, sah);
   }
   if (T > 0 && V > 0) {   // the vertex-triangle lists depend on the topology only
-    k_vertex_curv<<<nblk(8 * V), BS, 0, s>>>(d.verts, d.tris, sc->voff, sc->vcnt, sc->adj, V, d.G);
+    vertex_curv(d.verts, d.tris, sc->voff, sc->vcnt, sc->adj, V, d.G, s);
     k_tri_curv<<<nblk(T), BS, 0, s>>>(d.verts, d.tris, T, d.G, area_ref, d.C);
   }
   ET_HIP(hipGetLastError());

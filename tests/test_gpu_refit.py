@@ -119,3 +119,26 @@ def test_refit_rejects_bad_arguments(et, ctx, frames):
     assert et.lib().et_scene_refit(ctx.h, sc.h, None, 0.0) == -1          # no vertices
     assert et.lib().et_scene_refit(ctx.h, None, v, 0.0) == -1             # no scene
     assert et.lib().et_scene_refit(ctx.h, sc.h, v, float("nan")) == -1    # area_ref not finite
+
+
+def test_half_a_billion_vertices(et):
+    """2^29 + 40 vertices, nearly all of them in no triangle (a launch with eight threads per vertex would take more than
+    2^32 of them): the curvature of a fan over the last ones, built and refitted, is the small mesh's."""
+    import torch
+    ctx = et.Context(0)
+    V, rim = (1 << 29) + 40, 39
+    ang = np.linspace(0, 2 * np.pi, rim, endpoint=False)
+    fan = np.concatenate([[[3.0, 0.0, 0.3]], np.stack([3.0 + 0.05 * np.sin(3 * ang), np.cos(ang), np.sin(ang)], 1)]).astype(np.float32)
+    t = np.array([[0, 1 + i, 1 + (i + 1) % rim] for i in range(rim)], np.int32)
+    rest = {"tri_material": np.zeros(rim, np.int32), "tri_object": np.zeros(rim, np.int32), "n_objects": 1}
+    small = et.Scene(ctx, {"vertices": fan, "tris": t, **rest}, area_ref=0.01)
+    v = torch.zeros(V, 3, device="cuda")
+    v[-40:] = torch.as_tensor(fan, device="cuda")
+    large = et.Scene(ctx, {"vertices": v, "tris": t + np.int32(V - 40), **rest}, area_ref=0.01)
+    for scale in (1.0, 1.25):
+        if scale != 1.0:
+            small.refit(fan * np.float32(scale), area_ref=0.01)
+            large.refit(v * scale, area_ref=0.01)
+        (C, G), (C1, G1) = small.curvature(), large.curvature()
+        assert torch.equal(C, C1) and torch.equal(G, G1[-40:]) and float(G.min()) > 0
+        assert int(torch.count_nonzero(G1)) == 40

@@ -420,6 +420,12 @@ int convolve_lg(int64_t L) {
 
 inline size_t al(size_t b) { return (b + 255) / 256 * 256; }
 
+// An output that shares memory with an input: a workgroup would write what others have yet to read, so such calls take
+// the stages, which copy their inputs to the workspace first (sized for them whichever way a call goes).
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 }  // namespace
 
 int64_t conv_length(int64_t n_t, int64_t L) {
@@ -429,12 +435,10 @@ int64_t conv_length(int64_t n_t, int64_t L) {
 }
 
 size_t impulse_ws_bytes(int64_t M, int64_t n_t) {
-  if (impulse_lg(n_t) >= 0) return al(1);
   return 2 * al(sizeof(float2) * (size_t)M * n_t) + al(sizeof(float2) * (size_t)n_t);
 }
 
 size_t signal_ws_bytes(int64_t M, int64_t n_t, int64_t L) {
-  if (convolve_lg(L) >= 0) return al(1);
   const int64_t P = conv_length(n_t, L);
   return 2 * al(sizeof(float2) * (size_t)(M + 1) * P) + al(sizeof(float2) * (size_t)P);
 }
@@ -443,7 +447,7 @@ void impulse_run(int64_t M, int64_t F, double f_lo, double df, int sigma, const 
                  float* h, hipStream_t s) {
   const double f_lo_dt = f_lo * (1.0 / ((double)n_t * df)), scale = 2.0 * df;
   const int lg = impulse_lg(n_t);
-  if (lg >= 0) {
+  if (lg >= 0 && !overlap(spectra, sizeof(float) * 2 * (size_t)M * F, h, sizeof(float) * (size_t)M * n_t)) {
     const int D = (int)(n_t >> lg);
     for (int64_t m0 = 0; m0 < M; m0 += 65535) {   // (the grid's second dimension)
       const dim3 grid((unsigned)D, (unsigned)std::min<int64_t>(M - m0, 65535));
@@ -473,7 +477,9 @@ void impulse_run(int64_t M, int64_t F, double f_lo, double df, int sigma, const 
 void signal_run(int64_t M, int64_t n_t, const float* h, int64_t L, const float* se, double dt, void* ws, float* out,
                 hipStream_t s) {
   const int lg = convolve_lg(L);
-  if (lg >= 0) {
+  const size_t out_bytes = sizeof(float) * (size_t)M * (n_t + L - 1);
+  if (lg >= 0 && !overlap(h, sizeof(float) * (size_t)M * n_t, out, out_bytes) &&
+      !overlap(se, sizeof(float) * (size_t)L, out, out_bytes)) {
     const int64_t V = (int64_t(1) << lg) - L + 1, n_out = n_t + L - 1;
     for (int64_t m0 = 0; m0 < M; m0 += 65535) {
       const dim3 grid((unsigned)((n_out + V - 1) / V), (unsigned)std::min<int64_t>(M - m0, 65535));

@@ -242,3 +242,27 @@ def test_any_band_layout_matches_the_per_term_kernel(et, ctx, seed):
     k = ctx.stats().synth_kernel
     D = et.synthesize(ctx, et.Sim(sim, flags=flags | et.ET_SYNTH_DIRECT), P).cpu().numpy()
     check_spectra(H, D, f"F={F}, {Bk} bands, {M} receivers, flags {flags}: kernel {k}", tol=1e-5)
+
+
+@pytest.mark.parametrize("F,jobs,kernel,rows", [(256, "hh", 1, 0), (256, "hr", 2, 1), (256, "rh", 2, 1), (250, "hh", 2, 1), (250, "hrr", 2, 1),
+                                                (256, "ht", 2, 0), (250, "rt", 2, 0), (2100, "rrr", 2, 1)])
+def test_batch_takes_one_kernel_for_its_jobs(et, ctx, F, jobs, kernel, rows):
+    """Jobs whose own layouts call for halves (bands on whole runs of 64 bins), rows (a directivity of three bands) and single
+    terms (asked for): the batch runs them all by the most general one, each job as it comes out alone.
+    The kernel in halves is within 2e-6 of the sum on such spectra, those in FP32 within 1e-6; 4e-6 between two."""
+    g = W.rng(F)
+    scenes = [et.Scene(ctx, _soup(120, 60 + i)) for i in range(2)]
+    sims = []
+    for i, k in enumerate(jobs):
+        _, sim = W.tiny_scene(seed=70 + i, n_rays=900 + 100 * i, F=F)
+        sim = dict(sim, refl_k=g.uniform(0.3, 0.99, (1, 4)).astype(np.float32), lobe_beta=np.full((1, 4), 1.0, np.float32),
+                   diff_coef=np.full((1, 4), 0.1, np.float32))
+        if k == "r":
+            sim["directivity"] = W.directivity_table(g, len(sim["rx_pos"]), Bd=3, El=8, Az=16)
+        sims.append(et.Sim(sim, flags=et.ET_SPECULAR | (et.ET_SYNTH_DIRECT if k == "t" else 0)))
+    b = et.Batch(ctx, [(scenes[i % 2], s) for i, s in enumerate(sims)])
+    H = b.run().cpu().numpy()
+    st = ctx.stats()
+    assert (st.synth_kernel, st.synth_rows) == (kernel, rows)
+    for i, s in enumerate(sims):
+        check_spectra(H[i], et.simulate(ctx, scenes[i % 2], s).cpu().numpy(), f"{F} bins, job {i} of {jobs}", tol=4e-6)

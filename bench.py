@@ -428,24 +428,24 @@ def adj_kernel_name(s) -> str:
 
 
 def trace_roofline(cnt, ms_trace: float, traffic_key: str = "k_walk<256, false, false, false>") -> dict:
-    """The traversal against HBM bandwidth: the node, triangle and ray bytes its visits touch
-    (counting pass) over the trace time of the step.  Caches serve most of them, so they can
-    exceed what HBM delivers; the measured HBM bytes of the walk kernel are `traffic`.  The
-    arithmetic of the same visits against the vector-ALU lane rate is reported beside it."""
+    """The traversal against the vector ALUs' lane rate, which bounds it (vector instructions issue all the time, with
+    half of the lanes active): the operations of its node visits, triangle tests and rays (counting
+    pass) over the trace time of the step.  The bytes that the same visits touch are beside it; caches serve
+    most of them, so against HBM bandwidth they can exceed 1; the measured HBM bytes of the walk kernel are
+    `traffic`."""
     nodes, tris = cnt.nodes_closest + cnt.nodes_any, cnt.tris_closest + cnt.tris_any
     rays = cnt.rays_closest + cnt.rays_any
     trav_bytes = nodes * NODE_BYTES + tris * TRI_BYTES + rays * RAY_IO_BYTES
     gbs = trav_bytes / (ms_trace * 1e-3) / 1e9
     ops = nodes * NODE_OPS + tris * TRI_OPS + rays * RAY_OPS
     tops = ops / (ms_trace * 1e-3) / 1e12
-    return {"kernel": "k_walk<256, false, false, false>", "bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS,
-            "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS, "traffic": counter_for(traffic_key),
-            "algorithmic_bytes": trav_bytes,
-            "per_unit": f"{NODE_BYTES} B per node visit, {TRI_BYTES} B per triangle test, {RAY_IO_BYTES} B per ray "
+    return {"kernel": "k_walk<256, false, false, false>", "bound": "valu", "achieved": tops, "peak": PEAK_VALU_TOPS,
+            "unit": "Top/s", "frac": tops / PEAK_VALU_TOPS, "traffic": counter_for(traffic_key),
+            "algorithmic_ops": ops,
+            "per_unit": f"{NODE_OPS} ops per node visit, {TRI_OPS} per triangle test, {RAY_OPS} per ray "
                         f"(closest-hit and line-of-sight traversals)",
-            "alu": {"achieved": tops, "peak": PEAK_VALU_TOPS, "unit": "Top/s", "frac": tops / PEAK_VALU_TOPS,
-                    "algorithmic_ops": ops,
-                    "per_unit": f"{NODE_OPS} ops per node visit, {TRI_OPS} per triangle test, {RAY_OPS} per ray"}}
+            "touched": {"achieved": gbs, "hbm_peak": PEAK_HBM_GBS, "unit": "GB/s", "bytes": trav_bytes,
+                        "per_unit": f"{NODE_BYTES} B per node visit, {TRI_BYTES} B per triangle test, {RAY_IO_BYTES} B per ray"}}
 
 
 def configs_leg(ctx, et, W, reps):

@@ -369,7 +369,7 @@ int et_eq_directions(et_ctx* ctx, int64_t N, double cone_half_angle, void* ws, s
 
 /* ------------------------------------------------------------------ tuning of fused batches
  * Launch shapes kept per context: the workgroups that the record chunks of the synthesis and
- * adjoint kernels aim at, and the grid of the bounce kernels (grid-stride over the active
+ * adjoint kernels aim at, and the grid of the traversal kernels (grid-stride over the active
  * rays).  Workspaces from et_batch_workspace_size serve every allowed value. */
 typedef struct {
   int32_t synth_wgs;      /* 64 .. 16384 (default 4096) */
@@ -387,7 +387,7 @@ int et_set_tuning(et_ctx* ctx, const et_tuning* t);   /* ET_E_INVALID outside th
 
 /* Autotuner: runs the fused batch (as et_simulate_batch, with the adjoint when grad_spectra
  * is given) once per candidate shape (synthesis and adjoint workgroups 1024, 2048, 4096, 8192,
- * 16384; bounce grids 1024, 2048, 4096, 6144, 8192 blocks), times the trace phase, the synthesis
+ * 16384; traversal grids 1024, 2048, 4096, 6144, 8192 blocks), times the trace phase, the synthesis
  * kernel and the adjoint kernel with events, keeps for each knob its fastest candidate in
  * the context (its runs take the job waves in order on the context's stream, so that the
  * phases do not interact) and returns the choice with its times.  The outputs hold the

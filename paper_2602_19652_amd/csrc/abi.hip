@@ -137,8 +137,6 @@ int64_t diff_draws_max(const et_sim_desc* s) {
   return s->diff_K * ((s->flags & ET_DIFF_PER_MESH) ? s->diff_max_meshes : 1);
 }
 
-// Line-of-sight rays per specular record.
-
 int64_t records_upper_bound(const et_sim_desc* s) {
   int64_t n = 0;
   if (s->flags & ET_SPECULAR) n += s->N * (int64_t)s->max_bounces;
@@ -153,7 +151,7 @@ size_t paths_bytes(int64_t cap) {   // the arrays of carve_paths, each aligned t
   return al(cap * (24 + 12 + 8 + 4 + 4 + 4 + 1 + 1 + 8 + 8)) + al(8 * sizeof(int64_t)) + 10 * 256;
 }
 
-// A batch runs fused (all rays in shared bounce kernels, all records in shared synthesis
+// A batch runs fused (all rays in shared walks, all records in shared synthesis
 // kernels) when every job is specular-only; otherwise jobs run one after another.
 bool batch_fused(int32_t J, const et_job* jobs) {
   if (J > 65536) return false;   // the ray sort keys hold the job in 16 bits

@@ -715,7 +715,8 @@ __global__ void k_widen(const Node2* __restrict__ nodes, int64_t n_inner, float4
 
 __global__ void k_single_leaf(Node2* nodes, float4* wide) {
   Node2 n;
-  // child 0 is leaf 0 with an infinite box; child 1 is an empty box (never hit)
+  // both children are leaf 0: child 0 with an infinite box, child 1 with its planes swapped, which the slab test orders
+  // (every ray tests the one triangle twice)
   n.xy0 = make_float4(-INFINITY, INFINITY, -INFINITY, INFINITY);
   n.xy1 = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
   n.zz = make_float4(-INFINITY, INFINITY, INFINITY, -INFINITY);

@@ -73,8 +73,8 @@ struct __align__(16) NodeB {
 // bits (>= 0 node, < 0 leaf ~position, INT32_MIN none).
 constexpr int TRAV_WAVES_PER_SIMD = 6;
 constexpr int TRAV_STACK = 64;         // deepest binary tree that is traversed
-// entries of a ray's stack: a four-wide step leaves three behind for two binary levels (25 KB of LDS per
-// 256-thread block, so six blocks, six waves per SIMD, fit the compute unit's 160 KB)
+// entries of a ray's stack: a four-wide step leaves three behind for two binary levels (with the rays' results 26.9 KB of
+// LDS per 256-thread block, so six blocks, six waves per SIMD, fit the compute unit's 160 KB)
 constexpr int QUAD_STACK = TRAV_STACK / 2 * 3;
 constexpr int TRAV_BLOCK = 256;
 constexpr int PLOC_RADIUS = 16;
@@ -206,7 +206,7 @@ struct TraceWS {
 
 // Workspace layout of et_trace.  base == nullptr: only computes the size.
 size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* base, TraceWS* ws);
-// Fused batch (specular jobs): all jobs' rays share the bounce kernels; records carry the
+// Fused batch (specular jobs): all jobs' rays share the walks; records carry the
 // job index in their ray field.  dev_jobs holds trace_batch_jobs_bytes(J) bytes.
 size_t trace_batch_jobs_bytes(int32_t J);
 int64_t trace_batch_rays(int32_t J, const et_job* jobs);
@@ -244,7 +244,7 @@ struct SynthWS {
   float* plc;                // [cap][Bk] path-product reading: each record's lobe coefficient
 };
 size_t synth_ws_layout(const et_sim_desc* sim, int64_t cap, char* base, SynthWS* ws);
-// returns 1 for the factorised MFMA kernel, 2 for the direct kernel
+// returns the forward kernel (FwdKernel)
 // kb/ke (optional) are recorded around the main synthesis kernel alone
 int synth_run(const et_sim_desc* sim, const et_paths* paths, const SynthWS& ws, Ctl* ctl, float* spectra,
               hipStream_t s, hipEvent_t kb = nullptr, hipEvent_t ke = nullptr);
@@ -299,7 +299,7 @@ void signal_run(int64_t M, int64_t n_t, const float* h, int64_t L, const float* 
 struct BatchTune {
   int32_t synth_wgs = 4096;       // (the autotuner's choice for the 320-job batch of 2048-bin jobs)
   int32_t adjoint_wgs = 4096;
-  int32_t trace_blocks = 4096;    // grid of the bounce kernels (grid-stride over the active rays)
+  int32_t trace_blocks = 4096;    // grid of the walks (grid-stride over the active rays)
   int64_t wave_rays = 1ll << 23;  // rays of a job wave: jobs run in waves whose rays add up to this
 };
 constexpr int64_t MIN_WAVE_RAYS = 1024;
@@ -331,10 +331,9 @@ struct SynthBatchWS {
   int rows;                     // the most rows of a job's spectrum (factorised kernels)
   void* row_tables;             // [J][rows + 1] row tables
 };
-bool synth_batch_factorised(int32_t J, const et_job* jobs, bool adjoint);
 size_t synth_batch_ws_layout(int32_t J, const et_job* jobs, int64_t cap, const BatchTune& tune, bool adjoint,
                              char* base, SynthBatchWS* ws);
-// returns the forward kernel (1 MFMA, 2 direct); *adjoint_kernel likewise when grad != nullptr
+// returns the forward kernel (FwdKernel); *adjoint_kernel as synth_bwd_run when grad != nullptr
 // ev (optional): 4 events recorded around the synthesis kernel and the adjoint kernel
 int synth_batch_run(int32_t J, const et_job* jobs, const et_paths* paths, const SynthBatchWS& w, Ctl* ctl,
                     float* spectra, const float* grad, double* grad_k, double* grad_rx, int* adjoint_kernel,

@@ -17,22 +17,19 @@
 // accumulation are FP32 (v_sin/v_cos take revolutions, so the FP64 reduction hands them
 // a fraction of a cycle).
 //
-// Two kernels compute the same sum:
-//  * factorised (MFMA): with k = 64 k1 + k2, amplitude and phase separate as
-//      A e^{j phi} = X[n,k1] * Y[n,k2],
-//      X = exp2(base + 64 k1 slope + band(k1)) e^{j 2 pi (c0 + 64 k1 cb)},
-//      Y = exp2(k2 slope) e^{j 2 pi k2 cb},
-//    whenever the material/directivity bands are constant over each run of 64 bins, so
-//    H_m[k1, k2] = sum_n X[n,k1] Y[n,k2] is a complex matrix product contracting over the
-//    records.  It runs on the f16 matrix cores (v_mfma_f32_16x16x32_f16) with every FP32
-//    operand split into two f16 halves and three half products per real product (FP32
-//    accumulation); X and Y themselves come from 32 exp2/sin/cos factors per (record,
-//    receiver) (a second 8 x 8 split) plus the band factors (one exp2 per band segment, or
-//    folded into the first factor when the band edges fall on groups of 8 outer indices),
-//    so only about 40 transcendental triples remain of the 4096 per (record, receiver) of a
-//    4096-bin grid.
-//  * direct: one sin/cos/exp2 per (record, receiver, bin), any band layout.
-// Both write per-chunk partial spectra that a final kernel sums in a fixed order
+// Three kernels compute the same sum.  With k = 64 k1 + k2, amplitude and phase separate as
+//   A e^{j phi} = X[n,k1] * Y[n,k2],
+//   X = exp2(base + 64 k1 slope + band(k1)) e^{j 2 pi (c0 + 64 k1 cb)},
+//   Y = exp2(k2 slope) e^{j 2 pi k2 cb},
+// where the material/directivity bands are constant over a run of 64 bins, so
+// H_m[k1, k2] = sum_n X[n,k1] Y[n,k2] is a complex matrix product contracting over the records.  X and Y themselves
+// come from 32 exp2/sin/cos factors per (record, receiver) (a second 8 x 8 split) plus the band factors, so only
+// about 40 transcendental triples remain of the 4096 per (record, receiver) of a 4096-bin grid.
+//  * k_synth_mfma (bands on whole runs of 64 bins): on the f16 matrix cores (v_mfma_f32_32x32x16_f16), every FP32
+//    operand split into two f16 halves and three half products per real product, FP32 accumulation.
+//  * k_synth_rows (other layouts): rows cut at the band edges, on the FP32 matrix cores (v_mfma_f32_32x32x2_f32).
+//  * k_synth_direct (many bands in few bins, or asked for): one sin/cos/exp2 per (record, receiver, bin).
+// Each writes per-chunk partial spectra that a final kernel sums in a fixed order
 // (bit-reproducible results).
 #include "internal.hpp"
 
@@ -764,18 +761,17 @@ __device__ inline float2 cexp2(float lg, float rev) {
 }
 __device__ inline float2 cmul(float2 a, float2 b) { return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
 
-// One wave computes the generating factors of RPW records (sub-stage t of its 64 set-up
+// (Adjoint.)  One wave computes the generating factors of RPW records (sub-stage t of its 64 set-up
 // records): Xa, Xb, Ya, Yb (8 each) and the band factor of every (record, band segment) of the
 // tile, into its WaveScratch.  esh (log2) scales every X of the sub-stage.
-// KFREE: the specular band factor leaves out k (see band_log2_v).
+// The specular band factor leaves out k (see band_log2_v).
 // FOLD 4: every band segment is a union of whole half groups of 4 rows (segl, segh: the segments
 // of rows 8 j and 8 j + 4 of this lane's group j): the band factor is folded into Xa, one copy
 // per half group (Xa for rows 8 j .. 8 j + 3, Xh for 8 j + 4 .. 8 j + 7), and no table is written.
 // FOLD 8: whole groups of 8 rows, one copy (Xa).
-template <bool KFREE = false, int FOLD = 0>
-__device__ inline void gen_factors(const SynthArgs& a, const PairLean& q, int t, int m, int k1_0, int nk1, int lane,
-                                   int nseg, const SegTable& st, float esh, WaveScratch& W, int segl = 0,
-                                   int segh = 0) {
+template <int FOLD>
+__device__ inline void gen_factors(const SynthArgs& a, const PairLean& q, int t, int k1_0, int nk1, int lane, int nseg,
+                                   const SegTable& st, float esh, WaveScratch& W, int segl, int segh) {
   const int r = lane >> 3, j = lane & 7;
   const int src = t * RPW + r;                 // lane that set up record r of this sub-stage
   const float base_r = __shfl(q.base, src), slope_r = __shfl(q.slope, src);
@@ -792,8 +788,8 @@ __device__ inline void gen_factors(const SynthArgs& a, const PairLean& q, int t,
     // the band factors of the two half groups (no record's bound needed: each is its own)
     const float g_r = __shfl(q.gamma, src);
     const int m_r = __shfl(q.mat, src), k_r = __shfl(q.kind, src);
-    float ll = band_log2_v<KFREE>(a, k_r, m_r, g_r, st.sb[segl]);
-    float lh = FOLD == 4 ? band_log2_v<KFREE>(a, k_r, m_r, g_r, st.sb[segh]) : 0.f;
+    float ll = band_log2_v<true>(a, k_r, m_r, g_r, st.sb[segl]);
+    float lh = FOLD == 4 ? band_log2_v<true>(a, k_r, m_r, g_r, st.sb[segh]) : 0.f;
     const float rev = (float)(int32_t)(a_r + k1a * bx_r) * S;
     const float c = __builtin_amdgcn_cosf(rev), sn = __builtin_amdgcn_sinf(rev);
     const float al = ok && 8 * j < nk1 ? __builtin_amdgcn_exp2f(lg0 + ll) : 0.f;
@@ -811,11 +807,9 @@ __device__ inline void gen_factors(const SynthArgs& a, const PairLean& q, int t,
   W.ya[r][j] = cexp2((float)(8 * j) * slope_r, (float)(int32_t)((uint32_t)(8 * j) * by_r) * S);
   W.yb[r][j] = cexp2((float)j * slope_r, (float)(int32_t)((uint32_t)j * by_r) * S);
   // band factors of every (record, segment), and zero for the segment past the tile
-  if (FOLD) {
-    // (folded into Xa and Xh)
-  } else {
-    // the adjoint (no directivity): the pairs enumerated over the wave, each lane fetching its
-    // record's data (fewer registers live across the loop: measured faster in that kernel)
+  if (!FOLD) {
+    // the pairs enumerated over the wave, each lane fetching its record's data (fewer registers live across the
+    // loop: measured faster)
     for (int i0 = 0; i0 < RPW * nseg; i0 += 64) {
       const int i = i0 + lane;
       const int rr = min(i / nseg, RPW - 1), sg = i - (i / nseg) * nseg;
@@ -830,7 +824,6 @@ __device__ inline void gen_factors(const SynthArgs& a, const PairLean& q, int t,
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
-
 
 // Maximum over the wave's lanes, the same (scalar) value in every lane: lane moves within rows of 16,
 // then the four rows' values.
@@ -876,8 +869,6 @@ __device__ inline float dir_log2_max(const SynthArgs& a, int m, int tid, float* 
   __syncthreads();
   return log2f(v);
 }
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
@@ -2106,7 +2097,7 @@ __global__ __launch_bounds__(256, SPLIT && FOLD ? 3 : 2) void k_synth_bwd_mfma(S
   for (int64_t s = 0; s < nst; ++s) {
     const int t = (int)(s & 7);
     if (t == 0) pair_adj(a, P, idx, lo + (s >> 3) * (8 * RB) + wv * 64 + lane, hi, m, q);
-    gen_factors<true, FOLD>(a, q, t, m, k1_0, nk1, lane, nseg, st, 0.f, wscr[wv], segl, segh);
+    gen_factors<FOLD>(a, q, t, k1_0, nk1, lane, nseg, st, 0.f, wscr[wv], segl, segh);
     write_bwd(wscr[wv], lane, wv, bb);
     {
       // each generated record's row of k factors
@@ -2810,12 +2801,6 @@ int chunk_target(const et_sim_desc* s0, bool mf, int32_t wgs) {
 }
 }  // namespace
 
-bool synth_batch_factorised(int32_t J, const et_job* jobs, bool adjoint) {
-  for (int32_t i = 0; i < J; ++i)
-    if (!(adjoint ? synth_bwd_factorised_ok(jobs[i].sim) : synth_factorised_ok(jobs[i].sim))) return false;
-  return true;
-}
-
 size_t synth_batch_ws_layout(int32_t J, const et_job* jobs, int64_t cap, const BatchTune& tune, bool adjoint,
                              char* base, SynthBatchWS* ws) {
   const et_sim_desc* s0 = jobs[0].sim;
@@ -2833,7 +2818,8 @@ size_t synth_batch_ws_layout(int32_t J, const et_job* jobs, int64_t cap, const B
     if (w.fwd == FWD_TERM) break;
   }
   for (int32_t i = 0; i < J; ++i) w.rows = std::max(w.rows, synth_rows(jobs[i].sim, nullptr));
-  w.mf_bwd = adjoint && synth_batch_factorised(J, jobs, true);
+  w.mf_bwd = adjoint;
+  for (int32_t i = 0; i < J; ++i) w.mf_bwd = w.mf_bwd && synth_bwd_factorised_ok(jobs[i].sim);
   w.fold = 8;   // the coarsest folding every job allows
   for (int32_t i = 0; i < J; ++i) w.fold = std::min(w.fold, bands_fold(jobs[i].sim));
   const bool mf = w.fwd != FWD_TERM;

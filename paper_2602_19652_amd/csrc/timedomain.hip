@@ -12,7 +12,7 @@
 // one workgroup's registers (16 points a thread) and are exchanged through LDS between radix-16 passes.  An impulse
 // response of N = D N1 points is D such transforms, one per residue n mod D (decimation in
 // frequency), padding and carrier in the same kernel; the convolution is cut into blocks (overlap-save).
-// Longer rows and calls run radix-4
+// Longer rows and calls, and outputs that share memory with an input, run radix-4
 // Stockham stages over global memory (plus one radix-2 stage for an odd power of two), each a streaming pass, with
 // twiddles from a table, computed in FP64 and rounded to FP32; in a workgroup they stay in FP64, and a product is
 // rounded once.

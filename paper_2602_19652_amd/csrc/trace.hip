@@ -8,7 +8,7 @@
 //   k_mask_sums sums of the waves' hit and continue masks (large ray sets; small ones are summed in place)
 //   k_records   stable compaction: records in ray order after the earlier bounces' records, the list of the
 //               rays that go on in ray order
-// Ray order: a ray set larger than one round of the bounce grid (the threads the chip holds at
+// Ray order: a ray set larger than one round of the walks' grid (the threads the chip holds at
 // once) is first sorted (stably) by a 16-bit octahedral Morton key of its world direction, so
 // that the rays of a wave walk nearby parts of the BVH; the stable compaction keeps that order
 // through the bounces, and records carry their ray.  Whole pose in the room with 2^20 rays: 11.98 ms
@@ -28,8 +28,9 @@ namespace {
 
 constexpr int BS = TRAV_BLOCK;
 constexpr int EMPTY = INT32_MIN;
-// Grids of up to 8192 blocks: the room's 2^20 rays and their line-of-sight rays are a chunk of 64 per wave, so the
-// hardware dispatcher balances uneven chunks (1536 blocks, one round that strides: 3% slower poses, foliage 6%).
+// Grids of up to 8192 blocks (then whole rounds of resident ones, see trace_run): the room's 2^20 rays and their
+// line-of-sight rays are 32,768 chunks of 64, one or two to a wave, so the hardware dispatcher balances uneven chunks
+// (1536 blocks, one round that strides: 3% slower poses, foliage 6%).
 constexpr int MAX_BLOCKS = 8192;
 
 // Waves that a traversal of few rays is spread over, 16 rays to a wave at the least (see k_walk).
@@ -782,8 +783,6 @@ __global__ void k_obj_fov(SceneDev S, DiffArgs a, uint8_t* oel) {
   oel[o] = psi <= a.cone + asin(rad / dist);
 }
 
-// Largest C_i over the field-of-view objects: positive doubles order as their bit patterns, so
-// a wave takes the maximum of the bits by shuffles and issues one atomic.
 // Largest C_i over the triangles of eligible objects, as the bit pattern of a non-negative double
 // (ordered like the value): a grid-strided maximum per thread, then per wave and per block, and
 // one atomic per block (one per wave left the room's 193,212 triangles waiting on about 3000 atomics).
@@ -1081,7 +1080,7 @@ size_t trace_ws_layout(int64_t N, int64_t T, int32_t n_obj, int64_t K, char* bas
 }
 
 namespace {
-// Threads of the bounce kernel that the current device holds at once (blocks per compute unit
+// Threads of k_walk that the current device holds at once (blocks per compute unit
 // at its occupancy, times the compute units), queried once per device.
 int64_t bounce_resident_threads() {
   static std::atomic<int64_t> cache[64];
@@ -1172,7 +1171,7 @@ void trace_batch_run(int32_t J, const et_job* jobs, void* dev_jobs, const et_pat
   const et_paths P = *paths;
   k_trace_init<<<1, 1, 0, s>>>(ctl, N, carry ? 1 : 0, 0);
   ET_HIP(hipGetLastError());
-  // bounce grid: the tuned block count
+  // walks' grid: the tuned block count
   const int64_t cap_blocks = std::max<int64_t>(1, blocks);
   const unsigned gb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((N + BS - 1) / BS, cap_blocks));
   if (N > 0) {
@@ -1213,7 +1212,7 @@ void trace_run(const SceneDev& S, const et_sim_desc* sim, const et_paths* paths,
     // leave compute units idle in a small pose (some twenty launches of 2 to 10 us: 50,003 rays in the
     // room with samples on 61 meshes 500 us in order, 382 us beside; an animated frame 980 and 847 us).
     if (diff && side) ET_HIP(hipEventRecord(side->fork, s));
-    // bounce grid: whole rounds of resident blocks (no partly filled last round), the chunks taken by grid
+    // walks' grid: whole rounds of resident blocks (no partly filled last round), the chunks taken by grid
     // stride (2^20 rays, room and foliage pose: 12.10 and 8.30 ms; a block per four chunks 12.20 and 8.48; one round
     // 12.48 and 8.81)
     const double* rx = perrx ? sim->rx_pos : nullptr;

@@ -1376,10 +1376,11 @@ __device__ inline float2 row_factor(float k, float hi, float lo, uint32_t ph) {
 // Workgroup and waves as in k_synth_mfma.  A wave sets up 64 records and, 32 at a time, writes their factors to its own
 // LDS; lane l forms X of row l % 32 (+ 32) and Y of bin l % 32 (+ 32) for records 4 j + 2 (l / 32) and the next, two
 // steps of v_mfma_f32_32x32x2_f32 (a record per half wave).
-// Bound by the FP32 matrix pipe where records are many (250,000 x 32 receivers x 2000 bins: 1.74 ms, 105 TFLOP/s
+// Bound by the FP32 matrix pipe where records are many (250,000 x 32 receivers x 2000 bins: 1.75 ms, 105 TFLOP/s
 // executed, two thirds of the peak; per term 6.7 ms), and by the set-up and the factors of part-filled groups where a wave
-// has few (60,000 x 6 receivers x 3000 bins in 7 bands: 129 us, per term 540).  Error against 64 bits over random grids of
-// 200 to 4160 bins 1.7e-7 to 4.5e-7 of the norm, per term 2.1e-7 to 1.3e-6.
+// has few (60,000 x 6 receivers x 3000 bins in 7 bands: 129 us, matrix pipe 42% and vector unit 23% busy; per term 540).
+// Error against 64 bits over 70 random grids of 192 to 4160 bins 1.7e-7 to 6.0e-7 of the norm, per term 2.1e-7 to 1.3e-6,
+// lower in each.
 template <bool BATCH, int NRB, bool DIR>
 __global__ __launch_bounds__(256, 2) void k_synth_rows(SynthArgs a0, const SynthArgs* __restrict__ jobs, ChunkTab ct,
                                                        et_paths P, const int32_t* __restrict__ idx, const Ctl* ctl,
@@ -2329,16 +2330,27 @@ inline size_t al(size_t b) { return (b + 255) / 256 * 256; }
 // Tiles of at most 64 rows of a pose's spectrum.
 int64_t row_tiles(const et_sim_desc* sim) { return ((int64_t)synth_rows(sim, nullptr) + KT1 - 1) / KT1; }
 
-int choose_P(const et_sim_desc* sim, int64_t cap, bool mfma) {
-  // matrix-core kernels: about sixteen workgroups per CU over the launch (measured on the
+// Record chunks of a launch of the kernel fk (the factorised adjoint as FWD_HALVES).
+int choose_P(const et_sim_desc* sim, int64_t cap, FwdKernel fk) {
+  // kernels in halves: about sixteen workgroups per CU over the launch (measured on the
   // room's 32 x 4096 adjoint: 2048 workgroups 20.16 ms, 3072 20.05, 4096 19.87, 6144 19.98, 8192
   // 19.92 ms).  Chunk count a multiple of 8 so that every receiver's workgroups of one chunk share an
   // XCD's L2.
-  const int64_t tiles = (int64_t)sim->M * (mfma ? row_tiles(sim) : (sim->F + DTILE - 1) / DTILE);
-  const int64_t target = mfma ? 4096 : 2048;
+  const int64_t tiles = (int64_t)sim->M * (fk != FWD_TERM ? row_tiles(sim) : (sim->F + DTILE - 1) / DTILE);
+  const int64_t target = fk == FWD_HALVES ? 4096 : 2048;
   int64_t P = std::max<int64_t>(1, (target + tiles - 1) / tiles);
   if (P >= 8) P = (P + 7) / 8 * 8;
-  P = std::min<int64_t>(P, std::max<int64_t>(1, cap / 64));
+  int64_t most = std::max<int64_t>(1, cap / 64);
+  if (fk == FWD_ROWS) {
+    // no fewer chunks than per term has for as many tiles: a wave then sums a quarter of the records in a row (with 1024
+    // workgroups 60,000 records x 6 receivers x 3000 bins take 113 us instead of 130, but sums of many records in few
+    // bins came out less accurate than per term); chunks of 128 records (20,011 x 4 x 1500: 29 us, of 64 36, of
+    // 512 34) beyond the first 16
+    P = std::max<int64_t>(1, 2048 / tiles);
+    if (P >= 8) P = P / 8 * 8;
+    most = std::max(std::min<int64_t>(most, 16), cap / 128);
+  }
+  P = std::min(P, most);
   return (int)std::min<int64_t>(P, 256);
 }
 
@@ -2643,7 +2655,7 @@ FwdKernel fwd_kernel(const et_sim_desc* sim) {
 
 size_t synth_ws_layout(const et_sim_desc* sim, int64_t cap, char* base, SynthWS* ws) {
   cap = std::max<int64_t>(cap, 1);
-  const int P = choose_P(sim, cap, fwd_kernel(sim) != FWD_TERM);
+  const int P = choose_P(sim, cap, fwd_kernel(sim));
   size_t off = 0;
   SynthWS w{};
   w.P = P;
@@ -2697,7 +2709,7 @@ int synth_run_noalloc(const et_sim_desc* sim, const et_paths* paths, void* buf, 
   ET_CHECK(tables + chunk <= bytes, ET_E_UNSUPPORTED,
            "receivers x bins too large for the device scratch of the allocation-free call");
   // record chunks: the usual choice, as many as the scratch holds, a multiple of 8 above 8
-  int64_t P = std::min<int64_t>(choose_P(sim, cap, fk != FWD_TERM), (int64_t)((bytes - tables) / chunk));
+  int64_t P = std::min<int64_t>(choose_P(sim, cap, fk), (int64_t)((bytes - tables) / chunk));
   if (P > 8) P = P / 8 * 8;
   char* base = (char*)buf;
   table_ws(sim, base, 0, w);
@@ -2743,7 +2755,7 @@ size_t synth_bwd_ws_layout(const et_sim_desc* sim, int64_t cap, char* base, Synt
   const int64_t T1 = mf ? (sim->F / K2 + KT1 - 1) / KT1 : 1;
   int64_t P;
   if (mf) {
-    P = choose_P(sim, cap, true);
+    P = choose_P(sim, cap, FWD_HALVES);
   } else {
     P = std::max<int64_t>(1, (1024 + sim->M - 1) / sim->M);
     P = std::min<int64_t>(P, std::max<int64_t>(1, (cap + GB - 1) / GB));
